@@ -375,6 +375,34 @@ def test_attend_large_logits_in_either_half_of_a_key_block(ctx, dt):
     assert np.abs(O_g - ref).max() <= ATTN_TOL[q.dtype]
 
 
+@pytest.mark.parametrize("m", [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 255, 256, 257, 289, 321, 513, 600])
+@pytest.mark.parametrize("course", ["rise", "jump", "fall", "saw"])
+def test_attend_softmax_reference_at_block_borders(ctx, m, course):
+    """Kept counts around the 32-key blocks, 64-key tiles and 256-query items of the bf16 kernel, with
+    logits that rise by up to 190 powers of two over the row, all at once or steadily, fall, or do
+    both in turns: the softmax reference has to follow at every block a wave treats in a way of its
+    own (first, inner, masked, last).  Tolerance: a row is a convex combination of bf16 value rows
+    whatever the logits, so the bound of the other attention tests holds."""
+    _say("attend reference m=%d %s" % (m, course))
+    n = m + 7
+    q, k, v, _ = synth.make_random_qkv(1, 2, 1, n, 128, dtype="bf16", seed=600 + m)
+    idx = np.arange(3, 3 + m, dtype=np.int32)[None]
+    x = torch.arange(m, dtype=torch.float32) / max(m - 1, 1)
+    c = {"rise": 3 * x, "jump": 3 * (x > 0.5).float(), "fall": 3 * (1 - x), "saw": 3 * ((5 * x) % 1.0)}[course]
+    k = k.float() * 0.05
+    k[0, :, 3:3 + m] += 2.0 * c[:, None]                       # logit 2 * 2 * 128 / sqrt(128) * c nats
+    q = q.float() * 0.05 + 2.0
+    q, k = q.bfloat16(), k.bfloat16()
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.0)
+    buf = B.Buffers(p, "cuda:0")
+    buf.O.fill_(float("nan"))
+    ctx.tf_attend(p, q.cuda(), k.cuda(), v.cuda(), torch.from_numpy(idx).cuda(), m, buf.O, buf.ws)
+    torch.cuda.synchronize()
+    O_g = buf.O.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(O_g).all()
+    assert np.abs(O_g - oracle.attend(q, k, v, idx)).max() <= ATTN_TOL[q.dtype]
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_attend_zero_rows_with_long_gaps(ctx, dt):
     """Kept sets with filtered runs of every length (before the first kept token, between kept
