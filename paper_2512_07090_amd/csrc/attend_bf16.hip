@@ -6,26 +6,31 @@
 // Flash-style kernel for gfx950.  One work item covers 256 kept queries: eight waves of 32, two
 // per SIMD with 256 registers each.  It walks the key tiles (64 kept keys) once, K and V rows
 // gathered through kept_idx into LDS (two stages each).
-//   S^T = K Q^T   v_mfma_f32_32x32x16_bf16, A = K rows from LDS, B = Q fragments held in
+//   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = K rows from LDS, B = Q fragments held in
 //                 registers for the whole item.  The transposed product puts one query per
 //                 lane column, so P^T goes from the accumulators to the next product's operand
 //                 without leaving the lane.
 //   O^T += V^T P^T  A = V^T from LDS, written there already transposed (a pair of lanes swaps halves
 //                 and permutes 16-bit words), so that a fragment is one 16-byte read: the
 //                 transposing LDS read moves half as much per instruction.  The contraction
-//                 order over keys is permuted the same way for both operands (accumulator
-//                 register v of a 32-key block is key 8 (v / 4) + 4 (lane / 32) + v % 4).
+//                 order over keys is permuted the same way for both operands (k-slot 8 g + e of a
+//                 32-key block is key 4 g + e, or 16 + 4 g + e - 4 for e >= 4).
+//   LDS layout    K rows padded to 288 bytes, V^T slots XOR-ed: the 16 lanes that LDS serves together
+//                 in a 16-byte read touch every bank once (4.7 cycles a read instead of 8 to 12).
+//   MFMA shape    16x16x32 rather than 32x32x16: same rate, same operands from LDS, but on normally
+//                 distributed data the card clocks down less (2.03 against 1.78 PFLOP/s in a loop
+//                 of nothing else, 2.45 both on zeros).
 //   softmax       fp32, base 2 (scale * log2 e folded into one FMA per score), against a reference
-//                 that moves only when a weight outgrows it (TF_RESCUE): no row maximum on the
-//                 way.  The denominators are summed on the matrix pipe from the weights as
-//                 rounded (l_ones), so every output row is an exact convex combination of value
-//                 rows; v_dot2_f32_bf16, which did it before, occupies that pipe for about 20
-//                 cycles each (0.66 against 0.60 us per 64 keys in a copy of the loop).
+//                 that does not move within an item (see neg_mc): no row maximum on the way.
+//                 The denominators are summed on the matrix pipe from the weights as rounded
+//                 (l_ones), so every output row is an exact convex combination of value rows;
+//                 v_dot2_f32_bf16, which did it before, occupies that pipe for about 20 cycles each
+//                 (0.66 against 0.60 us per 32 keys in a copy of the loop).
 //   pipeline      Scores run one 32-key block ahead of the weights and the product with V one block
-//                 behind them, so that in a block the 8 + 8 MFMAs, the 16 exponentials and the 16
-//                 LDS reads do not depend on each other; they are interleaved chunk by chunk in
-//                 program order.  The blocks that begin and end a wave's walk are instances of
-//                 the same body with parts left out.
+//                 behind them, so that in a block the MFMAs, the 16 exponentials and the 16 LDS reads
+//                 do not depend on each other; they are interleaved chunk by chunk in program
+//                 order.  The blocks that begin and end a wave's walk are instances of the same
+//                 body with parts left out.
 //   tile loads    A tile's rows are requested right after the registers they land in have been
 //                 written to LDS, a whole iteration ahead of their use, and land in one register
 //                 set (requested at the start of the iteration that delivers them the launch took
@@ -35,9 +40,10 @@
 //   scheduling    One persistent workgroup per CU walks a static list of pairs of query tiles
 //                 (tile p with tile n_qt - 1 - p: equal causal work); see the kernel.
 // What bounds it: with real data the card runs at its power limit (1.4 kW) and clocks down; a
-// library GEMM of 8192^3 reaches 1.2-1.36 PFLOP/s there, this kernel 1.1 at 16384 kept tokens.
-// 8 x 32 heads x 2048 kept: 0.356 -> 0.346 ms (all-zero inputs, no power limit: 0.301 -> 0.282);
-// 32 heads on 8 KV heads x 16384 kept: 2.06 -> 1.98 ms (1.72 -> 1.52).
+// library GEMM of 8192^3 reaches 1.2-1.36 PFLOP/s there, this kernel 1.25 at 32 heads x 16384 kept
+// tokens (1.99 -> 1.76 ms; all-zero inputs 1.72 -> 1.54).  With short rows each item's start and
+// end show: 8 x 32 heads x 2048 kept 0.341 -> 0.311 ms, of which about 8 x 11 us are the items'
+// first loads, masked tiles and output rows.
 #include "tf_kernels.h"
 #include <algorithm>
 
@@ -48,30 +54,20 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBN = 64;                  // kept keys per tile
-constexpr int kKStr = kHeadDim + 8;      // K tile row stride, elements (272 B)
-constexpr int kVStr = kBN + 8;           // V^T tile row stride (one row per column of V), elements (144 B)
+constexpr int kKStr = kHeadDim + 16;     // K tile row stride, elements (288 B)
+constexpr int kVStr = kBN;               // V^T tile row stride (one row per column of V), elements (128 B)
 constexpr int kKTile = kBN * kKStr;      // elements per K tile
 constexpr int kVTile = kHeadDim * kVStr; // elements per V^T tile
 constexpr int kOStr = kHeadDim + 8;      // output staging row stride, elements
-constexpr float kRefBits = 16.f;         // headroom of the softmax reference, in powers of two
+constexpr float kSumLimit = 1.0995116e12f;  // 2^40: largest softmax denominator, see below
 constexpr float kMasked = -1e30f;
 
-// One 16-byte chunk of the row at position `pos`: `base` is uniform over the workgroup (the
-// (batch, head) slice plus nothing else), the lane's part is a 32-bit byte offset
-// pos * row_bytes + col_bytes formed by one 24-bit multiply-add (the launcher checks that a
-// slice spans less than 4 GiB and that positions and row strides stay below 2^24).
-__device__ __forceinline__ u32x4 load16(const char* base, int pos, unsigned row_bytes, unsigned col_bytes)
-{
-    const unsigned off = __umul24((unsigned)pos, row_bytes) + col_bytes;
-    return *reinterpret_cast<const u32x4*>(base + off);
-}
 // Two floats rounded to bf16 and packed into one register (v_cvt_pk_bf16_f32).  The words are handled as plain
 // unsigned values and only the assembled operand is reinterpreted as eight bf16 values:
 // extracting words from a bf16 vector after element-wise stores made this compiler read the
@@ -91,7 +87,7 @@ __device__ __forceinline__ void store_streaming(uint16_t* dst, uint4 v)
 // in r0, r1; the upper lane: keys k + 2, k + 3) to the V^T tile: the half swap gives the lower
 // lane columns 0-3 of all four keys and the upper lane columns 4-7, then 16-bit permutes put the
 // four keys of a column side by side.  dst: this lane's first column at the keys' place.
-__device__ __forceinline__ void store_v_transposed(u32x4 r0, u32x4 r1, uint16_t* dst)
+__device__ __forceinline__ void store_v_transposed(u32x4 r0, u32x4 r1, uint16_t* tile, int off)
 {
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
@@ -101,9 +97,29 @@ __device__ __forceinline__ void store_v_transposed(u32x4 r0, u32x4 r1, uint16_t*
         const unsigned k0 = s0[0], k2 = s0[1], k1 = s1[0], k3 = s1[1];
         const u32x2 even = {__builtin_amdgcn_perm(k1, k0, 0x05040100u), __builtin_amdgcn_perm(k3, k2, 0x05040100u)};
         const u32x2 odd = {__builtin_amdgcn_perm(k1, k0, 0x07060302u), __builtin_amdgcn_perm(k3, k2, 0x07060302u)};
-        *reinterpret_cast<u32x2*>(dst + (2 * w) * kVStr) = even;
-        *reinterpret_cast<u32x2*>(dst + (2 * w + 1) * kVStr) = odd;
+        // column i of the lane's four is row i and carries i in its slot's XOR
+        *reinterpret_cast<u32x2*>(tile + ((off ^ (8 * (2 * w))) + (2 * w) * kVStr)) = even;
+        *reinterpret_cast<u32x2*>(tile + ((off ^ (8 * (2 * w + 1))) + (2 * w + 1) * kVStr)) = odd;
     }
+}
+
+// c += a b, and c = a b, as instructions of their own whose accumulator stays in one place: left to
+// itself the compiler gives every such MFMA a destination of its own and spills.  It does not
+// know their latency either: what the tile loop reads of a result (scores, two chunks later)
+// and writes of an operand is far enough away; elsewhere mfma_settle() comes first.
+__device__ __forceinline__ void mfma_add(f32x4& c, bf16x8 a, bf16x8 b)
+{
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_first(f32x4& c, bf16x8 a, bf16x8 b)
+{
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 template <int NW>
@@ -125,6 +141,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     // a workgroup barrier on either side, so the waves leave an item, and start on the next
     // item's first loads, as each gets there.
     __shared__ __attribute__((aligned(16))) uint16_t ostage[kBM * kOStr];
+
+    __shared__ int overflow;   // a row of the item at hand has outgrown its reference
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -168,6 +186,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     const int n_main = split_rest ? n_entries - rest : n_entries;  // entries dealt as pairs
     const int whole_groups = split_rest ? ng - rest : ng;          // groups that keep all their pairs
     int rb = g_lo / d.Hq, row_e0 = 0;
+    bool exact = false;  // the item is done again, see below
     for (int it = 0;; ++it) {
     const int e = j + (it >> 1) * nwx;
     int pr, bh, m, nq;
@@ -231,7 +250,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     uint16_t* Ob = O + (long long)b * d.os[0] + (long long)hq * d.os[1];
     const unsigned kv_row_bytes = (unsigned)d.kvs[2] * 2u;
 
-    const int col = lane & 31, hh = lane >> 5;
+    const int c16 = lane & 15, g4 = lane >> 4;  // row or column of a 16x16 operand, its group of 8 k-slots
+    const int hh = lane >> 5;
 
     const int i0 = qt * kBM;
     // Waves w and w + NW / 2 share a SIMD.  Causal work grows with the row block, so the
@@ -242,38 +262,45 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     const int i_last = min(i0 + kBM, m) - 1;
     const int n_kt = i_last / kBN + 1;
     const int m_last = m - 1;
-    const int lim = min(iw + col, m_last);        // last key rank this lane's query may see
-    const int h_diag = iw > m_last ? -1 : iw / 32;  // the wave's last block of 32 keys, the masked one
+    // last key rank this lane's queries (c16 of the wave's two blocks of 16) may see
+    const int lim[2] = {min(iw + c16, m_last), min(iw + 16 + c16, m_last)};
+    const int q_last = iw > m_last ? 0 : iw / kBN;  // the last key tile the wave needs
 
     // tile-load roles: in pass p a thread moves columns 8 c .. + 7 of two neighbouring keys; the
     // lane 32 further holds the two keys after them, so that a pair of lanes can transpose four
     // keys of V, and the waves' keys are dealt so that a wave fills 16-byte slots of V^T.
     // Rows past the last kept token re-read the last kept row: finite values that the mask turns
     // into zero weights, so the loads need no branch.
+    // A row's address is the uniform (batch, head) base plus a 32-bit byte offset formed by one 24-bit
+    // multiply-add (the launcher checks that a slice spans less than 4 GiB and that positions
+    // and row strides stay below 2^24).
     const int c8 = lane & 15;
-    // A operand that sums the weights of each query on the matrix pipe: the 64 lanes of a P^T operand
-    // read as the B operand of a 16x16x32 MFMA are 16 columns x four groups of 8 keys, queries q
-    // and q + 16 sharing column q; row 0 adds groups 0 and 2 (query q), row 1 groups 1 and 3.
-    const unsigned one2 = (lane & 15) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
-    const bf16x8 l_ones = __builtin_bit_cast(bf16x8, u32x4{one2, one2, one2, one2});
+    auto load_idx = [&](int j) -> int {
+        return *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(idx) + 4u * (unsigned)min(j, m_last));
+    };
     int key0[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int vw = wave + NW * p;
-        key0[p] = 16 * (vw >> 1) + 4 * (vw & 1) + 8 * ((lane >> 4) & 1) + 2 * hh;
+        key0[p] = 32 * (vw >> 2) + 4 * (vw & 3) + 16 * (g4 & 1) + 2 * hh;
     }
     u32x4 kreg[NP][2], vreg[NP][2];
-    int pos_k[NP][2], pos_v[NP][2], pos_n[NP][2];
+    // byte offsets of the rows requested next (K and V share them), positions of those after
+    unsigned off_k[NP][2], off_v[NP][2];
+    int pos_n[NP][2];
 #define TF_LOAD_IDX(P, J0)                                                                     \
     _Pragma("unroll") for (int p = 0; p < NP; ++p) {                                           \
-        P[p][0] = idx[min((J0) + key0[p], m_last)];                                            \
-        P[p][1] = idx[min((J0) + key0[p] + 1, m_last)];                                        \
+        P[p][0] = load_idx((J0) + key0[p]);                                                    \
+        P[p][1] = load_idx((J0) + key0[p] + 1);                                                \
     }
-#define TF_LOAD_ROWS(R, BASE, P)                                                               \
-    _Pragma("unroll") for (int p = 0; p < NP; ++p) {                                           \
-        R[p][0] = load16(BASE, P[p][0], kv_row_bytes, 16u * c8);                               \
-        R[p][1] = load16(BASE, P[p][1], kv_row_bytes, 16u * c8);                               \
-    }
+#define TF_OFFSETS(F, P)                                                                       \
+    _Pragma("unroll") for (int p = 0; p < NP; ++p)                                             \
+        _Pragma("unroll") for (int i = 0; i < 2; ++i)                                          \
+            F[p][i] = __umul24((unsigned)P[p][i], kv_row_bytes) + 16u * c8
+#define TF_LOAD_ROWS(R, BASE, F)                                                               \
+    _Pragma("unroll") for (int p = 0; p < NP; ++p)                                             \
+        _Pragma("unroll") for (int i = 0; i < 2; ++i)                                          \
+            R[p][i] = *reinterpret_cast<const u32x4*>(BASE + F[p][i])
 #define TF_STORE_K(STAGE)                                                                      \
     _Pragma("unroll") for (int p = 0; p < NP; ++p) {                                           \
         uint16_t* dst_ = k_wr + (STAGE) * kKTile + (key0[p] - key0[0]) * kKStr;                \
@@ -282,197 +309,220 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     }
 #define TF_STORE_V(STAGE)                                                                      \
     _Pragma("unroll") for (int p = 0; p < NP; ++p)                                             \
-        store_v_transposed(vreg[p][0], vreg[p][1], v_lds + (STAGE) * kVTile + v_wr[p])
+        store_v_transposed(vreg[p][0], vreg[p][1], v_lds + (STAGE) * kVTile, v_wr[p])
     uint16_t* const k_wr = k_lds + key0[0] * kKStr + 8 * c8;
-    // V^T: row = column of V; the 64 keys of a row are 8 slots of 16 bytes, slot 2 ks + hh holding the
-    // eight keys 16 ks + 4 hh + {0..3, 8..11} that lane half hh feeds to the MFMA of k-step ks.
-    // Slots are XOR-ed with the row's number / 8: eight consecutive rows (a read) start at different
-    // banks through the row stride, rows 8 apart (a write) through the XOR.
+    // V^T: row = column of V; the 64 keys of a row are 8 slots of 16 bytes, slot 4 h + g holding the
+    // eight keys 32 h + 4 g + {0..3, 16..19} that lane group g feeds to the MFMA of 32-key half h.
+    // A row's slots are XOR-ed with (row % 8) ^ (row / 8 % 8): the 16 lanes that LDS serves together in a
+    // 16-byte read then touch all 64 banks once (4.7 cycles a read; a padded row of 144 bytes
+    // XOR-ed with row / 8 alone: 12.1), and so do the lanes of a write (8.4).
     int v_wr[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const int vw = wave + NW * p;
-        v_wr[p] = (8 * c8 + 4 * hh) * kVStr + 8 * ((2 * (vw >> 1) + (vw & 1)) ^ (c8 & 7)) + 4 * ((lane >> 4) & 1);
+    for (int p = 0; p < NP; ++p)
+        v_wr[p] = (8 * c8 + 4 * hh) * kVStr + 8 * ((wave + NW * p) ^ (c8 & 7) ^ (4 * hh)) + 4 * (g4 & 1);
+
+    // The weights are taken against a reference that never moves: the row max of the first block of
+    // keys.  Later scores may exceed it: weights and sums have fp32's range.  Should a row's
+    // weights sum to more than 2^40 (its true max is some 28 above the reference in units of the
+    // natural logarithm; an overflow shows as an infinite sum), the item is done again against
+    // the true row maxima.  A running maximum cost 18 vector instructions and a branch per block.
+    float neg_mc[2] = {0.f, 0.f};   // minus the reference of a lane's queries, scaled to base 2
+    if (tid == 0) overflow = 0;
+    if (exact) {
+        // scores only, tile by tile, for the row maxima
+        float mx[2] = {kMasked, kMasked};
+        bf16x8 qm[2][4];
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                qm[qb][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
+                    Qb + (long long)idx[lim[qb]] * d.qs[2] + 32 * s + 8 * g4));
+        for (int j0 = 0; j0 <= i_last; j0 += kBN) {
+            __syncthreads();
+            TF_LOAD_IDX(pos_n, j0);
+            TF_OFFSETS(off_k, pos_n);
+            TF_LOAD_ROWS(kreg, Kb, off_k);
+            TF_STORE_K(0);
+            __syncthreads();
+#pragma unroll 1
+            for (int kb = 0; kb < kBN / 16; ++kb) {
+                f32x4 sm[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const bf16x8 km = *reinterpret_cast<const bf16x8*>(k_lds + (16 * kb + c16) * kKStr + 32 * s + 8 * g4);
+                    sm[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(km, qm[0][s], sm[0], 0, 0, 0);
+                    sm[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(km, qm[1][s], sm[1], 0, 0, 0);
+                }
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (j0 + 16 * kb + 4 * g4 + v <= lim[qb]) mx[qb] = fmaxf(mx[qb], sm[qb][v]);
+            }
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            mx[qb] = fmaxf(mx[qb], __shfl_xor(mx[qb], 16));
+            mx[qb] = fmaxf(mx[qb], __shfl_xor(mx[qb], 32));
+            neg_mc[qb] = -mx[qb] * scale_log2;
+        }
+        __syncthreads();
     }
 
     // ---- prologue: every index first, then every row load, no wait in between -------------
-    const int qpos = idx[lim];   // position of this lane's query
-    int pos_0[NP][2];
+    const int qp[2] = {idx[lim[0]], idx[lim[1]]};
+    const int qpos = (lane & 16) ? qp[1] : qp[0];   // position of query lane % 32 of the wave
+    int pos_0[NP][2], pos_1[NP][2];
     TF_LOAD_IDX(pos_0, 0);
-    TF_LOAD_IDX(pos_v, kBN);
-    TF_LOAD_IDX(pos_k, 2 * kBN);
-    // Q fragments (B operand of S^T = K Q^T): lane (col, hh) holds, for k-step s, the 8 elements
-    // 16 s + 8 hh .. +7 of query row iw + col.
-    bf16x8 qf[8];
-    {
-        const uint16_t* src = Qb + (long long)qpos * d.qs[2];
+    TF_LOAD_IDX(pos_1, kBN);
+    TF_LOAD_IDX(pos_n, 2 * kBN);
+    // Q fragments (B operand of S^T = K Q^T): for query block qb and k-step s, the 8 elements
+    // 32 s + 8 g4 .. +7 of query row iw + 16 qb + c16.
+    bf16x8 qf[2][4];
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-            qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * s + 8 * hh));
+    for (int qb = 0; qb < 2; ++qb) {
+        const uint16_t* src = Qb + (long long)qp[qb] * d.qs[2] + 8 * g4;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qf[qb][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 32 * s));
     }
-    TF_LOAD_ROWS(kreg, Kb, pos_0);
-    TF_LOAD_ROWS(vreg, Vb, pos_0);
+    TF_OFFSETS(off_k, pos_0);
+    TF_LOAD_ROWS(kreg, Kb, off_k);
+    TF_LOAD_ROWS(vreg, Vb, off_k);
     TF_STORE_K(0);
-    TF_LOAD_ROWS(kreg, Kb, pos_v);
+    TF_OFFSETS(off_k, pos_1);
+    TF_LOAD_ROWS(kreg, Kb, off_k);
     __syncthreads();
 
     // LDS offsets of this lane's operand fragments inside a K / V^T stage
-    const int k_off = col * kKStr + 8 * hh;
-    const int v_off0 = col * kVStr + 8 * (hh ^ (col >> 3));
-    const int v_off1 = col * kVStr + 8 * ((2 + hh) ^ (col >> 3));
-
-    f32x16 oacc[4];
+    const int k_off = c16 * kKStr + 8 * g4;
+    int v_off[4];
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
-    f32x4 l_acc = {0.f, 0.f, 0.f, 0.f};  // softmax denominators, see l_ones
-    float neg_mc = 0.f;                  // minus the softmax reference, scaled to base 2
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 s_x = zero16, s_y = zero16;   // raw scores of an even / odd block of 32 keys
-    u32x4 p_a[2], p_b[2];                // P^T of an even / odd block, per 16-key k-step
+    for (int x4 = 0; x4 < 4; ++x4) v_off[x4] = c16 * kVStr + 8 * (g4 ^ (c16 & 7) ^ (c16 >> 3) ^ (2 * x4));
 
-    // fragment i (0..7) of half `half` of a stage
+    const f32x4 zero4f = {0.f, 0.f, 0.f, 0.f};
+    f32x4 oacc[8][2];          // O^T: 16 columns of V x 16 queries
+    f32x4 l_acc[2];            // softmax denominators (row 0), see l_ones
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        l_acc[qb] = zero4f;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) oacc[db][qb] = zero4f;
+    }
+    f32x4 s_x[2][2], s_y[2][2];     // raw scores of an even / odd block of 32 keys: [16 keys][16 queries]
+    u32x4 p_a[2], p_b[2];           // P^T of an even / odd block, per query block
+    // A operand whose row 0 sums the weights of each query
+    const unsigned one2 = c16 == 0 ? 0x3f803f80u : 0u;
+    const bf16x8 l_ones = __builtin_bit_cast(bf16x8, u32x4{one2, one2, one2, one2});
+
+    // fragment i (0..7) of half `half` of a stage: 16 keys i / 4 and k-step i % 4; 16 columns of V
     auto read_k = [&](const uint16_t* ks, int half, int i) -> bf16x8 {
-        return *reinterpret_cast<const bf16x8*>(ks + k_off + half * (32 * kKStr) + 16 * i);
+        return *reinterpret_cast<const bf16x8*>(ks + k_off + (32 * half + 16 * (i >> 2)) * kKStr + 32 * (i & 3));
     };
     auto read_v = [&](const uint16_t* vs, int half, int i) -> bf16x8 {
-        const int ks2 = i >> 2, dt = i & 3;   // k-step 2 half + ks2 of the tile, 32 columns
-        return *reinterpret_cast<const bf16x8*>(vs + (ks2 ? v_off1 : v_off0) + 32 * dt * kVStr + 32 * (half ^ (dt & 1)));
+        return *reinterpret_cast<const bf16x8*>(vs + v_off[(2 * half) ^ (i & 3)] + 16 * i * kVStr);
     };
-    auto row_max = [&](const f32x16& s) -> float {
-        float mx = fmaxf(s[0], s[1]), my = fmaxf(s[2], s[3]);
-#pragma unroll
-        for (int v = 4; v < 16; v += 4) {
-            mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);
-            my = fmaxf(fmaxf(my, s[v + 2]), s[v + 3]);
-        }
-        mx = fmaxf(mx, my);
-        // the other half of this query's keys sits 32 lanes away: swap halves in the VALU
-        const FloatPair sw = swap32(mx, mx);
-        return fmaxf(sw.first, sw.second);
+    auto row_max = [&](const f32x4& a, const f32x4& b) -> float {
+        float mx = fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
+        // the other keys of this query sit 16, 32 and 48 lanes away
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        return fmaxf(mx, __shfl_xor(mx, 32));
     };
-    // causal mask of accumulator registers 2 i, 2 i + 1 of the block that starts at key rank J0:
-    // register v is key J0 + 8 (v / 4) + 4 hh + v % 4
+    // Chunk i of a block's weights: query block i / 4, 16 keys (i / 2) % 2, accumulator registers
+    // 2 (i % 2) and the next; register v is key J0 + 16 (i / 2 % 2) + 4 g4 + v.
 #define TF_MASK(S, I, J0)                                                                      \
     do {                                                                                       \
-        const int t_ = (J0) + 4 * hh - lim + 8 * ((I) >> 1) + ((2 * (I)) & 3);                 \
-        if (t_ > 0) S[2 * (I)] = kMasked;                                                      \
-        if (t_ + 1 > 0) S[2 * (I) + 1] = kMasked;                                              \
+        const int t_ = (J0) + 16 * (((I) >> 1) & 1) + 2 * ((I) & 1) + 4 * g4 - lim[(I) >> 2];  \
+        f32x4& s_ = S[((I) >> 1) & 1][(I) >> 2];                                               \
+        if (t_ > 0) s_[2 * ((I) & 1)] = kMasked;                                               \
+        if (t_ + 1 > 0) s_[2 * ((I) & 1) + 1] = kMasked;                                       \
     } while (0)
-    // weights of accumulator registers 2 i, 2 i + 1, rounded and packed; their bits to ANY
-#define TF_WEIGHTS(S, P, I, ANY)                                                               \
+    // One half of an iteration's chunk: fragment i against both query blocks.
+#define TF_CHUNK(QK, EX, PV, S_NEW, S_OLD, P_NEW, P_OLD, J_OLD)                                \
     do {                                                                                       \
-        const float e0_ = __builtin_amdgcn_exp2f(fmaf(S[2 * (I)], scale_log2, neg_mc));        \
-        const float e1_ = __builtin_amdgcn_exp2f(fmaf(S[2 * (I) + 1], scale_log2, neg_mc));    \
-        const unsigned w_ = pack_bf16x2(e0_, e1_);                                             \
-        P[(I) >> 2][(I) & 3] = w_;                                                             \
-        if (((I) & 1) == 0) w_even = w_; else ANY |= w_ | w_even;                              \
-    } while (0)
-    // The weights of a block are taken against a reference that only moves when it has to: the row
-    // max of the first block plus kRefBits, until a weight reaches 2 (a weight that overflowed
-    // included): a score more than kRefBits + 1 bits above the reference's max.  Then that
-    // query's reference becomes this block's max, what has been accumulated is rescaled and the
-    // block's weights are taken again.  Nothing is lost on the way: the sums stay far inside
-    // fp32's range, and the test is an OR over the packed weights instead of a row maximum per
-    // block (18 fewer vector instructions on the way from the scores to the weights).
-#define TF_RESCUE(S, P, ANY)                                                                   \
-    do {                                                                                       \
-        if (__any(ANY & 0x40004000u)) {                                                        \
-            const bool move_ = ((ANY | (unsigned)__shfl_xor((int)(ANY), 32)) & 0x40004000u) != 0; \
-            const float new_mc_ = move_ ? -row_max(S) * scale_log2 - kRefBits : neg_mc;        \
-            const float corr_ = __builtin_amdgcn_exp2f(new_mc_ - neg_mc);                      \
-            neg_mc = new_mc_;                                                                  \
-            l_acc[0] *= corr_;                                                                 \
-            l_acc[1] *= __shfl(corr_, (lane & 15) + 16);                                       \
-            _Pragma("unroll") for (int dt = 0; dt < 4; ++dt)                                   \
-                _Pragma("unroll") for (int v = 0; v < 16; ++v) oacc[dt][v] *= corr_;           \
-            _Pragma("unroll") for (int i = 0; i < 8; ++i) TF_WEIGHTS(S, P, i, ANY);            \
+        const f32x4& s_ = S_OLD[(i >> 1) & 1][i >> 2];                                         \
+        float e0_ = 0.f, e1_ = 0.f;                                                            \
+        if (EX == 2) TF_MASK(S_OLD, i, J_OLD);                                                 \
+        if (QK && (i & 3) == 0) mfma_first(S_NEW[i >> 2][0], kf[r], qf[0][0]);                 \
+        if (QK && (i & 3) != 0) mfma_add(S_NEW[i >> 2][0], kf[r], qf[0][i & 3]);               \
+        __builtin_amdgcn_sched_barrier(0);                                                     \
+        if (EX) {                                                                              \
+            e0_ = __builtin_amdgcn_exp2f(fmaf(s_[2 * (i & 1)], scale_log2, neg_mc[i >> 2]));   \
+            e1_ = fmaf(s_[2 * (i & 1) + 1], scale_log2, neg_mc[i >> 2]);                       \
         }                                                                                      \
-        ANY = 0;                                                                               \
+        if (PV) mfma_add(oacc[i][0], vf[r], __builtin_bit_cast(bf16x8, P_OLD[0]));             \
+        __builtin_amdgcn_sched_barrier(0);                                                     \
+        if (EX) e1_ = __builtin_amdgcn_exp2f(e1_);                                             \
+        if (QK && (i & 3) == 0) mfma_first(S_NEW[i >> 2][1], kf[r], qf[1][0]);                 \
+        if (QK && (i & 3) != 0) mfma_add(S_NEW[i >> 2][1], kf[r], qf[1][i & 3]);               \
+        __builtin_amdgcn_sched_barrier(0);                                                     \
+        if (EX) P_NEW[i >> 2][i & 3] = pack_bf16x2(e0_, e1_);                                  \
+        if (PV) mfma_add(oacc[i][1], vf[r], __builtin_bit_cast(bf16x8, P_OLD[1]));             \
+        if (PV && i < 2) mfma_add(l_acc[i], l_ones, __builtin_bit_cast(bf16x8, P_OLD[i]));     \
     } while (0)
     // One iteration of the tile loop over two blocks of 32 keys (halves A and B of 8 chunks each); QK,
     // EX (1: weights, 2: with the causal mask) and PV say at compile time what a half has to do.
-    // A chunk is one MFMA of the scores, two weights and one MFMA of the product; nothing moves
+    // A chunk is two MFMAs of the scores, two weights and two MFMAs of the product; nothing moves
     // across chunk borders, so the two pipes always have each other's work next to theirs, and
     // operand fragments are read from LDS kRing - 1 chunks ahead.
-#define TF_TILE(QK_A, EX_A, PV_A, QK_B, EX_B, PV_B, FIRST, MORE)                                   \
+#define TF_TILE(QK_A, EX_A, PV_A, QK_B, EX_B, PV_B, FIRST, MORE)                               \
     do {                                                                                       \
         bf16x8 kf[kRing], vf[kRing];                                                           \
-        unsigned any = 0, w_even = 0;                                                          \
         _Pragma("unroll") for (int j = 0; j < kRing - 1; ++j) {                                \
             if (QK_A) kf[j] = read_k(ks, 0, j);                                                \
             if (PV_A) vf[j] = read_v(vs, 0, j);                                                \
         }                                                                                      \
-        TF_REQUEST(MORE);                                                                      \
         __builtin_amdgcn_sched_barrier(0);                                                     \
         _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                       \
             const int i = j & 7, n = j + kRing - 1, r = j % kRing;                             \
             if (n < 16 && (n < 8 ? QK_A : QK_B)) kf[n % kRing] = read_k(ks, n >> 3, n & 7);    \
             if (n < 16 && (n < 8 ? PV_A : PV_B)) vf[n % kRing] = read_v(vs, n >> 3, n & 7);    \
-            if (j < 8) {                                                                       \
-                if (QK_A) s_x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[r], qf[i], i ? s_x : zero16, 0, 0, 0); \
-                if (EX_A == 2) TF_MASK(s_y, i, 64 * kt - 32);                                  \
-                if (EX_A) TF_WEIGHTS(s_y, p_b, i, any);                                        \
-                if (PV_A) {                                                                    \
-                    if ((i & 3) == 0)                                                          \
-                        l_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l_ones, __builtin_bit_cast(bf16x8, p_a[i >> 2]), l_acc, 0, 0, 0); \
-                    oacc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                     \
-                        vf[r], __builtin_bit_cast(bf16x8, p_a[i >> 2]), oacc[i & 3], 0, 0, 0); \
-                }                                                                              \
-            } else {                                                                           \
-                if (QK_B) s_y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[r], qf[i], i ? s_y : zero16, 0, 0, 0); \
-                if (EX_B == 2) TF_MASK(s_x, i, 64 * kt);                                       \
-                if (EX_B) TF_WEIGHTS(s_x, p_a, i, any);                                        \
-                if (PV_B) {                                                                    \
-                    if ((i & 3) == 0)                                                          \
-                        l_acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l_ones, __builtin_bit_cast(bf16x8, p_b[i >> 2]), l_acc, 0, 0, 0); \
-                    oacc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                     \
-                        vf[r], __builtin_bit_cast(bf16x8, p_b[i >> 2]), oacc[i & 3], 0, 0, 0); \
-                }                                                                              \
-            }                                                                                  \
+            if (j < 8) TF_CHUNK(QK_A, EX_A, PV_A, s_x, s_y, p_b, p_a, 64 * kt - 32);           \
+            else TF_CHUNK(QK_B, EX_B, PV_B, s_y, s_x, p_a, p_b, 64 * kt);                      \
             __builtin_amdgcn_sched_barrier(0);                                                 \
             if (j == 7) {                                                                      \
-                if (EX_A) TF_RESCUE(s_y, p_b, any);                                            \
                 if (FIRST) {                                                                   \
-                    if (FIRST == 2) { _Pragma("unroll") for (int v = 0; v < 8; ++v) TF_MASK(s_x, v, 0); } \
-                    neg_mc = -row_max(s_x) * scale_log2 - kRefBits;                            \
+                    mfma_settle();                                                             \
+                    _Pragma("unroll") for (int v = 0; v < 8; ++v) TF_MASK(s_x, v, 0);          \
+                    if (!exact) {                                                              \
+                        _Pragma("unroll") for (int qb = 0; qb < 2; ++qb)                       \
+                            neg_mc[qb] = -row_max(s_x[0][qb], s_x[1][qb]) * scale_log2;            \
+                    }                                                                          \
                 }                                                                              \
             }                                                                                  \
             if (j == 11) TF_DELIVER_K(MORE);                                                   \
             if (j == 13) TF_DELIVER_V(MORE);                                                   \
         }                                                                                      \
-        if (EX_B) TF_RESCUE(s_x, p_a, any);                                                    \
     } while (0)
 
     // Iteration kt: scores of the two blocks of K tile kt, weights of blocks 2 kt - 1 and 2 kt, products
-    // of blocks 2 kt - 2 and 2 kt - 1 with V tile kt - 1.  It requests K(kt + 1) and V(kt) at its
-    // start and writes them to the stages that K(kt - 1) and V(kt - 2) have left; iteration
-    // n_kt only finishes.  A wave runs n_kt + 1 iterations with a barrier after each but the
+    // of blocks 2 kt - 2 and 2 kt - 1 with V tile kt - 1.  It writes K(kt + 1) and V(kt) to
+    // the stages that K(kt - 1) and V(kt - 2) have left; iteration n_kt only finishes.  A wave runs n_kt + 1 iterations with a barrier after each but the
     // last, whatever it has to compute in them.
-    // (pos_k: rows of K tile kt + 2, pos_v: of V tile kt + 1, requested in iteration kt)
-#define TF_REQUEST(MORE)                                                                       \
-    do {                                                                                       \
-        if (MORE) TF_LOAD_IDX(pos_n, (kt + 3) * kBN);                                          \
-    } while (0)
+    // Delivering K(kt + 1) requests K(kt + 2) into the same registers, V(kt) likewise V(kt + 1), with
+    // off_k and off_v; the positions of the tile after (pos_n) are requested before the rows, because
+    // loads return in order and positions behind a row that misses the L2 would hold up the
+    // next request.
 #define TF_DELIVER_K(MORE)                                                                     \
     do {                                                                                       \
         if (MORE) {                                                                            \
             TF_STORE_K((kt & 1) ^ 1);                                                          \
-            TF_LOAD_ROWS(kreg, Kb, pos_k);                                                     \
+            _Pragma("unroll") for (int p = 0; p < NP; ++p)                                     \
+                _Pragma("unroll") for (int i = 0; i < 2; ++i) off_v[p][i] = off_k[p][i];       \
+            TF_OFFSETS(off_k, pos_n);                                                          \
+            TF_LOAD_IDX(pos_n, (kt + 3) * kBN);                                                \
+            TF_LOAD_ROWS(kreg, Kb, off_k);                                                     \
         }                                                                                      \
     } while (0)
 #define TF_DELIVER_V(MORE)                                                                     \
     do {                                                                                       \
         if (MORE) {                                                                            \
             TF_STORE_V(kt & 1);                                                                \
-            TF_LOAD_ROWS(vreg, Vb, pos_v);                                                     \
+            TF_LOAD_ROWS(vreg, Vb, off_v);                                                     \
         }                                                                                      \
     } while (0)
 #define TF_ADVANCE()                                                                           \
     do {                                                                                       \
-        _Pragma("unroll") for (int p = 0; p < NP; ++p)                                         \
-            _Pragma("unroll") for (int i = 0; i < 2; ++i) { pos_v[p][i] = pos_k[p][i]; pos_k[p][i] = pos_n[p][i]; } \
         ++kt;                                                                                  \
         ks = k_lds + (kt & 1) * kKTile;                                                        \
         vs = v_lds + ((kt & 1) ^ 1) * kVTile;                                                  \
@@ -481,40 +531,22 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     int kt = 0;
     const uint16_t* ks = k_lds;
     const uint16_t* vs = v_lds + kVTile;
-    if (h_diag > 0) {
-        TF_TILE(true, 0, false, true, 1, false, 1, true);
-    } else if (h_diag == 0) {
-        TF_TILE(true, 0, false, false, 1, false, 2, true);
-    } else {
-        TF_REQUEST(true);
-        TF_DELIVER_K(true);
-        TF_DELIVER_V(true);
-    }
+    TF_TILE(true, 0, false, true, 1, false, true, true);
     TF_ADVANCE();
-    while (2 * kt + 1 <= h_diag) {
-        TF_TILE(true, 1, true, true, 1, true, 0, true);
+    while (kt < q_last) {
+        TF_TILE(true, 1, true, true, 1, true, false, true);
         TF_ADVANCE();
     }
-    // the wave's masked block: the first half of K tile kt, or the second half of the one before
-    if (h_diag >= 0) {
-        bool last_even = h_diag == 0;
-        if (h_diag > 0 && (h_diag & 1) == 0) {
-            TF_TILE(true, 1, true, false, 2, true, 0, true);
-            TF_ADVANCE();
-            last_even = true;
-        }
-        if (last_even) {
-            TF_TILE(false, 0, true, false, 0, false, 0, kt < n_kt);
-        } else {
-            TF_TILE(false, 2, true, false, 0, true, 0, kt < n_kt);
-        }
-        if (kt < n_kt) TF_ADVANCE();
-        else ++kt;
+    // the wave's last tile, whose two blocks are masked
+    if (q_last > 0) {
+        TF_TILE(true, 1, true, true, 2, true, false, true);
+        TF_ADVANCE();
     }
+    TF_TILE(false, 2, true, false, 0, true, false, kt < n_kt);
+    if (kt < n_kt) TF_ADVANCE();
+    else ++kt;
     // nothing left to compute: only the tiles of the others
-    while (kt <= n_kt) {
-        if (kt == n_kt) break;
-        TF_REQUEST(true);
+    while (kt < n_kt) {
         TF_DELIVER_K(true);
         TF_DELIVER_V(true);
         TF_ADVANCE();
@@ -522,35 +554,41 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
 #undef TF_ADVANCE
 #undef TF_DELIVER_V
 #undef TF_DELIVER_K
-#undef TF_REQUEST
 #undef TF_TILE
-#undef TF_RESCUE
-#undef TF_WEIGHTS
+#undef TF_CHUNK
 #undef TF_MASK
 #undef TF_STORE_V
 #undef TF_STORE_K
 #undef TF_LOAD_ROWS
+#undef TF_OFFSETS
 #undef TF_LOAD_IDX
 
+    mfma_settle();
+    if (__any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit) && lane == 0) overflow = 1;
+    __syncthreads();
+    if (!exact && __builtin_amdgcn_readfirstlane(overflow)) {
+        exact = true;
+        --it;
+        continue;
+    }
+    exact = false;
     // normalise, transpose through LDS and write whole rows
     // (the lane number goes through an opaque move so that the addresses below are formed
     // here, per item, instead of being carried in registers across the tile loop)
     int ln = lane;
     asm volatile("" : "+v"(ln));
     uint16_t* os = ostage + wave * (WQ * kOStr);  // [WQ queries][kOStr], this wave's alone
-    {
-        const float l_lo = __shfl(l_acc[0], ln & 15), l_hi = __shfl(l_acc[1], ln & 15);
-        const float l_tot = (ln & 16) ? l_hi : l_lo;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        const float l_tot = __shfl(l_acc[qb][0], ln & 15);
         const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+        for (int db = 0; db < 8; ++db) {
+            bf16x4 o4;
 #pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
-                bf16x4 o4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[dt][4 * v4 + e] * inv);
-                *reinterpret_cast<bf16x4*>(os + (ln & 31) * kOStr + 32 * dt + 8 * v4 + 4 * (ln >> 5)) = o4;
-            }
+            for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][qb][e] * inv);
+            *reinterpret_cast<bf16x4*>(os + (16 * qb + (ln & 15)) * kOStr + 16 * db + 4 * (ln >> 4)) = o4;
+        }
     }
     // the rows are read back by other lanes of this wave only: LDS operations of one wave
     // complete in order, the compiler must just not move them across this point
