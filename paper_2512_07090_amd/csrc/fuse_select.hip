@@ -202,125 +202,227 @@ __global__ __launch_bounds__(kSelThreads) void compact_kernel(const uint8_t* __r
 
 // ------------------------------------------------------------------------------ decision + compaction
 // Same decision as select_kernel followed by compact_kernel, in one launch, for rows of up to
-// 1024 * IPT tokens: a thread keeps its IPT consecutive scores in registers, so the four radix
-// passes and the two ordered scans (rank among the threshold's equals, rank among the kept)
-// touch only registers and LDS.
+// 1024 * IPT tokens.  Thread i holds tokens i, i + 1024, ... as keys in registers (loads and
+// stores are then contiguous over a wave).  The want-th smallest (score, index) is found by
+//   1. a histogram over kBins equal steps between the smallest and the largest score (scores are
+//      spread over that range, while their bit patterns share a handful of exponents, so that a
+//      histogram of bit patterns is 1024 threads adding to a few bins), and again between the
+//      smallest and the largest score of the bin that holds the wanted rank, until that bin
+//      holds at most kMaxCand tokens (once or twice; after kLevels times, as when an outlier
+//      stretches the range over and over, four radix passes over the bit patterns take over);
+//   2. those tokens compared with each other.  Where the bin holds equal scores only, the
+//      wanted one is picked by its rank in token order.
+// Everything at or below the token found is kept.  What bounds it: short rows a chain of some 15
+// barriers and LDS round trips, long rows the passes over 32 scores a thread on the one compute unit
+// that works on a row.  One row of 32768 tokens: 55 -> 24 us against four radix passes in thread
+// order, 2 x 8192: 16 -> 9.3, 8 x 4096: 11.4 -> 7.4, 333: 8.1 -> 4.9.
+constexpr int kBins = 2048;
+constexpr int kMaxCand = 256;
+constexpr int kLevels = 4;
+
+// Positions of flagged tokens in token order: base[i * kSelWaves + wave] + the lane's rank in its
+// ballot.  `base` holds IPT * kSelWaves ints; returns the number of flagged tokens; ends with a
+// barrier.
+template <int IPT>
+__device__ __forceinline__ int ordered_bases(const unsigned long long* ballots, int* base, int* scan_lds)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) base[i * kSelWaves + wave] = __popcll(ballots[i]);
+    }
+    __syncthreads();
+    const int v = threadIdx.x < IPT * kSelWaves ? base[threadIdx.x] : 0;
+    int total;
+    const int before = block_excl_scan(v, scan_lds, &total);
+    if (threadIdx.x < IPT * kSelWaves) base[threadIdx.x] = before;
+    __syncthreads();
+    return total;
+}
+__device__ __forceinline__ int rank_below(unsigned long long ballot)
+{
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ballot, 0));
+}
+
 template <int IPT>
 __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
     const float* __restrict__ fused, int n, int m, int warmup, uint8_t* __restrict__ keep,
     int32_t* __restrict__ kept_idx, float* __restrict__ tau)
 {
-    __shared__ int hist[256];
+    // copies of the histogram, one per lane residue: a wave's tokens fall into few bins at times
+    // (runs of like tokens), and lanes adding to one word take turns
+    constexpr int kCopies = IPT >= 8 ? 8 : 2;
+    __shared__ __attribute__((aligned(16))) int hist[kBins * kCopies];
+    __shared__ float cand[kMaxCand];
+    __shared__ int cand_idx[kMaxCand];
+    __shared__ int base[IPT * kSelWaves];
     __shared__ int scan_lds[kSelWaves + 1];
-    __shared__ unsigned sel_prefix;
-    __shared__ int sel_k;
+    __shared__ float lo_lds[kSelWaves], hi_lds[kSelWaves];
+    __shared__ unsigned sel_u;
+    __shared__ float sel_f;
+    __shared__ int sel_k, sel_cnt, n_cand;
 
     const int b = blockIdx.x;
     const float* S = fused + (long long)b * n;
     uint8_t* kp = keep + (long long)b * n;
     int32_t* out = kept_idx + (long long)b * m;
-    const int tid = threadIdx.x;
-    const int t0 = tid * IPT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int forced = min(max(warmup, 0), m);
     const int want = m - forced;
     const bool all = m >= n;            // nothing is filtered
     const bool none = want <= 0;        // no non-forced token is kept
 
-    // keys of this thread's tokens; forced tokens and the tail past n take no part in the
-    // selection (cand = false)
-    unsigned key[IPT];
-    bool cand[IPT];
+    // (every load is issued whatever the token, so that none waits for the one before; forced tokens
+    // and the tail past n take no part in the selection: they stay above every score)
+    float sc[IPT];
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        const int t = t0 + i;
-        cand[i] = t >= forced && t < n;
-        key[i] = cand[i] ? f2key(S[t]) : 0xffffffffu;
-    }
+    for (int i = 0; i < IPT; ++i) sc[i] = S[min(i * kSelThreads + tid, n - 1)];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i)
+        if (i * kSelThreads + tid < forced || i * kSelThreads + tid >= n) sc[i] = INFINITY;
 
-    unsigned tkey = 0;
-    int k_eq = 0;
+    // smallest and largest score over the workgroup; one barrier before the result, none after
+    auto min_max = [&](float& lo, float& hi) {
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            lo = fminf(lo, __shfl_xor(lo, off));
+            hi = fmaxf(hi, __shfl_xor(hi, off));
+        }
+        if (lane == 0) { lo_lds[wave] = lo; hi_lds[wave] = hi; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSelWaves; ++w) { lo = fminf(lo, lo_lds[w]); hi = fmaxf(hi, hi_lds[w]); }
+    };
+
+    float tf_ = 0.f;
+    int tidx = -1;   // kept: forced, or (score, index) <= (tf_, tidx)
     if (!all && !none) {
-        unsigned prefix = 0;
-        int k = want;  // 1-based rank still to find inside the current prefix bucket
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
-            const unsigned himask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
-            if (tid < 256) hist[tid] = 0;
-            __syncthreads();
-            // a thread's consecutive tokens that fall into the same bin share one atomic: scores
-            // are cosines, so in the first passes nearly all of them do, and colliding atomics
-            // are what this loop costs
-            int run_bin = -1, run_len = 0;
+        // the wanted token is the k-th smallest of those with scores lo .. hi (in bin `bin` of that range)
+        float lo = INFINITY, hi = -INFINITY, to_bin = 0.f;
+        int k = want, cnt = n - forced, bin = 0;
+        // monotone in the score: a rounded difference times a constant, truncated
+        auto bin_of = [&](float x) -> int { return (int)fminf((x - lo) * to_bin, (float)(kBins - 1)); };
 #pragma unroll
-            for (int i = 0; i < IPT; ++i) {
-                if (cand[i] && (key[i] & himask) == prefix) {
-                    const int bin = (int)((key[i] >> shift) & 255u);
-                    if (bin != run_bin) {
-                        if (run_len) atomicAdd(&hist[run_bin], run_len);
-                        run_bin = bin;
-                        run_len = 0;
-                    }
-                    ++run_len;
-                }
-            }
-            if (run_len) atomicAdd(&hist[run_bin], run_len);
+        for (int i = 0; i < IPT; ++i) {
+            lo = fminf(lo, sc[i]);
+            hi = fmaxf(hi, sc[i] == INFINITY ? -INFINITY : sc[i]);
+        }
+        bool few = false;
+        for (int level = 0;; ++level) {
+            for (int i = 4 * tid; i < kBins * kCopies; i += 4 * kSelThreads) *reinterpret_cast<int4*>(&hist[i]) = make_int4(0, 0, 0, 0);
+            if (tid == 0) n_cand = 0;
+            min_max(lo, hi);
+            if (lo == hi || level == kLevels) break;
+            to_bin = fminf((float)kBins / (hi - lo), 3e38f);
+#pragma unroll
+            for (int i = 0; i < IPT; ++i)
+                if (sc[i] >= lo && sc[i] <= hi) atomicAdd(&hist[bin_of(sc[i]) * kCopies + (lane & (kCopies - 1))], 1);
             __syncthreads();
-            const int cnt = tid < 256 ? hist[tid] : 0;
+            int c0 = 0, c1 = 0;
+#pragma unroll
+            for (int c = 0; c < kCopies; ++c) { c0 += hist[2 * tid * kCopies + c]; c1 += hist[(2 * tid + 1) * kCopies + c]; }
             int total;
-            const int before = block_excl_scan(cnt, scan_lds, &total);
-            if (tid < 256 && before < k && k <= before + cnt) {
-                sel_prefix = prefix | ((unsigned)tid << shift);
-                sel_k = k - before;
+            const int before = block_excl_scan(c0 + c1, scan_lds, &total);
+            if (before < k && k <= before + c0) { sel_u = 2 * tid; sel_k = k - before; sel_cnt = c0; }
+            else if (before + c0 < k && k <= before + c0 + c1) { sel_u = 2 * tid + 1; sel_k = k - before - c0; sel_cnt = c1; }
+            __syncthreads();
+            bin = (int)sel_u;
+            k = sel_k;
+            cnt = sel_cnt;
+            few = cnt <= kMaxCand;
+            if (few) break;
+            float lo2 = INFINITY, hi2 = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < IPT; ++i)
+                if (sc[i] >= lo && sc[i] <= hi && bin_of(sc[i]) == bin) { lo2 = fminf(lo2, sc[i]); hi2 = fmaxf(hi2, sc[i]); }
+            lo = lo2;
+            hi = hi2;
+        }
+        bool tie = false;   // the wanted token is the k-th of those with score tf_, in token order
+        if (few) {
+#pragma unroll
+            for (int i = 0; i < IPT; ++i)
+                if (sc[i] >= lo && sc[i] <= hi && bin_of(sc[i]) == bin) {
+                    const int c = atomicAdd(&n_cand, 1);
+                    cand[c] = sc[i];
+                    cand_idx[c] = i * kSelThreads + tid;
+                }
+            __syncthreads();
+            if (tid < cnt) {
+                const float mine = cand[tid];
+                const int my_idx = cand_idx[tid];
+                int rank = 0;
+                for (int c = 0; c < cnt; ++c) {
+                    const float other = cand[c];
+                    rank += (other < mine || (other == mine && cand_idx[c] < my_idx)) ? 1 : 0;
+                }
+                if (rank == k - 1) { sel_f = mine; sel_k = my_idx; }
             }
             __syncthreads();
-            prefix = sel_prefix;
-            k = sel_k;
+            tf_ = sel_f;
+            tidx = sel_k;
+        } else if (lo == hi) {
+            tf_ = lo;
+            tie = true;
+        } else {
+            unsigned prefix = 0;
+            k = want;  // 1-based rank still to find inside the current prefix bucket
+            for (int pass = 0; pass < 4; ++pass) {
+                const int shift = 24 - 8 * pass;
+                const unsigned himask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
+                if (tid < 256) hist[tid] = 0;
+                __syncthreads();
+                for (int i = 0; i < IPT; ++i) {
+                    const unsigned key = f2key(sc[i]);
+                    if (sc[i] != INFINITY && (key & himask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
+                }
+                __syncthreads();
+                const int c = tid < 256 ? hist[tid] : 0;
+                int total;
+                const int before = block_excl_scan(c, scan_lds, &total);
+                if (tid < 256 && before < k && k <= before + c) {
+                    sel_u = prefix | ((unsigned)tid << shift);
+                    sel_k = k - before;
+                }
+                __syncthreads();
+                prefix = sel_u;
+                k = sel_k;
+                __syncthreads();
+            }
+            tf_ = key2f(prefix);
+            tie = true;
+        }
+        if (tie) {
+            unsigned long long eq[IPT];
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) eq[i] = __ballot(sc[i] == tf_);
+            ordered_bases<IPT>(eq, base, scan_lds);
+#pragma unroll
+            for (int i = 0; i < IPT; ++i)
+                if (((eq[i] >> lane) & 1) && base[i * kSelWaves + wave] + rank_below(eq[i]) == k - 1)
+                    sel_k = i * kSelThreads + tid;
             __syncthreads();
-        }
-        tkey = prefix;
-        k_eq = k;
-    }
-    if (tid == 0 && tau) tau[b] = all ? INFINITY : (none ? -INFINITY : key2f(tkey));
-
-    // rank of this thread's threshold-equal tokens among all of them, in index order
-    int n_eq = 0;
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) n_eq += (cand[i] && !all && !none && key[i] == tkey) ? 1 : 0;
-    int total_eq;
-    int eq_rank = block_excl_scan(n_eq, scan_lds, &total_eq);
-
-    bool kept[IPT];
-    int n_kept = 0;
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        const int t = t0 + i;
-        bool kflag;
-        if (t >= n)
-            kflag = false;
-        else if (all || t < forced)
-            kflag = true;
-        else if (none)
-            kflag = false;
-        else if (key[i] < tkey)
-            kflag = true;
-        else if (key[i] == tkey)
-            kflag = eq_rank++ < k_eq;
-        else
-            kflag = false;
-        kept[i] = kflag;
-        n_kept += kflag ? 1 : 0;
-    }
-    int total_kept;
-    int pos = block_excl_scan(n_kept, scan_lds, &total_kept);
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        const int t = t0 + i;
-        if (t < n) kp[t] = kept[i] ? 1 : 0;
-        if (kept[i]) {
-            if (pos < m) out[pos] = t;
-            ++pos;
+            tidx = sel_k;
         }
     }
+    if (tid == 0 && tau) tau[b] = all ? INFINITY : (none ? -INFINITY : tf_);
+
+    unsigned long long kept[IPT];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+        const int t = i * kSelThreads + tid;
+        const bool chosen = !none && (sc[i] < tf_ || (sc[i] == tf_ && t <= tidx));
+        const bool mine = t < n && (all || t < forced || chosen);
+        kept[i] = __ballot(mine);
+        if (t < n) kp[t] = mine ? 1 : 0;
+    }
+    ordered_bases<IPT>(kept, base, scan_lds);
+#pragma unroll
+    for (int i = 0; i < IPT; ++i)
+        if ((kept[i] >> lane) & 1) {
+            const int pos = base[i * kSelWaves + wave] + rank_below(kept[i]);
+            if (pos < m) out[pos] = i * kSelThreads + tid;
+        }
 }
 
 // ------------------------------------------------------------------------------ online decision
@@ -464,7 +566,9 @@ hipError_t launch_select_compact(const Dims& d, int warmup, const float* fused, 
                                  int32_t* kept_idx, float* tau, hipStream_t s)
 {
     const int ipt = (d.n + kSelThreads - 1) / kSelThreads;
-    if (ipt <= 4)
+    if (ipt <= 1)
+        select_compact_kernel<1><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);
+    else if (ipt <= 4)
         select_compact_kernel<4><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);
     else if (ipt <= 8)
         select_compact_kernel<8><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);

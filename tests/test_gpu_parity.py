@@ -306,6 +306,39 @@ def test_select_bit_exact_on_identical_scores(ctx, case):
     np.testing.assert_array_equal(buf.tau.cpu().numpy(), tau_r)
 
 
+@pytest.mark.parametrize("kind", ["spread", "two_values", "equal", "outlier", "wide", "few_bins"])
+@pytest.mark.parametrize("n", [1, 2, 63, 1023, 1024, 1025, 4096, 4097, 8193, 32767, 32768])
+def test_select_histogram_and_its_fallback(ctx, kind, n):
+    """Rows around the kernel's sizes whose scores spread over the histogram's bins, or share one bin
+    (ties, an outlier that stretches the range), so that both ways of finding the threshold run;
+    the decision is exact, so it must agree bit for bit."""
+    _say("select histogram %s n=%d" % (kind, n))
+    rng = np.random.default_rng(n + len(kind))
+    x = rng.uniform(-1, 1, (2, n))
+    if kind == "two_values":
+        x = np.where(x > 0.2, 0.75, 0.5)
+    elif kind == "equal":
+        x[:] = 0.25
+    elif kind == "outlier":
+        x[:, n // 2] = -1e30
+    elif kind == "wide":
+        x = np.sign(x) * np.exp(rng.uniform(-80, 80, x.shape))
+        x[:, 0] = -3e38
+        x[:, -1] = 3e38
+    elif kind == "few_bins":
+        x = 0.5 + np.round(x * 3) / 8 + rng.uniform(0, 1e-6, x.shape)
+    S = x.astype(np.float32)
+    for r, W in ((0.5, 1), (0.25, 0), (0.9, 5)):
+        keep_r, idx_r, tau_r = oracle.select(S, r, W)
+        p = B.make_params((2, 1, n, 128), (2, 1, n, 128), torch.float32, r, W)
+        buf = B.Buffers(p, "cuda:0")
+        ctx.tf_select(p, torch.from_numpy(S).cuda(), buf.keep, buf.kept_idx, buf.tau, buf.ws)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(buf.keep.cpu().numpy(), keep_r)
+        np.testing.assert_array_equal(buf.kept_idx.cpu().numpy(), idx_r)
+        np.testing.assert_array_equal(buf.tau.cpu().numpy(), tau_r)
+
+
 # ------------------------------------------------------------------ attention stage
 
 @pytest.mark.parametrize("shape", [
