@@ -428,13 +428,38 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
 // ------------------------------------------------------------------------------ online decision
 // Adaptive threshold (Algorithm 1 threshold / skip lines, warm-up of Section 3.2, Eq. 4): a
 // sequential recurrence over a row's tokens,
-//   tau <- fma(eta, (float)skipped * (1 / t) - target, tau);  skip iff t >= W and S_t > tau,
+//   skip iff t >= W and S_t > tau;  tau <- fma(eta, (float)skipped * (1 / (t + 1)) - target, tau),
 // all in float so that the result is reproducible bit for bit.  One workgroup per batch row
 // walks the row in chunks of kOnChunk tokens: all threads stage the chunk's scores and the
-// reciprocals 1 / t in LDS, thread 0 runs the recurrence and leaves the running count of
-// skipped tokens in place of the scores, then all threads read the decisions off the counts
-// and compact them.
+// reciprocals in LDS, wave 0 decides 64 tokens at a time, then all threads compact the decisions.
+//
+// 64 tokens at once: the decisions are guessed, the thresholds that follow from them are computed
+// for all 64 tokens together, and the decisions that follow from those replace the guess, until
+// they agree.  The first wrong guess is right the next time (all before it were), so this ends
+// after at most 64 rounds; it takes one or two, because the threshold moves little over 64 tokens.
+// The thresholds of given decisions: the skipped counts are a prefix sum of bits, so every
+// product and difference is formed as the recurrence forms it; what is left, a chain of 64 fma
+// roundings, is a prefix sum as well as long as the threshold stays inside one binade: it is then
+// a multiple of one ulp g, and rounding tau + eta * diff to a multiple of g rounds the exact
+// product eta * diff (formed in double) to a multiple of g, ties apart.  Where the threshold leaves
+// its binade or a tie occurs, the tokens before are taken, that one step is made with the fma
+// itself, and the next 64 tokens begin after it.
+// A lone wave waits about 10 cycles for every dependent result: token by token that is 30 ns each
+// (4096 tokens: 122 us); 64 at a time 11 ns each (4096 tokens: 53 us for the slowest of 8 rows,
+// 3001 tokens: 79 -> 32 us).
 constexpr int kOnChunk = 4096;
+
+// inclusive prefix sum over the wave (row_shr 1, 2, 4, 8, then row_bcast 15 and 31)
+__device__ __forceinline__ int wave_incl_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
 
 __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     const float* __restrict__ fused, int n, int warmup, float target, float eta, float tau0,
@@ -444,79 +469,98 @@ __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     // every product and difference below is rounded on its own (the only fused operations are
     // the fmaf calls): the recurrence is defined operation by operation
 #pragma clang fp contract(off)
-    __shared__ __attribute__((aligned(16))) float s_lds[kOnChunk];
-    __shared__ __attribute__((aligned(16))) float inv_lds[kOnChunk];
+    __shared__ float s_lds[kOnChunk + 64];    // scores, then decisions (1 = skipped)
+    __shared__ float inv_lds[kOnChunk + 64];
+    __shared__ int base_lds[kOnChunk / kSelThreads * kSelWaves];
     __shared__ int scan_lds[kSelWaves + 1];
-    __shared__ float skip_base;  // skipped tokens before the current chunk
 
     const int b = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* S = fused + (long long)b * n;
     uint8_t* kp = keep + (long long)b * n;
     int32_t* out = kept_idx + (long long)b * n;
 
-    // state of the recurrence (meaningful in thread 0): tau is the threshold token t0 of the
-    // next chunk will be judged with, already updated for it
-    float skipped = 0.f;  // exact in float up to 2^24 tokens
+    // state of the recurrence (meaningful in wave 0, the same in all its lanes): tau is the threshold
+    // the next token will be judged with, already updated for it
+    int skipped = 0;  // exact in float up to 2^24 tokens
     float tau = fmaf(eta, 0.f - target, tau0);
+    float drift = eta * (0.f - target);   // its latest movement (only the guess depends on it)
     float tau_judged = tau;  // the threshold the latest token was judged with
     int base = 0;            // kept tokens so far
     for (int t0 = 0; t0 < n; t0 += kOnChunk) {
         const int len = min(kOnChunk, n - t0);
-        // (warm-up tokens and the padding up to a multiple of 8 get a score that is never above
-        // the threshold, so the chain below needs no test for them)
-        for (int i = tid; i < ((len + 7) & ~7); i += kSelThreads)
+        // (warm-up tokens and the padding get a score that is never above the threshold, so the
+        // rule below needs no test for them)
+        for (int i = tid; i < len + 64; i += kSelThreads) {
             s_lds[i] = (i < len && t0 + i >= warmup) ? S[t0 + i] : -INFINITY;
-        // reciprocal of the NEXT token's index: inv_lds[i] = 1 / (t0 + i + 1)
-        for (int i = tid; i < ((len + 7) & ~7); i += kSelThreads) inv_lds[i] = 1.0f / (float)(t0 + i + 1);
+            inv_lds[i] = 1.0f / (float)(t0 + i + 1);   // reciprocal of the NEXT token's index
+        }
         __syncthreads();
-        if (tid == 0) {
-            // eight tokens at a time: their scores and reciprocals are fetched together (two
-            // 16-byte LDS reads each) and the eight steps of the chain run from registers.  A
-            // step is five dependent operations (compare, select, multiply, subtract, fma); a
-            // lone wave waits about as long for a dependent result as it takes to issue two
-            // instructions, so forming both outcomes ahead of the comparison (a shorter chain,
-            // twice the instructions) measured slower than this plain form.  The running count
-            // of skipped tokens replaces the scores in LDS: the other threads read the
-            // decisions off it afterwards (a token was skipped iff the count moved).
-            skip_base = skipped;
-            for (int i0 = 0; i0 < len; i0 += 8) {
-                float sv[8], iv[8], sk[8];
-                *reinterpret_cast<float4*>(&sv[0]) = *reinterpret_cast<const float4*>(&s_lds[i0]);
-                *reinterpret_cast<float4*>(&sv[4]) = *reinterpret_cast<const float4*>(&s_lds[i0 + 4]);
-                *reinterpret_cast<float4*>(&iv[0]) = *reinterpret_cast<const float4*>(&inv_lds[i0]);
-                *reinterpret_cast<float4*>(&iv[4]) = *reinterpret_cast<const float4*>(&inv_lds[i0 + 4]);
-                float tau_in[8];  // the threshold each of the eight tokens is judged with
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    tau_in[u] = tau;
-                    const float s1 = skipped + 1.f;
-                    skipped = sv[u] > tau ? s1 : skipped;
-                    const float p_next = skipped * iv[u];
-                    const float diff = p_next - target;
-                    tau = fmaf(eta, diff, tau);
-                    sk[u] = skipped;
+        if (wave == 0) {
+            float s_u = s_lds[lane], inv = inv_lds[lane];
+            for (int i0 = 0; i0 < len;) {
+                const int ahead = min(i0 + 64, len) + lane;   // the next 64, if all of these are taken
+                const float s_next = s_lds[ahead], inv_next = inv_lds[ahead];
+                // tau as a multiple of its ulp
+                const unsigned tau_bits = __builtin_bit_cast(unsigned, tau);
+                const int ex = (int)((tau_bits >> 23) & 255u) - 127;
+                const bool grid = ex > -100 && ex < 127;   // an ordinary number
+                const int mant = (int)((tau_bits & 0x7fffffu) | 0x800000u);
+                const float ulp = __builtin_bit_cast(float, (unsigned)max(ex - 23 + 127, 1) << 23);
+                // eta in ulps; its sign makes up for tau's, so that magnitudes are added
+                const double per_ulp = __builtin_bit_cast(double, (unsigned long long)(1023 + 23 - ex) << 52);
+                const double eta_ulp = (tau_bits >> 31) ? -(double)eta * per_ulp : (double)eta * per_ulp;
+                unsigned long long d = __ballot(s_u > fmaf((float)lane, drift, tau));
+                float tau_u, diff;
+                int taken;   // tokens 0 .. taken - 1 of the 64 are decided
+                for (;;) {
+                    const int cnt = skipped + rank_below(d) + (int)((d >> lane) & 1);
+                    const float p_next = (float)cnt * inv;
+                    diff = p_next - target;
+                    const double steps = eta_ulp * (double)diff;   // exact
+                    const double whole = rint(steps);
+                    const bool odd = !(fabs(steps) < 8388608.0) || fabs(steps - whole) == 0.5;
+                    const int mag = mant + wave_incl_scan(odd ? 0 : (int)whole);   // at most 65 * 2^23
+                    // the first token whose step is not a plain sum
+                    const unsigned long long stop = __ballot(!grid || odd || mag <= 0x800000 || mag >= 0x1000000);
+                    const int j = stop ? __builtin_ctzll(stop) : 64;
+                    const float mag_f = (float)mag * ulp;
+                    const float after = (tau_bits >> 31) ? -mag_f : mag_f;
+                    // wave_shr 1: the threshold after the token before
+                    tau_u = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                        __builtin_bit_cast(int, tau), __builtin_bit_cast(int, after), 0x138, 0xf, 0xf, false));
+                    const unsigned long long seen = __ballot(s_u > tau_u);
+                    const unsigned long long known = j >= 63 ? ~0ull : (2ull << j) - 1;   // thresholds 0 .. j
+                    taken = min(j + 1, 64);
+                    if (((seen ^ d) & known) == 0) break;
+                    d = (seen & known) | (d & ~known);
                 }
-                *reinterpret_cast<float4*>(&s_lds[i0]) = *reinterpret_cast<const float4*>(&sk[0]);
-                *reinterpret_cast<float4*>(&s_lds[i0 + 4]) = *reinterpret_cast<const float4*>(&sk[4]);
-                if (i0 + 8 >= len) {  // the group that holds the row's last token
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (t0 + i0 + u == n - 1) tau_judged = tau_in[u];
-                }
+                taken = min(taken, len - i0);
+                if (lane < taken) s_lds[i0 + lane] = (d >> lane) & 1 ? 1.f : 0.f;
+                tau_judged = __shfl(tau_u, taken - 1);
+                tau = __shfl(fmaf(eta, diff, tau_u), taken - 1);
+                drift = tau - tau_judged;
+                skipped += __popcll(d & (taken == 64 ? ~0ull : (1ull << taken) - 1));
+                i0 += taken;
+                s_u = s_next;
+                inv = inv_next;
+                if (taken < 64 && i0 < len) { s_u = s_lds[i0 + lane]; inv = inv_lds[i0 + lane]; }
             }
         }
         __syncthreads();
-        for (int i0 = 0; i0 < len; i0 += kSelThreads) {
-            const int i = i0 + tid;
-            // kept iff the count of skipped tokens did not move at token i
-            const int flag = i < len ? (s_lds[i] == (i > 0 ? s_lds[i - 1] : skip_base)) : 0;
-            int total;
-            const int pos = base + block_excl_scan(flag, scan_lds, &total);
-            base += total;
-            if (i < len) kp[t0 + i] = (uint8_t)flag;
-            if (flag) out[pos] = t0 + i;
+        unsigned long long kept[kOnChunk / kSelThreads];
+#pragma unroll
+        for (int i = 0; i < kOnChunk / kSelThreads; ++i) {
+            const int t = i * kSelThreads + tid;
+            const bool mine = t < len && s_lds[t] == 0.f;
+            kept[i] = __ballot(mine);
+            if (t < len) kp[t0 + t] = mine ? 1 : 0;
         }
+        const int chunk_kept = ordered_bases<kOnChunk / kSelThreads>(kept, base_lds, scan_lds);
+#pragma unroll
+        for (int i = 0; i < kOnChunk / kSelThreads; ++i)
+            if ((kept[i] >> lane) & 1) out[base + base_lds[i * kSelWaves + wave] + rank_below(kept[i])] = t0 + i * kSelThreads + tid;
+        base += chunk_kept;
         __syncthreads();
     }
     for (int i = base + tid; i < n; i += kSelThreads) out[i] = -1;

@@ -878,6 +878,38 @@ def test_attend_ragged_rows(ctx, dt):
         assert np.all(O_g[b][:, filtered] == 0)
 
 
+@pytest.mark.parametrize("case", [
+    # (target, eta, tau0, W): thresholds that leave their binade again and again, pass zero, are
+    # negative, tie (powers of two), never move, jump by many binades
+    (0.5, 0.02, 0.5, 8), (0.5, 0.3, 0.01, 0), (0.3, 0.05, -0.2, 1), (0.5, 0.25, 0.5, 0),
+    (0.5, 2.0 ** -24, 0.75, 0), (0.5, 0.0, 0.4, 3), (0.9, 1e4, 0.1, 0), (0.1, 1e-6, 0.3, 2),
+])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 1000, 4095, 4097, 8200])
+def test_select_online_groups_of_64(ctx, case, n):
+    """Rows around the groups of 64 and chunks of 4096, scores in runs (guesses hold), spread (they
+    hold mostly) and on few values (they equal the threshold at times): bit for bit."""
+    target, eta, tau0, W = case
+    _say("select online groups %s n=%d" % (case, n))
+    rng = np.random.default_rng(n)
+    S = np.empty((3, n), dtype=np.float32)
+    S[0] = np.repeat(rng.uniform(-0.2, 1, n // 8 + 1), 8)[:n]
+    S[1] = rng.uniform(-0.5, 1, n)
+    S[2] = np.round(rng.uniform(0, 1, n) * 4) / 4
+    keep_r, idx_r, cnt_r, tau_r = oracle.select_online(S, target, eta, tau0, W)
+    p = B.make_params((3, 1, n, 128), (3, 1, n, 128), torch.float32, target, W)
+    ws = torch.empty(B.tf_workspace_bytes(p), dtype=torch.uint8, device="cuda:0")
+    keep = torch.empty((3, n), dtype=torch.uint8, device="cuda:0")
+    idx = torch.empty((3, n), dtype=torch.int32, device="cuda:0")
+    cnt = torch.empty(3, dtype=torch.int32, device="cuda:0")
+    tau = torch.empty(3, dtype=torch.float32, device="cuda:0")
+    ctx.tf_select_online(p, eta, tau0, torch.from_numpy(S).cuda(), keep, idx, cnt, tau, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(keep.cpu().numpy(), keep_r)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_r)
+    np.testing.assert_array_equal(idx.cpu().numpy(), idx_r)
+    np.testing.assert_array_equal(tau.cpu().numpy(), tau_r)
+
+
 @pytest.mark.parametrize("wl", [0, 1])
 def test_whole_path_online_threshold(ctx, wl):
     _say("whole path online cfg%d" % (wl + 1))
