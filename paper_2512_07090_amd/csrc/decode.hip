@@ -327,47 +327,67 @@ __global__ __launch_bounds__(128) void decode_merge_kernel(const float* __restri
 }
 
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
-// One workgroup per (tensor, batch row, KV head); a 16-lane group folds every 16th row in
-// Horner form, A <- g^16 A + x (g = 1 for the exact mean, whose state is the plain sum), brings
-// its partial to the end of the prompt with g^(rows after its last one), and the 16 partials
-// are added through LDS.  All in double.  Rows further back than `window` from the end are
-// skipped (the incremental anchor forgets them: g^window is far below double resolution).
-template <typename T>
-__global__ __launch_bounds__(256) void decode_seed_anchor_kernel(
+// One workgroup per (tensor, batch row, KV head) and 8 * LANES columns: a group of LANES lanes folds
+// every (1024 / LANES)-th row in Horner form, A <- g^stride A + x (g = 1 for the exact mean, whose
+// state is the plain sum), brings its partial to the end of the prompt with g^(rows after its last
+// one), and the partials are added through shuffles and LDS.  All in double.  Rows further back
+// than `window` from the end are skipped (the incremental anchor forgets them: g^window is far
+// below double resolution).
+// What bounds it is the latency of a thread's loads, one row after the other, so the rows are spread
+// over many groups and four are in flight per group; with few chains (LANES = 4: a quarter of the
+// columns each) there are four times the workgroups.  16 chains x 3001 rows: 62 -> 9 us against
+// 16 groups of 16 lanes.
+template <typename T, int LANES>
+__global__ __launch_bounds__(1024) void decode_seed_anchor_kernel(
     const T* __restrict__ K, const T* __restrict__ V, double* __restrict__ anchor_k,
     double* __restrict__ anchor_v, int Hkv, int n, long long s_b, long long s_h, long long s_t,
     double g, double weight, int window)
 {
-    __shared__ double part[16][kHeadDim];
-    const int w = blockIdx.x & 1, bh = blockIdx.x >> 1;
+    constexpr int kGroups = 1024 / LANES, kParts = 16 / LANES;   // row groups; workgroups per chain
+    __shared__ double part[16][8 * LANES];
+    const int q = blockIdx.x % kParts, chain = blockIdx.x / kParts;
+    const int w = chain & 1, bh = chain >> 1;
     const int b = bh / Hkv, h = bh % Hkv;
-    const int grp = threadIdx.x >> 4, c8 = threadIdx.x & 15;
-    const T* X = (w ? V : K) + b * s_b + h * s_h + c8 * 8;
-    double g16 = g;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) g16 *= g16;
+    const int grp = threadIdx.x / LANES, c8 = threadIdx.x % LANES;
+    const T* X = (w ? V : K) + b * s_b + h * s_h + (q * LANES + c8) * 8;
+    double g_step = g;
+    for (int i = 1; i < kGroups; i *= 2) g_step *= g_step;
     double a[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) a[c] = 0.0;
     const int j0 = (n - window > 0 ? n - window : 0);
     int last = -1;
-    for (int j = j0 + grp; j < n; j += 16) {
-        float x[8];
-        load8(X + (long long)j * s_t, x);
+    for (int j = j0 + grp; j < n; j += 4 * kGroups) {
+        float x[4][8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) a[c] = g16 * a[c] + (double)x[c];
-        last = j;
+        for (int u = 0; u < 4; ++u) load8(X + (long long)min(j + u * kGroups, n - 1) * s_t, x[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j + u * kGroups < n) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) a[c] = g_step * a[c] + (double)x[u][c];
+                last = j + u * kGroups;
+            }
     }
-    double tail = weight;  // weight * g^(n - 1 - last)
-    for (int i = last; last >= 0 && i < n - 1; ++i) tail *= g;
+    double tail = last >= 0 ? weight : 0.0;  // weight * g^(n - 1 - last)
+    double pw = g;
+    for (int e = last >= 0 ? n - 1 - last : 0; e > 0; e >>= 1) {
+        if (e & 1) tail *= pw;
+        pw *= pw;
+    }
 #pragma unroll
-    for (int c = 0; c < 8; ++c) part[grp][c8 * 8 + c] = last >= 0 ? a[c] * tail : 0.0;
+    for (int c = 0; c < 8; ++c) {
+        double v = a[c] * tail;
+#pragma unroll
+        for (int step = LANES; step < 64; step *= 2) v += __shfl_xor(v, step);
+        if ((threadIdx.x & 63) < LANES) part[threadIdx.x >> 6][c8 * 8 + c] = v;
+    }
     __syncthreads();
-    if (threadIdx.x < kHeadDim) {
+    if (threadIdx.x < 8 * LANES) {
         double sum = 0.0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) sum += part[q][threadIdx.x];
-        (w ? anchor_v : anchor_k)[(long long)bh * kHeadDim + threadIdx.x] = sum;
+        for (int i = 0; i < 16; ++i) sum += part[i][threadIdx.x];
+        (w ? anchor_v : anchor_k)[(long long)bh * kHeadDim + q * 8 * LANES + threadIdx.x] = sum;
     }
 }
 
@@ -405,8 +425,15 @@ hipError_t launch_decode_seed_t(const DecodeArgs& a, const T* K, const T* V, con
         const double rows = g > 0.0 ? ceil(-92.2 / log(g)) : 1.0;
         window = rows < (double)n ? (int)rows : n;
     }
-    decode_seed_anchor_kernel<T><<<dim3(2 * a.B * a.Hkv), dim3(256), 0, s>>>(
-        K, V, a.anchor_k, a.anchor_v, a.Hkv, n, kvs[0], kvs[1], kvs[2], g, a.ema ? 1.0 - a.gamma : 1.0, window);
+    const double wt = a.ema ? 1.0 - a.gamma : 1.0;
+    const int chains = 2 * a.B * a.Hkv;
+    // below one workgroup per two compute units a chain's columns are shared out
+    if (chains < 128)
+        decode_seed_anchor_kernel<T, 4><<<dim3(4 * chains), dim3(1024), 0, s>>>(
+            K, V, a.anchor_k, a.anchor_v, a.Hkv, n, kvs[0], kvs[1], kvs[2], g, wt, window);
+    else
+        decode_seed_anchor_kernel<T, 16><<<dim3(chains), dim3(1024), 0, s>>>(
+            K, V, a.anchor_k, a.anchor_v, a.Hkv, n, kvs[0], kvs[1], kvs[2], g, wt, window);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     decode_seed_cache_kernel<T><<<dim3((n + 15) / 16, a.B * a.Hkv), dim3(256), 0, s>>>(
