@@ -1,8 +1,8 @@
 // Per-token form of the layer (Algorithm 1 called once per new token): score the new key and
 // value against the caller-held anchors, move the threshold, decide, absorb the token into the
 // anchors, append a kept token to the cache of kept keys / values and attend over that cache.
-// Three launches per step: decode_score_kernel (one workgroup per batch row), the split
-// attention over the cache, and the merge of the splits.
+// Two launches per step: decode_score_kernel (one workgroup per batch row) and the attention over
+// the cache, split over workgroups of which the last to end merges the slices.
 #include <algorithm>
 
 #include "tf_kernels.h"
@@ -33,6 +33,24 @@ __device__ __forceinline__ void load8(const float* p, float* x)
     x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
     x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
+// the same in two steps: the bytes, and the floats they hold
+template <typename T> struct Raw8;
+template <> struct Raw8<uint16_t> { typedef uint4 type; };
+template <> struct Raw8<float> { struct type { float4 lo, hi; }; };
+__device__ __forceinline__ void unpack8(uint4 r, float* x)
+{
+    const unsigned w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        x[2 * i] = __uint_as_float(w[i] << 16);
+        x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+}
+__device__ __forceinline__ void unpack8(const Raw8<float>::type& r, float* x)
+{
+    x[0] = r.lo.x; x[1] = r.lo.y; x[2] = r.lo.z; x[3] = r.lo.w;
+    x[4] = r.hi.x; x[5] = r.hi.y; x[6] = r.hi.z; x[7] = r.hi.w;
+}
 __device__ __forceinline__ void copy8(uint16_t* dst, const uint16_t* src)
 {
     *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
@@ -49,12 +67,23 @@ __device__ __forceinline__ void store_out(uint16_t* p, float v)
 }
 __device__ __forceinline__ void store_out(float* p, float v) { *p = v; }
 
+// A double moved between lanes of its 16-lane row in the VALU (two 32-bit DPP moves): the shuffles
+// that go through LDS were most of the scoring kernel's latency.
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ double dpp_mov_f64(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROW_MASK, 0xf, false);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROW_MASK, 0xf, false);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+// sum over each aligned group of 16 lanes; every lane ends with the total
 __device__ __forceinline__ double group16_sum(double v)
 {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 8);
+    v += dpp_mov_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_mov_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+    v += dpp_mov_f64<0x141>(v);  // row_half_mirror
+    v += dpp_mov_f64<0x140>(v);  // row_mirror
     return v;
 }
 
@@ -76,9 +105,12 @@ __global__ void decode_init_kernel(double* anchor_k, double* anchor_v, long long
 #pragma clang fp contract(off)
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int s = 1; s < 64; s *= 2) v += __shfl_xor(v, s);
-    return v;
+    v = group16_sum(v);
+    v += dpp_mov_f64<0x142, 0xa>(v);   // row_bcast 15: rows 1 and 3 add the row before them
+    v += dpp_mov_f64<0x143, 0xc>(v);   // row_bcast 31: rows 2 and 3 add rows 0 and 1
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);   // lane 63 holds the sum
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, 63), hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), 63);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
 }
 
 template <typename T>
@@ -88,13 +120,15 @@ __global__ __launch_bounds__(1024) void decode_score_kernel(
     float* __restrict__ tau, int32_t* __restrict__ cache_len, int32_t* __restrict__ overflow,
     T* __restrict__ k_cache, T* __restrict__ v_cache, int capacity, int Hkv, int ema, double gamma,
     int inclusive, int fusion, int warmup, float target, float eta,
-    uint8_t* __restrict__ skip_out, float* __restrict__ fused_out)
+    uint8_t* __restrict__ skip_out, float* __restrict__ fused_out, int32_t* __restrict__ tickets,
+    int n_tickets)
 {
     __shared__ double cosb[2][128];
     __shared__ int slot_s;
     const int b = blockIdx.x;
     const int grp = threadIdx.x >> 4, c8 = threadIdx.x & 15, n_grp = blockDim.x >> 4;
     const int t = seen[b];
+    for (int i = threadIdx.x; i < n_tickets; i += blockDim.x) tickets[b * n_tickets + i] = 0;
     int n_skipped = 0, len = 0;
     float th_old = 0.f;
     if (threadIdx.x == 0) { n_skipped = skipped[b]; len = cache_len[b]; th_old = tau[b]; }
@@ -196,48 +230,90 @@ __global__ __launch_bounds__(1024) void decode_score_kernel(
 }
 #pragma clang fp contract(fast)
 
+// sum over the four lanes that share lane % 16
+__device__ __forceinline__ float wave_group_sum(float v)
+{
+    const FloatPair a = swap16(v, v);
+    v = a.first + a.second;
+    const FloatPair b = swap32(v, v);
+    return b.first + b.second;
+}
+__device__ __forceinline__ float wave_group_max(float v)
+{
+    const FloatPair a = swap16(v, v);
+    v = fmaxf(a.first, a.second);
+    const FloatPair b = swap32(v, v);
+    return fmaxf(b.first, b.second);
+}
+
+// A float to or from memory past the caches that are not shared between the dies (relaxed, device
+// scope): written and read this way, a partial result needs no cache to be written back or
+// invalidated on its way from one workgroup to another.
+__device__ __forceinline__ void put_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get_shared(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // Attention of the new token over one slice of its row's cache, for the G query heads that
 // share a KV head.  A 16-lane group owns every 16th key of the slice and keeps its own running
-// (max, sum, numerators); groups are merged through shuffles and LDS, the slices by
-// decode_merge_kernel.  Partial result per (row, query head, slice): kPartStride floats.
+// (max, sum, numerators), four keys at a time with the next four already requested; groups are
+// merged through shuffles and LDS.  With one slice the result is final; with more, each slice
+// leaves a partial result of kPartStride floats per query head, and the workgroup that draws the
+// last ticket of its heads merges them (no order among the slices is assumed, and nobody
+// waits).  A skipped row's first slice writes the zero row.
 template <typename T, int G>
-__global__ __launch_bounds__(256) void decode_attend_kernel(
+__global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_attend_kernel(
     const T* __restrict__ q, const T* __restrict__ k_cache, const T* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
-    float* __restrict__ part, int Hq, int Hkv, int capacity, int n_split, float scale_log2e)
+    float* __restrict__ part, int32_t* __restrict__ tickets, T* __restrict__ o, int Hq, int Hkv,
+    int capacity, int n_split, float scale_log2e)
 {
     __shared__ float merge[4][G][kPartStride];
+    __shared__ float weight[G][kDecodeMaxSplit + 1];
+    __shared__ int drawn;
     const int sp = blockIdx.x % n_split;
     const int hg = (blockIdx.x / n_split) % (Hq / G);  // group of G query heads
     const int b = blockIdx.x / n_split / (Hq / G);
-    if (skip[b]) return;  // the merge kernel writes the zero row
     const int hq0 = hg * G, hk = hq0 / (Hq / Hkv);
     const int len = cache_len[b];
-    int chunk = (len + n_split - 1) / n_split;
-    chunk = (chunk + 15) & ~15;
-    const int lo = sp * chunk, hi = min(len, lo + chunk);
+    const bool skipped = skip[b] != 0;
     const int grp = threadIdx.x >> 4, c8 = threadIdx.x & 15, wave = threadIdx.x >> 6;
+    T* const out = o + ((long long)b * Hq + hq0) * kHeadDim;
 
     float qf[G][8], acc[G][8], mx[G], sum[G];
 #pragma unroll
+    for (int g = 0; g < G; ++g) load8(q + ((long long)b * Hq + hq0 + g) * kHeadDim + c8 * 8, qf[g]);
+    if (skipped) {
+        if (sp == 0)
+            for (int i = threadIdx.x; i < G * kHeadDim; i += 256) store_out(out + i, 0.f);
+        return;
+    }
+#pragma unroll
     for (int g = 0; g < G; ++g) {
-        load8(q + ((long long)b * Hq + hq0 + g) * kHeadDim + c8 * 8, qf[g]);
 #pragma unroll
         for (int c = 0; c < 8; ++c) { qf[g][c] *= scale_log2e; acc[g][c] = 0.f; }
         mx[g] = kLowest; sum[g] = 0.f;
     }
+    int chunk = (len + n_split - 1) / n_split;
+    chunk = (chunk + 15) & ~15;
+    const int lo = sp * chunk, hi = min(len, lo + chunk);
     const long long row0 = ((long long)b * Hkv + hk) * capacity;
     const T* kb = k_cache + row0 * kHeadDim + c8 * 8;
     const T* vb = v_cache + row0 * kHeadDim + c8 * 8;
 
-    for (int j = lo + grp; j < hi; j += 64) {
-        float kk[4][8], vv[4][8];
+    typename Raw8<T>::type k_raw[4], v_raw[4];
+    auto request = [&](int j) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int ju = min(j + 16 * u, hi - 1);  // a valid row; its score is discarded below
-            load8(kb + (long long)ju * kHeadDim, kk[u]);
-            load8(vb + (long long)ju * kHeadDim, vv[u]);
+            k_raw[u] = *reinterpret_cast<const typename Raw8<T>::type*>(kb + (long long)ju * kHeadDim);
+            v_raw[u] = *reinterpret_cast<const typename Raw8<T>::type*>(vb + (long long)ju * kHeadDim);
         }
+    };
+    if (lo + grp < hi) request(lo + grp);
+    for (int j = lo + grp; j < hi; j += 64) {
+        float kk[4][8], vv[4][8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { unpack8(k_raw[u], kk[u]); unpack8(v_raw[u], vv[u]); }
+        if (j + 64 < hi) request(j + 64);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             float s[4];
@@ -250,10 +326,10 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(
                 s[u] = (j + 16 * u < hi) ? d : kLowest;
             }
             const float m_new = fmaxf(fmaxf(mx[g], fmaxf(s[0], s[1])), fmaxf(s[2], s[3]));
-            const float scale_old = exp2f(mx[g] - m_new);
+            const float scale_old = __builtin_amdgcn_exp2f(mx[g] - m_new);
             float p[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) p[u] = exp2f(s[u] - m_new);
+            for (int u = 0; u < 4; ++u) p[u] = __builtin_amdgcn_exp2f(s[u] - m_new);
             sum[g] = fmaf(sum[g], scale_old, (p[0] + p[1]) + (p[2] + p[3]));
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
@@ -269,16 +345,13 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(
     // merge the four groups of a wave (lanes 16 and 32 apart), then the four waves through LDS
 #pragma unroll
     for (int g = 0; g < G; ++g) {
+        // (half swaps in the VALU; the exponent is at most 0)
+        const float m_wave = wave_group_max(mx[g]);
+        const float w_me = __builtin_amdgcn_exp2f(mx[g] - m_wave);
+        mx[g] = m_wave;
+        sum[g] = wave_group_sum(sum[g] * w_me);
 #pragma unroll
-        for (int step = 16; step <= 32; step *= 2) {
-            const float m_o = __shfl_xor(mx[g], step);
-            const float m_new = fmaxf(mx[g], m_o);
-            const float w_me = exp2f(mx[g] - m_new), w_o = exp2f(m_o - m_new);
-            sum[g] = sum[g] * w_me + __shfl_xor(sum[g], step) * w_o;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc[g][c] = acc[g][c] * w_me + __shfl_xor(acc[g][c], step) * w_o;
-            mx[g] = m_new;
-        }
+        for (int c = 0; c < 8; ++c) acc[g][c] = wave_group_sum(acc[g][c] * w_me);
         if ((threadIdx.x & 63) < 16) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) merge[wave][g][c8 * 8 + c] = acc[g][c];
@@ -286,44 +359,59 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < G * kPartStride; i += blockDim.x) {
+    float* const part0 = part + ((long long)b * Hq + hq0) * n_split * kPartStride;   // [head][slice]
+    for (int i = threadIdx.x; i < G * kPartStride; i += 256) {
         const int g = i / kPartStride, c = i - g * kPartStride;
         float m_all = kLowest;
 #pragma unroll
         for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, merge[w][g][kHeadDim]);
-        float out;
-        if (c == kHeadDim) {
-            out = m_all;
-        } else {
-            out = 0.f;
+        float v = m_all, den = 0.f;
+        if (c != kHeadDim) {
+            v = 0.f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) out = fmaf(merge[w][g][c], exp2f(merge[w][g][kHeadDim] - m_all), out);
+            for (int w = 0; w < 4; ++w) {
+                const float wt = __builtin_amdgcn_exp2f(merge[w][g][kHeadDim] - m_all);
+                v = fmaf(merge[w][g][c], wt, v);
+                den = fmaf(merge[w][g][kHeadDim + 1], wt, den);
+            }
         }
-        part[(((long long)b * Hq + hq0 + g) * n_split + sp) * kPartStride + c] = out;
+        if (n_split > 1) put_shared(part0 + ((long long)g * n_split + sp) * kPartStride + c, v);
+        else if (c < kHeadDim) store_out(out + g * kHeadDim + c, v / den);
     }
-}
+    if (n_split == 1) return;
 
-// One workgroup of 128 threads per (row, query head): weighted sum of the slices' partial
-// results, or the zero row of a skipped token.
-template <typename T>
-__global__ __launch_bounds__(128) void decode_merge_kernel(const float* __restrict__ part,
-                                                           const uint8_t* __restrict__ skip,
-                                                           T* __restrict__ o, int Hq, int n_split)
-{
-    const int b = blockIdx.x / Hq;
-    const int c = threadIdx.x;
-    T* out = o + (long long)blockIdx.x * kHeadDim + c;
-    if (skip[b]) { store_out(out, 0.f); return; }
-    const float* pr = part + (long long)blockIdx.x * n_split * kPartStride;
-    float m_all = kLowest;
-    for (int s = 0; s < n_split; ++s) m_all = fmaxf(m_all, pr[s * kPartStride + kHeadDim]);
-    float num = 0.f, den = 0.f;
-    for (int s = 0; s < n_split; ++s) {
-        const float w = exp2f(pr[s * kPartStride + kHeadDim] - m_all);
-        num = fmaf(pr[s * kPartStride + c], w, num);
-        den = fmaf(pr[s * kPartStride + kHeadDim + 1], w, den);
+    // every partial result of this workgroup is in memory before its ticket is drawn
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add(&tickets[b * (Hq / G) + hg], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (drawn != n_split - 1) return;
+
+    // weights of the slices, per head, and the reciprocal of their weighted sum behind them
+    for (int g = wave; g < G; g += 4) {
+        const int l = threadIdx.x & 63;
+        const float* pr = part0 + ((long long)g * n_split + l) * kPartStride;
+        const float m_l = l < n_split ? get_shared(pr + kHeadDim) : kLowest;
+        const float s_l = l < n_split ? get_shared(pr + kHeadDim + 1) : 0.f;
+        float m_all = m_l;
+#pragma unroll
+        for (int step = 1; step < 64; step *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, step));
+        const float wt = __builtin_amdgcn_exp2f(m_l - m_all);
+        float den = s_l * wt;
+#pragma unroll
+        for (int step = 1; step < 64; step *= 2) den += __shfl_xor(den, step);
+        if (l < n_split) weight[g][l] = wt;
+        if (l == 0) weight[g][kDecodeMaxSplit] = den;
     }
-    store_out(out, num / den);
+    __syncthreads();
+    for (int i = threadIdx.x; i < G * kHeadDim; i += 256) {
+        const int g = i / kHeadDim, c = i % kHeadDim;
+        const float* pr = part0 + (long long)g * n_split * kPartStride + c;
+        float num = 0.f;
+#pragma unroll 8
+        for (int l = 0; l < n_split; ++l) num = fmaf(get_shared(pr + l * kPartStride), weight[g][l], num);
+        store_out(out + i, num / weight[g][kDecodeMaxSplit]);
+    }
 }
 
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
@@ -447,30 +535,47 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
                                 hipStream_t s)
 {
     const int threads = std::min(1024, (32 * a.Hkv + 63) / 64 * 64);  // 16 lanes per (tensor, head)
+    const int g = decode_heads_per_wg(a.Hq, a.Hkv);
+    // tickets of the attention's workgroups behind the partial results
+    int32_t* const tickets = (int32_t*)(a.part + (size_t)a.B * a.Hq * a.n_split * kDecodePartFloats);
     decode_score_kernel<T><<<dim3(a.B), dim3(threads), 0, s>>>(
         k, v, a.anchor_k, a.anchor_v, a.seen, a.skipped, a.tau, a.cache_len, a.overflow,
         (T*)a.k_cache, (T*)a.v_cache, a.capacity, a.Hkv, a.ema, a.gamma, a.inclusive, a.fusion, a.warmup,
-        a.target, a.eta, a.skip, a.fused);
+        a.target, a.eta, a.skip, a.fused, tickets, a.n_split > 1 ? a.Hq / g : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int group = a.Hq / a.Hkv;
     const float sl2 = a.scale * 1.4426950408889634f;
 #define TF_DECODE_ATTEND(G)                                                                       \
     decode_attend_kernel<T, G><<<dim3(a.B * (a.Hq / G) * a.n_split), dim3(256), 0, s>>>(          \
-        q, (const T*)a.k_cache, (const T*)a.v_cache, a.cache_len, a.skip, a.part, a.Hq, a.Hkv,     \
-        a.capacity, a.n_split, sl2)
-    if (group == 8) TF_DECODE_ATTEND(8);
-    else if (group == 4) TF_DECODE_ATTEND(4);
-    else if (group == 2) TF_DECODE_ATTEND(2);
-    else TF_DECODE_ATTEND(1);  // other ratios: one query head per workgroup
+        q, (const T*)a.k_cache, (const T*)a.v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, \
+        a.Hkv, a.capacity, a.n_split, sl2)
+    if (g == 8) TF_DECODE_ATTEND(8);
+    else if (g == 4) TF_DECODE_ATTEND(4);
+    else if (g == 2) TF_DECODE_ATTEND(2);
+    else TF_DECODE_ATTEND(1);
 #undef TF_DECODE_ATTEND
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    decode_merge_kernel<T><<<dim3(a.B * a.Hq), dim3(128), 0, s>>>(a.part, a.skip, o, a.Hq, a.n_split);
     return hipGetLastError();
 }
 
 }  // namespace
+
+int decode_heads_per_wg(int Hq, int Hkv)
+{
+    const int group = Hq / Hkv;
+    return group == 2 || group == 4 || group == 8 ? group : 1;  // other ratios: one query head per workgroup
+}
+
+int decode_max_split(int B, int Hq, int Hkv)
+{
+    const int rows = B * (Hq / decode_heads_per_wg(Hq, Hkv));
+    return std::min(kDecodeMaxSplit, std::max(1, (kDecodeWorkgroups + rows - 1) / rows));
+}
+
+size_t decode_scratch_bytes(int B, int Hq, int Hkv)
+{
+    const size_t rows = (size_t)B * Hq;
+    return (rows * decode_max_split(B, Hq, Hkv) * kDecodePartFloats + rows) * sizeof(float);
+}
 
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s)
 {

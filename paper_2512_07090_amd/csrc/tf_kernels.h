@@ -74,7 +74,12 @@ hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const v
                               const int32_t* counts, long long idx_stride, hipStream_t s);
 
 // ---- per-token (decoding) form ----------------------------------------------------------------
-constexpr int kDecodeMaxSplit = 16;                 // slices of a row's cache per query head
+// Slices of a row's cache per group of query heads: as many as make kDecodeWorkgroups workgroups in
+// all, at most one per lane of the wave that weighs them.  One row of 8 groups x 16384 keys, half of the
+// tokens attending: 16 slices and a launch to merge them 12.4 us a step, 64 slices merged by
+// the last 7.6 us.
+constexpr int kDecodeMaxSplit = 64;
+constexpr int kDecodeWorkgroups = 1024;
 constexpr int kDecodePartFloats = kHeadDim + 2;     // floats of one slice's partial result
 struct DecodeArgs {
     int B, Hq, Hkv, capacity;
@@ -87,9 +92,12 @@ struct DecodeArgs {
     float target, eta, scale;
     uint8_t* skip;                                  // out [B]
     float* fused;                                   // out [B]
-    float* part;                                    // scratch [B][Hq][n_split][kDecodePartFloats]
-    int n_split;                                    // 1 .. kDecodeMaxSplit
+    float* part;                                    // scratch [B][Hq][n_split][kDecodePartFloats], tickets
+    int n_split;                                    // 1 .. decode_max_split()
 };
+int decode_heads_per_wg(int Hq, int Hkv);           // query heads one workgroup handles (they share a KV head)
+int decode_max_split(int B, int Hq, int Hkv);
+size_t decode_scratch_bytes(int B, int Hq, int Hkv);
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s);
 // state after a prompt of n rows that the batched online path has processed: anchors from K and
 // V (element strides kvs for batch, head, position), caches from the kept rows (kept_idx

@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 
 #include "../../include/tokfilt.h"
@@ -462,7 +463,7 @@ size_t tf_decode_workspace_bytes(const tf_params* p)
 {
     const char* why;
     if (check_shape(p, &why) != TF_OK) return 0;
-    return align256((size_t)p->batch * p->n_q_heads * tf::kDecodeMaxSplit * tf::kDecodePartFloats * sizeof(float));
+    return align256(tf::decode_scratch_bytes(p->batch, p->n_q_heads, p->n_kv_heads));
 }
 
 tf_status tf_decode_init(tf_ctx* ctx, const tf_params* p, const tf_decode_state* state, float tau0,
@@ -540,14 +541,8 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
     a.skip = skip;
     a.fused = fused;
     a.part = (float*)ws;
-    // enough workgroups for about four per compute unit, each slice at least one pass of keys
-    const int group = p->n_q_heads / p->n_kv_heads;
-    const int heads_per_wg = (group == 2 || group == 4 || group == 8) ? group : 1;
-    const int rows = p->batch * (p->n_q_heads / heads_per_wg);
-    int n_split = (4 * ctx->n_cu + rows - 1) / rows;
-    n_split = n_split < 1 ? 1 : (n_split > tf::kDecodeMaxSplit ? tf::kDecodeMaxSplit : n_split);
-    const int by_len = (state->capacity + 63) / 64;
-    a.n_split = n_split > by_len ? by_len : n_split;
+    // each slice at least one pass of keys
+    a.n_split = std::min(tf::decode_max_split(p->batch, p->n_q_heads, p->n_kv_heads), (state->capacity + 63) / 64);
     return dev(ctx, tf::launch_decode_step(a, p->dtype, q, k, v, o, (hipStream_t)stream), "decode step launch");
 }
 
