@@ -122,14 +122,20 @@ def lib():
     return _lib
 
 
+# Pointers and streams are passed as plain integers: the argument types of lib() convert them, and
+# at one token per call the wrapper objects cost as much as the kernel launches.
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _bytes(t: Optional[torch.Tensor]):
+    return 0 if t is None else t.nbytes
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def make_params(q_shape, kv_shape, dtype: torch.dtype, prune_ratio: float, warmup: int = 1,
@@ -222,13 +228,13 @@ class Context:
         self._check(lib().tf_decode_prefill(
             self._h, ctypes.byref(p), float(eta), float(tau0), ctypes.byref(state), _ptr(Q),
             _ptr(K), _ptr(V), _ptr(keep), _ptr(kept_idx), _ptr(count), _ptr(fused), _ptr(O),
-            _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+            _ptr(ws), _bytes(ws), _stream(stream)))
 
     def tf_decode_step(self, p, eta, state, q, k, v, o, skip, fused, ws, stream=None):
         self._check(lib().tf_decode_step(
             self._h, ctypes.byref(p), float(eta), ctypes.byref(state), _ptr(q), _ptr(k), _ptr(v),
             _ptr(o), _ptr(skip), _ptr(fused), _ptr(ws),
-            0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+            _bytes(ws), _stream(stream)))
 
     def __init__(self, device: int = 0):
         self._h = ctypes.c_void_p()
@@ -258,26 +264,26 @@ class Context:
     def tf_score(self, p, K, V, fused, sim_k, sim_v, ws, stream=None):
         self._check(lib().tf_score(self._h, ctypes.byref(p), _ptr(K), _ptr(V), _ptr(fused),
                                    _ptr(sim_k), _ptr(sim_v), _ptr(ws),
-                                   0 if ws is None else ws.numel() * ws.element_size(),
+                                   _bytes(ws),
                                    _stream(stream)))
 
     def tf_select(self, p, fused, keep, kept_idx, tau, ws, stream=None):
         self._check(lib().tf_select(self._h, ctypes.byref(p), _ptr(fused), _ptr(keep),
                                     _ptr(kept_idx), _ptr(tau), _ptr(ws),
-                                    0 if ws is None else ws.numel() * ws.element_size(),
+                                    _bytes(ws),
                                     _stream(stream)))
 
     def tf_attend(self, p, Q, K, V, kept_idx, m, O, ws, stream=None):
         self._check(lib().tf_attend(self._h, ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V),
                                     _ptr(kept_idx), int(m), _ptr(O), _ptr(ws),
-                                    0 if ws is None else ws.numel() * ws.element_size(),
+                                    _bytes(ws),
                                     _stream(stream)))
 
     def tf_filtered_attention(self, p, Q, K, V, keep, kept_idx, fused, tau, O, ws, stream=None):
         self._check(lib().tf_filtered_attention(
             self._h, ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(keep), _ptr(kept_idx),
             _ptr(fused), _ptr(tau), _ptr(O), _ptr(ws),
-            0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+            _bytes(ws), _stream(stream)))
 
     def tf_filtered_attention_static(self, p, Q, K, V, keep, kept_idx, fused, tau, O, stream=None):
         self._check(lib().tf_filtered_attention_static(
@@ -288,12 +294,12 @@ class Context:
         self._check(lib().tf_select_online(
             self._h, ctypes.byref(p), float(eta), float(tau0), _ptr(fused), _ptr(keep),
             _ptr(kept_idx), _ptr(count), _ptr(tau), _ptr(ws),
-            0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+            _bytes(ws), _stream(stream)))
 
     def tf_attend_ragged(self, p, Q, K, V, kept_idx, count, O, ws, stream=None):
         self._check(lib().tf_attend_ragged(
             self._h, ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(kept_idx), _ptr(count),
-            _ptr(O), _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(),
+            _ptr(O), _ptr(ws), _bytes(ws),
             _stream(stream)))
 
     def tf_filtered_attention_online(self, p, eta, tau0, Q, K, V, keep, kept_idx, count, fused,
@@ -301,7 +307,7 @@ class Context:
         self._check(lib().tf_filtered_attention_online(
             self._h, ctypes.byref(p), float(eta), float(tau0), _ptr(Q), _ptr(K), _ptr(V),
             _ptr(keep), _ptr(kept_idx), _ptr(count), _ptr(fused), _ptr(tau), _ptr(O), _ptr(ws),
-            0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+            _bytes(ws), _stream(stream)))
 
     def tf_filtered_attention_layers(self, p, ratios, Q, K, V, keep, kept_idx, fused, tau, O, ws,
                                      stream=None):
@@ -316,7 +322,7 @@ class Context:
         self._check(lib().tf_filtered_attention_layers(
             self._h, ctypes.byref(p), n_layers, r, arr(Q), arr(K), arr(V), arr(keep),
             arr(kept_idx), arr(fused), arr(tau), arr(O), _ptr(ws),
-            0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+            _bytes(ws), _stream(stream)))
 
     def tf_stage_timing_enable(self, on: bool):
         self._check(lib().tf_stage_timing_enable(self._h, 1 if on else 0))
