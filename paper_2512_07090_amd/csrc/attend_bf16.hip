@@ -3,8 +3,8 @@
 // queries and keys are the kept tokens, addressed through kept_idx, so "causal" means key rank
 // <= query rank in the compacted order).
 //
-// Flash-style kernel for gfx950.  One work item covers 256 kept queries: eight waves of 32, two
-// per SIMD with 256 registers each.  It walks the key tiles (64 kept keys) once, K and V rows
+// Flash-style kernel for gfx950.  One work item covers 256 (NW = 8) or 128 (NW = 4) kept queries: waves of
+// 32, two per SIMD with 256 registers each.  It walks the key tiles (64 kept keys) once, K and V rows
 // gathered through kept_idx into LDS (two stages each).
 //   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = K rows from LDS, B = Q fragments held in
 //                 registers for the whole item.  The transposed product puts one query per
@@ -37,8 +37,9 @@
 //                 0.299 instead of 0.282 ms at 8 x 32 heads x 2048 kept on all-zero inputs).
 //   zero rows     The rows of the filtered positions between a query and the next kept token
 //                 are written as zeros together with the query's row (kept_idx is ascending).
-//   scheduling    One persistent workgroup per CU walks a static list of pairs of query tiles
-//                 (tile p with tile n_qt - 1 - p: equal causal work); see the kernel.
+//   scheduling    One persistent workgroup of eight waves per CU (or two of four) walks a static list of pairs
+//                 of query tiles (tile p with tile n_qt - 1 - p: equal causal work) or, where there
+//                 are too few pairs to go round, of single tiles; see the kernel and plan_attend().
 // What bounds it: with real data the card runs at its power limit (1.4 kW) and clocks down; a
 // library GEMM of 8192^3 reaches 1.2-1.36 PFLOP/s there, this kernel 1.25 at 32 heads x 16384 kept
 // tokens (1.99 -> 1.76 ms; all-zero inputs 1.72 -> 1.54).  With short rows each item's start and
@@ -122,7 +123,7 @@ __device__ __forceinline__ void mfma_settle()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int NW>
+template <int NW, bool SINGLES>
 __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     Dims d, float scale_log2, int n_qt, int n_xcd, const uint16_t* __restrict__ Q,
     const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -137,10 +138,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kKTile + 2 * kVTile];
     uint16_t* const k_lds = smem;               // 2 stages of K
     uint16_t* const v_lds = smem + 2 * kKTile;  // 2 stages of V^T
-    // Output staging of its own (141 KB of LDS in all): a wave stages and writes its rows without
+    // Eight waves: output staging of its own (141 KB of LDS in all): a wave stages and writes its rows without
     // a workgroup barrier on either side, so the waves leave an item, and start on the next
-    // item's first loads, as each gets there.
-    __shared__ __attribute__((aligned(16))) uint16_t ostage[kBM * kOStr];
+    // item's first loads, as each gets there.  Four waves: two workgroups share a CU's LDS (70 KB each)
+    // and overlap each other's item ends, the rows are staged over the K tiles.
+    constexpr bool kOwnStage = NW == 8;
+    __shared__ __attribute__((aligned(16))) uint16_t own_stage[kOwnStage ? kBM * kOStr : 8];
+    uint16_t* const ostage = kOwnStage ? own_stage : k_lds;
+    static_assert(kOwnStage || kBM * kOStr <= 2 * kKTile, "staging fits the K stages");
 
     __shared__ int overflow;   // a row of the item at hand has outgrown its reference
 
@@ -156,7 +161,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     // K and V of the few groups it is working on.  Correctness does not depend on where a
     // workgroup really runs, only the L2 hit rate does.
     const int n_groups = d.B * d.Hq;
-    // Static schedule: workgroup j of XCD x (x = id % n_xcd, as the dispatcher deals them) walks
+    // Static schedule (SINGLES: an entry is one tile; uniform rows list the longest tiles of all groups first): workgroup j of XCD x (x = id % n_xcd, as the dispatcher deals them) walks
     // entries j, j + W, ... of the XCD's list of (group, pair of query tiles); a pair joins
     // query tile p with n_qt - 1 - p, so every entry is the same amount of causal work, and the
     // workgroups that share a group start on it together and stream the same K / V tiles.
@@ -164,7 +169,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     const int nwx = (gridDim.x + n_xcd - 1 - x) / n_xcd;  // workgroups whose id % n_xcd is x
     const int g_lo = x * n_groups / n_xcd;
     const int ng = (x + 1) * n_groups / n_xcd - g_lo;
-    const int n_pairs = (n_qt + 1) >> 1;
+    const int n_pairs = SINGLES ? n_qt : (n_qt + 1) >> 1;
     const int n_entries = ng * n_pairs;
 
     // Ragged rows (counts != null: every batch row has its own number of kept tokens, read here
@@ -182,13 +187,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     // neighbours share a group).  The last round then lasts one middle tile instead of a pair.
     const int full_rounds = n_entries / nwx;
     const int rest = n_entries - full_rounds * nwx;
-    const bool split_rest = !counts && rest > 0 && 2 * rest <= nwx && rest <= ng && n_pairs >= 2 && (n_qt & 1) == 0;
+    const bool split_rest = !SINGLES && !counts && rest > 0 && 2 * rest <= nwx && rest <= ng && n_pairs >= 2 && (n_qt & 1) == 0;
     const int n_main = split_rest ? n_entries - rest : n_entries;  // entries dealt as pairs
     const int whole_groups = split_rest ? ng - rest : ng;          // groups that keep all their pairs
     int rb = g_lo / d.Hq, row_e0 = 0;
     bool exact = false;  // the item is done again, see below
     for (int it = 0;; ++it) {
-    const int e = j + (it >> 1) * nwx;
+    const int e = j + (SINGLES ? it : it >> 1) * nwx;
     int pr, bh, m, nq;
     bool single = false;  // this entry is one tile of a split middle pair
     if (counts) {
@@ -199,7 +204,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
             if (rb >= d.B || hi <= lo) { done = true; break; }
             m = __builtin_amdgcn_readfirstlane(counts[rb]);  // kept tokens of this row
             nq = (m + kBM - 1) / kBM;                        // its query tiles
-            P = m == 0 ? 1 : (nq + 1) >> 1;
+            P = m == 0 ? 1 : (SINGLES ? nq : (nq + 1) >> 1);
             if (e < row_e0 + (hi - lo) * P) break;
             row_e0 += (hi - lo) * P;
             ++rb;
@@ -213,7 +218,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
         nq = n_qt;
         if (e < n_main) {
             const int e_whole = whole_groups * n_pairs;  // entries of the groups with all pairs
-            if (e < e_whole) {
+            if (SINGLES) {   // longest first
+                pr = e / ng;
+                bh = g_lo + e % ng;
+            } else if (e < e_whole) {
                 pr = e % n_pairs;
                 bh = g_lo + e / n_pairs;
             } else {  // the last groups have given their middle pair away
@@ -232,16 +240,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     const int hk = hq / (d.Hq / d.Hkv);
     if (m == 0) {
         // a row without kept tokens: nothing attends, every output row is zero
-        if (pr == 0 && !(it & 1)) {
+        if (pr == 0 && (SINGLES || !(it & 1))) {
             uint16_t* Oz = O + (long long)b * d.os[0] + (long long)hq * d.os[1] + 8 * (tid & 15);
             for (int g = tid >> 4; g < d.n; g += NT / 16)
                 *reinterpret_cast<uint4*>(Oz + (long long)g * d.os[2]) = make_uint4(0, 0, 0, 0);
         }
         continue;
     }
-    if (pr >= (nq + 1) >> 1) continue;
-    const int qt = single ? ((j & 1) ? pr : nq - 1 - pr) : ((it & 1) ? pr : nq - 1 - pr);
-    if (!single && (it & 1) && pr == nq - 1 - pr) continue;  // the middle tile of an odd count is alone
+    if (pr >= (SINGLES ? nq : (nq + 1) >> 1)) continue;
+    const bool lower = single ? j & 1 : it & 1;
+    const int qt = lower && !SINGLES ? pr : nq - 1 - pr;
+    if (!SINGLES && !single && (it & 1) && pr == nq - 1 - pr) continue;  // the middle tile of an odd count is alone
 
     const int32_t* idx = kept_idx + (long long)b * idx_stride;
     const uint16_t* Qb = Q + (long long)b * d.qs[0] + (long long)hq * d.qs[1];
@@ -389,6 +398,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     TF_OFFSETS(off_k, pos_0);
     TF_LOAD_ROWS(kreg, Kb, off_k);
     TF_LOAD_ROWS(vreg, Vb, off_k);
+    if (!kOwnStage) __syncthreads();   // the rows of the item before are staged where K goes
     TF_STORE_K(0);
     TF_OFFSETS(off_k, pos_1);
     TF_LOAD_ROWS(kreg, Kb, off_k);
@@ -567,6 +577,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     if (__any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit) && lane == 0) overflow = 1;
     __syncthreads();
     if (!exact && __builtin_amdgcn_readfirstlane(overflow)) {
+        __syncthreads();   // everybody has read the flag before the item's second start clears it
         exact = true;
         --it;
         continue;
@@ -648,26 +659,80 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
 
 }  // namespace
 
+// How the query tiles are dealt out.  Costs are in key tiles of 64 on one compute unit; a tile of 256
+// queries costs its key tiles (4 per 256 ranks) and kItemCost more for its first loads, the masked and
+// the finishing iteration and its output rows (fitted: 11 us an item, 1.47 us a key tile).
+constexpr double kItemCost = 7.5, kKeyTiles = 4.0;
+struct AttendPlan {
+    int waves;     // per workgroup: 32 queries each
+    bool singles;  // tiles one by one, longest first, instead of in pairs of equal work
+};
+
+static AttendPlan plan_attend(int groups, int m, bool ragged, int n_cu, int n_xcd)
+{
+    const int nq = (m + 255) / 256, n_pairs = (nq + 1) / 2;
+    const long long items8 = (long long)groups * nq, items4 = (long long)groups * ((m + 127) / 128);
+    // one XCD: its groups, workgroups and pairs
+    const int ng = (groups + n_xcd - 1) / n_xcd, nwx = std::max(1, n_cu / n_xcd);
+    const long long entries = (long long)ng * n_pairs;
+    bool singles = false;
+    // Pairs are all alike, so they are best when they fill whole rounds (1 x 40 heads x 2500 kept tokens: 83 us
+    // against 97 one by one) and when there are many of them; with few, the last round, or the only
+    // one, keeps some workgroups busy with a whole pair while the others have nothing
+    // (1 x 32 x 1024: 44 against 35 us; 3 x 32 x 2048: 140 against 131).
+    if (nq > 1 && entries <= 16 * nwx) {
+        auto tile = [](int t) { return kItemCost + kKeyTiles * t; };   // t: in tiles of 256 ranks, 1-based
+        const int full = (int)(entries / nwx), rest = (int)(entries % nwx);
+        double in_pairs = 0;
+        if (!ragged && full >= 2 && rest > 0 && 2 * rest <= nwx && rest <= ng && nq % 2 == 0)
+            in_pairs = full * (tile(nq) + tile(1)) + tile(nq / 2 + 1);   // the kernel splits the last round's pairs
+        else
+            for (int j = 0; j < nwx; ++j) {
+                double sum = 0;
+                for (long long e = j; e < entries; e += nwx) {
+                    const int pr = (int)(e % n_pairs);
+                    sum += tile(nq - pr) + (pr != nq - 1 - pr ? tile(pr + 1) : 0.0);
+                }
+                in_pairs = std::max(in_pairs, sum);
+            }
+        double one_by_one = 0;
+        for (long long e = 0; e < (long long)ng * nq; e += nwx) one_by_one += tile(nq - (int)(e / ng));
+        // (ragged rows are listed row by row, not by length: only where every tile has a place at once)
+        singles = one_by_one < 0.97 * in_pairs && (!ragged || items8 <= n_cu);
+    }
+    // Tiles of 128 queries, two workgroups a compute unit: while those fit at once the shorter tiles win (1 x 32 x
+    // 1024: 28 against 35 us, 1 x 32 x 167: 12.3 against 14.3), beyond they load every key tile
+    // twice as often (8 x 32 x 2048: 410 against 326 us; 8 x 32 x 700: 78 against 66).  A row that half fills a
+    // tile of 256 never pays for the other half (8 x 40 x 120: 16.7 against 20.5); one that fills it
+    // is best left whole when there is one for each compute unit (8 x 32 x 240: 22 against 19.5).
+    const bool four = (nq == 1 || singles) && (m <= 128 || items4 <= n_cu || (nq >= 2 && items4 <= 2 * n_cu));
+    return {four ? 4 : 8, singles || four};
+}
+
 hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const void* K,
                               const void* V, const int32_t* kept_idx, void* O, int n_cu, int n_xcd,
-                              const int32_t* counts, long long idx_stride, hipStream_t s)
+                              const int32_t* counts, int expected, long long idx_stride, hipStream_t s)
 {
     // the tile gathers address a row as a 32-bit byte offset from its (batch, head) slice
     if (d.n > (1 << 24) || d.kvs[2] * 2 >= (1 << 24) || (long long)d.n * d.kvs[2] * 2 >= (1ll << 32))
         return hipErrorInvalidValue;
     n_xcd = std::max(n_xcd, 1);
+    n_cu = std::max(n_cu, 1);
+    const AttendPlan plan = plan_attend(d.B * d.Hq, counts ? std::min(expected, d.m) : d.m, counts != nullptr, n_cu, n_xcd);
     // with per-row counts d.m is the bound (the longest possible row)
-    constexpr int NW = 8;
-    constexpr int kBM = 32 * NW, wg_per_cu = 8 / NW;
-    const int n_qt = (d.m + kBM - 1) / kBM;
+    const int n_qt = (d.m + 32 * plan.waves - 1) / (32 * plan.waves);
     const long long items = (long long)d.B * d.Hq * n_qt;
     // persistent workgroups: as many as are resident at once; at least one per XCD, so that every
     // residue of id % n_xcd owns a share of the groups
-    const int grid = (int)std::max<long long>(n_xcd, std::min<long long>(items, (long long)wg_per_cu * std::max(n_cu, 1)));
-    attend_bf16_kernel<NW><<<dim3(grid), dim3(64 * NW), 0, s>>>(
-        d, scale * 1.44269504088896340736f, n_qt, n_xcd, (const uint16_t*)Q,
-        (const uint16_t*)K, (const uint16_t*)V, kept_idx, (uint16_t*)O, counts,
-        counts ? idx_stride : (long long)d.m);
+    const int grid = (int)std::max<long long>(n_xcd, std::min<long long>(items, (long long)(8 / plan.waves) * n_cu));
+#define TF_ATTEND(NW, SINGLES)                                                                 \
+    attend_bf16_kernel<NW, SINGLES><<<dim3(grid), dim3(64 * NW), 0, s>>>(                      \
+        d, scale * 1.44269504088896340736f, n_qt, n_xcd, (const uint16_t*)Q, (const uint16_t*)K, \
+        (const uint16_t*)V, kept_idx, (uint16_t*)O, counts, counts ? idx_stride : (long long)d.m)
+    if (plan.waves == 4) TF_ATTEND(4, true);
+    else if (plan.singles) TF_ATTEND(8, true);
+    else TF_ATTEND(8, false);
+#undef TF_ATTEND
     return hipGetLastError();
 }
 

@@ -177,7 +177,8 @@ tf_status run_attend(tf_ctx* ctx, const tf_params* p, const tf::Dims& d, const v
     }
     // the bf16 kernel writes the zero rows itself
     mark(ctx, slot, TF_STAGE_ATTEND, s);
-    return dev(ctx, tf::launch_attend_bf16(d, scale, Q, K, V, kept_idx, O, ctx->n_cu, ctx->n_xcd, counts, p->seq, s),
+    return dev(ctx, tf::launch_attend_bf16(d, scale, Q, K, V, kept_idx, O, ctx->n_cu, ctx->n_xcd, counts,
+                                           tf_keep_count(p->seq, p->prune_ratio), p->seq, s),
                "bf16 attention launch");
 }
 

@@ -436,6 +436,65 @@ def test_attend_softmax_reference_at_block_borders(ctx, m, course):
     assert np.abs(O_g - oracle.attend(q, k, v, idx)).max() <= ATTN_TOL[q.dtype]
 
 
+@pytest.mark.parametrize("shape", [   # batch, query heads, KV heads, kept, per-row counts
+    (8, 32, 32, 300, False),    # pairs of tiles of 256 queries
+    (8, 32, 8, 249, False),     # one such tile a group
+    (8, 32, 32, 600, False),    # tiles of 256, one by one, an odd number of them
+    (2, 40, 8, 1025, False),    # the same with a last tile of one row
+    (8, 40, 40, 127, False),    # half a tile a group: tiles of 128
+    (8, 32, 32, 300, True),     # pairs, rows of different length, one of them empty
+    (4, 12, 4, 385, True),      # tiles of 128, ditto
+])
+@pytest.mark.parametrize("rising", [False, True])
+def test_attend_many_groups_as_a_few_of_them(ctx, shape, rising):
+    """Which tile size and order of tiles a call gets depends on how much there is to do: groups of
+    a large call against the same groups in a call of their own, which gets tiles of 128 (compared with
+    the oracle by the other tests).  A query's arithmetic is the same in every plan, so the rows are
+    equal bit for bit; with logits that outgrow the softmax reference a tile is done again as a whole,
+    rows that did not need it included, so there both results are within the tolerance of the
+    oracle comparison and within twice that of each other."""
+    b, hq, hkv, m, ragged = shape
+    _say("attend groups %s %s" % (shape, rising))
+    n = 2 * m + 3
+    g = torch.Generator(device="cuda").manual_seed(m)
+    q, k, v = (torch.randn(b, h, n, 128, device="cuda", generator=g) for h in (hq, hkv, hkv))
+    if rising:
+        q, k = q * 0.05 + 2.0, k * 0.05 + 3.0 * torch.arange(n, device="cuda")[:, None] / n
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    idx = torch.stack([torch.randperm(n, device="cuda", generator=g)[:m].sort().values for _ in range(b)]).int()
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 1.0 - m / n)
+    buf = B.Buffers(p, "cuda:0")
+    if ragged:
+        count = torch.tensor([max(0, m - 37 * i * i) for i in range(b - 1)] + [0], dtype=torch.int32, device="cuda")
+        full = torch.full((b, n), -1, dtype=torch.int32, device="cuda")
+        full[:, :m] = idx
+
+    def attend(rows, h0, h1):
+        r = hq // hkv
+        qq, kk, vv = q[rows, h0 * r:h1 * r].contiguous(), k[rows, h0:h1].contiguous(), v[rows, h0:h1].contiguous()
+        pp = B.make_params(tuple(qq.shape), tuple(kk.shape), q.dtype, 1.0 - m / n)
+        O = torch.full_like(qq, float("nan"))
+        ws = B.Buffers(pp, "cuda:0").ws
+        if ragged:
+            ctx.tf_attend_ragged(pp, qq, kk, vv, full[rows].contiguous(), count[rows].contiguous(), O, ws)
+        else:
+            ctx.tf_attend(pp, qq, kk, vv, idx[rows].contiguous(), m, O, ws)
+        torch.cuda.synchronize()
+        return O
+
+    whole = attend(slice(0, b), 0, hkv).float()
+    assert not torch.isnan(whole).any()
+    r = hq // hkv
+    for row in (0, 1, b - 2, b - 1):
+        for h in (0, hkv // 2, hkv - 1):
+            part = attend(slice(row, row + 1), h, h + 1).float()
+            got = whole[row:row + 1, h * r:(h + 1) * r]
+            if rising:
+                assert (part - got).abs().max() <= 2 * ATTN_TOL[q.dtype]
+            else:
+                assert torch.equal(part, got)
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_attend_zero_rows_with_long_gaps(ctx, dt):
     """Kept sets with filtered runs of every length (before the first kept token, between kept
