@@ -209,7 +209,8 @@ __global__ __launch_bounds__(kSelThreads) void compact_kernel(const uint8_t* __r
 //      histogram of bit patterns is 1024 threads adding to a few bins), and again between the
 //      smallest and the largest score of the bin that holds the wanted rank, until that bin
 //      holds at most kMaxCand tokens (once or twice; after kLevels times, as when an outlier
-//      stretches the range over and over, four radix passes over the bit patterns take over);
+//      stretches the range over and over, or at once when a score is infinite or no number, four
+//      radix passes over the bit patterns take over);
 //   2. those tokens compared with each other.  Where the bin holds equal scores only, the
 //      wanted one is picked by its rank in token order.
 // Everything at or below the token found is kept.  What bounds it: short rows a chain of some 15
@@ -277,9 +278,12 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
     float sc[IPT];
 #pragma unroll
     for (int i = 0; i < IPT; ++i) sc[i] = S[min(i * kSelThreads + tid, n - 1)];
+    auto takes_part = [&](int i) { return i * kSelThreads + tid >= forced && i * kSelThreads + tid < n; };
+    bool finite = true;
 #pragma unroll
     for (int i = 0; i < IPT; ++i)
-        if (i * kSelThreads + tid < forced || i * kSelThreads + tid >= n) sc[i] = INFINITY;
+        if (!takes_part(i)) sc[i] = INFINITY;
+        else finite = finite && fabsf(sc[i]) < INFINITY;
 
     // smallest and largest score over the workgroup; one barrier before the result, none after
     auto min_max = [&](float& lo, float& hi) {
@@ -294,7 +298,8 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
         for (int w = 0; w < kSelWaves; ++w) { lo = fminf(lo, lo_lds[w]); hi = fmaxf(hi, hi_lds[w]); }
     };
 
-    float tf_ = 0.f;
+    float tf_ = 0.f, tau_ = 0.f;   // tau_: the score itself where tf_ stands for its key
+    bool by_key = false;
     int tidx = -1;   // kept: forced, or (score, index) <= (tf_, tidx)
     if (!all && !none) {
         // the wanted token is the k-th smallest of those with scores lo .. hi (in bin `bin` of that range)
@@ -307,12 +312,13 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
             lo = fminf(lo, sc[i]);
             hi = fmaxf(hi, sc[i] == INFINITY ? -INFINITY : sc[i]);
         }
+        if (!finite) hi = INFINITY;
         bool few = false;
         for (int level = 0;; ++level) {
             for (int i = 4 * tid; i < kBins * kCopies; i += 4 * kSelThreads) *reinterpret_cast<int4*>(&hist[i]) = make_int4(0, 0, 0, 0);
             if (tid == 0) n_cand = 0;
             min_max(lo, hi);
-            if (lo == hi || level == kLevels) break;
+            if (lo == hi || level == kLevels || hi == INFINITY) break;
             to_bin = fminf((float)kBins / (hi - lo), 3e38f);
 #pragma unroll
             for (int i = 0; i < IPT; ++i)
@@ -361,7 +367,7 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
             __syncthreads();
             tf_ = sel_f;
             tidx = sel_k;
-        } else if (lo == hi) {
+        } else if (lo == hi && hi != INFINITY) {
             tf_ = lo;
             tie = true;
         } else {
@@ -374,7 +380,7 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
                 __syncthreads();
                 for (int i = 0; i < IPT; ++i) {
                     const unsigned key = f2key(sc[i]);
-                    if (sc[i] != INFINITY && (key & himask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
+                    if (takes_part(i) && (key & himask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
                 }
                 __syncthreads();
                 const int c = tid < 256 ? hist[tid] : 0;
@@ -389,7 +395,14 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
                 k = sel_k;
                 __syncthreads();
             }
-            tf_ = key2f(prefix);
+            // from here on only the order of the keys matters (a NaN compares with nothing)
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) {
+                const unsigned key = f2key(sc[i]);
+                sc[i] = !takes_part(i) || key > prefix ? 1.f : (key == prefix ? 0.f : -1.f);
+            }
+            tau_ = key2f(prefix);
+            by_key = true;
             tie = true;
         }
         if (tie) {
@@ -405,7 +418,7 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
             tidx = sel_k;
         }
     }
-    if (tid == 0 && tau) tau[b] = all ? INFINITY : (none ? -INFINITY : tf_);
+    if (tid == 0 && tau) tau[b] = all ? INFINITY : (none ? -INFINITY : (by_key ? tau_ : tf_));
 
     unsigned long long kept[IPT];
 #pragma unroll

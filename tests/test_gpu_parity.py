@@ -339,6 +339,32 @@ def test_select_histogram_and_its_fallback(ctx, kind, n):
         np.testing.assert_array_equal(buf.tau.cpu().numpy(), tau_r)
 
 
+@pytest.mark.parametrize("kind", ["inf", "neg_inf", "nan", "all_inf", "mixed"])
+@pytest.mark.parametrize("n", [2, 333, 1025, 4097, 8193, 32768])
+def test_select_scores_that_are_no_numbers(ctx, kind, n):
+    """Infinite scores and NaNs handed to tf_select are outside the contract, but the decision stays
+    one: exactly m tokens, ordered by the bit patterns as in the rows too long for the histogram."""
+    _say("select %s n=%d" % (kind, n))
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((2, n)).astype(np.float32)
+    odd = {"inf": [np.inf], "neg_inf": [-np.inf], "nan": [np.nan], "all_inf": [np.inf], "mixed": [np.inf, -np.inf, np.nan]}[kind]
+    where = np.ones((2, n), bool) if kind == "all_inf" else rng.random((2, n)) < 0.6
+    x[where] = rng.choice(np.array(odd, np.float32), where.sum())
+    warm = 1
+    p = B.make_params((2, 1, n, 128), (2, 1, n, 128), torch.bfloat16, 0.5, warm)
+    buf = B.Buffers(p, "cuda:0")
+    ctx.tf_select(p, torch.from_numpy(x).cuda(), buf.keep, buf.kept_idx, buf.tau, buf.ws)
+    torch.cuda.synchronize()
+    u = np.where(x.view(np.uint32) == 0x80000000, 0, x.view(np.uint32)).astype(np.uint64)
+    key = np.where(u & 0x80000000, ~u & 0xffffffff, u | 0x80000000)
+    m = B.tf_keep_count(n, 0.5)
+    for b in range(2):
+        order = warm + np.argsort(key[b, warm:], kind="stable")[:m - warm]
+        want = np.sort(np.concatenate([np.arange(warm), order]))
+        assert np.array_equal(buf.kept_idx[b].cpu().numpy(), want)
+        assert np.array_equal(np.flatnonzero(buf.keep[b].cpu().numpy()), want)
+
+
 # ------------------------------------------------------------------ attention stage
 
 @pytest.mark.parametrize("shape", [
