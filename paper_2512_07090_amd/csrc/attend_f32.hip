@@ -2,10 +2,11 @@
 // attention output; the rest attend as usual, here to kept tokens only).  Queries and keys are
 // addressed through kept_idx, so "causal" is "key rank <= query rank" in the compacted order.
 //
-//   zero_filtered_kernel  writes the zero rows of O for filtered positions;
-//   attend_f32_kernel     plain fp32 tiles (the fp32 correctness configuration).
+//   zero_filtered_kernel  writes zero rows of O from a mask (a layer that filters every token);
+//   attend_f32_kernel     fp32 on the matrix cores' fp32 form, zero rows included.
 // The bf16 MFMA kernel lives in attend_bf16.hip.
 #include "tf_kernels.h"
+#include <algorithm>
 
 namespace tf {
 
@@ -32,127 +33,184 @@ __global__ __launch_bounds__(256) void zero_filtered_kernel(Dims d, const uint8_
 }
 
 // ------------------------------------------------------------------------------ fp32 path
-constexpr int kFM = 32, kFN = 32, kFStride = kHeadDim + 4;
+// One workgroup per 16 kept queries of a head: its four waves hold the same queries and take the
+// 16-key blocks in turns, each with its own softmax state, and are merged through LDS at the end.
+//   S^T = K Q^T       v_mfma_f32_16x16x4_f32, fp32 products and sums; lane group g = lane / 16 feeds
+//                     k-slot g of step 4 j + e with column 16 j + 4 g + e, so a lane's operands are
+//                     16-byte loads
+//   O^T += V^T P^T    the accumulator of S^T (key 4 g + r of the block in register r, query lane % 16) is
+//                     the B operand of step r as it stands; row i of the A operand's block db is
+//                     column 8 i + db, so a lane reads 32 contiguous bytes of a V row and a
+//                     16-lane group the whole row
+// Keys and values go from the caches straight to registers (no two waves of a workgroup need the
+// same ones): the next block's K is requested when the products have consumed this one's, V one
+// block's scores ahead of its use.
+// What bounds it: a block is 64 MFMAs of 32 cycles (2.0 times that in all at long rows: three waves a SIMD,
+// limited by their registers, do not hide all of the softmax), at short rows one wave's latency chain. Plain FMAs on 32 x 32
+// tiles in LDS with the zero rows in a launch of their own against this: 32 heads x 256 kept
+// tokens of 512 75 -> 22 us, 40 x 1350 of 1500 856 -> 252 us, distance from 64 bits 3.0e-7 -> 2.0e-7 (fewer
+// roundings in a row). 32 queries a workgroup halve the loads but take 346 us there (two waves a SIMD).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr float kNone = -1e30f;   // masked score, and the maximum of a row without keys
 
-__global__ __launch_bounds__(256) void attend_f32_kernel(Dims d, float scale,
+__device__ __forceinline__ float across_groups_max(float v)
+{
+    const FloatPair a = swap16(v, v);
+    v = fmaxf(a.first, a.second);
+    const FloatPair b = swap32(v, v);
+    return fmaxf(b.first, b.second);
+}
+__device__ __forceinline__ float across_groups_sum(float v)
+{
+    const FloatPair a = swap16(v, v);
+    v = a.first + a.second;
+    const FloatPair b = swap32(v, v);
+    return b.first + b.second;
+}
+
+__global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
                                                          const float* __restrict__ Q,
                                                          const float* __restrict__ K,
                                                          const float* __restrict__ V,
                                                          const int32_t* __restrict__ kept_idx,
                                                          float* __restrict__ O,
                                                          const int32_t* __restrict__ counts,
-                                                         long long idx_stride)
+                                                         long long idx_stride, int parts)
 {
-    __shared__ float Qs[kFM][kFStride];
-    __shared__ float Ks[kFN][kFStride];
-    __shared__ float Vs[kFN][kHeadDim];
-    __shared__ float Ps[kFM][kFN + 1];
+    constexpr int kRows = 16, kStride = kHeadDim + 4;
+    __shared__ __attribute__((aligned(16))) float part[4][kRows][kStride];
+    __shared__ float part_m[4][kRows], part_l[4][kRows];
 
-    const int qt = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
+    // the longest first; of the `parts` workgroups of a tile the others only help with its zero rows
+    const int qt = (gridDim.x - 1 - blockIdx.x) / parts, zp = (gridDim.x - 1 - blockIdx.x) % parts;
+    const int hq = blockIdx.y, b = blockIdx.z;
     const int hk = hq / (d.Hq / d.Hkv);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, g = lane >> 4;
     // kept tokens of this batch row (per row when counts is given: d.m is then the bound)
     const int m = counts ? counts[b] : d.m;
-    if (blockIdx.x * kFM >= m) return;
+    const int i0 = qt * kRows;
+    float* Ob = O + (long long)b * d.os[0] + (long long)hq * d.os[1];
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i0 >= m) {
+        // a row without kept tokens (its grid is the one of a full row): every output row is zero
+        if (m == 0)
+            for (int r = i0 + (tid >> 5); r < min(i0 + kRows, d.n); r += 8)
+                reinterpret_cast<float4*>(Ob + (long long)r * d.os[2])[tid & 31] = zero;
+        return;
+    }
     const int32_t* idx = kept_idx + (long long)b * idx_stride;
     const float* Qb = Q + (long long)b * d.qs[0] + (long long)hq * d.qs[1];
     const float* Kb = K + (long long)b * d.kvs[0] + (long long)hk * d.kvs[1];
     const float* Vb = V + (long long)b * d.kvs[0] + (long long)hk * d.kvs[1];
-    const int tid = threadIdx.x;
-    const int row = tid >> 3, g = tid & 7;  // tile row handled when loading / computing
-    const int i0 = qt * kFM;
-    const int i = i0 + row;                 // this thread's query rank
-
-    {
-        const bool ok = i < m;
-        const float* src = ok ? Qb + (long long)idx[i] * d.qs[2] : Qb;
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-            const int col = 4 * (g + 8 * c4);
-            const float4 v = ok ? *reinterpret_cast<const float4*>(src + col) : make_float4(0, 0, 0, 0);
-            *reinterpret_cast<float4*>(&Qs[row][col]) = v;
+    const int i_last = min(i0 + kRows, m) - 1;
+    const int n_blocks = i_last / 16 + 1;
+    // the filtered positions behind each query of the tile (and before the first one) are zero rows
+    const int col = 4 * (tid & 31);   // 32 threads a row, four columns each
+    auto zero_rows = [&]() {
+        for (int i = i0 == 0 ? -1 : i0; i <= i_last; ++i) {
+            const int lo = i < 0 ? 0 : idx[i] + 1, hi = i + 1 < m ? idx[i + 1] : d.n;
+            for (int z = lo + 8 * zp + (tid >> 5); z < hi; z += 8 * parts)
+                *reinterpret_cast<float4*>(Ob + (long long)z * d.os[2] + col) = zero;
         }
+    };
+    if (zp > 0) {
+        zero_rows();
+        return;
     }
 
-    float m_run = -1e30f, l_run = 0.f;
-    float o[16];
+    // positions of the block's keys as the K and the V operand need them (keys past the last
+    // kept one repeat it: finite values whose weights are zero)
+    int pos_k, pos_v[4];
+    auto request_pos = [&](int kb) {
+        pos_k = idx[min(16 * kb + c16, m - 1)];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) o[e] = 0.f;
+        for (int r = 0; r < 4; ++r) pos_v[r] = idx[min(16 * kb + 4 * g + r, m - 1)];
+    };
+    f32x4 kr[8], vr[4][2];
+    auto request_k = [&]() {
+        const float* src = Kb + (long long)pos_k * d.kvs[2] + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) kr[j] = *reinterpret_cast<const f32x4*>(src + 16 * j);
+    };
 
-    for (int kt = 0; kt <= qt; ++kt) {
-        const int j0 = kt * kFN;
-        __syncthreads();
-        {
-            const int j = j0 + row;
-            const bool ok = j < m;
-            const long long p = ok ? idx[j] : 0;
+    const int i = min(i0 + c16, m - 1);   // rank of this lane's query: the last key it may see
+    const float* q_src = Qb + (long long)idx[i] * d.qs[2] + 4 * g;
+    request_pos(wave);
+    f32x4 qf[8];
 #pragma unroll
-            for (int c4 = 0; c4 < 4; ++c4) {
-                const int col = 4 * (g + 8 * c4);
-                const float4 z = make_float4(0, 0, 0, 0);
-                *reinterpret_cast<float4*>(&Ks[row][col]) =
-                    ok ? *reinterpret_cast<const float4*>(Kb + p * d.kvs[2] + col) : z;
-                *reinterpret_cast<float4*>(&Vs[row][col]) =
-                    ok ? *reinterpret_cast<const float4*>(Vb + p * d.kvs[2] + col) : z;
-            }
-        }
-        __syncthreads();
+    for (int j = 0; j < 8; ++j) qf[j] = *reinterpret_cast<const f32x4*>(q_src + 16 * j);
+    request_k();
 
-        // scores of query `row` against keys g, g+8, g+16, g+24 of the tile
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-        for (int c = 0; c < kHeadDim; ++c) {
-            const float qv = Qs[row][c];
+    f32x4 acc[8];                         // O^T: column 8 (4 g + r) + db in register r, query c16
+    float m_run = kNone, l_run = 0.f;     // l_run: this lane's keys only
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) s[kk] = fmaf(qv, Ks[g + 8 * kk][c], s[kk]);
-        }
-        float mx = -1e30f;
+    for (int db = 0; db < 8; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = wave; kb < n_blocks; kb += 4) {
+        // this block's V, behind the positions of the wave's next block: loads return in order
+        const float* v_src[4];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const int j = j0 + g + 8 * kk;
-            s[kk] = (j <= i && j < m) ? s[kk] * scale : -1e30f;
-            mx = fmaxf(mx, s[kk]);
+        for (int r = 0; r < 4; ++r) v_src[r] = Vb + (long long)pos_v[r] * d.kvs[2] + 8 * c16;
+        request_pos(kb + 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            vr[r][0] = *reinterpret_cast<const f32x4*>(v_src[r]);
+            vr[r][1] = *reinterpret_cast<const f32x4*>(v_src[r] + 4);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 1));
-        mx = fmaxf(mx, __shfl_xor(mx, 2));
-        mx = fmaxf(mx, __shfl_xor(mx, 4));
-        const float m_new = fmaxf(m_run, mx);
+        f32x4 s[2];   // two chains of dependent MFMAs
+        s[0] = s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j][e], qf[j][e], s[e & 1], 0, 0, 0);
+        request_k();
+        float sc[4], p[4], mx = kNone;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            sc[r] = 16 * kb + 4 * g + r <= i ? (s[0][r] + s[1][r]) * scale : kNone;
+            mx = fmaxf(mx, sc[r]);
+        }
+        const float m_new = fmaxf(m_run, across_groups_max(mx));
         const float corr = expf(m_run - m_new);
-        float psum = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const float p = s[kk] > -1e29f ? expf(s[kk] - m_new) : 0.f;
-            Ps[row][g + 8 * kk] = p;
-            psum += p;
-        }
-        psum += __shfl_xor(psum, 1);
-        psum += __shfl_xor(psum, 2);
-        psum += __shfl_xor(psum, 4);
-        l_run = l_run * corr + psum;
         m_run = m_new;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) o[e] *= corr;
-        __syncthreads();
-        // output columns 4g + 32q4 + (0..3), q4 = 0..3
-        for (int k = 0; k < kFN; ++k) {
-            const float p = Ps[row][k];
+        for (int r = 0; r < 4; ++r) p[r] = sc[r] > -1e29f ? expf(sc[r] - m_new) : 0.f;
+        l_run = l_run * corr + ((p[0] + p[1]) + (p[2] + p[3]));
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 v = *reinterpret_cast<const float4*>(&Vs[k][4 * g + 32 * q4]);
-                o[4 * q4 + 0] = fmaf(p, v.x, o[4 * q4 + 0]);
-                o[4 * q4 + 1] = fmaf(p, v.y, o[4 * q4 + 1]);
-                o[4 * q4 + 2] = fmaf(p, v.z, o[4 * q4 + 2]);
-                o[4 * q4 + 3] = fmaf(p, v.w, o[4 * q4 + 3]);
-            }
+        for (int db = 0; db < 8; ++db) acc[db] *= corr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int db = 0; db < 8; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r][db >> 2][db & 3], p[r], acc[db], 0, 0, 0);
+    }
+
+    l_run = across_groups_sum(l_run);
+    float* mine = part[wave][c16] + 32 * g;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        *reinterpret_cast<float4*>(mine + 8 * r) = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+        *reinterpret_cast<float4*>(mine + 8 * r + 4) = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+    }
+    if (g == 0) { part_m[wave][c16] = m_run; part_l[wave][c16] = l_run; }
+    __syncthreads();
+    for (int row = tid >> 5; row < kRows && i0 + row < m; row += 8) {
+        float m_all = part_m[0][row];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) m_all = fmaxf(m_all, part_m[w][row]);
+        float4 o = zero;
+        float l = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float f = expf(part_m[w][row] - m_all);
+            const float4 x = *reinterpret_cast<const float4*>(&part[w][row][col]);
+            o.x = fmaf(f, x.x, o.x); o.y = fmaf(f, x.y, o.y); o.z = fmaf(f, x.z, o.z); o.w = fmaf(f, x.w, o.w);
+            l = fmaf(f, part_l[w][row], l);
         }
+        const float inv = 1.0f / l;
+        const int p = idx[i0 + row];
+        *reinterpret_cast<float4*>(Ob + (long long)p * d.os[2] + col) = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
     }
-    if (i < m) {
-        float* dst = O + (long long)b * d.os[0] + (long long)hq * d.os[1] + (long long)idx[i] * d.os[2];
-        const float inv = 1.0f / l_run;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-            *reinterpret_cast<float4*>(dst + 4 * g + 32 * q4) =
-                make_float4(o[4 * q4] * inv, o[4 * q4 + 1] * inv, o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv);
-    }
+    zero_rows();
 }
 
 }  // namespace
@@ -172,9 +230,11 @@ hipError_t launch_attend_f32(const Dims& d, float scale, const float* Q, const f
                              const float* V, const int32_t* kept_idx, float* O,
                              const int32_t* counts, long long idx_stride, hipStream_t s)
 {
-    dim3 grid((d.m + kFM - 1) / kFM, d.Hq, d.B);
+    // where few tokens are kept, a tile's zero rows are more than one workgroup should write
+    const int parts = counts ? 1 : std::min(64, std::max(1, d.n / (32 * d.m)));
+    const dim3 grid((d.m + 15) / 16 * parts, d.Hq, d.B);
     attend_f32_kernel<<<grid, dim3(256), 0, s>>>(d, scale, Q, K, V, kept_idx, O, counts,
-                                                 counts ? idx_stride : (long long)d.m);
+                                                 counts ? idx_stride : (long long)d.m, parts);
     return hipGetLastError();
 }
 

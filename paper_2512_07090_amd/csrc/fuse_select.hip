@@ -583,24 +583,6 @@ __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     }
 }
 
-__global__ void mask_from_idx_kernel(const int32_t* __restrict__ kept_idx, int n, int m,
-                                     uint8_t* __restrict__ keep,
-                                     const int32_t* __restrict__ counts, long long idx_stride)
-{
-    const int b = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < (counts ? counts[b] : m)) {
-        const int p = kept_idx[(long long)b * idx_stride + i];
-        if (p >= 0 && p < n) keep[(long long)b * n + p] = 1;
-    }
-}
-
-__global__ void clear_bytes_kernel(uint8_t* p, long long count)
-{
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0;
-}
-
 }  // namespace
 
 hipError_t launch_fuse(const Dims& d, int fusion, const float* sim_k, const float* sim_v,
@@ -684,16 +666,6 @@ __global__ void keep_none_kernel(int n, uint8_t* __restrict__ keep, float* __res
 hipError_t launch_keep_none(const Dims& d, uint8_t* keep, float* tau, hipStream_t s)
 {
     keep_none_kernel<<<dim3((d.n + 255) / 256, d.B), dim3(256), 0, s>>>(d.n, keep, tau);
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_from_idx(const Dims& d, const int32_t* kept_idx, uint8_t* keep,
-                                const int32_t* counts, long long idx_stride, hipStream_t s)
-{
-    const long long count = (long long)d.B * d.n;
-    clear_bytes_kernel<<<dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s>>>(keep, count);
-    mask_from_idx_kernel<<<dim3((d.m + 255) / 256, d.B), dim3(256), 0, s>>>(
-        kept_idx, d.n, d.m, keep, counts, counts ? idx_stride : (long long)d.m);
     return hipGetLastError();
 }
 

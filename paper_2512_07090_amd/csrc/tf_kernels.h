@@ -54,19 +54,17 @@ hipError_t launch_keep_all(const Dims& d, uint8_t* keep, int32_t* kept_idx, floa
                            hipStream_t s);
 // no token kept: keep = 0, tau = -inf (tau may be null)
 hipError_t launch_keep_none(const Dims& d, uint8_t* keep, float* tau, hipStream_t s);
-// keep mask from an index list (for callers that bring their own kept set)
-hipError_t launch_mask_from_idx(const Dims& d, const int32_t* kept_idx, uint8_t* keep,
-                                const int32_t* counts, long long idx_stride, hipStream_t s);
 
 // ---- attention over the kept tokens -------------------------------------------------------
 hipError_t launch_zero_filtered(const Dims& d, int dtype, const uint8_t* keep, void* O,
                                 hipStream_t s);
 // counts (may be null): per-row numbers of kept tokens [B]; kept_idx rows are then idx_stride
-// apart and d.m is only the bound on a row's count
+// apart and d.m is only the bound on a row's count.  Both write the zero rows of filtered positions too
+// (kept_idx strictly ascending).
 hipError_t launch_attend_f32(const Dims& d, float scale, const float* Q, const float* K,
                              const float* V, const int32_t* kept_idx, float* O,
                              const int32_t* counts, long long idx_stride, hipStream_t s);
-// also writes the zero rows of filtered positions (kept_idx strictly ascending).  n_cu: compute
+// n_cu: compute
 // units of the device (one persistent workgroup each, or two half as large); n_xcd: its accelerator dies (each with an
 // L2 of its own); expected: with counts, about how many tokens a row keeps (only the speed depends on it).  hipErrorInvalidValue if a (batch, head) slice of K / V spans 4 GiB or more.
 hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const void* K,

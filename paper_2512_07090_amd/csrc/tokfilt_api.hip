@@ -49,7 +49,7 @@ tf_status fail(tf_ctx* c, tf_status s, const char* fmt, ...)
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Workspace {
-    size_t sim_k, sim_v, seg_tot, keep_tmp, total;  // byte offsets
+    size_t sim_k, sim_v, seg_tot, spare, total;  // byte offsets
 };
 
 // Pure shape validation, usable without a context.
@@ -127,7 +127,7 @@ Workspace carve(const tf_params* p)
     w.sim_k = off; off += sims;
     w.sim_v = off; off += sims;
     w.seg_tot = off; off += align256(tf::score_scratch_floats(d) * sizeof(float));
-    w.keep_tmp = off; off += align256((size_t)p->batch * p->seq);
+    w.spare = off; off += align256((size_t)p->batch * p->seq);   // not used any more; part of the size callers know
     w.total = off;
     return w;
 }
@@ -164,19 +164,15 @@ void mark(tf_ctx* ctx, int slot, int stage, hipStream_t s)
 // and d.m is the bound p->seq
 tf_status run_attend(tf_ctx* ctx, const tf_params* p, const tf::Dims& d, const void* Q,
                      const void* K, const void* V, const int32_t* kept_idx,
-                     const uint8_t* keep, void* O, hipStream_t s, int slot,
+                     void* O, hipStream_t s, int slot,
                      const int32_t* counts = nullptr)
 {
     const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->head_dim);
-    if (p->dtype == TF_F32) {
-        tf_status st = dev(ctx, tf::launch_zero_filtered(d, p->dtype, keep, O, s), "zero-fill launch");
-        if (st != TF_OK) return st;
-        mark(ctx, slot, TF_STAGE_ATTEND, s);
+    // (both kernels write the zero rows themselves)
+    mark(ctx, slot, TF_STAGE_ATTEND, s);
+    if (p->dtype == TF_F32)
         return dev(ctx, tf::launch_attend_f32(d, scale, (const float*)Q, (const float*)K, (const float*)V,
                                               kept_idx, (float*)O, counts, p->seq, s), "fp32 attention launch");
-    }
-    // the bf16 kernel writes the zero rows itself
-    mark(ctx, slot, TF_STAGE_ATTEND, s);
     return dev(ctx, tf::launch_attend_bf16(d, scale, Q, K, V, kept_idx, O, ctx->n_cu, ctx->n_xcd, counts,
                                            tf_keep_count(p->seq, p->prune_ratio), p->seq, s),
                "bf16 attention launch");
@@ -241,7 +237,7 @@ tf_status run_path(tf_ctx* ctx, const tf_params* p, const Workspace& w, const vo
     if (st != TF_OK) return st;
     mark(ctx, slot, 3, s);  // compaction is part of the decision kernel
     mark(ctx, slot, 4, s);
-    st = run_attend(ctx, p, d, Q, K, V, kept_idx, keep, O, s, slot);
+    st = run_attend(ctx, p, d, Q, K, V, kept_idx, O, s, slot);
     if (st != TF_OK) return st;
     mark(ctx, slot, TF_N_STAGES, s);
     return TF_OK;
@@ -380,12 +376,7 @@ tf_status tf_attend(tf_ctx* ctx, const tf_params* p, const void* Q, const void* 
     if (m < 1 || m > p->seq) return fail(ctx, TF_ERR_INVALID_ARG, "m must be in [1, seq]");
     const tf::Dims d = make_dims(p, m);
     hipStream_t s = (hipStream_t)stream;
-    uint8_t* keep = (uint8_t*)((char*)ws + w.keep_tmp);
-    if (p->dtype == TF_F32) {  // the fp32 path zero-fills from a mask
-        st = dev(ctx, tf::launch_mask_from_idx(d, kept_idx, keep, nullptr, 0, s), "mask launch");
-        if (st != TF_OK) return st;
-    }
-    return run_attend(ctx, p, d, Q, K, V, kept_idx, keep, O, s, -1);
+    return run_attend(ctx, p, d, Q, K, V, kept_idx, O, s, -1);
 }
 
 tf_status tf_select_online(tf_ctx* ctx, const tf_params* p, float eta, float tau0,
@@ -420,12 +411,7 @@ tf_status tf_attend_ragged(tf_ctx* ctx, const tf_params* p, const void* Q, const
         return fail(ctx, TF_ERR_INVALID_ARG, "Q, K, V and O must be 16-byte aligned");
     const tf::Dims d = make_dims(p, p->seq);
     hipStream_t s = (hipStream_t)stream;
-    uint8_t* keep = (uint8_t*)((char*)ws + w.keep_tmp);
-    if (p->dtype == TF_F32) {  // the fp32 path zero-fills from a mask
-        st = dev(ctx, tf::launch_mask_from_idx(d, kept_idx, keep, count, p->seq, s), "mask launch");
-        if (st != TF_OK) return st;
-    }
-    return run_attend(ctx, p, d, Q, K, V, kept_idx, keep, O, s, -1, count);
+    return run_attend(ctx, p, d, Q, K, V, kept_idx, O, s, -1, count);
 }
 
 tf_status tf_filtered_attention_online(tf_ctx* ctx, const tf_params* p, float eta, float tau0,
@@ -457,7 +443,7 @@ tf_status tf_filtered_attention_online(tf_ctx* ctx, const tf_params* p, float et
     st = dev(ctx, tf::launch_select_online(d, p->warmup, (float)p->prune_ratio, eta, tau0, fused, keep,
                                            kept_idx, count, tau, s), "online decision launch");
     if (st != TF_OK) return st;
-    return run_attend(ctx, p, d, Q, K, V, kept_idx, keep, O, s, -1, count);
+    return run_attend(ctx, p, d, Q, K, V, kept_idx, O, s, -1, count);
 }
 
 size_t tf_decode_workspace_bytes(const tf_params* p)
@@ -515,7 +501,7 @@ tf_status tf_decode_prefill(tf_ctx* ctx, const tf_params* p, float eta, float ta
     st = dev(ctx, tf::launch_select_online(d, p->warmup, (float)p->prune_ratio, eta, tau0, fused, keep,
                                            kept_idx, count, state->tau, s), "online decision launch");
     if (st != TF_OK) return st;
-    st = run_attend(ctx, p, d, Q, K, V, kept_idx, keep, O, s, -1, count);
+    st = run_attend(ctx, p, d, Q, K, V, kept_idx, O, s, -1, count);
     if (st != TF_OK) return st;
     return dev(ctx, tf::launch_decode_seed(a, p->dtype, K, V, kept_idx, count, p->seq, d.kvs, s),
                "decode state hand-off launch");
@@ -636,7 +622,7 @@ tf_status tf_filtered_attention_layers(tf_ctx* ctx, const tf_params* p, int32_t 
             // nothing to filter: no scoring, every token kept, plain causal attention
             const tf::Dims d = make_dims(&pl, p->seq);
             st = dev(ctx, tf::launch_keep_all(d, keep[l], kept_idx[l], tau_l, s), "keep-all launch");
-            if (st == TF_OK) st = run_attend(ctx, &pl, d, Q[l], K[l], V[l], kept_idx[l], keep[l], O[l], s, -1);
+            if (st == TF_OK) st = run_attend(ctx, &pl, d, Q[l], K[l], V[l], kept_idx[l], O[l], s, -1);
         } else {
             st = run_path(ctx, &pl, w, Q[l], K[l], V[l], keep[l], kept_idx[l], fused[l], tau_l, O[l], ws, s);
         }

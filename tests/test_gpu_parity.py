@@ -521,6 +521,26 @@ def test_attend_many_groups_as_a_few_of_them(ctx, shape, rising):
                 assert torch.equal(part, got)
 
 
+@pytest.mark.parametrize("m", [1, 4, 15, 16, 17, 48, 63, 64, 65, 79, 80, 81, 129, 200])
+@pytest.mark.parametrize("gap", [1, 2, 100])
+def test_attend_f32_blocks_of_16(ctx, m, gap):
+    """Kept counts around the fp32 kernel's blocks of 16 keys and its four waves, with every token kept,
+    every second one, or so few that several workgroups share a tile's zero rows."""
+    _say("attend f32 m=%d gap=%d" % (m, gap))
+    n = m if gap == 1 else gap * m + 5
+    q, k, v, _ = synth.make_random_qkv(1, 2, 1, n, 128, dtype="f32", seed=m)
+    idx = np.sort(np.random.default_rng(m).choice(n, m, replace=False)).astype(np.int32)[None]
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.0)
+    buf = B.Buffers(p, "cuda:0")
+    buf.O.fill_(float("nan"))
+    ctx.tf_attend(p, q.cuda(), k.cuda(), v.cuda(), torch.from_numpy(idx).cuda(), m, buf.O, buf.ws)
+    torch.cuda.synchronize()
+    O_g = buf.O.cpu().numpy().astype(np.float64)
+    assert not np.isnan(O_g).any()
+    assert np.all(np.delete(O_g, idx[0], axis=2) == 0)
+    assert np.abs(O_g - oracle.attend(q, k, v, idx)).max() <= ATTN_TOL[q.dtype]
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_attend_zero_rows_with_long_gaps(ctx, dt):
     """Kept sets with filtered runs of every length (before the first kept token, between kept
