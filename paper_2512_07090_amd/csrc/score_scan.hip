@@ -359,22 +359,43 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
 
 }  // namespace
 
-ScorePlan plan_score(int B, int Hkv, int n)
+struct ScorePlan {
+    int nseg;     // sequence segments per (tensor, batch, head) chain
+    int seg_len;  // tokens per segment, a multiple of the scan tile
+};
+
+// Segments of a chain: as many as keep every workgroup of the launch resident at once (their registers
+// allow two bf16 workgroups a compute unit, one fp32), never one more: a second round of a
+// few workgroups takes as long as the first.  Whole calls of tf_score at `chains` x tokens, with the
+// segment count of a chain rounded up before and down now: incremental anchor 160 x 1777 37.4 -> 29.9 us,
+// fp32 80 x 1400 32.0 -> 28.0.
+// Exact mean: what the totals pass reads twice is not worth it from kOneSegment chains on (160 x 1777: 33.2 us
+// with one segment, 34.1 with three; 192 x 3000 58.7 -> 50.5 with one, 240 x 3000 63.0 -> 51.9;
+// 128 x 3000 48.6 with one, 39.9 with four).  A segment has at least two tiles where there are many (16 x 3001
+// 16.4 -> 14.7 us), four behind the incremental anchor's warm-up (16 x 8192 20.9 -> 17.7).
+constexpr int kResidentBf16 = 512, kResidentF32 = 256, kOneSegment = 150;
+
+// chains: of this launch (one tensor's for the key-only and value-only scores); most: segments a chain's totals have
+// room for.
+static ScorePlan plan_score(int chains, int most, int n, bool f32, bool ema)
 {
-    const int chains = 2 * B * Hkv;
     const int tiles = (n + kTile - 1) / kTile;
-    int want = chains >= 256 ? 1 : (512 + chains - 1) / chains;
-    int nseg = want < tiles ? want : tiles;
-    if (nseg < 1) nseg = 1;
-    const int tiles_per_seg = (tiles + nseg - 1) / nseg;
+    int nseg = std::max(1, (f32 ? kResidentF32 : kResidentBf16) / chains);
+    if (!ema && chains >= kOneSegment) nseg = 1;
+    nseg = std::min({nseg, tiles, std::max(1, most)});
+    const int least = tiles < 20 ? 1 : (ema ? 4 : 2);
+    const int tiles_per_seg = std::max(least, (tiles + nseg - 1) / nseg);
     nseg = (tiles + tiles_per_seg - 1) / tiles_per_seg;
     return ScorePlan{nseg, tiles_per_seg * kTile};
 }
 
 size_t score_scratch_floats(const Dims& d)
 {
-    const ScorePlan p = plan_score(d.B, d.Hkv, d.n);
-    return (size_t)2 * d.B * d.Hkv * p.nseg * kHeadDim;
+    // room for at least as many segments as any plan has (the size is part of what callers allocate)
+    const int chains = 2 * d.B * d.Hkv, tiles = (d.n + kTile - 1) / kTile;
+    int nseg = std::min(tiles, chains >= 256 ? 1 : (512 + chains - 1) / chains);
+    nseg = (tiles + (tiles + nseg - 1) / nseg - 1) / ((tiles + nseg - 1) / nseg);
+    return (size_t)chains * nseg * kHeadDim;
 }
 
 // Rows of warm-up before a segment of the incremental anchor: gamma^rows <= 1e-10, in whole
@@ -401,13 +422,13 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
                                  float* sim_v, float* seg_tot, int tensors, int anchor,
                                  float gamma, hipStream_t s)
 {
-    ScorePlan p = plan_score(d.B, d.Hkv, d.n);
     const int BH = d.B * d.Hkv;
     const int n_tensors = tensors == 0 ? 2 : 1;
     const int first_tensor = tensors == 2 ? 1 : 0;
     const int chains = n_tensors * BH;
     const int inclusive = anchor >> 1;  // bit 1 of `anchor`: the anchor of a row includes the row
     anchor &= 1;
+    ScorePlan p = plan_score(chains, (int)(score_scratch_floats(d) / kHeadDim / chains), d.n, sizeof(T) == 4, anchor == 1);
     // Tensors that together exceed the last-level cache (256 MB Infinity Cache) are streamed past
     // the L2: measured on whole steps, workload 2 (537 MB) -2.6 %, workload 3 (336 MB) -1.2 %;
     // below that size the later kernels find the rows in the caches and streaming costs

@@ -19,11 +19,6 @@ struct Dims {
 };
 
 // ---- scoring: exclusive prefix sums of K and V along the sequence + per-head cosines -----
-struct ScorePlan {
-    int nseg;     // sequence segments per (tensor, batch, head) chain
-    int seg_len;  // tokens per segment, a multiple of the scan tile
-};
-ScorePlan plan_score(int B, int Hkv, int n);
 size_t score_scratch_floats(const Dims& d);  // segment totals
 // sim_k / sim_v: [B][Hkv][n] float.  seg_tot: scratch of score_scratch_floats() floats.
 // tensors: 0 = K and V, 1 = K only, 2 = V only.  anchor: bit 0: 0 = exact mean, 1 = incremental

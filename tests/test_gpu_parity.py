@@ -243,6 +243,32 @@ def test_score_parity_exact_mean_on_a_stale_workspace(ctx, shape):
             assert_scores_close(buf.fused.cpu().numpy(), oracle.fuse(ck, cv, mode), "fused mode %d" % mode)
 
 
+@pytest.mark.parametrize("shape", [
+    # (dtype, B, Hkv, n, gamma or None): chains and tiles on both sides of the segment plan's borders
+    ("bf16", 1, 74, 1920, None), ("bf16", 1, 76, 1920, None), ("bf16", 1, 8, 2432, None), ("bf16", 1, 8, 2433, None),
+    ("f32", 1, 40, 1400, None), ("f32", 1, 16, 2433, None), ("bf16", 2, 40, 1777, 0.9), ("bf16", 1, 8, 2433, 0.9),
+    ("f32", 1, 8, 2049, 0.9),
+])
+def test_score_parity_at_the_borders_of_the_segment_plan(ctx, shape):
+    """Both tensors and one alone (which has half the chains) against the oracle, on a stale workspace."""
+    dt, Bn, H, n, gamma = shape
+    _say("score plan %s" % (shape,))
+    q, k, v, _ = synth.make_random_qkv(Bn, H, H, n, 128, dtype=dt, seed=700 + n + H)
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.5, ema_gamma=gamma)
+    buf = B.Buffers(p, "cuda:0", with_sims=True)
+    buf.ws.fill_(0xFF)
+    ck, cv = (oracle.anchor_cosine(x) if gamma is None else oracle.anchor_cosine_ema(x, gamma) for x in (k, v))
+    for mode in (B.TF_FUSE_EQ2, B.TF_FUSE_KEY_ONLY, B.TF_FUSE_VALUE_ONLY):
+        p.fusion = mode
+        ctx.tf_score(p, k.cuda(), v.cuda(), buf.fused, buf.sim_k, buf.sim_v, buf.ws)
+        torch.cuda.synchronize()
+        if mode != B.TF_FUSE_VALUE_ONLY:
+            assert_scores_close(buf.sim_k.cpu().numpy(), ck, "sim_k")
+        if mode != B.TF_FUSE_KEY_ONLY:
+            assert_scores_close(buf.sim_v.cpu().numpy(), cv, "sim_v")
+        assert_scores_close(buf.fused.cpu().numpy(), oracle.fuse(ck, cv, mode), "fused mode %d" % mode)
+
+
 def test_whole_path_incremental_anchor(ctx):
     _say("whole path ema")
     w = synth.scaled(synth.workload(1), batch=2, seq=1800, n_q_heads=8, n_kv_heads=8)
