@@ -100,8 +100,9 @@ __global__ void decode_init_kernel(double* anchor_k, double* anchor_v, long long
 // The float operations of the threshold rule are the ones of the batched online decision, in
 // the same order, with contraction switched off, so both forms agree bit for bit.
 // Latency is what this kernel costs, so the row's scalars are fetched up front by the lane
-// that needs them, the head statistics are reduced by one wave rather than one lane, and the
-// first pair of a group stays in registers for the anchor update.
+// that needs them, the head statistics are reduced by one wave rather than one lane, the anchors
+// are stored before the decision, which they do not depend on, and the first row of a group stays in
+// registers for the cache.
 #pragma clang fp contract(off)
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -137,28 +138,29 @@ __global__ __launch_bounds__(1024) void decode_score_kernel(
     const double f_a = ema ? (inclusive ? gamma : 1.0) : (rows_in > 0 ? 1.0 / (double)rows_in : 0.0);
     const double f_x = inclusive ? (ema ? 1.0 - gamma : f_a) : 0.0;
 
-    float x0[8];       // the group's first pair, kept for the update below
-    double a0[8];
+    typename Raw8<T>::type raw0;   // the group's first row, kept for the cache
     for (int pr = grp; pr < 2 * Hkv; pr += n_grp) {
         const int w = pr >= Hkv, h = pr - w * Hkv;
         const long long off = ((long long)b * Hkv + h) * kHeadDim + c8 * 8;
-        float x[8];
-        load8((w ? v : k) + off, x);
-        const double* a = (w ? anchor_v : anchor_k) + off;
+        const typename Raw8<T>::type raw = *reinterpret_cast<const typename Raw8<T>::type*>((w ? v : k) + off);
+        double* a = (w ? anchor_v : anchor_k) + off;
         double av[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) av[c] = a[c];
-        if (pr == grp) {
+        float x[8];
+        unpack8(raw, x);
+        if (pr == grp) raw0 = raw;
+        // the token is absorbed whatever is decided about it, and nobody else reads these columns
 #pragma unroll
-            for (int c = 0; c < 8; ++c) { x0[c] = x[c]; a0[c] = av[c]; }
-        }
+        for (int c = 0; c < 8; ++c)
+            a[c] = ema ? gamma * av[c] + (1.0 - gamma) * (double)x[c] : av[c] + (double)x[c];
         double dot = 0.0, na = 0.0, nx = 0.0;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const double ac = av[c] * f_a + (double)x[c] * f_x;
-            dot += ac * (double)x[c];
-            na += ac * ac;
-            nx += (double)x[c] * (double)x[c];
+            const double xc = (double)x[c], ac = fma(av[c], f_a, xc * f_x);
+            dot = fma(ac, xc, dot);
+            na = fma(ac, ac, na);
+            nx = fma(xc, xc, nx);
         }
         dot = group16_sum(dot); na = group16_sum(na); nx = group16_sum(nx);
         double den = sqrt(na) * sqrt(nx);
@@ -206,26 +208,13 @@ __global__ __launch_bounds__(1024) void decode_score_kernel(
     __syncthreads();
     const int slot = slot_s;
 
+    if (slot < 0) return;
     for (int pr = grp; pr < 2 * Hkv; pr += n_grp) {
         const int w = pr >= Hkv, h = pr - w * Hkv;
-        const long long off = ((long long)b * Hkv + h) * kHeadDim + c8 * 8;
-        const T* src = (w ? v : k) + off;
-        double* a = (w ? anchor_v : anchor_k) + off;
-        float x[8];
-        double av[8];
-        if (pr == grp) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) { x[c] = x0[c]; av[c] = a0[c]; }
-        } else {
-            load8(src, x);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) av[c] = a[c];
-        }
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-            a[c] = ema ? gamma * av[c] + (1.0 - gamma) * (double)x[c] : av[c] + (double)x[c];
-        if (slot >= 0)
-            copy8((w ? v_cache : k_cache) + (((long long)b * Hkv + h) * capacity + slot) * kHeadDim + c8 * 8, src);
+        typename Raw8<T>::type raw = raw0;
+        if (pr != grp)
+            raw = *reinterpret_cast<const typename Raw8<T>::type*>((w ? v : k) + ((long long)b * Hkv + h) * kHeadDim + c8 * 8);
+        *reinterpret_cast<typename Raw8<T>::type*>((w ? v_cache : k_cache) + (((long long)b * Hkv + h) * capacity + slot) * kHeadDim + c8 * 8) = raw;
     }
 }
 #pragma clang fp contract(fast)
