@@ -45,10 +45,10 @@ __global__ __launch_bounds__(256) void zero_filtered_kernel(Dims d, const uint8_
 // Keys and values go from the caches straight to registers (no two waves of a workgroup need the
 // same ones): the next block's K is requested when the products have consumed this one's, V one
 // block's scores ahead of its use.
-// What bounds it: a block is 64 MFMAs of 32 cycles (2.0 times that in all at long rows: three waves a SIMD,
+// What bounds it: a block is 64 MFMAs of 32 cycles (1.7 times that in all at long rows: three waves a SIMD,
 // limited by their registers, do not hide all of the softmax), at short rows one wave's latency chain. Plain FMAs on 32 x 32
 // tiles in LDS with the zero rows in a launch of their own against this: 32 heads x 256 kept
-// tokens of 512 75 -> 22 us, 40 x 1350 of 1500 856 -> 252 us, distance from 64 bits 3.0e-7 -> 2.0e-7 (fewer
+// tokens of 512 75 -> 18 us, 40 x 1350 of 1500 856 -> 215 us, distance from 64 bits 3.0e-7 -> 2.0e-7 (fewer
 // roundings in a row). 32 queries a workgroup halve the loads but take 346 us there (two waves a SIMD).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kNone = -1e30f;   // masked score, and the maximum of a row without keys
@@ -80,10 +80,14 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
     constexpr int kRows = 16, kStride = kHeadDim + 4;
     __shared__ __attribute__((aligned(16))) float part[4][kRows][kStride];
     __shared__ float part_m[4][kRows], part_l[4][kRows];
+    __shared__ int tile_pos[kRows + 1];
 
-    // the longest first; of the `parts` workgroups of a tile the others only help with its zero rows
-    const int qt = (gridDim.x - 1 - blockIdx.x) / parts, zp = (gridDim.x - 1 - blockIdx.x) % parts;
-    const int hq = blockIdx.y, b = blockIdx.z;
+    // The longest tiles of all heads first, so that they spread over the dies and the short ones fill in behind
+    // them (head by head, 32 heads x 256 kept tokens took 21.3 instead of 17.6 us, 8 x 32 x 125 45 instead of 35); of the `parts` workgroups of
+    // a tile the others only help with its zero rows.
+    const int groups = d.B * d.Hq, bh = blockIdx.x % groups, rank = blockIdx.x / groups;
+    const int qt = (gridDim.x / groups - 1 - rank) / parts, zp = rank % parts;
+    const int hq = bh % d.Hq, b = bh / d.Hq;
     const int hk = hq / (d.Hq / d.Hkv);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c16 = lane & 15, g = lane >> 4;
@@ -105,16 +109,28 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
     const float* Vb = V + (long long)b * d.kvs[0] + (long long)hk * d.kvs[1];
     const int i_last = min(i0 + kRows, m) - 1;
     const int n_blocks = i_last / 16 + 1;
-    // the filtered positions behind each query of the tile (and before the first one) are zero rows
+    // positions of the tile's queries and of the kept token after them (or the row's end)
+    if (tid <= kRows) tile_pos[tid] = i0 + tid < m ? idx[i0 + tid] : d.n;
+    // The filtered positions behind each query of the tile (and before the first one) are zero rows, written
+    // without a look at the gaps one by one: with z_i = the zero rows before query i of the tile, the k-th one
+    // sits at position_0 + 1 + k + #{i >= 1 : z_i <= k}, and the count is a ballot.  (After a barrier.)
     const int col = 4 * (tid & 31);   // 32 threads a row, four columns each
     auto zero_rows = [&]() {
-        for (int i = i0 == 0 ? -1 : i0; i <= i_last; ++i) {
-            const int lo = i < 0 ? 0 : idx[i] + 1, hi = i + 1 < m ? idx[i + 1] : d.n;
-            for (int z = lo + 8 * zp + (tid >> 5); z < hi; z += 8 * parts)
-                *reinterpret_cast<float4*>(Ob + (long long)z * d.os[2] + col) = zero;
+        const int n_q = i_last - i0 + 1, half = lane >> 5, qi = lane & 31;
+        const int first = tile_pos[0], n_zero = tile_pos[n_q] - first - n_q;
+        const int z_mine = qi >= 1 && qi < n_q ? tile_pos[qi] - first - qi : 0x7fffffff;
+        for (int k0 = 8 * zp + 2 * wave; k0 < n_zero; k0 += 8 * parts) {
+            const int k = k0 + half;
+            const unsigned long long below = __ballot(z_mine <= k);
+            const int p = first + 1 + k + __popc((unsigned)(below >> (32 * half)));
+            if (k < n_zero) *reinterpret_cast<float4*>(Ob + (long long)p * d.os[2] + col) = zero;
         }
+        if (i0 == 0)
+            for (int z = 8 * zp + (tid >> 5); z < first; z += 8 * parts)
+                *reinterpret_cast<float4*>(Ob + (long long)z * d.os[2] + col) = zero;
     };
     if (zp > 0) {
+        __syncthreads();
         zero_rows();
         return;
     }
@@ -207,7 +223,7 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
             l = fmaf(f, part_l[w][row], l);
         }
         const float inv = 1.0f / l;
-        const int p = idx[i0 + row];
+        const int p = tile_pos[row];
         *reinterpret_cast<float4*>(Ob + (long long)p * d.os[2] + col) = make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv);
     }
     zero_rows();
@@ -232,8 +248,8 @@ hipError_t launch_attend_f32(const Dims& d, float scale, const float* Q, const f
 {
     // where few tokens are kept, a tile's zero rows are more than one workgroup should write
     const int parts = counts ? 1 : std::min(64, std::max(1, d.n / (32 * d.m)));
-    const dim3 grid((d.m + 15) / 16 * parts, d.Hq, d.B);
-    attend_f32_kernel<<<grid, dim3(256), 0, s>>>(d, scale, Q, K, V, kept_idx, O, counts,
+    const unsigned grid = (unsigned)((d.m + 15) / 16 * parts) * d.Hq * d.B;   // far below 2^31: a row of Q has 512 bytes
+    attend_f32_kernel<<<dim3(grid), dim3(256), 0, s>>>(d, scale, Q, K, V, kept_idx, O, counts,
                                                  counts ? idx_stride : (long long)d.m, parts);
     return hipGetLastError();
 }
