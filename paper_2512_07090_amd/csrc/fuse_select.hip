@@ -15,6 +15,35 @@ namespace {
 constexpr int kFuseTokens = 64;
 constexpr int kFuseThreads = 256;
 
+// One token's score from its per-head cosines, `stride` apart.
+__device__ __forceinline__ float fuse_token(const float* ck, const float* cv, int stride, int H, int mode)
+{
+    float sk = 0.f, sv = 0.f;
+    for (int h = 0; h < H; ++h) {
+        sk += ck[h * stride];
+        sv += cv[h * stride];
+    }
+    const float inv_h = 1.0f / (float)H;
+    sk *= inv_h;
+    sv *= inv_h;
+    float vk = 0.f, vv = 0.f;
+    for (int h = 0; h < H; ++h) {
+        const float dk = ck[h * stride] - sk;
+        const float dv = cv[h * stride] - sv;
+        vk = fmaf(dk, dk, vk);
+        vv = fmaf(dv, dv, vv);
+    }
+    const float ek = vk * inv_h + 1e-12f, ev = vv * inv_h + 1e-12f;
+    float alpha;
+    if (mode == 0)
+        alpha = ek / (ek + ev);  // = (1/ev) / (1/ek + 1/ev), the printed form of Eq. 2
+    else if (mode == 1)
+        alpha = ev / (ek + ev);  // = (1/ek) / (1/ek + 1/ev)
+    else
+        alpha = mode == 2 ? 1.f : 0.f;
+    return alpha * sk + (1.f - alpha) * sv;
+}
+
 __global__ __launch_bounds__(kFuseThreads) void fuse_kernel(const float* __restrict__ sim_k,
                                                             const float* __restrict__ sim_v,
                                                             int H, int n, int mode,
@@ -38,30 +67,7 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_kernel(const float* __restr
     }
     __syncthreads();
     if (hg != 0 || t >= n) return;
-    float sk = 0.f, sv = 0.f;
-    for (int h = 0; h < H; ++h) {
-        sk += ck[h * kFuseTokens + tok];
-        sv += cv[h * kFuseTokens + tok];
-    }
-    const float inv_h = 1.0f / (float)H;
-    sk *= inv_h;
-    sv *= inv_h;
-    float vk = 0.f, vv = 0.f;
-    for (int h = 0; h < H; ++h) {
-        const float dk = ck[h * kFuseTokens + tok] - sk;
-        const float dv = cv[h * kFuseTokens + tok] - sv;
-        vk = fmaf(dk, dk, vk);
-        vv = fmaf(dv, dv, vv);
-    }
-    const float ek = vk * inv_h + 1e-12f, ev = vv * inv_h + 1e-12f;
-    float alpha;
-    if (mode == 0)
-        alpha = ek / (ek + ev);  // = (1/ev) / (1/ek + 1/ev), the printed form of Eq. 2
-    else if (mode == 1)
-        alpha = ev / (ek + ev);  // = (1/ek) / (1/ek + 1/ev)
-    else
-        alpha = mode == 2 ? 1.f : 0.f;
-    fused[(long long)b * n + t] = alpha * sk + (1.f - alpha) * sv;
+    fused[(long long)b * n + t] = fuse_token(ck + tok, cv + tok, kFuseTokens, H, mode);
 }
 
 // ------------------------------------------------------------------------------ block scan
@@ -245,10 +251,19 @@ __device__ __forceinline__ int rank_below(unsigned long long ballot)
     return __builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ballot, 0));
 }
 
-template <int IPT>
+//
+// FUSE: the scores are not there yet; the workgroup makes them from the row's cosines (at most
+// kFuseFloats a tensor, staged in LDS) with the arithmetic of fuse_kernel and writes them to `fused`.
+// That takes about 2 us here and 4 in a launch of its own; a longer row, or one with more heads, would keep
+// one compute unit loading what fuse_kernel spreads over many.  Whole calls: 32 heads x 333 tokens
+// 29.4 -> 27.3 us, fp32 32 x 512 36.9 -> 35.5; 8 heads x 2048 tokens (four a thread) 0.5 us slower a call.
+constexpr int kFuseFloats = 16384;
+
+template <int IPT, bool FUSE>
 __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
-    const float* __restrict__ fused, int n, int m, int warmup, uint8_t* __restrict__ keep,
-    int32_t* __restrict__ kept_idx, float* __restrict__ tau)
+    float* __restrict__ fused, int n, int m, int warmup, uint8_t* __restrict__ keep,
+    int32_t* __restrict__ kept_idx, float* __restrict__ tau, const float* __restrict__ sim_k,
+    const float* __restrict__ sim_v, int H, int mode)
 {
     // copies of the histogram, one per lane residue: a wave's tokens fall into few bins at times
     // (runs of like tokens), and lanes adding to one word take turns
@@ -264,7 +279,7 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
     __shared__ int sel_k, sel_cnt, n_cand;
 
     const int b = blockIdx.x;
-    const float* S = fused + (long long)b * n;
+    float* S = fused + (long long)b * n;
     uint8_t* kp = keep + (long long)b * n;
     int32_t* out = kept_idx + (long long)b * m;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -276,8 +291,24 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
     // (every load is issued whatever the token, so that none waits for the one before; forced tokens
     // and the tail past n take no part in the selection: they stay above every score)
     float sc[IPT];
+    if constexpr (FUSE) {
+        __shared__ float cos_k[kFuseFloats], cos_v[kFuseFloats];   // [head][token], as in memory
+        // (key-only / value-only scores read one tensor's cosines, the other was not computed)
+        const float* pk = (mode == 3 ? sim_v : sim_k) + (long long)b * H * n;
+        const float* pv = (mode == 2 ? sim_k : sim_v) + (long long)b * H * n;
+#pragma unroll 8
+        for (int i = tid; i < H * n; i += kSelThreads) { cos_k[i] = pk[i]; cos_v[i] = pv[i]; }
+        __syncthreads();
 #pragma unroll
-    for (int i = 0; i < IPT; ++i) sc[i] = S[min(i * kSelThreads + tid, n - 1)];
+        for (int i = 0; i < IPT; ++i) {
+            const int t = i * kSelThreads + tid;
+            sc[i] = 0.f;
+            if (t < n) S[t] = sc[i] = fuse_token(cos_k + t, cos_v + t, n, H, mode);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) sc[i] = S[min(i * kSelThreads + tid, n - 1)];
+    }
     auto takes_part = [&](int i) { return i * kSelThreads + tid >= forced && i * kSelThreads + tid < n; };
     bool finite = true;
 #pragma unroll
@@ -605,19 +636,31 @@ hipError_t launch_select_compact(const Dims& d, int warmup, const float* fused, 
                                  int32_t* kept_idx, float* tau, hipStream_t s)
 {
     const int ipt = (d.n + kSelThreads - 1) / kSelThreads;
-    if (ipt <= 1)
-        select_compact_kernel<1><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);
-    else if (ipt <= 4)
-        select_compact_kernel<4><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);
-    else if (ipt <= 8)
-        select_compact_kernel<8><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);
-    else if (ipt <= 32)
-        select_compact_kernel<32><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau);
+    // (the kernel only reads the scores here)
+    float* S = const_cast<float*>(fused);
+#define TF_SELECT(IPT) \
+    select_compact_kernel<IPT, false><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(S, d.n, d.m, warmup, keep, kept_idx, tau, nullptr, nullptr, 0, 0)
+    if (ipt <= 1) TF_SELECT(1);
+    else if (ipt <= 4) TF_SELECT(4);
+    else if (ipt <= 8) TF_SELECT(8);
+    else if (ipt <= 32) TF_SELECT(32);
+#undef TF_SELECT
     else {
         // longer rows: scores stay in global memory, decision and compaction in two launches
         select_kernel<<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, tau);
         compact_kernel<<<dim3(d.B), dim3(kSelThreads), 0, s>>>(keep, d.n, d.m, kept_idx);
     }
+    return hipGetLastError();
+}
+
+bool fuse_select_fits(const Dims& d) { return d.n <= kSelThreads && (long long)d.Hkv * d.n <= kFuseFloats; }
+
+hipError_t launch_fuse_select(const Dims& d, int fusion, const float* sim_k, const float* sim_v,
+                              int warmup, float* fused, uint8_t* keep, int32_t* kept_idx, float* tau, hipStream_t s)
+{
+    if (!fuse_select_fits(d)) return hipErrorInvalidValue;
+    select_compact_kernel<1, true><<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, kept_idx, tau, sim_k,
+                                                                           sim_v, d.Hkv, fusion);
     return hipGetLastError();
 }
 

@@ -39,6 +39,10 @@ hipError_t launch_compact(const Dims& d, const uint8_t* keep, int32_t* kept_idx,
 // kernels above)
 hipError_t launch_select_compact(const Dims& d, int warmup, const float* fused, uint8_t* keep,
                                  int32_t* kept_idx, float* tau, hipStream_t s);
+// fusion and the two in one launch, for the short rows that fuse_select_fits() names
+bool fuse_select_fits(const Dims& d);
+hipError_t launch_fuse_select(const Dims& d, int fusion, const float* sim_k, const float* sim_v,
+                              int warmup, float* fused, uint8_t* keep, int32_t* kept_idx, float* tau, hipStream_t s);
 // online decision with an adaptive threshold: keep [B][n], kept_idx [B][n] (kept positions
 // ascending, then -1), count [B], tau [B] (may be null)
 hipError_t launch_select_online(const Dims& d, int warmup, float target, float eta, float tau0,

@@ -229,11 +229,14 @@ tf_status run_path(tf_ctx* ctx, const tf_params* p, const Workspace& w, const vo
                                              score_tensors(p), anchor_bits(p), p->ema_gamma, s), "score launch");
     if (st != TF_OK) return st;
     mark(ctx, slot, 1, s);
-    st = dev(ctx, tf::launch_fuse(d, p->fusion, sk, sv, fused, s), "fuse launch");
-    if (st != TF_OK) return st;
+    const bool one_launch = tf::fuse_select_fits(d);   // the fusion is then part of the decision kernel
+    if (!one_launch) {
+        st = dev(ctx, tf::launch_fuse(d, p->fusion, sk, sv, fused, s), "fuse launch");
+        if (st != TF_OK) return st;
+    }
     mark(ctx, slot, 2, s);
-    st = dev(ctx, tf::launch_select_compact(d, p->warmup, fused, keep, kept_idx, tau, s),
-             "select launch");
+    st = one_launch ? dev(ctx, tf::launch_fuse_select(d, p->fusion, sk, sv, p->warmup, fused, keep, kept_idx, tau, s), "fuse and select launch")
+                    : dev(ctx, tf::launch_select_compact(d, p->warmup, fused, keep, kept_idx, tau, s), "select launch");
     if (st != TF_OK) return st;
     mark(ctx, slot, 3, s);  // compaction is part of the decision kernel
     mark(ctx, slot, 4, s);

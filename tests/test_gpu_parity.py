@@ -391,6 +391,27 @@ def test_select_scores_that_are_no_numbers(ctx, kind, n):
         assert np.array_equal(np.flatnonzero(buf.keep[b].cpu().numpy()), want)
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 32, 63), (1, 40, 130), (1, 32, 512), (1, 32, 513), (3, 16, 1024), (1, 16, 1025),
+                                   (2, 40, 409), (1, 40, 410), (1, 128, 128)])
+@pytest.mark.parametrize("mode", [B.TF_FUSE_EQ2, B.TF_FUSE_INVVAR, B.TF_FUSE_KEY_ONLY, B.TF_FUSE_VALUE_ONLY])
+def test_short_rows_fuse_and_select_in_one_launch(ctx, shape, mode):
+    """Short rows are fused and decided in one kernel inside the whole path, in two behind tf_score and
+    tf_select: the arithmetic is the same, so scores, masks and positions are equal bit for bit."""
+    Bn, H, n = shape
+    _say("fuse and select %s mode %d" % (shape, mode))
+    q, k, v, _ = synth.make_random_qkv(Bn, H, H, n, 128, dtype="bf16", seed=n + H)
+    q, k, v = q.cuda(), k.cuda(), v.cuda()
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.5, 1, mode)
+    one, two = B.Buffers(p, "cuda:0"), B.Buffers(p, "cuda:0")
+    one.fused.fill_(7.0)
+    ctx.tf_filtered_attention(p, q, k, v, one.keep, one.kept_idx, one.fused, one.tau, one.O, one.ws)
+    ctx.tf_score(p, k, v, two.fused, None, None, two.ws)
+    ctx.tf_select(p, two.fused, two.keep, two.kept_idx, two.tau, two.ws)
+    torch.cuda.synchronize()
+    for x, y in ((one.fused, two.fused), (one.keep, two.keep), (one.kept_idx, two.kept_idx), (one.tau, two.tau)):
+        assert torch.equal(x, y)
+
+
 # ------------------------------------------------------------------ attention stage
 
 @pytest.mark.parametrize("shape", [
