@@ -178,6 +178,13 @@ tf_status run_attend(tf_ctx* ctx, const tf_params* p, const tf::Dims& d, const v
                "bf16 attention launch");
 }
 
+// A decoding workspace of this size (16 slices of a row's cache per query head) is always enough; few rows
+// are cut into more slices where there is room for them.
+size_t decode_least_bytes(const tf_params* p)
+{
+    return align256((size_t)p->batch * p->n_q_heads * 16 * tf::kDecodePartFloats * sizeof(float));
+}
+
 // validation shared by the decode calls; fills everything of `a` the state and params determine
 tf_status decode_args(tf_ctx* ctx, const tf_params* p, const tf_decode_state* st, tf::DecodeArgs* a)
 {
@@ -453,7 +460,7 @@ size_t tf_decode_workspace_bytes(const tf_params* p)
 {
     const char* why;
     if (check_shape(p, &why) != TF_OK) return 0;
-    return align256(tf::decode_scratch_bytes(p->batch, p->n_q_heads, p->n_kv_heads));
+    return std::max(decode_least_bytes(p), align256(tf::decode_scratch_bytes(p->batch, p->n_q_heads, p->n_kv_heads)));
 }
 
 tf_status tf_decode_init(tf_ctx* ctx, const tf_params* p, const tf_decode_state* state, float tau0,
@@ -524,15 +531,17 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
         return fail(ctx, TF_ERR_INVALID_ARG, "q, k, v and o must be 16-byte aligned");
     if (!(eta >= 0.f) || isinf(eta)) return fail(ctx, TF_ERR_INVALID_ARG, "eta must be finite and >= 0");
     if (!ws || misaligned(ws)) return fail(ctx, TF_ERR_INVALID_ARG, "workspace must be a 16-byte aligned pointer");
-    const size_t need = tf_decode_workspace_bytes(p);
+    const size_t need = decode_least_bytes(p);
     if (ws_bytes < need)
         return fail(ctx, TF_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", ws_bytes, need);
     a.eta = eta;
     a.skip = skip;
     a.fused = fused;
     a.part = (float*)ws;
-    // each slice at least one pass of keys
-    a.n_split = std::min(tf::decode_max_split(p->batch, p->n_q_heads, p->n_kv_heads), (state->capacity + 63) / 64);
+    // each slice at least one pass of keys, and no more slices than the workspace holds with their tickets
+    const size_t rows = (size_t)p->batch * p->n_q_heads;
+    const int room = (int)std::min<size_t>(tf::kDecodeMaxSplit, (ws_bytes / sizeof(float) - rows) / (rows * tf::kDecodePartFloats));
+    a.n_split = std::min({tf::decode_max_split(p->batch, p->n_q_heads, p->n_kv_heads), (state->capacity + 63) / 64, room});
     return dev(ctx, tf::launch_decode_step(a, p->dtype, q, k, v, o, (hipStream_t)stream), "decode step launch");
 }
 

@@ -146,6 +146,32 @@ def test_decode_full_cache_sets_overflow_and_writes_nothing_past_it(ctx):
     assert np.all(kc[2 * 2 * 5:] == -77.0)
 
 
+@pytest.mark.parametrize("heads", [(32, 8), (4, 4)])
+def test_decode_in_the_smallest_workspace(ctx, heads):
+    """16 partial results per query head have always been enough; a larger workspace only allows
+    more slices, whose merged rows differ by the rounding of the partial sums."""
+    _say("decode smallest workspace %s" % (heads,))
+    cap, n = 4096, 6
+    q, k, v, _ = synth.make_random_qkv(1, heads[0], heads[1], n, 128, dtype="bf16", seed=8)
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.5)
+    outs = []
+    for small in (False, True):
+        buf = B.DecodeBuffers(p, cap)
+        g = torch.Generator(device="cuda").manual_seed(3)
+        for c in (buf.k_cache, buf.v_cache):
+            c.copy_(torch.randn(c.shape, device="cuda", generator=g))
+        ctx.tf_decode_init(p, buf.state, 50.0)            # nothing is skipped
+        buf.cache_len.fill_(cap - n - 3)
+        ws = buf.ws[:heads[0] * 16 * 130 * 4] if small else buf.ws
+        for t in range(n):
+            a = [x[:, :, t].contiguous().cuda() for x in (q, k, v)]
+            ctx.tf_decode_step(p, 0.0, buf.state, *a, buf.o, buf.skip, buf.fused, ws)
+        torch.cuda.synchronize()
+        assert buf.skip.item() == 0
+        outs.append(buf.o.float())
+    assert (outs[0] - outs[1]).abs().max() <= 2 * ATTN_TOL[torch.bfloat16]
+
+
 def test_decode_argument_errors(ctx):
     q, k, v, _ = synth.make_random_qkv(1, 2, 2, 4, 128, dtype="bf16", seed=7)
     p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.5)
