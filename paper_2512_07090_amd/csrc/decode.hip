@@ -414,12 +414,32 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_
 // over many groups and four are in flight per group; with few chains (LANES = 4: a quarter of the
 // columns each) there are four times the workgroups.  16 chains x 3001 rows: 62 -> 9 us against
 // 16 groups of 16 lanes.
+// The workgroups behind those `anchors` copy 64 kept rows of K and V each, in order, into the caches and
+// set the controller's counters (5 us when they were a launch of their own; neither part fills the chip).
 template <typename T, int LANES>
-__global__ __launch_bounds__(1024) void decode_seed_anchor_kernel(
+__global__ __launch_bounds__(1024) void decode_seed_kernel(
     const T* __restrict__ K, const T* __restrict__ V, double* __restrict__ anchor_k,
     double* __restrict__ anchor_v, int Hkv, int n, long long s_b, long long s_h, long long s_t,
-    double g, double weight, int window)
+    double g, double weight, int window, int anchors, const int32_t* __restrict__ kept_idx,
+    const int32_t* __restrict__ count, T* __restrict__ k_cache, T* __restrict__ v_cache,
+    int32_t* __restrict__ seen, int32_t* __restrict__ skipped, int32_t* __restrict__ cache_len,
+    int32_t* __restrict__ overflow, int capacity)
 {
+    if ((int)blockIdx.x >= anchors) {
+        const int row_blocks = (n + 63) / 64, rb = (blockIdx.x - anchors) % row_blocks;
+        const int bh = (blockIdx.x - anchors) / row_blocks, b = bh / Hkv, h = bh % Hkv;
+        const int m = count[b];
+        if (rb == 0 && h == 0 && threadIdx.x == 0) {
+            seen[b] = n; skipped[b] = n - m; cache_len[b] = m; overflow[b] = 0;
+        }
+        const int i = rb * 64 + (threadIdx.x >> 4), c8 = threadIdx.x & 15;
+        if (i >= m) return;
+        const long long src = b * s_b + h * s_h + (long long)kept_idx[(long long)b * n + i] * s_t + c8 * 8;
+        const long long dst = ((long long)bh * capacity + i) * kHeadDim + c8 * 8;
+        copy8(k_cache + dst, K + src);
+        copy8(v_cache + dst, V + src);
+        return;
+    }
     constexpr int kGroups = 1024 / LANES, kParts = 16 / LANES;   // row groups; workgroups per chain
     __shared__ double part[16][8 * LANES];
     const int q = blockIdx.x % kParts, chain = blockIdx.x / kParts;
@@ -468,29 +488,6 @@ __global__ __launch_bounds__(1024) void decode_seed_anchor_kernel(
     }
 }
 
-// Hand-off from the batched path: the kept rows of K and V, in order, into the caches, and
-// the controller's counters.  Grid: (row blocks of 16, batch * KV heads).
-template <typename T>
-__global__ __launch_bounds__(256) void decode_seed_cache_kernel(
-    const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ kept_idx,
-    const int32_t* __restrict__ count, T* __restrict__ k_cache, T* __restrict__ v_cache,
-    int32_t* __restrict__ seen, int32_t* __restrict__ skipped, int32_t* __restrict__ cache_len,
-    int32_t* __restrict__ overflow, int Hkv, int n, int capacity, long long s_b, long long s_h,
-    long long s_t)
-{
-    const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
-    const int m = count[b];
-    if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0) {
-        seen[b] = n; skipped[b] = n - m; cache_len[b] = m; overflow[b] = 0;
-    }
-    const int i = blockIdx.x * 16 + (threadIdx.x >> 4), c8 = threadIdx.x & 15;
-    if (i >= m) return;
-    const long long src = b * s_b + h * s_h + (long long)kept_idx[(long long)b * n + i] * s_t + c8 * 8;
-    const long long dst = ((long long)bh * capacity + i) * kHeadDim + c8 * 8;
-    copy8(k_cache + dst, K + src);
-    copy8(v_cache + dst, V + src);
-}
-
 template <typename T>
 hipError_t launch_decode_seed_t(const DecodeArgs& a, const T* K, const T* V, const int32_t* kept_idx,
                                 const int32_t* count, int n, const long long* kvs, hipStream_t s)
@@ -505,17 +502,15 @@ hipError_t launch_decode_seed_t(const DecodeArgs& a, const T* K, const T* V, con
     const double wt = a.ema ? 1.0 - a.gamma : 1.0;
     const int chains = 2 * a.B * a.Hkv;
     // below one workgroup per two compute units a chain's columns are shared out
-    if (chains < 128)
-        decode_seed_anchor_kernel<T, 4><<<dim3(4 * chains), dim3(1024), 0, s>>>(
-            K, V, a.anchor_k, a.anchor_v, a.Hkv, n, kvs[0], kvs[1], kvs[2], g, wt, window);
-    else
-        decode_seed_anchor_kernel<T, 16><<<dim3(chains), dim3(1024), 0, s>>>(
-            K, V, a.anchor_k, a.anchor_v, a.Hkv, n, kvs[0], kvs[1], kvs[2], g, wt, window);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    decode_seed_cache_kernel<T><<<dim3((n + 15) / 16, a.B * a.Hkv), dim3(256), 0, s>>>(
-        K, V, kept_idx, count, (T*)a.k_cache, (T*)a.v_cache, a.seen, a.skipped, a.cache_len, a.overflow,
-        a.Hkv, n, a.capacity, kvs[0], kvs[1], kvs[2]);
+    const int anchors = chains < 128 ? 4 * chains : chains;
+    const unsigned grid = (unsigned)anchors + (unsigned)((n + 63) / 64) * a.B * a.Hkv;
+#define TF_DECODE_SEED(LANES)                                                                     \
+    decode_seed_kernel<T, LANES><<<dim3(grid), dim3(1024), 0, s>>>(                               \
+        K, V, a.anchor_k, a.anchor_v, a.Hkv, n, kvs[0], kvs[1], kvs[2], g, wt, window, anchors, kept_idx, \
+        count, (T*)a.k_cache, (T*)a.v_cache, a.seen, a.skipped, a.cache_len, a.overflow, a.capacity)
+    if (chains < 128) TF_DECODE_SEED(4);
+    else TF_DECODE_SEED(16);
+#undef TF_DECODE_SEED
     return hipGetLastError();
 }
 
