@@ -134,7 +134,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     constexpr int NP = 8 / NW;     // passes of the workgroup over a tile when loading it
     constexpr int WQ = 32;         // queries per wave
     constexpr int kBM = WQ * NW;   // kept queries per work item
-    constexpr int kRing = 3;       // operand fragments in flight from LDS, per tensor
+    constexpr int kRing = NW == 8 ? 3 : 2;   // operand fragments in flight from LDS, per tensor (four waves, three: 24 registers spilled, 1-2 % slower)
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kKTile + 2 * kVTile];
     uint16_t* const k_lds = smem;               // 2 stages of K
     uint16_t* const v_lds = smem + 2 * kKTile;  // 2 stages of V^T
