@@ -26,8 +26,8 @@ Prints ONE JSON line.  Besides the whole-path throughput it carries
   score_variants  the rows built beyond the headline path, on the headline workload.
 
 Stage times come from events the library records between its launches (a second pass of K
-steps); "select_compact" is the decision and compaction launch, "attend" includes the launch
-that zero-fills filtered rows on the fp32 path.  Every stage figure carries the cost of one
+steps); "select_compact" is the decision and compaction launch (rows of at most 1024 tokens are
+fused in it too), "attend" includes the zero rows.  Every stage figure carries the cost of one
 event record (a few microseconds).
 """
 from __future__ import annotations

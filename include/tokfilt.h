@@ -106,7 +106,9 @@ typedef struct {
                               a K whose last row is the current token) */
 } tf_params;
 
-/* Stages of the path, the order of tf_stage_timing_read's output. */
+/* Stages of the path, the order of tf_stage_timing_read's output.  A stage that a call does inside
+ * the next one's launch reads as the cost of its event: compaction is part of the decision, the
+ * fusion of short rows too, the zero rows are part of the attention. */
 enum { TF_STAGE_SCORE = 0, TF_STAGE_FUSE = 1, TF_STAGE_SELECT = 2, TF_STAGE_COMPACT = 3,
        TF_STAGE_ZERO_ROWS = 4, TF_STAGE_ATTEND = 5, TF_N_STAGES = 6 };
 
