@@ -106,8 +106,13 @@ __device__ __forceinline__ void store_v_transposed(u32x4 r0, u32x4 r1, uint16_t*
 
 // c += a b, and c = a b, as instructions of their own whose accumulator stays in one place: left to
 // itself the compiler gives every such MFMA a destination of its own and spills.  It does not
-// know their latency either: what the tile loop reads of a result (scores, two chunks later)
-// and writes of an operand is far enough away; elsewhere mfma_settle() comes first.
+// know their latency either, so what else reads a result, or takes over its registers, is tied to a place
+// behind the MFMA where it has been written:
+//   mfma_settle()  waits out the MFMAs issued before it; the two accumulators it names are read, and
+//                  all their registers (l_acc: also the rows nobody reads) stay theirs, up to here;
+//   mfma_result()  names a result where it is first read, in the tile loop two chunks, that is at least
+//                  four MFMAs, after its last one (they leave the pipe in order).
+// Neither moves against an MFMA.  tests/test_mfma_distances.py measures the distances in the assembly.
 __device__ __forceinline__ void mfma_add(f32x4& c, bf16x8 a, bf16x8 b)
 {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
@@ -116,12 +121,13 @@ __device__ __forceinline__ void mfma_first(f32x4& c, bf16x8 a, bf16x8 b)
 {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma_settle()
+__device__ __forceinline__ void mfma_settle(f32x4& c0, f32x4& c1)
 {
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(c0), "+v"(c1) : : "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
+__device__ __forceinline__ void mfma_result(f32x4& c) { asm volatile("" : "+v"(c)); }
 
 template <int NW, bool SINGLES>
 __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
@@ -452,6 +458,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     do {                                                                                       \
         const f32x4& s_ = S_OLD[(i >> 1) & 1][i >> 2];                                         \
         float e0_ = 0.f, e1_ = 0.f;                                                            \
+        if (EX && (i & 1) == 0) mfma_result(S_OLD[(i >> 1) & 1][i >> 2]);                      \
         if (EX == 2) TF_MASK(S_OLD, i, J_OLD);                                                 \
         if (QK && (i & 3) == 0) mfma_first(S_NEW[i >> 2][0], kf[r], qf[0][0]);                 \
         if (QK && (i & 3) != 0) mfma_add(S_NEW[i >> 2][0], kf[r], qf[0][i & 3]);               \
@@ -492,7 +499,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
             __builtin_amdgcn_sched_barrier(0);                                                 \
             if (j == 7) {                                                                      \
                 if (FIRST) {                                                                   \
-                    mfma_settle();                                                             \
+                    mfma_settle(s_x[0][0], s_x[0][1]);                                         \
+                    mfma_result(s_x[1][0]);                                                    \
+                    mfma_result(s_x[1][1]);                                                    \
                     _Pragma("unroll") for (int v = 0; v < 8; ++v) TF_MASK(s_x, v, 0);          \
                     if (!exact) {                                                              \
                         _Pragma("unroll") for (int qb = 0; qb < 2; ++qb)                       \
@@ -573,7 +582,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
 #undef TF_OFFSETS
 #undef TF_LOAD_IDX
 
-    mfma_settle();
+    // (the output accumulators are first read in products with the reciprocals of these)
+    mfma_settle(l_acc[0], l_acc[1]);
     if (__any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit) && lane == 0) overflow = 1;
     __syncthreads();
     if (!exact && __builtin_amdgcn_readfirstlane(overflow)) {
