@@ -66,7 +66,7 @@ constexpr int kVStr = kBN;               // V^T tile row stride (one row per col
 constexpr int kKTile = kBN * kKStr;      // elements per K tile
 constexpr int kVTile = kHeadDim * kVStr; // elements per V^T tile
 constexpr int kOStr = kHeadDim + 8;      // output staging row stride, elements
-constexpr float kSumLimit = 1.0995116e12f;  // 2^40: largest softmax denominator, see below
+constexpr float kSumLimit = 16777216.f;  // 2^24: largest softmax denominator in the tile loop, see below
 constexpr float kMasked = -1e30f;
 
 // Two floats rounded to bf16 and packed into one register (v_cvt_pk_bf16_f32).  The words are handled as plain
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     constexpr int NP = 8 / NW;     // passes of the workgroup over a tile when loading it
     constexpr int WQ = 32;         // queries per wave
     constexpr int kBM = WQ * NW;   // kept queries per work item
-    constexpr int kRing = NW == 8 ? 3 : 2;   // operand fragments in flight from LDS, per tensor (four waves, three: 24 registers spilled, 1-2 % slower)
+    constexpr int kRing = NW == 8 ? 3 : 2;   // operand fragments in flight from LDS, per tensor
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kKTile + 2 * kVTile];
     uint16_t* const k_lds = smem;               // 2 stages of K
     uint16_t* const v_lds = smem + 2 * kKTile;  // 2 stages of V^T
@@ -336,11 +336,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     for (int p = 0; p < NP; ++p)
         v_wr[p] = (8 * c8 + 4 * hh) * kVStr + 8 * ((wave + NW * p) ^ (c8 & 7) ^ (4 * hh)) + 4 * (g4 & 1);
 
-    // The weights are taken against a reference that never moves: the row max of the first block of
-    // keys.  Later scores may exceed it: weights and sums have fp32's range.  Should a row's
-    // weights sum to more than 2^40 (its true max is some 28 above the reference in units of the
-    // natural logarithm; an overflow shows as an infinite sum), the item is done again against
-    // the true row maxima.  A running maximum cost 18 vector instructions and a branch per block.
+    // The weights are taken against a reference that stays where the first block of keys put it, the row
+    // max of that block, as long as that will do: a running maximum cost 18 vector instructions and a
+    // branch per block.  Later scores may exceed it: weights and sums have fp32's range.  Before
+    // each inner tile the sums are looked at (their limit is out of the reach of 2^24 weights of at most
+    // 1): a row that has outgrown it moves its reference by a power of two that brings its sum back
+    // to 1 .. 2, and takes what it has summed along, exactly (keep_range).  Only where scores rise by
+    // more than some 70 in natural logarithms within 192 keys is there no sum left to go on from: an
+    // item whose sums or numerators have overflowed is done again, against the true row maxima.
+    // 8 x 32 heads x 2048 kept: level logits 322 us, rising by 136 or late by 23 or 45 302 to 319 (done again
+    // as soon as a sum passed 2^40, as it was before: 670 to 735; a lazy running maximum 331 to 353).
     float neg_mc[2] = {0.f, 0.f};   // minus the reference of a lane's queries, scaled to base 2
     if (tid == 0) overflow = 0;
     if (exact) {
@@ -443,6 +448,32 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
         // the other keys of this query sit 16, 32 and 48 lanes away
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         return fmaxf(mx, __shfl_xor(mx, 32));
+    };
+    // Before an inner tile: rows whose weights so far sum to more than kSumLimit.  l_acc's last MFMAs are six
+    // chunks back, oacc's are waited for; p_a holds the weights that are not summed yet.  (Asked before a
+    // wave's last tiles as well it cost 7 spilled registers and 1 % of 8 x 32 x 4096.)
+    auto keep_range = [&]() {
+        mfma_result(l_acc[0]);
+        mfma_result(l_acc[1]);
+        if (!__any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit)) return;
+        mfma_settle(l_acc[0], l_acc[1]);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            const float sum = __shfl(l_acc[qb][0], c16);   // row 0 of the accumulator: lanes 0 - 15
+            const int up = sum > kSumLimit ? min(__builtin_bit_cast(int, sum) >> 23, 253) - 127 : 0;
+            const float down = __builtin_bit_cast(float, (127 - up) << 23);
+            neg_mc[qb] -= (float)up;
+            l_acc[qb] *= down;
+#pragma unroll
+            for (int db = 0; db < 8; ++db) {
+                mfma_result(oacc[db][qb]);
+                oacc[db][qb] *= down;
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                p_a[qb][w] = pack_bf16x2(__builtin_bit_cast(float, p_a[qb][w] << 16) * down,
+                                         __builtin_bit_cast(float, p_a[qb][w] & 0xffff0000u) * down);
+        }
     };
     // Chunk i of a block's weights: query block i / 4, 16 keys (i / 2) % 2, accumulator registers
     // 2 (i % 2) and the next; register v is key J0 + 16 (i / 2 % 2) + 4 g4 + v.
@@ -553,6 +584,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     TF_TILE(true, 0, false, true, 1, false, true, true);
     TF_ADVANCE();
     while (kt < q_last) {
+        keep_range();
         TF_TILE(true, 1, true, true, 1, true, false, true);
         TF_ADVANCE();
     }
@@ -584,7 +616,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
 
     // (the output accumulators are first read in products with the reciprocals of these)
     mfma_settle(l_acc[0], l_acc[1]);
-    if (__any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit) && lane == 0) overflow = 1;
+    if (!exact && __any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit)) {
+        // an infinity or no number among the results
+        auto lost = [](float x) { return (__builtin_bit_cast(unsigned, x) & 0x7f800000u) == 0x7f800000u; };
+        bool any_lost = lane < 16 && (lost(l_acc[0][0]) || lost(l_acc[1][0]));
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) any_lost = any_lost || lost(oacc[i >> 1][i & 1][e]);
+        if (__any(any_lost) && lane == 0) overflow = 1;
+    }
     __syncthreads();
     if (!exact && __builtin_amdgcn_readfirstlane(overflow)) {
         __syncthreads();   // everybody has read the flag before the item's second start clears it

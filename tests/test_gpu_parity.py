@@ -518,21 +518,22 @@ def test_attend_softmax_reference_at_block_borders(ctx, m, course):
     (8, 32, 32, 300, True),     # pairs, rows of different length, one of them empty
     (4, 12, 4, 385, True),      # tiles of 128, ditto
 ])
-@pytest.mark.parametrize("rising", [False, True])
-def test_attend_many_groups_as_a_few_of_them(ctx, shape, rising):
+@pytest.mark.parametrize("course", ["level", "rising", "leap"])
+def test_attend_many_groups_as_a_few_of_them(ctx, shape, course):
     """Which tile size and order of tiles a call gets depends on how much there is to do: groups of
     a large call against the same groups in a call of their own, which gets tiles of 128 (compared with
-    the oracle by the other tests).  A query's arithmetic is the same in every plan, so the rows are
-    equal bit for bit; with logits that outgrow the softmax reference a tile is done again as a whole,
-    rows that did not need it included, so there both results are within the tolerance of the
-    oracle comparison and within twice that of each other."""
+    the oracle by the other tests) and with the oracle.  A query's arithmetic is the same in every plan, so
+    the rows are equal bit for bit, also where logits outgrow the softmax reference ("rising").  Where
+    they leap by more than fp32 holds (a factor of 2^190 from one key to the next), a tile is done again as a
+    whole, rows that did not need it included: there both are within the tolerance of the oracle."""
     b, hq, hkv, m, ragged = shape
-    _say("attend groups %s %s" % (shape, rising))
+    _say("attend groups %s %s" % (shape, course))
     n = 2 * m + 3
     g = torch.Generator(device="cuda").manual_seed(m)
     q, k, v = (torch.randn(b, h, n, 128, device="cuda", generator=g) for h in (hq, hkv, hkv))
-    if rising:
-        q, k = q * 0.05 + 2.0, k * 0.05 + 3.0 * torch.arange(n, device="cuda")[:, None] / n
+    if course != "level":
+        x = torch.arange(n, device="cuda")[:, None] / n
+        q, k = q * 0.05 + 2.0, k * 0.05 + 3.0 * (x if course == "rising" else (x > 0.6) * 2.0)
     q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
     idx = torch.stack([torch.randperm(n, device="cuda", generator=g)[:m].sort().values for _ in range(b)]).int()
     p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 1.0 - m / n)
@@ -562,10 +563,67 @@ def test_attend_many_groups_as_a_few_of_them(ctx, shape, rising):
         for h in (0, hkv // 2, hkv - 1):
             part = attend(slice(row, row + 1), h, h + 1).float()
             got = whole[row:row + 1, h * r:(h + 1) * r]
-            if rising:
-                assert (part - got).abs().max() <= 2 * ATTN_TOL[q.dtype]
-            else:
+            if course != "leap":
                 assert torch.equal(part, got)
+            if row == 1 or course == "leap":
+                kept = idx[row:row + 1, :int(count[row]) if ragged else m].cpu().numpy()
+                if kept.shape[1]:
+                    ref = oracle.attend(q[row:row + 1, h * r:(h + 1) * r].cpu(), k[row:row + 1, h:h + 1].cpu(), v[row:row + 1, h:h + 1].cpu(), kept)
+                    for x in (part, got):
+                        assert np.abs(x.cpu().numpy() - ref).max() <= ATTN_TOL[q.dtype]
+
+
+def test_attend_late_keys_leave_earlier_queries_alone(ctx):
+    """Logits that jump far above a query's own keys behind it: its row does not see them, and it is the
+    same bit for bit with and without them, wherever in its tile the jump is."""
+    _say("attend late keys")
+    m, n = 700, 700
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn(8, 32, n, 128, device="cuda", generator=g) for _ in range(3))
+    q = (q * 0.05 + 2.0).bfloat16()
+    idx = torch.arange(n, dtype=torch.int32, device="cuda").repeat(8, 1)
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.0)
+    buf = B.Buffers(p, "cuda:0")
+    outs = {}
+    for at in (n, 33, 200, 301, 650):
+        kk = (k * 0.05 + 2.0 * (torch.arange(n, device="cuda")[:, None] >= at)).bfloat16()     # by 45 nats
+        ctx.tf_attend(p, q, kk, v.bfloat16(), idx, m, buf.O, buf.ws)
+        torch.cuda.synchronize()
+        outs[at] = buf.O.clone()
+        assert torch.equal(outs[at][:, :, :at], outs[n][:, :, :at])
+
+
+def _us_a_call(f, reps):
+    """Shortest of five runs of `reps` calls, in microseconds a call."""
+    best = float("inf")
+    for _ in range(5):
+        f()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / reps * 1e3)
+    return best
+
+
+def test_attend_late_peaks_cost_no_second_pass(ctx):
+    """Logits that rise over a row, or jump by 45 nats behind its first keys, take about as long as level ones (a second
+    pass over a tile would more than double the time; measured 0.94 to 0.99)."""
+    _say("attend late peaks, time")
+    n = 2048
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v = (torch.randn(4, 32, n, 128, device="cuda", generator=g) for _ in range(3))
+    idx = torch.arange(n, dtype=torch.int32, device="cuda").repeat(4, 1)
+    p = B.make_params(tuple(q.shape), tuple(k.shape), torch.bfloat16, 0.0)
+    buf = B.Buffers(p, "cuda:0")
+    x = torch.arange(n, device="cuda")[:, None] / n
+    t = {}
+    for course, add in (("level", 0.0 * x), ("rising", 3.0 * x), ("late", 2.0 * (x > 0.9))):
+        a = [(q * 0.05 + 2.0).bfloat16(), (k * 0.05 + add).bfloat16(), v.bfloat16()]
+        t[course] = _us_a_call(lambda: ctx.tf_attend(p, *a, idx, n, buf.O, buf.ws), 20)
+    assert max(t["rising"], t["late"]) <= 1.4 * t["level"], t
 
 
 @pytest.mark.parametrize("m", [1, 4, 15, 16, 17, 48, 63, 64, 65, 79, 80, 81, 129, 200])
