@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
 // 64 tokens at once: the decisions are guessed, the thresholds that follow from them are computed
 // for all 64 tokens together, and the decisions that follow from those replace the guess, until
 // they agree.  The first wrong guess is right the next time (all before it were), so this ends
-// after at most 64 rounds; it takes one or two, because the threshold moves little over 64 tokens.
+// after at most 64 rounds; it mostly takes one or two, because the threshold moves little over 64 tokens.
 // The thresholds of given decisions: the skipped counts are a prefix sum of bits, so every
 // product and difference is formed as the recurrence forms it; what is left, a chain of 64 fma
 // roundings, is a prefix sum as well as long as the threshold stays inside one binade: it is then
@@ -488,9 +488,18 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
 // product eta * diff (formed in double) to a multiple of g, ties apart.  Where the threshold leaves
 // its binade or a tie occurs, the tokens before are taken, that one step is made with the fma
 // itself, and the next 64 tokens begin after it.
-// A lone wave waits about 10 cycles for every dependent result: token by token that is 30 ns each
-// (4096 tokens: 122 us); 64 at a time 11 ns each (4096 tokens: 53 us for the slowest of 8 rows,
-// 3001 tokens: 79 -> 32 us).
+// What bounds it is a lone wave's chain: it waits about 10 cycles for every dependent result, which is 26 ns a
+// token one by one, and 0.34 us for a step of one round.  Scores spread about a threshold away
+// from zero take 1.0 to 1.3 steps per 64 tokens (8 rows of 4096: 32 us; all of it token by token 119).  A
+// threshold near zero leaves its binade often (4 to 5 steps per 64 tokens), one that rests on a power of
+// two ends every step at its first token, and an eta of few bits ties often (15 to 20 steps per 64 tokens
+// at 0.25 to 1): in such steps alone 8 rows of 4096 took 75 to 153, 1385, and 380 to 440 us.  So every kOnSteps
+// steps are looked at together: where they took fewer tokens than one by one in the same time, the row
+// goes on one by one, for longer and longer stretches while the kOnProbe steps tried in between do not pay
+// either: 79 to 119 us for all of these.
+constexpr int kOnStep = 13;                  // a step's cost, in tokens taken one by one
+constexpr int kOnSteps = 16, kOnProbe = 2;
+constexpr int kOnRun = 64;                   // tokens of the first stretch
 constexpr int kOnChunk = 4096;
 
 // inclusive prefix sum over the wave (row_shr 1, 2, 4, 8, then row_bcast 15 and 31)
@@ -505,6 +514,84 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     return v;
 }
 
+// Up to `many` tokens from token i0 of the chunk on, one after the other, with the decisions left as the
+// steps of 64 leave them; called by a whole wave, s_u and inv hold its next 64 tokens.  A function of its own:
+// inlined it costs the steps of 64 another 1.5 % (registers and branches in their loop).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) float lds_float;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+struct OneByOne { float tau, tau_judged; int skipped, i0; };
+__device__ __attribute__((noinline)) OneByOne take_one_by_one(
+    lds_float* s_lds, const lds_float* inv_lds, float s_u, float inv, float tau, float tau_judged,
+    int skipped, int i0, int len, int many, float eta, float target)
+{
+    const int lane = threadIdx.x & 63;
+    // 16 at a time from registers; a row may end inside such a block (what follows its last token is
+    // read by nobody).  The running count of skipped tokens replaces the scores.
+    const int i_first = i0, i_block = min((i0 + 15) & ~15, len);
+    const int stop_at = min((i0 + many + 15) & ~15, (len + 15) & ~15);
+    const float before = (float)skipped;
+    float cnt = before;
+    auto step = [&](float s, float iv) {
+#pragma clang fp contract(off)
+        const float s1 = cnt + 1.f;
+        cnt = s > tau ? s1 : cnt;
+        const float p_next = cnt * iv;
+        const float d = p_next - target;
+        tau = fmaf(eta, d, tau);
+    };
+    auto lane_of = [](float x, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l)); };
+    // (up to the first block: from the 64 at hand)
+    for (; i0 < i_block; ++i0) {
+        tau_judged = tau;
+        step(lane_of(s_u, i0 - i_first), lane_of(inv, i0 - i_first));
+        if (lane == 0) s_lds[i0] = cnt;
+    }
+    if (i0 < min(stop_at, len) && lane == 0) {   // i0 is a multiple of 16 then
+        struct Eight { f32x4 s[2], iv[2]; } a, c;   // one in use, the next requested
+        auto request = [&](Eight& e, int at) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                e.s[h] = *(const lds_f32x4*)(s_lds + at + 4 * h);
+                e.iv[h] = *(const lds_f32x4*)(inv_lds + at + 4 * h);
+            }
+        };
+        float tau_in[16];
+        auto eight = [&](const Eight& e, int at, float* in) {
+            f32x4 counts[2];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                in[u] = tau;
+                step(e.s[u >> 2][u & 3], e.iv[u >> 2][u & 3]);
+                counts[u >> 2][u & 3] = cnt;
+            }
+            *(lds_f32x4*)(s_lds + at) = counts[0];
+            *(lds_f32x4*)(s_lds + at + 4) = counts[1];
+        };
+        request(a, i0 & ~15);
+        for (int i = i0 & ~15; i < stop_at; i += 16) {
+            request(c, i + 8);
+            eight(a, i, tau_in);
+            request(a, i + 16);   // (64 entries of padding behind the chunk)
+            eight(c, i + 8, tau_in + 8);
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (stop_at - 16 + u < len) tau_judged = tau_in[u];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // lane 0's counts, read by the others
+    __builtin_amdgcn_wave_barrier();
+    // skipped where the count moved; from the back, because a token's count is its neighbour's too
+    i0 = max(i0, min(stop_at, len));
+    for (int i = i_first + ((i0 - 1 - i_first) & ~63); i >= i_first; i -= 64) {
+        const int t = i + lane;
+        const float mine = t < i0 ? s_lds[t] : 0.f;
+        const float prev = t == i_first ? before : (t < i0 ? s_lds[t - 1] : 0.f);
+        if (t < i0) s_lds[t] = mine != prev ? 1.f : 0.f;
+    }
+    return OneByOne{lane_of(tau, 0), lane_of(tau_judged, 0), (int)lane_of(cnt, 0), i0};
+}
+
 __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     const float* __restrict__ fused, int n, int warmup, float target, float eta, float tau0,
     uint8_t* __restrict__ keep, int32_t* __restrict__ kept_idx, int32_t* __restrict__ count,
@@ -513,13 +600,13 @@ __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     // every product and difference below is rounded on its own (the only fused operations are
     // the fmaf calls): the recurrence is defined operation by operation
 #pragma clang fp contract(off)
-    __shared__ float s_lds[kOnChunk + 64];    // scores, then decisions (1 = skipped)
-    __shared__ float inv_lds[kOnChunk + 64];
+    __shared__ __attribute__((aligned(16))) float s_lds[kOnChunk + 64];    // scores, then decisions (1 = skipped)
+    __shared__ __attribute__((aligned(16))) float inv_lds[kOnChunk + 64];
     __shared__ int base_lds[kOnChunk / kSelThreads * kSelWaves];
     __shared__ int scan_lds[kSelWaves + 1];
 
     const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float* S = fused + (long long)b * n;
     uint8_t* kp = keep + (long long)b * n;
     int32_t* out = kept_idx + (long long)b * n;
@@ -531,6 +618,9 @@ __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     float drift = eta * (0.f - target);   // its latest movement (only the guess depends on it)
     float tau_judged = tau;  // the threshold the latest token was judged with
     int base = 0;            // kept tokens so far
+    // steps still to make before they are looked at, of so many that began at token `mark` of the chunk;
+    // the next stretch of tokens one by one, what is left of this one
+    int left = kOnSteps, steps = kOnSteps, mark = 0, run = kOnRun, one_by_one = 0;
     for (int t0 = 0; t0 < n; t0 += kOnChunk) {
         const int len = min(kOnChunk, n - t0);
         // (warm-up tokens and the padding get a score that is never above the threshold, so the
@@ -542,54 +632,82 @@ __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
         __syncthreads();
         if (wave == 0) {
             float s_u = s_lds[lane], inv = inv_lds[lane];
-            for (int i0 = 0; i0 < len;) {
-                const int ahead = min(i0 + 64, len) + lane;   // the next 64, if all of these are taken
-                const float s_next = s_lds[ahead], inv_next = inv_lds[ahead];
-                // tau as a multiple of its ulp
-                const unsigned tau_bits = __builtin_bit_cast(unsigned, tau);
-                const int ex = (int)((tau_bits >> 23) & 255u) - 127;
-                const bool grid = ex > -100 && ex < 127;   // an ordinary number
-                const int mant = (int)((tau_bits & 0x7fffffu) | 0x800000u);
-                const float ulp = __builtin_bit_cast(float, (unsigned)max(ex - 23 + 127, 1) << 23);
-                // eta in ulps; its sign makes up for tau's, so that magnitudes are added
-                const double per_ulp = __builtin_bit_cast(double, (unsigned long long)(1023 + 23 - ex) << 52);
-                const double eta_ulp = (tau_bits >> 31) ? -(double)eta * per_ulp : (double)eta * per_ulp;
-                unsigned long long d = __ballot(s_u > fmaf((float)lane, drift, tau));
-                float tau_u, diff;
-                int taken;   // tokens 0 .. taken - 1 of the 64 are decided
-                for (;;) {
-                    const int cnt = skipped + rank_below(d) + (int)((d >> lane) & 1);
-                    const float p_next = (float)cnt * inv;
-                    diff = p_next - target;
-                    const double steps = eta_ulp * (double)diff;   // exact
-                    const double whole = rint(steps);
-                    const bool odd = !(fabs(steps) < 8388608.0) || fabs(steps - whole) == 0.5;
-                    const int mag = mant + wave_incl_scan(odd ? 0 : (int)whole);   // at most 65 * 2^23
-                    // the first token whose step is not a plain sum
-                    const unsigned long long stop = __ballot(!grid || odd || mag <= 0x800000 || mag >= 0x1000000);
-                    const int j = stop ? __builtin_ctzll(stop) : 64;
-                    const float mag_f = (float)mag * ulp;
-                    const float after = (tau_bits >> 31) ? -mag_f : mag_f;
-                    // wave_shr 1: the threshold after the token before
-                    tau_u = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-                        __builtin_bit_cast(int, tau), __builtin_bit_cast(int, after), 0x138, 0xf, 0xf, false));
-                    const unsigned long long seen = __ballot(s_u > tau_u);
-                    const unsigned long long known = j >= 63 ? ~0ull : (2ull << j) - 1;   // thresholds 0 .. j
-                    taken = min(j + 1, 64);
-                    if (((seen ^ d) & known) == 0) break;
-                    d = (seen & known) | (d & ~known);
+            for (int i0 = 0;;) {
+                while (one_by_one == 0) {
+                    const int ahead = min(i0 + 64, len) + lane;   // the next 64, if all of these are taken
+                    const float s_next = s_lds[ahead], inv_next = inv_lds[ahead];
+                    // tau as a multiple of its ulp
+                    const unsigned tau_bits = __builtin_bit_cast(unsigned, tau);
+                    const int ex = (int)((tau_bits >> 23) & 255u) - 127;
+                    const bool grid = ex > -100 && ex < 127;   // an ordinary number
+                    const int mant = (int)((tau_bits & 0x7fffffu) | 0x800000u);
+                    const float ulp = __builtin_bit_cast(float, (unsigned)max(ex - 23 + 127, 1) << 23);
+                    // eta in ulps; its sign makes up for tau's, so that magnitudes are added
+                    const double per_ulp = __builtin_bit_cast(double, (unsigned long long)(1023 + 23 - ex) << 52);
+                    const double eta_ulp = (tau_bits >> 31) ? -(double)eta * per_ulp : (double)eta * per_ulp;
+                    unsigned long long d = __ballot(s_u > fmaf((float)lane, drift, tau));
+                    float tau_u, diff;
+                    int taken;   // tokens 0 .. taken - 1 of the 64 are decided
+                    for (;;) {
+                        const int cnt = skipped + rank_below(d) + (int)((d >> lane) & 1);
+                        const float p_next = (float)cnt * inv;
+                        diff = p_next - target;
+                        const double in_ulps = eta_ulp * (double)diff;   // exact
+                        const double whole = rint(in_ulps);
+                        const bool odd = !(fabs(in_ulps) < 8388608.0) || fabs(in_ulps - whole) == 0.5;
+                        const int mag = mant + wave_incl_scan(odd ? 0 : (int)whole);   // at most 65 * 2^23
+                        // the first token whose step is not a plain sum
+                        const unsigned long long stop = __ballot(!grid || odd || mag <= 0x800000 || mag >= 0x1000000);
+                        const int j = stop ? __builtin_ctzll(stop) : 64;
+                        const float mag_f = (float)mag * ulp;
+                        const float after = (tau_bits >> 31) ? -mag_f : mag_f;
+                        // wave_shr 1: the threshold after the token before
+                        tau_u = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+                            __builtin_bit_cast(int, tau), __builtin_bit_cast(int, after), 0x138, 0xf, 0xf, false));
+                        const unsigned long long seen = __ballot(s_u > tau_u);
+                        const unsigned long long known = j >= 63 ? ~0ull : (2ull << j) - 1;   // thresholds 0 .. j
+                        taken = min(j + 1, 64);
+                        if (((seen ^ d) & known) == 0) break;
+                        d = (seen & known) | (d & ~known);
+                    }
+                    taken = min(taken, len - i0);
+                    if (lane < taken) s_lds[i0 + lane] = (d >> lane) & 1 ? 1.f : 0.f;
+                    tau_judged = __shfl(tau_u, taken - 1);
+                    tau = __shfl(fmaf(eta, diff, tau_u), taken - 1);
+                    drift = tau - tau_judged;
+                    skipped += __popcll(d & (taken == 64 ? ~0ull : (1ull << taken) - 1));
+                    i0 += taken;
+                    s_u = s_next;
+                    inv = inv_next;
+                    if (i0 >= len) break;
+                    if (taken < 64) { s_u = s_lds[i0 + lane]; inv = inv_lds[i0 + lane]; }
+                    if (--left == 0) {
+                        const bool pays = i0 - mark >= steps * kOnStep;
+                        if (pays && steps == kOnSteps) run = kOnRun;
+                        steps = left = pays ? kOnSteps : kOnProbe;
+                        mark = i0;
+                        if (!pays) {
+                            one_by_one = run;
+                            run = min(2 * run, kOnChunk);
+                            break;
+                        }
+                    }
                 }
-                taken = min(taken, len - i0);
-                if (lane < taken) s_lds[i0 + lane] = (d >> lane) & 1 ? 1.f : 0.f;
-                tau_judged = __shfl(tau_u, taken - 1);
-                tau = __shfl(fmaf(eta, diff, tau_u), taken - 1);
+                if (i0 >= len) break;
+                const OneByOne r = take_one_by_one((lds_float*)s_lds, (const lds_float*)inv_lds, s_u, inv, tau,
+                                                   tau_judged, skipped, i0, len, one_by_one, eta, target);
+                tau = r.tau;
+                tau_judged = r.tau_judged;
                 drift = tau - tau_judged;
-                skipped += __popcll(d & (taken == 64 ? ~0ull : (1ull << taken) - 1));
-                i0 += taken;
-                s_u = s_next;
-                inv = inv_next;
-                if (taken < 64 && i0 < len) { s_u = s_lds[i0 + lane]; inv = inv_lds[i0 + lane]; }
+                skipped = __builtin_amdgcn_readfirstlane(r.skipped);
+                mark = __builtin_amdgcn_readfirstlane(r.i0);
+                one_by_one = max(0, one_by_one - (mark - i0));
+                i0 = mark;
+                if (i0 >= len) break;
+                s_u = s_lds[i0 + lane];
+                inv = inv_lds[i0 + lane];
             }
+            mark -= kOnChunk;
         }
         __syncthreads();
         unsigned long long kept[kOnChunk / kSelThreads];
