@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
                                                          const int32_t* __restrict__ kept_idx,
                                                          float* __restrict__ O,
                                                          const int32_t* __restrict__ counts,
-                                                         long long idx_stride, int parts)
+                                                         long long idx_stride, int parts, unsigned n_wg)
 {
     constexpr int kRows = 16, kStride = kHeadDim + 4;
     __shared__ __attribute__((aligned(16))) float part[4][kRows][kStride];
@@ -85,8 +85,10 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
     // The longest tiles of all heads first, so that they spread over the dies and the short ones fill in behind
     // them (head by head, 32 heads x 256 kept tokens took 21.3 instead of 17.6 us, 8 x 32 x 125 45 instead of 35); of the `parts` workgroups of
     // a tile the others only help with its zero rows.
-    const int groups = d.B * d.Hq, bh = blockIdx.x % groups, rank = blockIdx.x / groups;
-    const int qt = (gridDim.x / groups - 1 - rank) / parts, zp = rank % parts;
+    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
+    if (id >= n_wg) return;
+    const int groups = d.B * d.Hq, bh = id % groups, rank = id / groups;
+    const int qt = (int)(n_wg / groups - 1 - rank) / parts, zp = rank % parts;
     const int hq = bh % d.Hq, b = bh / d.Hq;
     const int hk = hq / (d.Hq / d.Hkv);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -248,9 +250,11 @@ hipError_t launch_attend_f32(const Dims& d, float scale, const float* Q, const f
 {
     // where few tokens are kept, a tile's zero rows are more than one workgroup should write
     const int parts = counts ? 1 : std::min(64, std::max(1, d.n / (32 * d.m)));
-    const unsigned grid = (unsigned)((d.m + 15) / 16 * parts) * d.Hq * d.B;   // far below 2^31: a row of Q has 512 bytes
-    attend_f32_kernel<<<dim3(grid), dim3(256), 0, s>>>(d, scale, Q, K, V, kept_idx, O, counts,
-                                                 counts ? idx_stride : (long long)d.m, parts);
+    // far below 2^31 (each has a row of O of its own, 512 bytes), but not below 2^32 threads, which is as far
+    // as one dimension of a grid goes: 2^22 workgroups a line
+    const unsigned n_wg = (unsigned)((d.m + 15) / 16 * parts) * d.Hq * d.B, line = std::min(n_wg, 1u << 22);
+    attend_f32_kernel<<<dim3(line, (n_wg + line - 1) / line), dim3(256), 0, s>>>(
+        d, scale, Q, K, V, kept_idx, O, counts, counts ? idx_stride : (long long)d.m, parts, n_wg);
     return hipGetLastError();
 }
 

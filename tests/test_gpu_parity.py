@@ -646,6 +646,30 @@ def test_attend_f32_blocks_of_16(ctx, m, gap):
     assert np.abs(O_g - oracle.attend(q, k, v, idx)).max() <= ATTN_TOL[q.dtype]
 
 
+@pytest.mark.parametrize("ragged", [False, True])
+def test_attend_f32_more_heads_than_one_grid_dimension(ctx, ragged):
+    """257 heads of 65535 single-token rows: more workgroups than fit one dimension of a grid (2^32 threads).  A
+    lone token's output is its value row."""
+    _say("attend f32 grid ragged=%s" % ragged)
+    Bn, Hq = 65535, 257
+    q = torch.zeros(Bn, Hq, 1, 128, device="cuda")
+    k = torch.zeros(Bn, 1, 1, 128, device="cuda")
+    v = torch.randn(Bn, 1, 1, 128, device="cuda")
+    O = torch.full_like(q, float("nan"))
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.0)
+    ws = torch.empty(B.tf_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    idx = torch.zeros((Bn, 1), dtype=torch.int32, device="cuda")
+    if ragged:
+        count = (torch.arange(Bn, device="cuda") % 3 > 0).int()
+        ctx.tf_attend_ragged(p, q, k, v, idx, count, O, ws)
+        v = v * count[:, None, None, None]
+    else:
+        ctx.tf_attend(p, q, k, v, idx, 1, O, ws)
+    torch.cuda.synchronize()
+    for h in range(0, Hq, 16):
+        assert torch.equal(O[:, h:h + 16], v.expand(-1, min(16, Hq - h), -1, -1))
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
 def test_attend_zero_rows_with_long_gaps(ctx, dt):
     """Kept sets with filtered runs of every length (before the first kept token, between kept
