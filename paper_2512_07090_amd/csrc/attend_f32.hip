@@ -53,6 +53,13 @@ __global__ __launch_bounds__(256) void zero_filtered_kernel(Dims d, const uint8_
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kNone = -1e30f;   // masked score, and the maximum of a row without keys
 
+// Workgroups of a tile: where few tokens are kept its zero rows are more than one should write.
+__host__ __device__ __forceinline__ int zero_parts(int n, int m)
+{
+    const int parts = n / (32 * m);
+    return parts < 1 ? 1 : (parts > 64 ? 64 : parts);
+}
+
 __device__ __forceinline__ float across_groups_max(float v)
 {
     const FloatPair a = swap16(v, v);
@@ -75,7 +82,7 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
                                                          const int32_t* __restrict__ kept_idx,
                                                          float* __restrict__ O,
                                                          const int32_t* __restrict__ counts,
-                                                         long long idx_stride, int parts, unsigned n_wg)
+                                                         long long idx_stride, int parts, int ranks, unsigned line)
 {
     constexpr int kRows = 16, kStride = kHeadDim + 4;
     __shared__ __attribute__((aligned(16))) float part[4][kRows][kStride];
@@ -85,26 +92,35 @@ __global__ __launch_bounds__(256, 3) void attend_f32_kernel(Dims d, float scale,
     // The longest tiles of all heads first, so that they spread over the dies and the short ones fill in behind
     // them (head by head, 32 heads x 256 kept tokens took 21.3 instead of 17.6 us, 8 x 32 x 125 45 instead of 35); of the `parts` workgroups of
     // a tile the others only help with its zero rows.
-    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
-    if (id >= n_wg) return;
-    const int groups = d.B * d.Hq, bh = id % groups, rank = id / groups;
-    const int qt = (int)(n_wg / groups - 1 - rank) / parts, zp = rank % parts;
+    // Workgroups lie in lines of `line`, `ranks` of them per head.
+    const unsigned id = blockIdx.y * line + blockIdx.x, groups = d.B * d.Hq;
+    const int bh = id % groups, rank = id / groups;
+    if (rank >= ranks) return;   // behind the last one in the last line
+    int qt = (ranks - 1 - rank) / parts, zp = rank % parts;
     const int hq = bh % d.Hq, b = bh / d.Hq;
     const int hk = hq / (d.Hq / d.Hkv);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c16 = lane & 15, g = lane >> 4;
     // kept tokens of this batch row (per row when counts is given: d.m is then the bound)
     const int m = counts ? counts[b] : d.m;
-    const int i0 = qt * kRows;
     float* Ob = O + (long long)b * d.os[0] + (long long)hq * d.os[1];
     const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i0 >= m) {
+    if (m == 0) {
         // a row without kept tokens (its grid is the one of a full row): every output row is zero
-        if (m == 0)
-            for (int r = i0 + (tid >> 5); r < min(i0 + kRows, d.n); r += 8)
-                reinterpret_cast<float4*>(Ob + (long long)r * d.os[2])[tid & 31] = zero;
+        for (int r = qt * kRows + (tid >> 5); r < min(qt * kRows + kRows, d.n); r += 8)
+            reinterpret_cast<float4*>(Ob + (long long)r * d.os[2])[tid & 31] = zero;
         return;
     }
+    if (counts) {
+        // the workgroups that the row's tiles leave over (its grid is the one of a full row) help with their zero rows:
+        // with one workgroup a tile, 32 heads x 16384 with 16 kept took 191 us, 70 with them (a mask and a launch of its own: 78)
+        const int tiles = (m + kRows - 1) / kRows;
+        parts = min(zero_parts(d.n, m), ranks / tiles);
+        if (rank >= tiles * parts) return;
+        qt = tiles - 1 - rank % tiles;
+        zp = rank / tiles;
+    }
+    const int i0 = qt * kRows;
     const int32_t* idx = kept_idx + (long long)b * idx_stride;
     const float* Qb = Q + (long long)b * d.qs[0] + (long long)hq * d.qs[1];
     const float* Kb = K + (long long)b * d.kvs[0] + (long long)hk * d.kvs[1];
@@ -248,13 +264,13 @@ hipError_t launch_attend_f32(const Dims& d, float scale, const float* Q, const f
                              const float* V, const int32_t* kept_idx, float* O,
                              const int32_t* counts, long long idx_stride, hipStream_t s)
 {
-    // where few tokens are kept, a tile's zero rows are more than one workgroup should write
-    const int parts = counts ? 1 : std::min(64, std::max(1, d.n / (32 * d.m)));
+    const int parts = counts ? 1 : zero_parts(d.n, d.m);   // (per-row counts: the kernel deals its workgroups itself)
     // far below 2^31 (each has a row of O of its own, 512 bytes), but not below 2^32 threads, which is as far
     // as one dimension of a grid goes: 2^22 workgroups a line
-    const unsigned n_wg = (unsigned)((d.m + 15) / 16 * parts) * d.Hq * d.B, line = std::min(n_wg, 1u << 22);
+    const int ranks = (d.m + 15) / 16 * parts;
+    const unsigned n_wg = (unsigned)ranks * d.Hq * d.B, line = std::min(n_wg, 1u << 22);
     attend_f32_kernel<<<dim3(line, (n_wg + line - 1) / line), dim3(256), 0, s>>>(
-        d, scale, Q, K, V, kept_idx, O, counts, counts ? idx_stride : (long long)d.m, parts, n_wg);
+        d, scale, Q, K, V, kept_idx, O, counts, counts ? idx_stride : (long long)d.m, parts, ranks, line);
     return hipGetLastError();
 }
 

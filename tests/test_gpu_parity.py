@@ -646,6 +646,43 @@ def test_attend_f32_blocks_of_16(ctx, m, gap):
     assert np.abs(O_g - oracle.attend(q, k, v, idx)).max() <= ATTN_TOL[q.dtype]
 
 
+def test_attend_f32_ragged_rows_share_their_zero_rows(ctx):
+    """Rows that keep nothing, a few tokens, half, all but one and all of 3001 tokens: their tiles get from
+    none to 64 workgroups for the zero rows.  And rows that keep little are not left to one workgroup: about as
+    long as the same call with a uniform count (5 times as long with one a tile)."""
+    _say("attend f32 ragged zero rows")
+    n, counts = 3001, [0, 1, 15, 16, 17, 33, 200, 1500, 1501, 2985, 3000, 3001]
+    Bn = len(counts)
+    q, k, v, _ = synth.make_random_qkv(Bn, 2, 1, n, 128, dtype="f32", seed=31)
+    rng = np.random.default_rng(31)
+    idx = np.full((Bn, n), -1, dtype=np.int32)
+    for b, c in enumerate(counts):
+        idx[b, :c] = np.sort(rng.choice(n, c, replace=False))
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.5)
+    buf = B.Buffers(p, "cuda:0")
+    buf.O.fill_(float("nan"))
+    count = torch.tensor(counts, dtype=torch.int32, device="cuda")
+    ctx.tf_attend_ragged(p, q.cuda(), k.cuda(), v.cuda(), torch.from_numpy(idx).cuda(), count, buf.O, buf.ws)
+    torch.cuda.synchronize()
+    O_g = buf.O.cpu().numpy().astype(np.float64)
+    assert not np.isnan(O_g).any()
+    for b, c in enumerate(counts):
+        assert np.all(np.delete(O_g[b], idx[b, :c], axis=1) == 0)
+        if c:
+            ref = oracle.attend(q[b:b + 1], k[b:b + 1], v[b:b + 1], idx[b:b + 1, :c])
+            assert np.abs(O_g[b:b + 1] - ref).max() <= ATTN_TOL[q.dtype]
+    n, m = 16384, 16
+    q, k, v = (torch.randn(1, 32, n, 128, device="cuda") for _ in range(3))
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 0.5)
+    buf = B.Buffers(p, "cuda:0")
+    few = torch.arange(m, dtype=torch.int32, device="cuda")[None].contiguous()
+    row = torch.cat([few, torch.full((1, n - m), -1, dtype=torch.int32, device="cuda")], 1)
+    count = torch.tensor([m], dtype=torch.int32, device="cuda")
+    uniform = _us_a_call(lambda: ctx.tf_attend(p, q, k, v, few, m, buf.O, buf.ws), 20)
+    ragged = _us_a_call(lambda: ctx.tf_attend_ragged(p, q, k, v, row, count, buf.O, buf.ws), 20)
+    assert ragged <= 2.5 * uniform, (ragged, uniform)
+
+
 @pytest.mark.parametrize("ragged", [False, True])
 def test_attend_f32_more_heads_than_one_grid_dimension(ctx, ragged):
     """257 heads of 65535 single-token rows: more workgroups than fit one dimension of a grid (2^32 threads).  A
