@@ -369,21 +369,23 @@ struct ScorePlan {
 // few workgroups takes as long as the first.  Whole calls of tf_score at `chains` x tokens, with the
 // segment count of a chain rounded up before and down now: incremental anchor 160 x 1777 37.4 -> 29.9 us,
 // fp32 80 x 1400 32.0 -> 28.0.
-// Exact mean: what the totals pass reads twice is not worth it from kOneSegment chains on (160 x 1777: 33.2 us
-// with one segment, 34.1 with three; 192 x 3000 58.7 -> 50.5 with one, 240 x 3000 63.0 -> 51.9;
-// 128 x 3000 48.6 with one, 39.9 with four).  A segment has at least two tiles where there are many (16 x 3001
-// 16.4 -> 14.7 us), four behind the incremental anchor's warm-up (16 x 8192 20.9 -> 17.7).
-constexpr int kResidentBf16 = 512, kResidentF32 = 256, kOneSegment = 150;
+// Exact mean: the totals pass reads all but the last segment a second time, which is not worth it from
+// kOneSegment chains on, where that would make two segments (192 x 8192 117 us with one, 123 with two;
+// 240 x 16384 230 and 258), but is for three of a long row (160 x 3000 49.9 with one, 46.5 with three;
+// 160 x 8192 117 and 108; 160 x 32768 442 and 404; only 160 x 1777 33.9 and 34.7).  A segment has at least two
+// tiles where there are many (16 x 3001 16.4 -> 14.7 us), four behind the incremental anchor's warm-up (16 x
+// 8192 20.9 -> 17.7).
+constexpr int kOneSegment = 150, kManyTiles = 20;
 
 // chains: of this launch (one tensor's for the key-only and value-only scores); most: segments a chain's totals have
 // room for.
-static ScorePlan plan_score(int chains, int most, int n, bool f32, bool ema)
+static ScorePlan plan_score(int chains, int most, int n, bool f32, bool ema, int n_cu)
 {
     const int tiles = (n + kTile - 1) / kTile;
-    int nseg = std::max(1, (f32 ? kResidentF32 : kResidentBf16) / chains);
-    if (!ema && chains >= kOneSegment) nseg = 1;
+    int nseg = std::max(1, (f32 ? n_cu : 2 * n_cu) / chains);
+    if (!ema && chains >= kOneSegment && (nseg < 3 || tiles < kManyTiles)) nseg = 1;
     nseg = std::min({nseg, tiles, std::max(1, most)});
-    const int least = tiles < 20 ? 1 : (ema ? 4 : 2);
+    const int least = tiles < kManyTiles ? 1 : (ema ? 4 : 2);
     const int tiles_per_seg = std::max(least, (tiles + nseg - 1) / nseg);
     nseg = (tiles + tiles_per_seg - 1) / tiles_per_seg;
     return ScorePlan{nseg, tiles_per_seg * kTile};
@@ -420,7 +422,7 @@ static void launch_scan(bool stream_loads, int grid, hipStream_t s, Args... args
 template <typename T>
 static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* sim_k,
                                  float* sim_v, float* seg_tot, int tensors, int anchor,
-                                 float gamma, hipStream_t s)
+                                 float gamma, int n_cu, hipStream_t s)
 {
     const int BH = d.B * d.Hkv;
     const int n_tensors = tensors == 0 ? 2 : 1;
@@ -428,7 +430,7 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
     const int chains = n_tensors * BH;
     const int inclusive = anchor >> 1;  // bit 1 of `anchor`: the anchor of a row includes the row
     anchor &= 1;
-    ScorePlan p = plan_score(chains, (int)(score_scratch_floats(d) / kHeadDim / chains), d.n, sizeof(T) == 4, anchor == 1);
+    ScorePlan p = plan_score(chains, (int)(score_scratch_floats(d) / kHeadDim / chains), d.n, sizeof(T) == 4, anchor == 1, n_cu);
     // Tensors that together exceed the last-level cache (256 MB Infinity Cache) are streamed past
     // the L2: measured on whole steps, workload 2 (537 MB) -2.6 %, workload 3 (336 MB) -1.2 %;
     // below that size the later kernels find the rows in the caches and streaming costs
@@ -472,13 +474,13 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
 
 hipError_t launch_score(const Dims& d, int dtype, const void* K, const void* V, float* sim_k,
                         float* sim_v, float* seg_tot, int tensors, int anchor, float gamma,
-                        hipStream_t s)
+                        int n_cu, hipStream_t s)
 {
     if (dtype == 0)
         return launch_score_t<float>(d, (const float*)K, (const float*)V, sim_k, sim_v, seg_tot,
-                                     tensors, anchor, gamma, s);
+                                     tensors, anchor, gamma, n_cu, s);
     return launch_score_t<uint16_t>(d, (const uint16_t*)K, (const uint16_t*)V, sim_k, sim_v,
-                                    seg_tot, tensors, anchor, gamma, s);
+                                    seg_tot, tensors, anchor, gamma, n_cu, s);
 }
 
 }  // namespace tf

@@ -25,7 +25,7 @@ size_t score_scratch_floats(const Dims& d);  // segment totals
 // anchor with smoothing factor gamma; bit 1: the anchor of a row includes that row.
 hipError_t launch_score(const Dims& d, int dtype, const void* K, const void* V, float* sim_k,
                         float* sim_v, float* seg_tot, int tensors, int anchor, float gamma,
-                        hipStream_t s);
+                        int n_cu, hipStream_t s);
 
 // ---- head statistics + variance-aware fusion ----------------------------------------------
 hipError_t launch_fuse(const Dims& d, int fusion, const float* sim_k, const float* sim_v,

@@ -233,7 +233,7 @@ tf_status run_path(tf_ctx* ctx, const tf_params* p, const Workspace& w, const vo
 
     mark(ctx, slot, 0, s);
     tf_status st = dev(ctx, tf::launch_score(d, p->dtype, K, V, sk, sv, (float*)(base + w.seg_tot),
-                                             score_tensors(p), anchor_bits(p), p->ema_gamma, s), "score launch");
+                                             score_tensors(p), anchor_bits(p), p->ema_gamma, ctx->n_cu, s), "score launch");
     if (st != TF_OK) return st;
     mark(ctx, slot, 1, s);
     const bool one_launch = tf::fuse_select_fits(d);   // the fusion is then part of the decision kernel
@@ -355,7 +355,7 @@ tf_status tf_score(tf_ctx* ctx, const tf_params* p, const void* K, const void* V
     char* base = (char*)ws;
     float* sk = sim_k ? sim_k : (float*)(base + w.sim_k);
     float* sv = sim_v ? sim_v : (float*)(base + w.sim_v);
-    st = dev(ctx, tf::launch_score(d, p->dtype, K, V, sk, sv, (float*)(base + w.seg_tot), score_tensors(p), anchor_bits(p), p->ema_gamma, s), "score launch");
+    st = dev(ctx, tf::launch_score(d, p->dtype, K, V, sk, sv, (float*)(base + w.seg_tot), score_tensors(p), anchor_bits(p), p->ema_gamma, ctx->n_cu, s), "score launch");
     if (st != TF_OK) return st;
     return dev(ctx, tf::launch_fuse(d, p->fusion, sk, sv, fused, s), "fuse launch");
 }
@@ -446,7 +446,7 @@ tf_status tf_filtered_attention_online(tf_ctx* ctx, const tf_params* p, float et
     float* sk = (float*)(base + w.sim_k);
     float* sv = (float*)(base + w.sim_v);
     st = dev(ctx, tf::launch_score(d, p->dtype, K, V, sk, sv, (float*)(base + w.seg_tot),
-                                   score_tensors(p), anchor_bits(p), p->ema_gamma, s), "score launch");
+                                   score_tensors(p), anchor_bits(p), p->ema_gamma, ctx->n_cu, s), "score launch");
     if (st != TF_OK) return st;
     st = dev(ctx, tf::launch_fuse(d, p->fusion, sk, sv, fused, s), "fuse launch");
     if (st != TF_OK) return st;
@@ -503,7 +503,7 @@ tf_status tf_decode_prefill(tf_ctx* ctx, const tf_params* p, float eta, float ta
     float* sk = (float*)(base + w.sim_k);
     float* sv = (float*)(base + w.sim_v);
     st = dev(ctx, tf::launch_score(d, p->dtype, K, V, sk, sv, (float*)(base + w.seg_tot),
-                                   score_tensors(p), anchor_bits(p), p->ema_gamma, s), "score launch");
+                                   score_tensors(p), anchor_bits(p), p->ema_gamma, ctx->n_cu, s), "score launch");
     if (st != TF_OK) return st;
     st = dev(ctx, tf::launch_fuse(d, p->fusion, sk, sv, fused, s), "fuse launch");
     if (st != TF_OK) return st;

@@ -247,7 +247,7 @@ def test_score_parity_exact_mean_on_a_stale_workspace(ctx, shape):
     # (dtype, B, Hkv, n, gamma or None): chains and tiles on both sides of the segment plan's borders
     ("bf16", 1, 74, 1920, None), ("bf16", 1, 76, 1920, None), ("bf16", 1, 8, 2432, None), ("bf16", 1, 8, 2433, None),
     ("f32", 1, 40, 1400, None), ("f32", 1, 16, 2433, None), ("bf16", 2, 40, 1777, 0.9), ("bf16", 1, 8, 2433, 0.9),
-    ("f32", 1, 8, 2049, 0.9),
+    ("f32", 1, 8, 2049, 0.9), ("bf16", 1, 80, 2432, None), ("bf16", 2, 40, 2433, None), ("bf16", 1, 86, 2433, None),
 ])
 def test_score_parity_at_the_borders_of_the_segment_plan(ctx, shape):
     """Both tensors and one alone (which has half the chains) against the oracle, on a stale workspace."""
@@ -267,6 +267,19 @@ def test_score_parity_at_the_borders_of_the_segment_plan(ctx, shape):
         if mode != B.TF_FUSE_KEY_ONLY:
             assert_scores_close(buf.sim_v.cpu().numpy(), cv, "sim_v")
         assert_scores_close(buf.fused.cpu().numpy(), oracle.fuse(ck, cv, mode), "fused mode %d" % mode)
+
+
+def test_score_segments_of_long_rows(ctx):
+    """160 chains leave room for three segments each, 192 do not: the fewer chains, the less time (203 and 227 us
+    for 16384 tokens; as long as both had one segment, 226 and 227)."""
+    _say("score segments, time")
+    us = {}
+    for H in (80, 96):
+        k = torch.randn(1, H, 16384, 128, device="cuda", dtype=torch.bfloat16)
+        p = B.make_params(tuple(k.shape), tuple(k.shape), k.dtype, 0.5)
+        buf = B.Buffers(p, "cuda:0")
+        us[H] = _us_a_call(lambda: ctx.tf_score(p, k, k, buf.fused, None, None, buf.ws), 20)
+    assert us[80] <= 0.95 * us[96], us
 
 
 def test_whole_path_incremental_anchor(ctx):
