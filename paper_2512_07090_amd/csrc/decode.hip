@@ -244,7 +244,7 @@ __device__ __forceinline__ float get_shared(const float* p) { return __hip_atomi
 // Attention of the new token over one slice of its row's cache, for the G query heads that
 // share a KV head.  A 16-lane group owns every 16th key of the slice and keeps its own running
 // (max, sum, numerators), four keys at a time with the next four already requested; groups are
-// merged through shuffles and LDS.  With one slice the result is final; with more, each slice
+// merged through shuffles and LDS.  With one slice in use the result is final; with more, each slice
 // leaves a partial result of kPartStride floats per query head, and the workgroup that draws the
 // last ticket of its heads merges them (no order among the slices is assumed, and nobody
 // waits).  A skipped row's first slice writes the zero row.
@@ -266,28 +266,29 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_
     const bool skipped = skip[b] != 0;
     const int grp = threadIdx.x >> 4, c8 = threadIdx.x & 15, wave = threadIdx.x >> 6;
     T* const out = o + ((long long)b * Hq + hq0) * kHeadDim;
+    const long long row0 = ((long long)b * Hkv + hk) * capacity;
+    const T* kb = k_cache + row0 * kHeadDim + c8 * 8;
+    const T* vb = v_cache + row0 * kHeadDim + c8 * 8;
+    // Slices are of at least kDecodeSlice keys, whatever the cache has room for, and the workgroups of those
+    // without a key have nothing to do.  One row of 8 groups in a cache of 32768: 4 keys 20.8 -> 10.3 us a step, 300
+    // 21.1 -> 13.8, 2000 22.7 -> 16.9, against 64 slices of which the most were empty.
+    const int chunk = max(kDecodeSlice, ((len + n_split - 1) / n_split + 15) & ~15);
+    const int lo = sp * chunk, hi = min(len, lo + chunk);
+    if (skipped | (lo >= len)) {
+        if (skipped && sp == 0)
+            for (int i = threadIdx.x; i < G * kHeadDim; i += 256) store_out(out + i, 0.f);
+        return;
+    }
 
     float qf[G][8], acc[G][8], mx[G], sum[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) load8(q + ((long long)b * Hq + hq0 + g) * kHeadDim + c8 * 8, qf[g]);
-    if (skipped) {
-        if (sp == 0)
-            for (int i = threadIdx.x; i < G * kHeadDim; i += 256) store_out(out + i, 0.f);
-        return;
-    }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) { qf[g][c] *= scale_log2e; acc[g][c] = 0.f; }
         mx[g] = kLowest; sum[g] = 0.f;
     }
-    int chunk = (len + n_split - 1) / n_split;
-    chunk = (chunk + 15) & ~15;
-    const int lo = sp * chunk, hi = min(len, lo + chunk);
-    const long long row0 = ((long long)b * Hkv + hk) * capacity;
-    const T* kb = k_cache + row0 * kHeadDim + c8 * 8;
-    const T* vb = v_cache + row0 * kHeadDim + c8 * 8;
-
     typename Raw8<T>::type k_raw[4], v_raw[4];
     auto request = [&](int j) {
 #pragma unroll
@@ -364,24 +365,25 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_
                 den = fmaf(merge[w][g][kHeadDim + 1], wt, den);
             }
         }
-        if (n_split > 1) put_shared(part0 + ((long long)g * n_split + sp) * kPartStride + c, v);
+        if (len > chunk) put_shared(part0 + ((long long)g * n_split + sp) * kPartStride + c, v);
         else if (c < kHeadDim) store_out(out + g * kHeadDim + c, v / den);
     }
-    if (n_split == 1) return;
+    if (len <= chunk) return;   // this was the only slice
+    const int used = (len + chunk - 1) / chunk;
 
     // every partial result of this workgroup is in memory before its ticket is drawn
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add(&tickets[b * (Hq / G) + hg], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (drawn != n_split - 1) return;
+    if (drawn != used - 1) return;
 
     // weights of the slices, per head, and the reciprocal of their weighted sum behind them
     for (int g = wave; g < G; g += 4) {
         const int l = threadIdx.x & 63;
         const float* pr = part0 + ((long long)g * n_split + l) * kPartStride;
-        const float m_l = l < n_split ? get_shared(pr + kHeadDim) : kLowest;
-        const float s_l = l < n_split ? get_shared(pr + kHeadDim + 1) : 0.f;
+        const float m_l = l < used ? get_shared(pr + kHeadDim) : kLowest;
+        const float s_l = l < used ? get_shared(pr + kHeadDim + 1) : 0.f;
         float m_all = m_l;
 #pragma unroll
         for (int step = 1; step < 64; step *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, step));
@@ -389,16 +391,22 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_
         float den = s_l * wt;
 #pragma unroll
         for (int step = 1; step < 64; step *= 2) den += __shfl_xor(den, step);
-        if (l < n_split) weight[g][l] = wt;
+        weight[g][l] = wt;   // 0 from `used` on
         if (l == 0) weight[g][kDecodeMaxSplit] = den;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < G * kHeadDim; i += 256) {
         const int g = i / kHeadDim, c = i % kHeadDim;
         const float* pr = part0 + (long long)g * n_split * kPartStride + c;
+        // (16 loads at a time whatever the count: the last ones repeat a slice with weight 0)
         float num = 0.f;
-#pragma unroll 8
-        for (int l = 0; l < n_split; ++l) num = fmaf(get_shared(pr + l * kPartStride), weight[g][l], num);
+        for (int l = 0; l < used; l += 16) {
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = get_shared(pr + min(l + u, used - 1) * kPartStride);
+#pragma unroll
+            for (int u = 0; u < 16; ++u) num = fmaf(x[u], weight[g][l + u], num);
+        }
         store_out(out + i, num / weight[g][kDecodeMaxSplit]);
     }
 }
