@@ -449,7 +449,8 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
             tidx = sel_k;
         }
     }
-    if (tid == 0 && tau) tau[b] = all ? INFINITY : (none ? -INFINITY : (by_key ? tau_ : tf_));
+    // (-0 counts as +0 and is given as that, as the radix passes do)
+    if (tid == 0 && tau) tau[b] = all ? INFINITY : (none ? -INFINITY : (by_key ? tau_ : tf_ + 0.f));
 
     unsigned long long kept[IPT];
 #pragma unroll

@@ -378,6 +378,28 @@ def test_select_histogram_and_its_fallback(ctx, kind, n):
         np.testing.assert_array_equal(buf.tau.cpu().numpy(), tau_r)
 
 
+@pytest.mark.parametrize("n", [2, 333, 4096, 8193, 40000])
+def test_select_threshold_of_negative_zero(ctx, n):
+    """A score of -0 equals one of +0, and a threshold of zero has no sign, whichever way it is found."""
+    _say("select negative zero n=%d" % n)
+    for spread in (False, True):
+        S = np.full((2, n), -0.0, dtype=np.float32)
+        if spread:
+            S[:, : n // 4] = -np.linspace(0.5, 1.0, n // 4)
+            S[:, n - n // 4:] = np.linspace(0.5, 1.0, n // 4)
+            S[1, n // 4:n - n // 4:2] = 0.0
+        keep_r, idx_r, tau_r = oracle.select(S, 0.5, 1)
+        p = B.make_params((2, 1, n, 128), (2, 1, n, 128), torch.float32, 0.5, 1)
+        buf = B.Buffers(p, "cuda:0")
+        if buf.m < 2:
+            continue                                   # the forced token alone: no threshold
+        assert np.all(tau_r == 0)
+        ctx.tf_select(p, torch.from_numpy(S).cuda(), buf.keep, buf.kept_idx, buf.tau, buf.ws)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(buf.kept_idx.cpu().numpy(), idx_r)
+        assert np.all(buf.tau.cpu().numpy().view(np.uint32) == 0)
+
+
 @pytest.mark.parametrize("kind", ["inf", "neg_inf", "nan", "all_inf", "mixed"])
 @pytest.mark.parametrize("n", [2, 333, 1025, 4097, 8193, 32768])
 def test_select_scores_that_are_no_numbers(ctx, kind, n):
