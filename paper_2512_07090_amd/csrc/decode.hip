@@ -249,7 +249,7 @@ __device__ __forceinline__ float get_shared(const float* p) { return __hip_atomi
 // last ticket of its heads merges them (no order among the slices is assumed, and nobody
 // waits).  A skipped row's first slice writes the zero row.
 template <typename T, int G>
-__global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_attend_kernel(
+__global__ __launch_bounds__(256, G == 8 ? 2 : sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_attend_kernel(
     const T* __restrict__ q, const T* __restrict__ k_cache, const T* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
     float* __restrict__ part, int32_t* __restrict__ tickets, T* __restrict__ o, int Hq, int Hkv,
@@ -298,12 +298,16 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_
             v_raw[u] = *reinterpret_cast<const typename Raw8<T>::type*>(vb + (long long)ju * kHeadDim);
         }
     };
-    if (lo + grp < hi) request(lo + grp);
+    // (eight heads leave no registers for keys ahead: with them one workgroup was left on a compute unit, and 8 rows
+    // of 64 / 8 heads x 4000 took 80 us instead of 49; 64 before keys were requested ahead)
+    constexpr bool kAhead = G < 8;
+    if (kAhead && lo + grp < hi) request(lo + grp);
     for (int j = lo + grp; j < hi; j += 64) {
         float kk[4][8], vv[4][8];
+        if (!kAhead) request(j);
 #pragma unroll
         for (int u = 0; u < 4; ++u) { unpack8(k_raw[u], kk[u]); unpack8(v_raw[u], vv[u]); }
-        if (j + 64 < hi) request(j + 64);
+        if (kAhead && j + 64 < hi) request(j + 64);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             float s[4];
@@ -527,7 +531,7 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
                                 hipStream_t s)
 {
     const int threads = std::min(1024, (32 * a.Hkv + 63) / 64 * 64);  // 16 lanes per (tensor, head)
-    const int g = decode_heads_per_wg(a.Hq, a.Hkv);
+    const int g = decode_heads_per_wg(a.B, a.Hq, a.Hkv);
     // tickets of the attention's workgroups behind the partial results
     int32_t* const tickets = (int32_t*)(a.part + (size_t)a.B * a.Hq * a.n_split * kDecodePartFloats);
     decode_score_kernel<T><<<dim3(a.B), dim3(threads), 0, s>>>(
@@ -551,16 +555,21 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
 
 }  // namespace
 
-int decode_heads_per_wg(int Hq, int Hkv)
+int decode_heads_per_wg(int B, int Hq, int Hkv)
 {
     const int group = Hq / Hkv;
-    return group == 2 || group == 4 || group == 8 ? group : 1;  // other ratios: one query head per workgroup
+    // Eight heads take all the registers and one wave's time for each key; where few caches are read they are better
+    // shared out to two workgroups that read them twice (1 row of 16 / 2 heads x 16384 keys: 32.0 us a step with
+    // eight heads, 23.1 with four; 8 x 64 / 8 x 4000 49 and 54, fp32 16 x 64 / 8 x 4000 112 and 161).
+    if (group == 8) return B * Hkv < 48 ? 4 : 8;
+    return group == 2 || group == 4 ? group : 1;  // other ratios: one query head per workgroup
 }
 
 int decode_max_split(int B, int Hq, int Hkv)
 {
-    const int rows = B * (Hq / decode_heads_per_wg(Hq, Hkv));
-    return std::min(kDecodeMaxSplit, std::max(1, (kDecodeWorkgroups + rows - 1) / rows));
+    const int g = decode_heads_per_wg(B, Hq, Hkv), rows = B * (Hq / g);
+    const int most = kDecodeWorkgroups / (g == 8 ? 2 : 1);   // two of the large ones are resident on a compute unit
+    return std::min(kDecodeMaxSplit, std::max(1, (most + rows - 1) / rows));
 }
 
 size_t decode_scratch_bytes(int B, int Hq, int Hkv)

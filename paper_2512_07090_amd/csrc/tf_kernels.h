@@ -76,7 +76,7 @@ hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const v
 // tokens attending: 16 slices and a launch to merge them 12.4 us a step, 64 slices merged by
 // the last 7.6 us.
 constexpr int kDecodeMaxSplit = 64;
-constexpr int kDecodeWorkgroups = 1024;             // (the workspace has room for them; the step makes four a compute unit)
+constexpr int kDecodeWorkgroups = 1024;             // (four a compute unit of 256; two where a workgroup takes eight heads)
 constexpr int kDecodeSlice = 64;                    // keys of a slice at least: one pass of its workgroup
 constexpr int kDecodePartFloats = kHeadDim + 2;     // floats of one slice's partial result
 struct DecodeArgs {
@@ -93,7 +93,7 @@ struct DecodeArgs {
     float* part;                                    // scratch [B][Hq][n_split][kDecodePartFloats], tickets
     int n_split;                                    // 1 .. decode_max_split()
 };
-int decode_heads_per_wg(int Hq, int Hkv);           // query heads one workgroup handles (they share a KV head)
+int decode_heads_per_wg(int B, int Hq, int Hkv);           // query heads one workgroup handles (they share a KV head)
 int decode_max_split(int B, int Hq, int Hkv);
 size_t decode_scratch_bytes(int B, int Hq, int Hkv);
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s);

@@ -538,12 +538,13 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
     a.skip = skip;
     a.fused = fused;
     a.part = (float*)ws;
-    // about four workgroups per compute unit, each slice at least one pass of keys, and no more slices than the
-    // workspace holds with their tickets
+    // about as many workgroups as are resident at once, each slice at least one pass of keys, and no more slices
+    // than the workspace holds with their tickets
     const size_t rows = (size_t)p->batch * p->n_q_heads;
     const int room = (int)std::min<size_t>(tf::kDecodeMaxSplit, (ws_bytes / sizeof(float) - rows) / (rows * tf::kDecodePartFloats));
-    const long long wgs = (long long)rows / tf::decode_heads_per_wg(p->n_q_heads, p->n_kv_heads);
-    const int fill = (int)std::max(1ll, (4ll * ctx->n_cu + wgs - 1) / wgs);
+    const int g = tf::decode_heads_per_wg(p->batch, p->n_q_heads, p->n_kv_heads);
+    const long long wgs = (long long)rows / g, most = (long long)ctx->n_cu * (g == 8 ? 2 : 4);
+    const int fill = (int)std::max(1ll, (most + wgs - 1) / wgs);
     a.n_split = std::min({tf::decode_max_split(p->batch, p->n_q_heads, p->n_kv_heads), fill,
                           (state->capacity + tf::kDecodeSlice - 1) / tf::kDecodeSlice, room});
     return dev(ctx, tf::launch_decode_step(a, p->dtype, q, k, v, o, (hipStream_t)stream), "decode step launch");
