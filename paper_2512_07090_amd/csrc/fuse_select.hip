@@ -499,8 +499,9 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
 // goes on one by one, for longer and longer stretches while the kOnProbe steps tried in between do not pay
 // either: 79 to 119 us for all of these.
 constexpr int kOnStep = 13;                  // a step's cost, in tokens taken one by one
-constexpr int kOnSteps = 16, kOnProbe = 2;
+constexpr int kOnSteps = 4, kOnProbe = 2;    // (16: 3 us more in a row before it changes its pace)
 constexpr int kOnRun = 64;                   // tokens of the first stretch
+constexpr int kOnShort = 256;                // rows up to here are taken one by one: 7 us, 4 to 11 in steps
 constexpr int kOnChunk = 4096;
 
 // inclusive prefix sum over the wave (row_shr 1, 2, 4, 8, then row_bcast 15 and 31)
@@ -621,7 +622,7 @@ __global__ __launch_bounds__(kSelThreads) void select_online_kernel(
     int base = 0;            // kept tokens so far
     // steps still to make before they are looked at, of so many that began at token `mark` of the chunk;
     // the next stretch of tokens one by one, what is left of this one
-    int left = kOnSteps, steps = kOnSteps, mark = 0, run = kOnRun, one_by_one = 0;
+    int left = kOnSteps, steps = kOnSteps, mark = 0, run = kOnRun, one_by_one = n <= kOnShort ? n : 0;
     for (int t0 = 0; t0 < n; t0 += kOnChunk) {
         const int len = min(kOnChunk, n - t0);
         // (warm-up tokens and the padding get a score that is never above the threshold, so the
