@@ -568,7 +568,9 @@ int decode_heads_per_wg(int B, int Hq, int Hkv)
 int decode_max_split(int B, int Hq, int Hkv)
 {
     const int g = decode_heads_per_wg(B, Hq, Hkv), rows = B * (Hq / g);
-    const int most = kDecodeWorkgroups / (g == 8 ? 2 : 1);   // two of the large ones are resident on a compute unit
+    // as many as are resident at once: two on a compute unit where they take four or eight heads (8 x 32 / 8 heads x 4000
+    // 41 -> 34 us, 1 x 64 / 16 x 4000 35 -> 23, against 1024 workgroups for these too)
+    const int most = kDecodeWorkgroups / (g >= 4 ? 2 : 1);
     return std::min(kDecodeMaxSplit, std::max(1, (most + rows - 1) / rows));
 }
 

@@ -76,7 +76,7 @@ hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const v
 // tokens attending: 16 slices and a launch to merge them 12.4 us a step, 64 slices merged by
 // the last 7.6 us.
 constexpr int kDecodeMaxSplit = 64;
-constexpr int kDecodeWorkgroups = 1024;             // (four a compute unit of 256; two where a workgroup takes eight heads)
+constexpr int kDecodeWorkgroups = 1024;             // (four a compute unit of 256; half of it where a workgroup takes four or eight heads)
 constexpr int kDecodeSlice = 64;                    // keys of a slice at least: one pass of its workgroup
 constexpr int kDecodePartFloats = kHeadDim + 2;     // floats of one slice's partial result
 struct DecodeArgs {

@@ -543,7 +543,7 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
     const size_t rows = (size_t)p->batch * p->n_q_heads;
     const int room = (int)std::min<size_t>(tf::kDecodeMaxSplit, (ws_bytes / sizeof(float) - rows) / (rows * tf::kDecodePartFloats));
     const int g = tf::decode_heads_per_wg(p->batch, p->n_q_heads, p->n_kv_heads);
-    const long long wgs = (long long)rows / g, most = (long long)ctx->n_cu * (g == 8 ? 2 : 4);
+    const long long wgs = (long long)rows / g, most = (long long)ctx->n_cu * (g >= 4 ? 2 : 4);
     const int fill = (int)std::max(1ll, (most + wgs - 1) / wgs);
     a.n_split = std::min({tf::decode_max_split(p->batch, p->n_q_heads, p->n_kv_heads), fill,
                           (state->capacity + tf::kDecodeSlice - 1) / tf::kDecodeSlice, room});
