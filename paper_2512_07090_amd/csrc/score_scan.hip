@@ -364,17 +364,20 @@ struct ScorePlan {
     int seg_len;  // tokens per segment, a multiple of the scan tile
 };
 
-// Segments of a chain: as many as keep every workgroup of the launch resident at once (their registers
-// allow two bf16 workgroups a compute unit, one fp32), never one more: a second round of a
-// few workgroups takes as long as the first.  Whole calls of tf_score at `chains` x tokens, with the
-// segment count of a chain rounded up before and down now: incremental anchor 160 x 1777 37.4 -> 29.9 us,
-// fp32 80 x 1400 32.0 -> 28.0.
-// Exact mean: the totals pass reads all but the last segment a second time, which is not worth it from
-// kOneSegment chains on, where that would make two segments (192 x 8192 117 us with one, 123 with two;
-// 240 x 16384 230 and 258), but is for three of a long row (160 x 3000 49.9 with one, 46.5 with three;
-// 160 x 8192 117 and 108; 160 x 32768 442 and 404; only 160 x 1777 33.9 and 34.7).  A segment has at least two
-// tiles where there are many (16 x 3001 16.4 -> 14.7 us), four behind the incremental anchor's warm-up (16 x
-// 8192 20.9 -> 17.7).
+// Segments of a chain.  Never more than keep every workgroup of the launch resident at once (their registers
+// allow two bf16 workgroups a compute unit, one fp32): a second round of a few workgroups takes as long
+// as the first.  Times are whole calls of tf_score at `chains` x tokens.
+// Exact mean: a workgroup adds up the totals of all segments before its own, one load after the other, so the
+// time is about tiles / nseg + nseg / 10 tile times: at most sqrt(10 tiles) segments, or 16 where each has a
+// compute unit (8 x 16384 31.7 us with 64, 25.8 with 32; 2 x 32768 41.0 with 256, 27.9 with 52).  The totals pass reads all but the last
+// segment a second time, which is not worth it from kOneSegment chains on where that would make two
+// segments (192 x 8192 117 with one, 123 with two; 240 x 16384 230 and 258), but is for three of a long
+// row (160 x 3000 49.9 with one, 46.5 with three; 160 x 32768 442 and 404; only 160 x 1777 33.9 and 34.7).
+// A segment has at least two tiles where there are many (16 x 3001 16.4 -> 14.7).
+// Incremental anchor: a segment walks two more tiles to warm up (gamma 0.9).  As short as one workgroup a
+// compute unit allows (16 x 5000 14.4 us with 3 tiles, 15.9 with 4; 2 x 8192 11.5 with 2, 14.8 with 4; 48 x
+// 2688 20.9 with 5, 24.2 with 4 and two a compute unit), or, with four tiles or more, as two of them allow,
+// which slows each by about 1.45 (48 x 3968 24.3 with 4, 27 with 7; 160 x 1777 29.9 with 5, 37.4 with 4).
 constexpr int kOneSegment = 150, kManyTiles = 20;
 
 // chains: of this launch (one tensor's for the key-only and value-only scores); most: segments a chain's totals have
@@ -382,13 +385,19 @@ constexpr int kOneSegment = 150, kManyTiles = 20;
 static ScorePlan plan_score(int chains, int most, int n, bool f32, bool ema, int n_cu)
 {
     const int tiles = (n + kTile - 1) / kTile;
-    int nseg = std::max(1, (f32 ? n_cu : 2 * n_cu) / chains);
-    if (!ema && chains >= kOneSegment && (nseg < 3 || tiles < kManyTiles)) nseg = 1;
-    nseg = std::min({nseg, tiles, std::max(1, most)});
-    const int least = tiles < kManyTiles ? 1 : (ema ? 4 : 2);
-    const int tiles_per_seg = std::max(least, (tiles + nseg - 1) / nseg);
-    nseg = (tiles + tiles_per_seg - 1) / tiles_per_seg;
-    return ScorePlan{nseg, tiles_per_seg * kTile};
+    auto tiles_of = [&](int nseg) { return (tiles + nseg - 1) / nseg; };
+    most = std::max(1, std::min(most, tiles));
+    const int one_a_cu = std::max(1, n_cu / chains), resident = std::max(1, (f32 ? n_cu : 2 * n_cu) / chains);
+    int tiles_per_seg;
+    if (ema) {
+        const int few = std::max(2, tiles_of(std::min(one_a_cu, most))), many = std::max(4, tiles_of(std::min(resident, most)));
+        tiles_per_seg = few + 2 <= 1.45 * (many + 2) ? few : many;
+    } else {
+        int nseg = std::min({resident, most, std::max((int)sqrt(10.0 * tiles), std::min(one_a_cu, 16))});
+        if (chains >= kOneSegment && (nseg < 3 || tiles < kManyTiles)) nseg = 1;
+        tiles_per_seg = std::max(tiles < kManyTiles ? 1 : 2, tiles_of(nseg));
+    }
+    return ScorePlan{tiles_of(tiles_per_seg), tiles_per_seg * kTile};
 }
 
 size_t score_scratch_floats(const Dims& d)

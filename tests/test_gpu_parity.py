@@ -248,6 +248,8 @@ def test_score_parity_exact_mean_on_a_stale_workspace(ctx, shape):
     ("bf16", 1, 74, 1920, None), ("bf16", 1, 76, 1920, None), ("bf16", 1, 8, 2432, None), ("bf16", 1, 8, 2433, None),
     ("f32", 1, 40, 1400, None), ("f32", 1, 16, 2433, None), ("bf16", 2, 40, 1777, 0.9), ("bf16", 1, 8, 2433, 0.9),
     ("f32", 1, 8, 2049, 0.9), ("bf16", 1, 80, 2432, None), ("bf16", 2, 40, 2433, None), ("bf16", 1, 86, 2433, None),
+    # as many segments as there are at most, and few long ones, of either anchor
+    ("bf16", 1, 1, 12900, None), ("bf16", 1, 1, 12900, 0.9), ("f32", 1, 4, 5121, 0.9), ("bf16", 1, 24, 2561, 0.9), ("bf16", 1, 24, 2433, 0.99),
 ])
 def test_score_parity_at_the_borders_of_the_segment_plan(ctx, shape):
     """Both tensors and one alone (which has half the chains) against the oracle, on a stale workspace."""
@@ -267,6 +269,23 @@ def test_score_parity_at_the_borders_of_the_segment_plan(ctx, shape):
         if mode != B.TF_FUSE_KEY_ONLY:
             assert_scores_close(buf.sim_v.cpu().numpy(), cv, "sim_v")
         assert_scores_close(buf.fused.cpu().numpy(), oracle.fuse(ck, cv, mode), "fused mode %d" % mode)
+
+
+def test_score_of_few_chains(ctx):
+    """A few heads' rows are cut as finely as one workgroup a compute unit allows: the incremental anchor of 8192 tokens
+    takes about as long as of 2048 (11.5 and 10.9 us; 14.8 with segments of four tiles), one tensor's exact mean of
+    8 x 16384 no longer than of both tensors (27.0 and 29.5, one tensor in both places; 31.7 with 64 segments)."""
+    _say("score few chains, time")
+
+    def us(heads, n, mode, gamma):
+        k = torch.randn(1, heads, n, 128, device="cuda", dtype=torch.bfloat16)
+        p = B.make_params(tuple(k.shape), tuple(k.shape), k.dtype, 0.5, 1, mode, ema_gamma=gamma)
+        buf = B.Buffers(p, "cuda:0")
+        return _us_a_call(lambda: ctx.tf_score(p, k, k, buf.fused, None, None, buf.ws), 20)
+    long_row, short_row = us(1, 8192, B.TF_FUSE_EQ2, 0.9), us(1, 2048, B.TF_FUSE_EQ2, 0.9)
+    assert long_row <= 1.2 * short_row, (long_row, short_row)
+    one, both = us(8, 16384, B.TF_FUSE_KEY_ONLY, None), us(8, 16384, B.TF_FUSE_EQ2, None)
+    assert one <= both, (one, both)
 
 
 def test_score_segments_of_long_rows(ctx):
