@@ -416,7 +416,7 @@ def main():
              "score": {"algorithmic_bytes": sb, "GBps": round(sg, 1), "frac_of_hbm_peak": round(sg / PEAK_HBM_GBS, 4)},
              "attend": {"algorithmic_flops": af, "TFLOPs": round(at, 2),
                         "frac_of_bf16_mfma_peak": round(at / PEAK_BF16_TFLOPS, 4) if ww.dtype == "bf16" else None,
-                        "note": None if ww.dtype == "bf16" else "fp32 correctness path: plain FMA, no MFMA peak applies"}}
+                        "note": None if ww.dtype == "bf16" else "fp32 correctness path: fp32 MFMAs, whose peak is not the bf16 one"}}
         return d
 
     # every workload of the benchmark definition, timed like the headline

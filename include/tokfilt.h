@@ -255,7 +255,9 @@ typedef struct {
     int32_t reserved; /* must be 0 */
 } tf_decode_state;
 
-/* Bytes of workspace tf_decode_step needs for `p` (0 if p is invalid). */
+/* Bytes of workspace for tf_decode_step (0 if p is invalid).  A smaller one is accepted down to
+ * batch * n_q_heads * 16 * 130 floats, rounded up to 256 bytes: long caches of few rows are then cut
+ * into fewer slices. */
 size_t tf_decode_workspace_bytes(const tf_params *p);
 
 /* Start a sequence: anchors, counters, cache lengths and overflow flags to zero, tau to tau0. */

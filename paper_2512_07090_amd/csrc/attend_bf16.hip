@@ -16,12 +16,13 @@
 //                 order over keys is permuted the same way for both operands (k-slot 8 g + e of a
 //                 32-key block is key 4 g + e, or 16 + 4 g + e - 4 for e >= 4).
 //   LDS layout    K rows padded to 288 bytes, V^T slots XOR-ed: the 16 lanes that LDS serves together
-//                 in a 16-byte read touch every bank once (4.7 cycles a read instead of 8 to 12).
+//                 in a 16-byte read touch every bank once (4.7 cycles a read instead of 8 to 12); the
+//                 writes of V^T meet in half of the banks.
 //   MFMA shape    16x16x32 rather than 32x32x16: same rate, same operands from LDS, but on normally
 //                 distributed data the card clocks down less (2.03 against 1.78 PFLOP/s in a loop
 //                 of nothing else, 2.45 both on zeros).
 //   softmax       fp32, base 2 (scale * log2 e folded into one FMA per score), against a reference
-//                 that does not move within an item (see neg_mc): no row maximum on the way.
+//                 that moves only when a row outgrows it (see neg_mc): no row maximum on the way.
 //                 The denominators are summed on the matrix pipe from the weights as rounded
 //                 (l_ones), so every output row is an exact convex combination of value rows;
 //                 v_dot2_f32_bf16, which did it before, occupies that pipe for about 20 cycles each
@@ -140,7 +141,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     constexpr int NP = 8 / NW;     // passes of the workgroup over a tile when loading it
     constexpr int WQ = 32;         // queries per wave
     constexpr int kBM = WQ * NW;   // kept queries per work item
-    constexpr int kRing = NW == 8 ? 3 : 2;   // operand fragments in flight from LDS, per tensor
+    // operand fragments in flight from LDS, per tensor (four waves, which hold two passes of rows: with three 24 registers
+    // are spilled, 9 with two, all of them outside the tile loop; eight waves spill none in pairs, 2 one by one)
+    constexpr int kRing = NW == 8 ? 3 : 2;
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kKTile + 2 * kVTile];
     uint16_t* const k_lds = smem;               // 2 stages of K
     uint16_t* const v_lds = smem + 2 * kKTile;  // 2 stages of V^T
@@ -330,7 +333,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     // eight keys 32 h + 4 g + {0..3, 16..19} that lane group g feeds to the MFMA of 32-key half h.
     // A row's slots are XOR-ed with (row % 8) ^ (row / 8 % 8): the 16 lanes that LDS serves together in a
     // 16-byte read then touch all 64 banks once (4.7 cycles a read; a padded row of 144 bytes
-    // XOR-ed with row / 8 alone: 12.1), and so do the lanes of a write (8.4).
+    // XOR-ed with row / 8 alone: 12.1).  A write's rows are 8 apart, which is one half of the banks: two lanes to
+    // a bank, 8.4 cycles; the counted conflicts, a third of LDS's busy cycles, are these writes.
     int v_wr[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p)

@@ -745,13 +745,6 @@ hipError_t launch_fuse(const Dims& d, int fusion, const float* sim_k, const floa
     return hipGetLastError();
 }
 
-hipError_t launch_select(const Dims& d, int warmup, const float* fused, uint8_t* keep,
-                         float* tau, hipStream_t s)
-{
-    select_kernel<<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, d.m, warmup, keep, tau);
-    return hipGetLastError();
-}
-
 hipError_t launch_select_compact(const Dims& d, int warmup, const float* fused, uint8_t* keep,
                                  int32_t* kept_idx, float* tau, hipStream_t s)
 {
@@ -790,12 +783,6 @@ hipError_t launch_select_online(const Dims& d, int warmup, float target, float e
 {
     select_online_kernel<<<dim3(d.B), dim3(kSelThreads), 0, s>>>(fused, d.n, warmup, target, eta,
                                                                  tau0, keep, kept_idx, count, tau);
-    return hipGetLastError();
-}
-
-hipError_t launch_compact(const Dims& d, const uint8_t* keep, int32_t* kept_idx, hipStream_t s)
-{
-    compact_kernel<<<dim3(d.B), dim3(kSelThreads), 0, s>>>(keep, d.n, d.m, kept_idx);
     return hipGetLastError();
 }
 

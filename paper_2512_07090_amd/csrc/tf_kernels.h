@@ -32,11 +32,7 @@ hipError_t launch_fuse(const Dims& d, int fusion, const float* sim_k, const floa
                        float* fused, hipStream_t s);
 
 // ---- exact-count decision and stream compaction -------------------------------------------
-hipError_t launch_select(const Dims& d, int warmup, const float* fused, uint8_t* keep,
-                         float* tau, hipStream_t s);
-hipError_t launch_compact(const Dims& d, const uint8_t* keep, int32_t* kept_idx, hipStream_t s);
-// decision and compaction in one launch (rows of up to 32768 tokens; longer rows take the two
-// kernels above)
+// decision and compaction in one launch (rows of up to 32768 tokens; longer rows take two)
 hipError_t launch_select_compact(const Dims& d, int warmup, const float* fused, uint8_t* keep,
                                  int32_t* kept_idx, float* tau, hipStream_t s);
 // fusion and the two in one launch, for the short rows that fuse_select_fits() names

@@ -127,7 +127,7 @@ Workspace carve(const tf_params* p)
     w.sim_k = off; off += sims;
     w.sim_v = off; off += sims;
     w.seg_tot = off; off += align256(tf::score_scratch_floats(d) * sizeof(float));
-    w.spare = off; off += align256((size_t)p->batch * p->seq);   // not used any more; part of the size callers know
+    w.spare = off; off += align256((size_t)p->batch * p->seq);   // not used any more; kept so that sizes, and the shapes that fit the static scratch, stay what they were
     w.total = off;
     return w;
 }
