@@ -157,6 +157,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     static_assert(kOwnStage || kBM * kOStr <= 2 * kKTile, "staging fits the K stages");
 
     __shared__ int overflow;   // a row of the item at hand has outgrown its reference
+    __shared__ unsigned lost_rows[NW];   // a wave's queries that have, bit 16 qb + c16 (no registers in the tile loop)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -347,14 +348,17 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     // 1): a row that has outgrown it moves its reference by a power of two that brings its sum back
     // to 1 .. 2, and takes what it has summed along, exactly (keep_range).  Only where scores rise by
     // more than some 70 in natural logarithms within 192 keys is there no sum left to go on from: an
-    // item whose sums or numerators have overflowed is done again, against the true row maxima.
+    // item where sums or numerators have overflowed is done again, those rows against their true maxima and
+    // the others as before, so that no query's bits depend on later ones.
     // 8 x 32 heads x 2048 kept: level logits 322 us, rising by 136 or late by 23 or 45 302 to 319 (done again
     // as soon as a sum passed 2^40, as it was before: 670 to 735; a lazy running maximum 331 to 353).
     float neg_mc[2] = {0.f, 0.f};   // minus the reference of a lane's queries, scaled to base 2
     if (tid == 0) overflow = 0;
     if (exact) {
-        // scores only, tile by tile, for the row maxima
+        // scores only, tile by tile, for the row maxima (the others' over the first block, as above)
         float mx[2] = {kMasked, kMasked};
+        const unsigned lost = lost_rows[wave] >> c16;
+        const int top[2] = {lost & 1 ? lim[0] : min(lim[0], 31), lost >> 16 & 1 ? lim[1] : min(lim[1], 31)};
         bf16x8 qm[2][4];
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
@@ -382,7 +386,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
                 for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (j0 + 16 * kb + 4 * g4 + v <= lim[qb]) mx[qb] = fmaxf(mx[qb], sm[qb][v]);
+                        if (j0 + 16 * kb + 4 * g4 + v <= top[qb]) mx[qb] = fmaxf(mx[qb], sm[qb][v]);
             }
         }
 #pragma unroll
@@ -620,19 +624,29 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
 
     // (the output accumulators are first read in products with the reciprocals of these)
     mfma_settle(l_acc[0], l_acc[1]);
+    unsigned lost = 0;
     if (!exact && __any(fmaxf(l_acc[0][0], l_acc[1][0]) > kSumLimit)) {
-        // an infinity or no number among the results
-        auto lost = [](float x) { return (__builtin_bit_cast(unsigned, x) & 0x7f800000u) == 0x7f800000u; };
-        bool any_lost = lane < 16 && (lost(l_acc[0][0]) || lost(l_acc[1][0]));
+        // queries that have outgrown their reference and have an infinity or no number among their results
+        auto gone = [](float x) { return (__builtin_bit_cast(unsigned, x) & 0x7f800000u) == 0x7f800000u; };
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
+        for (int qb = 0; qb < 2; ++qb) {
+            const bool above = __shfl(l_acc[qb][0], c16) > kSumLimit;
+            bool any = lane < 16 && gone(l_acc[qb][0]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) any_lost = any_lost || lost(oacc[i >> 1][i & 1][e]);
-        if (__any(any_lost) && lane == 0) overflow = 1;
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) any = any || gone(oacc[i][qb][e]);
+            any = any && above;
+            // (the other columns of this query are 16, 32 and 48 lanes away)
+            const unsigned long long b = __ballot(any);
+            lost |= (unsigned)((b | b >> 16 | b >> 32 | b >> 48) & 0xffff) << 16 * qb;
+        }
+        if (lost && lane == 0) overflow = 1;
     }
     __syncthreads();
     if (!exact && __builtin_amdgcn_readfirstlane(overflow)) {
         __syncthreads();   // everybody has read the flag before the item's second start clears it
+        if (lane == 0) lost_rows[wave] = lost;
         exact = true;
         --it;
         continue;
