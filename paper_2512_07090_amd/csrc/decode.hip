@@ -4,6 +4,7 @@
 // Two launches per step: decode_score_kernel (one workgroup per batch row) and the attention over
 // the cache, split over workgroups of which the last to end merges the slices.
 #include <algorithm>
+#include <type_traits>
 
 #include "tf_kernels.h"
 
@@ -14,6 +15,9 @@ namespace {
 constexpr double kEpsCos = 1e-8;
 constexpr double kEpsVar = 1e-12;
 constexpr float kLowest = -1e30f;  // "no key yet": finite, so differences of two of them are 0
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPartStride = kDecodePartFloats;  // partial result: 128 numerators, running max, sum
 
 // eight consecutive elements of a row as floats
@@ -235,24 +239,89 @@ __device__ __forceinline__ float wave_group_max(float v)
     return fmaxf(b.first, b.second);
 }
 
-// A float to or from memory past the caches that are not shared between the dies (relaxed, device
+// Two floats to or from memory past the caches that are not shared between the dies (relaxed, device
 // scope): written and read this way, a partial result needs no cache to be written back or
 // invalidated on its way from one workgroup to another.
-__device__ __forceinline__ void put_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float get_shared(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+struct Float2 { float x, y; };
+__device__ __forceinline__ void put_shared(float* p, Float2 v)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ Float2 get_shared(const float* p)
+{
+    return __builtin_bit_cast(Float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
 
-// Attention of the new token over one slice of its row's cache, for the G query heads that
+// Behind a slice's partial result, which the workgroup has just written: the workgroup that draws the last ticket merges
+// the `used` slices of its G heads into the output rows.
+template <typename T, int G>
+__device__ __forceinline__ void merge_slices(float* part0, T* out, float (*weight)[kDecodeMaxSplit + 1], int* drawn,
+                                             int32_t* ticket, int used, int n_split)
+{
+    // every partial result of this workgroup is in memory before its ticket is drawn
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) *drawn = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (*drawn != used - 1) return;
+
+    // Numerators of the first kBatch slices of this thread's two columns, requested before their weights are known
+    // (16 slices at a time, one column a thread: eight round trips to memory in a row with 64 slices of four heads).
+    // The last ones of a batch repeat a slice with weight 0.
+    constexpr int kBatch = 32;
+    const int pairs = G * kHeadDim / 2;
+    Float2 x[kBatch];
+    auto fetch = [&](int i, int l) {
+        const float* pr = part0 + (long long)(i / (kHeadDim / 2)) * n_split * kPartStride + 2 * (i % (kHeadDim / 2));
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) x[u] = get_shared(pr + min(l + u, used - 1) * kPartStride);
+    };
+    if ((int)threadIdx.x < pairs) fetch(threadIdx.x, 0);
+    // weights of the slices, per head, and their weighted sum behind them
+    for (int g = threadIdx.x >> 6; g < G; g += 4) {
+        const int l = threadIdx.x & 63;
+        Float2 own = {kLowest, 0.f};
+        if (l < used) own = get_shared(part0 + ((long long)g * n_split + l) * kPartStride + kHeadDim);
+        float m_all = own.x;
+#pragma unroll
+        for (int step = 1; step < 64; step *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, step));
+        const float wt = __builtin_amdgcn_exp2f(own.x - m_all);
+        float den = own.y * wt;
+#pragma unroll
+        for (int step = 1; step < 64; step *= 2) den += __shfl_xor(den, step);
+        weight[g][l] = wt;   // 0 from `used` on
+        if (l == 0) weight[g][kDecodeMaxSplit] = den;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < pairs; i += 256) {
+        const int g = i / (kHeadDim / 2), c = 2 * (i % (kHeadDim / 2));
+        Float2 num = {0.f, 0.f};
+        for (int l = 0; l < used; l += kBatch) {
+            if (l > 0 || i >= 256) fetch(i, l);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                num.x = fmaf(x[u].x, weight[g][l + u], num.x);
+                num.y = fmaf(x[u].y, weight[g][l + u], num.y);
+            }
+        }
+        const float den = weight[g][kDecodeMaxSplit];
+        store_out(out + g * kHeadDim + c, num.x / den);
+        store_out(out + g * kHeadDim + c + 1, num.y / den);
+    }
+}
+
+// Attention of the new token over one slice of its row's cache in fp32, for the G query heads that
 // share a KV head.  A 16-lane group owns every 16th key of the slice and keeps its own running
 // (max, sum, numerators), four keys at a time with the next four already requested; groups are
 // merged through shuffles and LDS.  With one slice in use the result is final; with more, each slice
 // leaves a partial result of kPartStride floats per query head, and the workgroup that draws the
 // last ticket of its heads merges them (no order among the slices is assumed, and nobody
 // waits).  A skipped row's first slice writes the zero row.
-template <typename T, int G>
-__global__ __launch_bounds__(256, G == 8 ? 2 : sizeof(T) == 2 && G == 1 ? 4 : 1) void decode_attend_kernel(
-    const T* __restrict__ q, const T* __restrict__ k_cache, const T* __restrict__ v_cache,
+template <int G>
+__global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k_cache, const float* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
-    float* __restrict__ part, int32_t* __restrict__ tickets, T* __restrict__ o, int Hq, int Hkv,
+    float* __restrict__ part, int32_t* __restrict__ tickets, float* __restrict__ o, int Hq, int Hkv,
     int capacity, int n_split, float scale_log2e)
 {
     __shared__ float merge[4][G][kPartStride];
@@ -265,10 +334,10 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : sizeof(T) == 2 && G == 1 ? 4 : 1)
     const int len = cache_len[b];
     const bool skipped = skip[b] != 0;
     const int grp = threadIdx.x >> 4, c8 = threadIdx.x & 15, wave = threadIdx.x >> 6;
-    T* const out = o + ((long long)b * Hq + hq0) * kHeadDim;
+    float* const out = o + ((long long)b * Hq + hq0) * kHeadDim;
     const long long row0 = ((long long)b * Hkv + hk) * capacity;
-    const T* kb = k_cache + row0 * kHeadDim + c8 * 8;
-    const T* vb = v_cache + row0 * kHeadDim + c8 * 8;
+    const float* kb = k_cache + row0 * kHeadDim + c8 * 8;
+    const float* vb = v_cache + row0 * kHeadDim + c8 * 8;
     // Slices are of at least kDecodeSlice keys, whatever the cache has room for, and the workgroups of those
     // without a key have nothing to do.  One row of 8 groups in a cache of 32768: 4 keys 20.8 -> 10.3 us a step, 300
     // 21.1 -> 13.8, 2000 22.7 -> 16.9, against 64 slices of which the most were empty.
@@ -289,17 +358,16 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : sizeof(T) == 2 && G == 1 ? 4 : 1)
         for (int c = 0; c < 8; ++c) { qf[g][c] *= scale_log2e; acc[g][c] = 0.f; }
         mx[g] = kLowest; sum[g] = 0.f;
     }
-    typename Raw8<T>::type k_raw[4], v_raw[4];
+    Raw8<float>::type k_raw[4], v_raw[4];
     auto request = [&](int j) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int ju = min(j + 16 * u, hi - 1);  // a valid row; its score is discarded below
-            k_raw[u] = *reinterpret_cast<const typename Raw8<T>::type*>(kb + (long long)ju * kHeadDim);
-            v_raw[u] = *reinterpret_cast<const typename Raw8<T>::type*>(vb + (long long)ju * kHeadDim);
+            k_raw[u] = *reinterpret_cast<const Raw8<float>::type*>(kb + (long long)ju * kHeadDim);
+            v_raw[u] = *reinterpret_cast<const Raw8<float>::type*>(vb + (long long)ju * kHeadDim);
         }
     };
-    // (eight heads leave no registers for keys ahead: with them one workgroup was left on a compute unit, and 8 rows
-    // of 64 / 8 heads x 4000 took 80 us instead of 49; 64 before keys were requested ahead)
+    // (eight heads leave no registers for keys ahead: with them one workgroup is left on a compute unit)
     constexpr bool kAhead = G < 8;
     if (kAhead && lo + grp < hi) request(lo + grp);
     for (int j = lo + grp; j < hi; j += 64) {
@@ -354,65 +422,217 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : sizeof(T) == 2 && G == 1 ? 4 : 1)
     }
     __syncthreads();
     float* const part0 = part + ((long long)b * Hq + hq0) * n_split * kPartStride;   // [head][slice]
-    for (int i = threadIdx.x; i < G * kPartStride; i += 256) {
-        const int g = i / kPartStride, c = i - g * kPartStride;
+    constexpr int kPairs = kPartStride / 2;   // the last one: running max, sum
+    for (int i = threadIdx.x; i < G * kPairs; i += 256) {
+        const int g = i / kPairs, c = 2 * (i - g * kPairs);
         float m_all = kLowest;
 #pragma unroll
         for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, merge[w][g][kHeadDim]);
-        float v = m_all, den = 0.f;
-        if (c != kHeadDim) {
-            v = 0.f;
+        Float2 v = {0.f, 0.f};
+        float den = 0.f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float wt = __builtin_amdgcn_exp2f(merge[w][g][kHeadDim] - m_all);
-                v = fmaf(merge[w][g][c], wt, v);
-                den = fmaf(merge[w][g][kHeadDim + 1], wt, den);
-            }
+        for (int w = 0; w < 4; ++w) {
+            const float wt = __builtin_amdgcn_exp2f(merge[w][g][kHeadDim] - m_all);
+            v.x = fmaf(merge[w][g][c], wt, v.x);
+            v.y = fmaf(merge[w][g][c + 1], wt, v.y);
+            den = fmaf(merge[w][g][kHeadDim + 1], wt, den);
         }
+        if (c == kHeadDim) v.x = m_all;
         if (len > chunk) put_shared(part0 + ((long long)g * n_split + sp) * kPartStride + c, v);
-        else if (c < kHeadDim) store_out(out + g * kHeadDim + c, v / den);
+        else if (c < kHeadDim) { store_out(out + g * kHeadDim + c, v.x / den); store_out(out + g * kHeadDim + c + 1, v.y / den); }
     }
-    if (len <= chunk) return;   // this was the only slice
-    const int used = (len + chunk - 1) / chunk;
+    if (len > chunk)
+        merge_slices<float, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, n_split);
+}
 
-    // every partial result of this workgroup is in memory before its ticket is drawn
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add(&tickets[b * (Hq / G) + hg], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (drawn != used - 1) return;
-
-    // weights of the slices, per head, and the reciprocal of their weighted sum behind them
-    for (int g = wave; g < G; g += 4) {
-        const int l = threadIdx.x & 63;
-        const float* pr = part0 + ((long long)g * n_split + l) * kPartStride;
-        const float m_l = l < used ? get_shared(pr + kHeadDim) : kLowest;
-        const float s_l = l < used ? get_shared(pr + kHeadDim + 1) : 0.f;
-        float m_all = m_l;
-#pragma unroll
-        for (int step = 1; step < 64; step *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, step));
-        const float wt = __builtin_amdgcn_exp2f(m_l - m_all);
-        float den = s_l * wt;
-#pragma unroll
-        for (int step = 1; step < 64; step *= 2) den += __shfl_xor(den, step);
-        weight[g][l] = wt;   // 0 from `used` on
-        if (l == 0) weight[g][kDecodeMaxSplit] = den;
+// The same for bf16 rows, on the matrix pipe; a wave takes blocks of 32 keys.
+//   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = 16 rows of K as they lie in memory, B = the queries
+//                 (column c: head c % G), so a lane has the scores of one head for eight keys.
+//   O^T += V^T P^T  A: a lane loads 8 columns of the eight keys whose weights it holds (the contraction order over keys is
+//                 the one in which they come out of the first product) and transposes them within its own
+//                 registers; the 16 columns of product i are 8 c + i.
+//   weights       stay fp32: a weight is the exact sum of three bf16 parts (8 bits of the mantissa each), and the
+//                 parts of a head's weight are columns of their own of P^T (column c: part c / G), which with one
+//                 to five heads are there anyway.  Their products with V are added up in fp32 at the end.
+// What bounds it is the way of the keys from memory, and for short rows the first loads (2 to 4 us) and the merge (6 us). In fp32
+// on the vector pipe, as above, 480 instructions a wave went into 16 keys of four heads, 2 us for 64 keys with two
+// workgroups on a compute unit.  A step with a kept token, 1 x 32 / 8 heads x 2000, 16384 and 32768 keys: 17.0, 30.6, 39.4 -> 13.6,
+// 22.3, 31.0 us; 8 x 32 / 8 x 2048 27.3 -> 22.4; 1 x 32 / 32 x 2048 22.4 -> 18.3.  Distance from 64 bits as before (1.65e-3, the
+// rounding of the output).
+template <int G>
+__global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
+    const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
+    float* __restrict__ part, int32_t* __restrict__ tickets, uint16_t* __restrict__ o, int B, int Hq, int Hkv,
+    int capacity, int part_split, DecodeSplits splits, float scale_log2e)
+{
+    constexpr bool kTwice = 3 * G > 16;              // the third parts get a product of their own
+    constexpr int kCols = kTwice ? 2 * G : 3 * G;    // columns of O^T in use
+    constexpr int kRow = kHeadDim + 4;
+    __shared__ __attribute__((aligned(16))) float o_part[4][kCols][kRow];
+    __shared__ float stat[4][G][2];                  // a wave's running max and sum
+    __shared__ float weight[G][kDecodeMaxSplit + 1];
+    __shared__ int drawn;
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // The workgroups are dealt out to the rows that attend, as many slices a row as suit their number: with a share for
+    // the skipped ones too, half of the chip idles where half of the tokens are skipped (16 steps of 8 x 32 / 32 heads x 2048 keys
+    // with about half of the rows skipped: 589 us, 557 dealt out).
+    const int groups = Hq / G;   // of query heads
+    const bool dealt = B <= kDecodeDealt;
+    const int mine = min(dealt ? lane : (int)blockIdx.x / (groups * splits.n[0]), B - 1);
+    const int mine_len = cache_len[mine];
+    const bool attends = skip[mine] == 0 && (!dealt || lane < B);
+    const unsigned long long rows = __ballot(attends);
+    // zero rows, by the first workgroups of the grid
+    if (blockIdx.x < B * groups) {
+        const int zb = blockIdx.x / groups;
+        if (dealt ? !(rows >> zb & 1) : skip[zb] != 0)
+            for (int i = threadIdx.x; i < G * kHeadDim; i += 256) o[(long long)blockIdx.x * G * kHeadDim + i] = 0;
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < G * kHeadDim; i += 256) {
-        const int g = i / kHeadDim, c = i % kHeadDim;
-        const float* pr = part0 + (long long)g * n_split * kPartStride + c;
-        // (16 loads at a time whatever the count: the last ones repeat a slice with weight 0)
-        float num = 0.f;
-        for (int l = 0; l < used; l += 16) {
-            float x[16];
+    if (rows == 0) return;
+    const int n_split = splits.n[dealt ? __popcll(rows) - 1 : 0];
+    const int sp = blockIdx.x % n_split;
+    const int hg = (blockIdx.x / n_split) % groups;
+    int b = blockIdx.x / n_split / groups, len = mine_len;
+    if (dealt) {   // the b-th row that attends
+        const unsigned long long here = __ballot(attends && __popcll(rows & ((1ull << lane) - 1)) == b);
+        if (here == 0) return;
+        b = __builtin_ctzll(here);
+        len = __shfl(mine_len, b);
+    }
+    len = __builtin_amdgcn_readfirstlane(len);
+    const int hq0 = hg * G, hk = hq0 / (Hq / Hkv);
+    uint16_t* const out = o + ((long long)b * Hq + hq0) * kHeadDim;
+    const long long row0 = ((long long)b * Hkv + hk) * capacity;
+    const uint16_t* kb = k_cache + row0 * kHeadDim + 8 * g4;
+    const uint16_t* vb = v_cache + row0 * kHeadDim + 8 * c16;
+    const int chunk = max(kDecodeSliceBf16, ((len + n_split - 1) / n_split + 31) & ~31);
+    const int lo = sp * chunk, hi = min(len, lo + chunk);
+    if (lo >= len) return;
+
+    u32x4 k_raw[2][4], v_raw[8];
+    auto request_k = [&](int j) {   // (past the end: the last row again, its scores are masked)
 #pragma unroll
-            for (int u = 0; u < 16; ++u) x[u] = get_shared(pr + min(l + u, used - 1) * kPartStride);
+        for (int h = 0; h < 2; ++h) {
+            const uint16_t* row = kb + (long long)min(j + 16 * h + c16, hi - 1) * kHeadDim;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) num = fmaf(x[u], weight[g][l + u], num);
+            for (int s = 0; s < 4; ++s) k_raw[h][s] = *reinterpret_cast<const u32x4*>(row + 32 * s);
         }
-        store_out(out + i, num / weight[g][kDecodeMaxSplit]);
+    };
+    auto request_v = [&](int j) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v_raw[e] = *reinterpret_cast<const u32x4*>(vb + (long long)min(j + 16 * (e >> 2) + 4 * g4 + (e & 3), hi - 1) * kHeadDim);
+    };
+    int j = lo + 32 * wave;
+    if (j < hi) { request_k(j); request_v(j); }
+    bf16x8 qf[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+        qf[s] = *reinterpret_cast<const bf16x8*>(q + ((long long)b * Hq + hq0 + c16 % G) * kHeadDim + 32 * s + 8 * g4);
+    f32x4 acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mx = kLowest, sum = 0.f;
+    for (; j < hi; j += 128) {
+        float s[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k_raw[h][t]), qf[t], d, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s[4 * h + v] = j + 16 * h + 4 * g4 + v < hi ? d[v] * scale_log2e : kLowest;
+        }
+        if (j + 128 < hi) request_k(j + 128);
+        const float top = wave_group_max(fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7]))));
+        if (__any(top > mx)) {
+            const float m_new = fmaxf(mx, top), down = __builtin_amdgcn_exp2f(mx - m_new);
+            mx = m_new;
+            sum *= down;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] *= down;
+        }
+        u32x4 p1, p2;   // weights: the parts of this lane's column, and the third parts if they go by themselves
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            unsigned x[2], y[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float p = __builtin_amdgcn_exp2f(s[e + i] - mx);
+                sum += p;
+                const float r1 = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);    // without the first part
+                const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);  // without the second
+                x[i] = __float_as_uint(c16 < G ? p : c16 < 2 * G ? r1 : kTwice || c16 >= 3 * G ? 0.f : r2);
+                y[i] = __float_as_uint(c16 < G ? r2 : 0.f);
+            }
+            p1[e / 2] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);
+            if (kTwice) p2[e / 2] = __builtin_amdgcn_perm(y[1], y[0], 0x07060302u);
+        }
+        bf16x8 vt[8];   // column 8 c16 + i of the lane's eight keys
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            u32x4 t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                t[e] = __builtin_amdgcn_perm(v_raw[2 * e + 1][i / 2], v_raw[2 * e][i / 2], i & 1 ? 0x07060302u : 0x05040100u);
+            vt[i] = __builtin_bit_cast(bf16x8, t);
+        }
+        if (j + 128 < hi) request_v(j + 128);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[i], __builtin_bit_cast(bf16x8, p1), acc[i], 0, 0, 0);
+            if (kTwice) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[i], __builtin_bit_cast(bf16x8, p2), acc[i], 0, 0, 0);
+        }
     }
+
+    // the four waves' results through LDS (register v of product i is column 8 (4 g4 + v) + i)
+    sum = wave_group_sum(sum);
+    if (c16 < kCols)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float* dst = &o_part[wave][c16][8 * (4 * g4 + v)];
+            *reinterpret_cast<f32x4*>(dst) = f32x4{acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
+            *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[4][v], acc[5][v], acc[6][v], acc[7][v]};
+        }
+    if (lane < G) { stat[wave][lane][0] = mx; stat[wave][lane][1] = sum; }
+    __syncthreads();
+    float* const part0 = part + ((long long)b * Hq + hq0) * part_split * kPartStride;   // [head][slice]
+    constexpr int kPairs = kPartStride / 2;   // the last one: running max, sum
+    auto combine = [&](auto n_waves) {
+        for (int i = threadIdx.x; i < G * kPairs; i += 256) {
+            const int g = i / kPairs, c = 2 * (i - g * kPairs);
+            float m_all = kLowest;
+#pragma unroll
+            for (int w = 0; w < n_waves; ++w) m_all = fmaxf(m_all, stat[w][g][0]);
+            Float2 v = {0.f, 0.f};
+            float den = 0.f;
+#pragma unroll
+            for (int w = 0; w < n_waves; ++w) {
+                const float wt = __builtin_amdgcn_exp2f(stat[w][g][0] - m_all);
+                den = fmaf(stat[w][g][1], wt, den);
+                if (c == kHeadDim) continue;
+                Float2 n = {o_part[w][G + g][c], o_part[w][G + g][c + 1]};
+                if (!kTwice) {
+                    constexpr int third = kTwice ? 0 : 2 * G;
+                    n.x += o_part[w][third + g][c];
+                    n.y += o_part[w][third + g][c + 1];
+                }
+                v.x = fmaf(n.x + o_part[w][g][c], wt, v.x);
+                v.y = fmaf(n.y + o_part[w][g][c + 1], wt, v.y);
+            }
+            if (c == kHeadDim) v = {m_all, den};
+            if (len > chunk) put_shared(part0 + ((long long)g * part_split + sp) * kPartStride + c, v);
+            else if (c < kHeadDim) { store_out(out + g * kHeadDim + c, v.x / den); store_out(out + g * kHeadDim + c + 1, v.y / den); }
+        }
+    };
+    // (up to 32 keys are one wave's)
+    if (hi - lo <= 32) combine(std::integral_constant<int, 1>());
+    else combine(std::integral_constant<int, 4>());
+    if (len > chunk)
+        merge_slices<uint16_t, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, part_split);
 }
 
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
@@ -541,10 +761,30 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float sl2 = a.scale * 1.4426950408889634f;
+    const int groups = a.Hq / g;
 #define TF_DECODE_ATTEND(G)                                                                       \
-    decode_attend_kernel<T, G><<<dim3(a.B * (a.Hq / G) * a.n_split), dim3(256), 0, s>>>(          \
-        q, (const T*)a.k_cache, (const T*)a.v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, \
-        a.Hkv, a.capacity, a.n_split, sl2)
+    do {                                                                                          \
+        if constexpr (sizeof(T) == 2)                                                             \
+            decode_attend_bf16_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                        \
+                q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv,   \
+                a.capacity, a.n_split, splits, sl2);                                              \
+        else                                                                                      \
+            decode_attend_f32_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                         \
+                q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, a.Hkv,        \
+                a.capacity, a.n_split, sl2);                                                      \
+    } while (0)
+    const T *k_cache = (const T*)a.k_cache, *v_cache = (const T*)a.v_cache;
+    int grid = a.B * groups * a.n_split;
+    DecodeSplits splits;
+    if (sizeof(T) == 2) {
+        grid = 0;
+        const bool dealt = a.B <= kDecodeDealt;
+        for (int rows = dealt ? 1 : a.B; rows <= a.B; ++rows) {   // rows that attend
+            const int n = std::min(a.n_split, decode_slices(rows * groups, a.n_cu));
+            splits.n[dealt ? rows - 1 : 0] = (uint8_t)n;
+            grid = std::max(grid, rows * groups * n);
+        }
+    }
     if (g == 8) TF_DECODE_ATTEND(8);
     else if (g == 4) TF_DECODE_ATTEND(4);
     else if (g == 2) TF_DECODE_ATTEND(2);
@@ -558,26 +798,44 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
 int decode_heads_per_wg(int B, int Hq, int Hkv)
 {
     const int group = Hq / Hkv;
-    // Eight heads take all the registers and one wave's time for each key; where few caches are read they are better
-    // shared out to two workgroups that read them twice (1 row of 16 / 2 heads x 16384 keys: 32.0 us a step with
-    // eight heads, 23.1 with four; 8 x 64 / 8 x 4000 49 and 54, fp32 16 x 64 / 8 x 4000 112 and 161).
+    // Where few caches are read, eight heads are better shared out to two workgroups that read them twice: the slices of
+    // four are merged in half the time (a step of 1 row of 16 / 2 heads x 16384 keys: 20.8 us with eight heads, 18.0
+    // with four; 1 x 64 / 8 x 4000: 18.5 and 16.6; fp32 16 x 64 / 8 x 4000 112 and 161).
     if (group == 8) return B * Hkv < 48 ? 4 : 8;
     return group == 2 || group == 4 ? group : 1;  // other ratios: one query head per workgroup
 }
 
-int decode_max_split(int B, int Hq, int Hkv)
+int decode_slices(int rows, int n_cu)
 {
-    const int g = decode_heads_per_wg(B, Hq, Hkv), rows = B * (Hq / g);
-    // as many as are resident at once: two on a compute unit where they take four or eight heads (8 x 32 / 8 heads x 4000
-    // 41 -> 34 us, 1 x 64 / 16 x 4000 35 -> 23, against 1024 workgroups for these too)
-    const int most = kDecodeWorkgroups / (g >= 4 ? 2 : 1);
-    return std::min(kDecodeMaxSplit, std::max(1, (most + rows - 1) / rows));
+    // One workgroup on a compute unit has enough keys under way, and a merge of more slices costs more than more
+    // workgroups bring (a step of 1 x 32 / 8 heads x 16384: 25.7 us with 512, 22.3 with 256; 1 x 32 / 32 x 2048: 22.0,
+    // 19.6 and 18.3 with 1024, 512 and 256; 8 x 32 / 32 x 256: 21.7, 18.5 and 16).  Where rows do not fill whole
+    // rounds of the compute units, the fewest slices that come within a tenth of even shares, in up to four
+    // rounds (8 x 40 / 40 x 2048, 320 rows: 96 us with 320 workgroups, 80 with 640, 72.5 with 960).
+    const int most = std::min(kDecodeMaxSplit, 4 * n_cu / rows);
+    int split = std::min(kDecodeMaxSplit, std::max(1, n_cu / rows));
+    int busiest = (rows * split + n_cu - 1) / n_cu;   // workgroups of the busiest compute unit
+    for (int n = split + 1; n <= most && 10 * busiest * n_cu > 11 * rows * split; ++n) {
+        const int of_n = (rows * n + n_cu - 1) / n_cu;
+        if (of_n * split < busiest * n) { split = n; busiest = of_n; }
+    }
+    return split;
 }
 
-size_t decode_scratch_bytes(int B, int Hq, int Hkv)
+int decode_max_split(bool bf16, int B, int Hq, int Hkv, int n_cu)
+{
+    const int g = decode_heads_per_wg(B, Hq, Hkv), rows = B * (Hq / g);
+    // bf16: the slices of a row that attends alone
+    if (bf16) return decode_slices(B <= kDecodeDealt ? Hq / g : rows, n_cu);
+    // as many workgroups as are resident at once: four on a compute unit, two where they take four or eight heads (8 x 32 /
+    // 8 heads x 4000 41 -> 34 us, 1 x 64 / 16 x 4000 35 -> 23, against 1024 workgroups for these too)
+    return std::min(kDecodeMaxSplit, std::max(1, ((g >= 4 ? 2 : 4) * n_cu + rows - 1) / rows));
+}
+
+size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv)
 {
     const size_t rows = (size_t)B * Hq;
-    return (rows * decode_max_split(B, Hq, Hkv) * kDecodePartFloats + rows) * sizeof(float);
+    return (rows * decode_max_split(bf16, B, Hq, Hkv) * kDecodePartFloats + rows) * sizeof(float);
 }
 
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s)

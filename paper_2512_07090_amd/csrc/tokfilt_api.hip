@@ -460,7 +460,7 @@ size_t tf_decode_workspace_bytes(const tf_params* p)
 {
     const char* why;
     if (check_shape(p, &why) != TF_OK) return 0;
-    return std::max(decode_least_bytes(p), align256(tf::decode_scratch_bytes(p->batch, p->n_q_heads, p->n_kv_heads)));
+    return std::max(decode_least_bytes(p), align256(tf::decode_scratch_bytes(p->dtype != TF_F32, p->batch, p->n_q_heads, p->n_kv_heads)));
 }
 
 tf_status tf_decode_init(tf_ctx* ctx, const tf_params* p, const tf_decode_state* state, float tau0,
@@ -538,15 +538,14 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
     a.skip = skip;
     a.fused = fused;
     a.part = (float*)ws;
-    // about as many workgroups as are resident at once, each slice at least one pass of keys, and no more slices
-    // than the workspace holds with their tickets
+    a.n_cu = ctx->n_cu;
+    // each slice at least one pass of keys, and no more slices than the workspace holds with their tickets
+    const bool bf16 = p->dtype != TF_F32;
     const size_t rows = (size_t)p->batch * p->n_q_heads;
     const int room = (int)std::min<size_t>(tf::kDecodeMaxSplit, (ws_bytes / sizeof(float) - rows) / (rows * tf::kDecodePartFloats));
-    const int g = tf::decode_heads_per_wg(p->batch, p->n_q_heads, p->n_kv_heads);
-    const long long wgs = (long long)rows / g, most = (long long)ctx->n_cu * (g >= 4 ? 2 : 4);
-    const int fill = (int)std::max(1ll, (most + wgs - 1) / wgs);
-    a.n_split = std::min({tf::decode_max_split(p->batch, p->n_q_heads, p->n_kv_heads), fill,
-                          (state->capacity + tf::kDecodeSlice - 1) / tf::kDecodeSlice, room});
+    const int slice = bf16 ? tf::kDecodeSliceBf16 : tf::kDecodeSlice;
+    a.n_split = std::min({tf::decode_max_split(bf16, p->batch, p->n_q_heads, p->n_kv_heads, ctx->n_cu),
+                          (state->capacity + slice - 1) / slice, room});
     return dev(ctx, tf::launch_decode_step(a, p->dtype, q, k, v, o, (hipStream_t)stream), "decode step launch");
 }
 

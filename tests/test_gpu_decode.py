@@ -204,6 +204,49 @@ def test_decode_slices_follow_the_keys_held(ctx, case):
             assert err <= ATTN_TOL[dtype], (held, b, err)
 
 
+@pytest.mark.parametrize("case", [(5, 4, 4), (5, 4, 2), (5, 16, 4), (9, 64, 8), (3, 6, 2), (64, 8, 2), (65, 8, 2), (8, 40, 40)])
+def test_decode_rows_that_attend_share_the_grid(ctx, case):
+    """bf16: how many slices a row is cut into depends on how many rows attend.  Rows of different length around the
+    blocks of 32 keys, all, some, one or none of them skipped: attention in 64 bits over the rows held, zero rows
+    for the others, and the caches as they were outside of the new rows."""
+    Bn, Hq, Hkv = case
+    _say("decode dealt rows %s" % (case,))
+    cap = 1100
+    p = B.make_params((Bn, Hq, 1, 128), (Bn, Hkv, 1, 128), torch.bfloat16, 0.5, 0)
+    buf = B.DecodeBuffers(p, cap)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q, k, v = (torch.randn((Bn, h, 128), device="cuda", generator=g).bfloat16() for h in (Hq, Hkv, Hkv))
+    for c in (buf.k_cache, buf.v_cache):
+        c.copy_(torch.randn(c.shape, device="cuda", generator=g))
+    caches = [c.clone() for c in (buf.k_cache, buf.v_cache)]
+    held = [(1, 31, 32, 33, 64, 127, 128, 129, 161, 1023)[b % 10] for b in range(Bn)]
+    for skipped in ([], [0], list(range(0, Bn, 2)), list(range(Bn - 1)), list(range(Bn))):
+        ctx.tf_decode_init(p, buf.state, 50.0)
+        buf.tau[skipped] = -50.0
+        buf.cache_len.copy_(torch.tensor([n - 1 for n in held], dtype=torch.int32))
+        buf.ws.fill_(0xFF)
+        buf.o.fill_(float("nan"))
+        ctx.tf_decode_step(p, 0.0, buf.state, q, k, v, buf.o, buf.skip, buf.fused, buf.ws)
+        torch.cuda.synchronize()
+        assert buf.skip.nonzero().flatten().tolist() == skipped
+        for b, n in enumerate(held):
+            if b in skipped:
+                assert not buf.o[b].any()
+                continue
+            kk, vv = (c[b, :, :n].double().repeat_interleave(Hq // Hkv, 0) for c in (buf.k_cache, buf.v_cache))
+            w = torch.softmax((kk * q[b].double()[:, None]).sum(2) / 128 ** 0.5, 1)
+            out = (w[:, :, None] * vv).sum(1)
+            # the weights are fp32, so what is left is the output's rounding: half a unit of bf16
+            err = ((buf.o[b].double() - out).abs() - 2.0 ** -8 * out.abs()).max().item()
+            assert err <= 1e-5, (skipped, b, n, err)
+        for c, old, new in zip((buf.k_cache, buf.v_cache), caches, (k, v)):
+            for b, n in enumerate(held):
+                if b not in skipped:
+                    assert torch.equal(c[b, :, n - 1], new[b])
+                    c[b, :, n - 1] = old[b, :, n - 1]
+            assert torch.equal(c, old)
+
+
 def test_decode_step_with_eight_heads_per_kv_head(ctx):
     """Eight query heads read a cache once: 8 rows of 64 / 8 heads x 4000 keys take no longer than of 64 / 16 heads, twice
     the caches (46 and 59 us a step; 80 with the registers of one workgroup on a compute unit)."""
