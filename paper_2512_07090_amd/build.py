@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtokfilt.so")
 SOURCES = ("tokfilt_api.hip", "score_scan.hip", "fuse_select.hip", "attend_f32.hip", "attend_bf16.hip",
-           "decode.hip", "probes.hip")
+           "attend_bf16_halves.hip", "decode.hip", "probes.hip")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed fp32 VALU forms are kept out of the generated code
@@ -20,6 +20,7 @@ FILE_FLAGS = {
     # NaN inputs are outside the contract; without this every fmaxf of the online softmax is
     # preceded by a canonicalising v_max x, x
     "attend_bf16.hip": ["-fno-honor-nans"],
+    "attend_bf16_halves.hip": ["-fno-honor-nans"],
 }
 
 

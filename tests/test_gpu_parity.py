@@ -564,6 +564,50 @@ def test_attend_softmax_reference_at_block_borders(ctx, m, course):
 
 
 @pytest.mark.parametrize("shape", [   # batch, query heads, KV heads, kept, per-row counts
+    (1, 3, 1, 1, False), (1, 3, 1, 15, False), (1, 3, 3, 17, False), (1, 32, 8, 64, False), (2, 6, 2, 65, False),
+    (1, 32, 32, 127, False), (1, 32, 8, 129, False), (1, 3, 1, 385, False),   # one tile of 128 for each compute unit
+    (2, 32, 32, 600, False), (1, 32, 8, 1300, False),                         # two rounds of them, the second backwards
+    (2, 40, 40, 700, False), (8, 40, 40, 100, False),                         # four waves, two workgroups a compute unit
+    (3, 32, 32, 1100, False),                                                 # tiles of 256 in two rounds
+    (1, 32, 8, 1300, True), (3, 8, 2, 500, True), (2, 40, 40, 700, True),     # the same forms, listed row by row
+])
+def test_attend_tiles_of_128(ctx, shape):
+    """Tiles of 128 queries and the order they are dealt out in, at the tiles' edges: every row against attention in 64
+    bits, to the rounding of weights and outputs; the rows in between are zero."""
+    b, hq, hkv, m, ragged = shape
+    _say("attend tiles of 128 %s" % (shape,))
+    n = 2 * m + 3
+    g = torch.Generator(device="cuda").manual_seed(m)
+    q, k, v = (torch.randn(b, h, n, 128, device="cuda", generator=g).bfloat16() for h in (hq, hkv, hkv))
+    idx = torch.stack([torch.randperm(n, device="cuda", generator=g)[:m].sort().values for _ in range(b)])
+    p = B.make_params(tuple(q.shape), tuple(k.shape), q.dtype, 1.0 - m / n)
+    O, ws = torch.full_like(q, float("nan")), B.Buffers(p, "cuda:0").ws
+    counts = [m] * b
+    if ragged:
+        counts = [max(0, m - 131 * i * i) for i in range(b)]
+        full = torch.full((b, n), -1, dtype=torch.int32, device="cuda")
+        for i, c in enumerate(counts):
+            full[i, :c] = idx[i, :c]
+        ctx.tf_attend_ragged(p, q, k, v, full, torch.tensor(counts, dtype=torch.int32, device="cuda"), O, ws)
+    else:
+        ctx.tf_attend(p, q, k, v, idx.int(), m, O, ws)
+    torch.cuda.synchronize()
+    for i, c in enumerate(counts):
+        at = idx[i, :c]
+        rest = torch.ones(n, dtype=torch.bool, device="cuda")
+        rest[at] = False
+        assert not O[i, :, rest].any()
+        mask = torch.ones(c, c, dtype=torch.bool, device="cuda").tril()
+        for h in range(0, hq, 8):
+            qq = q[i, h:h + 8, at].double()
+            kk, vv = (x[i, :, at].double().repeat_interleave(hq // hkv, 0)[h:h + 8].contiguous() for x in (k, v))
+            w = torch.softmax((qq @ kk.transpose(1, 2).contiguous() / 128 ** 0.5).masked_fill(~mask, -float("inf")), 2)
+            # a weight and an output are rounded to bf16, 2^-9 of their size each, numerators and sums alike
+            bound = 2.0 ** -8 * (w @ vv.abs() + (w @ vv).abs()) + 1e-5
+            assert ((O[i, h:h + 8, at].double() - w @ vv).abs() <= bound).all(), (i, h)
+
+
+@pytest.mark.parametrize("shape", [   # batch, query heads, KV heads, kept, per-row counts
     (8, 32, 32, 300, False),    # pairs of tiles of 256 queries
     (8, 32, 8, 249, False),     # one such tile a group
     (8, 32, 32, 600, False),    # tiles of 256, one by one, an odd number of them
