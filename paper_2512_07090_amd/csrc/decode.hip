@@ -525,8 +525,12 @@ __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
         for (int e = 0; e < 8; ++e)
             v_raw[e] = *reinterpret_cast<const u32x4*>(vb + (long long)min(j + 16 * (e >> 2) + 4 * g4 + (e & 3), hi - 1) * kHeadDim);
     };
-    int j = lo + 32 * wave;
-    if (j < hi) { request_k(j); request_v(j); }
+    // A wave's blocks in turn, each KV head from another one on: workgroups that walk caches side by side in step meet in
+    // the same memory channels at some distances of the caches (8 x 32 / 32 heads x 2048 keys from memory: 70 us a
+    // step in caches of 2064 rows, 58 to 62 in others; like this 62 in all of them).
+    const int first = lo + 32 * wave, blocks = max(0, (hi - first + 127) / 128);
+    int j = blocks ? first + 128 * (hk % blocks) : hi;
+    if (blocks) { request_k(j); request_v(j); }
     bf16x8 qf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -535,7 +539,8 @@ __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     float mx = kLowest, sum = 0.f;
-    for (; j < hi; j += 128) {
+    for (int left = blocks; left > 0; --left) {
+        const int next = j + 128 < hi ? j + 128 : first;
         float s[8];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -546,7 +551,7 @@ __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
 #pragma unroll
             for (int v = 0; v < 4; ++v) s[4 * h + v] = j + 16 * h + 4 * g4 + v < hi ? d[v] * scale_log2e : kLowest;
         }
-        if (j + 128 < hi) request_k(j + 128);
+        if (left > 1) request_k(next);
         const float top = wave_group_max(fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7]))));
         if (__any(top > mx)) {
             const float m_new = fmaxf(mx, top), down = __builtin_amdgcn_exp2f(mx - m_new);
@@ -580,12 +585,13 @@ __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
                 t[e] = __builtin_amdgcn_perm(v_raw[2 * e + 1][i / 2], v_raw[2 * e][i / 2], i & 1 ? 0x07060302u : 0x05040100u);
             vt[i] = __builtin_bit_cast(bf16x8, t);
         }
-        if (j + 128 < hi) request_v(j + 128);
+        if (left > 1) request_v(next);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[i], __builtin_bit_cast(bf16x8, p1), acc[i], 0, 0, 0);
             if (kTwice) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[i], __builtin_bit_cast(bf16x8, p2), acc[i], 0, 0, 0);
         }
+        j = next;
     }
 
     // the four waves' results through LDS (register v of product i is column 8 (4 g4 + v) + i)
