@@ -9,8 +9,8 @@ namespace {
 
 // ------------------------------------------------------------------------------ fusion
 // 64 tokens per workgroup.  All 256 threads stage the tokens' per-head cosines in LDS
-// ([head][token]: global reads and LDS accesses are unit-stride across a wave; four head
-// groups load in parallel so enough loads are in flight); then one thread per token takes the
+// ([head][token]: global reads and LDS accesses are unit-stride across a wave), eight heads a thread under way at
+// once (one by one, as it was, 32 heads were eight round trips to memory in a row: 8 x 4096 tokens 6.3 -> 5.2 us); then one thread per token takes the
 // mean and the two-pass variance over the heads (the head count is a run-time value).
 constexpr int kFuseTokens = 64;
 constexpr int kFuseThreads = 256;
@@ -19,6 +19,7 @@ constexpr int kFuseThreads = 256;
 __device__ __forceinline__ float fuse_token(const float* ck, const float* cv, int stride, int H, int mode)
 {
     float sk = 0.f, sv = 0.f;
+#pragma unroll 8
     for (int h = 0; h < H; ++h) {
         sk += ck[h * stride];
         sv += cv[h * stride];
@@ -27,6 +28,7 @@ __device__ __forceinline__ float fuse_token(const float* ck, const float* cv, in
     sk *= inv_h;
     sv *= inv_h;
     float vk = 0.f, vv = 0.f;
+#pragma unroll 8
     for (int h = 0; h < H; ++h) {
         const float dk = ck[h * stride] - sk;
         const float dv = cv[h * stride] - sv;
@@ -60,9 +62,19 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_kernel(const float* __restr
         // key-only / value-only scores read one tensor's cosines (the other was not computed)
         const float* pk = (mode == 3 ? sim_v : sim_k) + (long long)b * H * n + t;
         const float* pv = (mode == 2 ? sim_k : sim_v) + (long long)b * H * n + t;
-        for (int h = hg; h < H; h += kFuseThreads / kFuseTokens) {
-            ck[h * kFuseTokens + tok] = pk[(long long)h * n];
-            cv[h * kFuseTokens + tok] = pv[(long long)h * n];
+        // eight heads of each tensor under way at a time (past the last head: that one again)
+        constexpr int kStep = kFuseThreads / kFuseTokens, kBatch = 8;
+        for (int h0 = hg; h0 < H; h0 += kStep * kBatch) {
+            float k[kBatch], v[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const long long at = (long long)min(h0 + u * kStep, H - 1) * n;
+                k[u] = pk[at];
+                v[u] = pv[at];
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+                if (const int h = h0 + u * kStep; h < H) { ck[h * kFuseTokens + tok] = k[u]; cv[h * kFuseTokens + tok] = v[u]; }
         }
     }
     __syncthreads();
@@ -80,12 +92,14 @@ constexpr int kSelWaves = kSelThreads / 64;
 __device__ __forceinline__ int block_excl_scan(int v, int* lds, int* total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // inclusive over the wave, in the VALU: shifts by 1, 2, 4, 8 within rows of 16 lanes, then the rows before
     int inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(inc, off);
-        if (lane >= off) inc += o;
-    }
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, true);   // row_shr
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, true);
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x142, 0xa, 0xf, true);   // row_bcast 15: rows 1 and 3
+    inc += __builtin_amdgcn_update_dpp(0, inc, 0x143, 0xc, 0xf, true);   // row_bcast 31: rows 2 and 3
     if (lane == 63) lds[wave] = inc;
     __syncthreads();
     int base = 0, tot = 0;
@@ -222,7 +236,8 @@ __global__ __launch_bounds__(kSelThreads) void compact_kernel(const uint8_t* __r
 // Everything at or below the token found is kept.  What bounds it: short rows a chain of some 15
 // barriers and LDS round trips, long rows the passes over 32 scores a thread on the one compute unit
 // that works on a row.  One row of 32768 tokens: 55 -> 24 us against four radix passes in thread
-// order, 2 x 8192: 16 -> 9.3, 8 x 4096: 11.4 -> 7.4, 333: 8.1 -> 4.9.
+// order, 2 x 8192: 16 -> 9.3, 8 x 4096: 11.4 -> 7.4, 333: 8.1 -> 4.9.  Reductions and scans of a wave in the VALU
+// (through LDS, a chain of twelve accesses for the range alone: 8 x 4096 9.4 -> 8.2, 1 x 2048 6.6 -> 5.8).
 constexpr int kBins = 2048;
 constexpr int kMaxCand = 256;
 constexpr int kLevels = 4;
@@ -256,7 +271,7 @@ __device__ __forceinline__ int rank_below(unsigned long long ballot)
 // kFuseFloats a tensor, staged in LDS) with the arithmetic of fuse_kernel and writes them to `fused`.
 // That takes about 2 us here and 4 in a launch of its own; a longer row, or one with more heads, would keep
 // one compute unit loading what fuse_kernel spreads over many.  Whole calls: 32 heads x 333 tokens
-// 29.4 -> 27.3 us, fp32 32 x 512 36.9 -> 35.5; 8 heads x 2048 tokens (four a thread) 0.5 us slower a call.
+// 29.4 -> 27.3 us, fp32 32 x 512 36.9 -> 35.5 (the kernel 9.5 -> 7.6 with all loads under way at once); 8 heads x 2048 tokens (four a thread) 0.5 us slower a call.
 constexpr int kFuseFloats = 16384;
 
 template <int IPT, bool FUSE>
@@ -296,8 +311,17 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
         // (key-only / value-only scores read one tensor's cosines, the other was not computed)
         const float* pk = (mode == 3 ? sim_v : sim_k) + (long long)b * H * n;
         const float* pv = (mode == 2 ? sim_k : sim_v) + (long long)b * H * n;
-#pragma unroll 8
-        for (int i = tid; i < H * n; i += kSelThreads) { cos_k[i] = pk[i]; cos_v[i] = pv[i]; }
+        constexpr int kEach = kFuseFloats / kSelThreads;   // all of a thread's loads under way at once
+        float k[kEach], v[kEach];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            const int i = min(u * kSelThreads + tid, H * n - 1);
+            k[u] = pk[i];
+            v[u] = pv[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            if (const int i = u * kSelThreads + tid; i < H * n) { cos_k[i] = k[u]; cos_v[i] = v[u]; }
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < IPT; ++i) {
@@ -318,11 +342,14 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
 
     // smallest and largest score over the workgroup; one barrier before the result, none after
     auto min_max = [&](float& lo, float& hi) {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            lo = fminf(lo, __shfl_xor(lo, off));
-            hi = fmaxf(hi, __shfl_xor(hi, off));
-        }
+        lo = fminf(lo, dpp_mov<0xB1>(lo));    hi = fmaxf(hi, dpp_mov<0xB1>(hi));    // as in row16_sum
+        lo = fminf(lo, dpp_mov<0x4E>(lo));    hi = fmaxf(hi, dpp_mov<0x4E>(hi));
+        lo = fminf(lo, dpp_mov<0x141>(lo));   hi = fmaxf(hi, dpp_mov<0x141>(hi));
+        lo = fminf(lo, dpp_mov<0x140>(lo));   hi = fmaxf(hi, dpp_mov<0x140>(hi));
+        const FloatPair lo16 = swap16(lo, lo), hi16 = swap16(hi, hi);
+        lo = fminf(lo16.first, lo16.second);  hi = fmaxf(hi16.first, hi16.second);
+        const FloatPair lo32 = swap32(lo, lo), hi32 = swap32(hi, hi);
+        lo = fminf(lo32.first, lo32.second);  hi = fmaxf(hi32.first, hi32.second);
         if (lane == 0) { lo_lds[wave] = lo; hi_lds[wave] = hi; }
         __syncthreads();
 #pragma unroll

@@ -15,10 +15,11 @@
 //   over the 16 row groups (bpermute inside a wave, 2 KB of LDS across the 4 waves);
 //   (3) each thread replays its 8 rows against its running prefix.
 // With nseg > 1 a first kernel reduces every segment but the last to its column totals and
-// the scan kernel starts from the sum of the totals before it.
+// the scan kernel starts from the sum of the totals before it; in rows of few tiles it makes them itself.
 #include "tf_kernels.h"
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace tf {
 
@@ -27,6 +28,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kR = 8;               // rows per thread per tile
 constexpr int kTile = 16 * kR;      // rows per tile
+constexpr int kOwnTotals = 4;       // segments of one tile up to which the scan adds up the totals by itself
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -217,7 +219,46 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
     float carry[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) carry[c] = 0.f;
-    for (int s = 0; !EMA && s < seg; ++s) {
+    if constexpr (!EMA) {
+        if (!seg_tot && seg > 0) {
+            __shared__ float before[kOwnTotals - 1][16][kHeadDim], totals[kOwnTotals - 1][kHeadDim];
+            auto add_up = [&](auto count) {
+                constexpr int N = decltype(count)::value;   // segments before this one, a tile each
+                Row8<T> rows[N][kR];
+#pragma unroll
+                for (int s = 0; s < N; ++s) load_tile<false>(rows[s], X, s_t, s * kTile + rg * kR, n, 8 * l);
+#pragma unroll
+                for (int s = 0; s < N; ++s) {
+                    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int r = 0; r < kR; ++r) {
+                        float x[8];
+                        rows[s][r].unpack(x);
+#pragma unroll
+                        for (int c = 0; c < 8; ++c) acc[c] += x[c];
+                    }
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) before[s][rg][8 * l + c] = acc[c];
+                }
+            };
+            static_assert(kOwnTotals == 4, "one case each");
+            if (seg == 1) add_up(std::integral_constant<int, 1>());
+            else if (seg == 2) add_up(std::integral_constant<int, 2>());
+            else add_up(std::integral_constant<int, 3>());
+            __syncthreads();
+            for (int i = tid; i < seg * kHeadDim; i += kThreads) {
+                float sum = 0.f;
+#pragma unroll
+                for (int g = 0; g < 16; ++g) sum += before[i / kHeadDim][g][i % kHeadDim];
+                totals[i / kHeadDim][i % kHeadDim] = sum;
+            }
+            __syncthreads();
+            for (int s = 0; s < seg; ++s)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) carry[c] += totals[s][8 * l + c];
+        }
+    }
+    for (int s = 0; !EMA && seg_tot && s < seg; ++s) {
         const float* p = seg_tot + ((long long)chain * nseg + s) * kHeadDim + 8 * l;
         const float4 a = *reinterpret_cast<const float4*>(p);
         const float4 b = *reinterpret_cast<const float4*>(p + 4);
@@ -465,7 +506,12 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
                                         first_tensor, gamma, warm);
         return hipGetLastError();
     }
-    if (p.nseg > 1) {
+    // A short row's segments of one tile add up the tiles before theirs by themselves, with the same arithmetic: up to
+    // three tiles more to load at once cost less than a launch for the totals (bf16, 64 chains x 333 rows: 3.0 and 5.6
+    // us -> 6.4; fp32, twice the bytes, x 512 with three tiles: 4.0 and 7.9 -> 12.8).
+    const bool own_totals = p.nseg <= (sizeof(T) == 2 ? kOwnTotals : 2) && p.seg_len == kTile;
+    if (own_totals) seg_tot = nullptr;
+    else if (p.nseg > 1) {
         segment_totals_kernel<T><<<dim3(chains * (p.nseg - 1)), dim3(kThreads), 0, s>>>(
             K, V, d.kvs[0], d.kvs[1], d.kvs[2], BH, d.Hkv, d.n, p.nseg, p.seg_len, seg_tot,
             first_tensor);

@@ -320,6 +320,35 @@ def test_whole_path_incremental_anchor(ctx):
     assert np.abs(O_g - O_ref).max() <= ATTN_TOL[q.dtype]
 
 
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("heads", [1, 9, 16])
+def test_score_short_rows_as_in_longer_ones(ctx, dt, heads):
+    """Up to four tiles of 128 rows the scan adds up the rows before a segment by itself, longer rows have a launch
+    for it: the same arithmetic, so the first rows of a longer sequence have the same scores bit for bit (of one
+    whose segments are one tile too: with up to 32 chains 700 rows are).
+    Tile edges, both anchors' inclusive form, and the fusion kernel's batches of heads."""
+    _say("score short rows %s %d" % (dt, heads))
+    g = torch.Generator(device="cuda").manual_seed(heads)
+    k, v = (torch.randn(1, heads, 700, 128, device="cuda", generator=g).to(dt) for _ in range(2))
+
+    def scores(n, fusion, inclusive):
+        kk, vv = (x[:, :, :n].contiguous() for x in (k, v))
+        p = B.make_params(tuple(kk.shape), tuple(kk.shape), dt, 0.5, 1, fusion, anchor_inclusive=inclusive)
+        buf = B.Buffers(p, "cuda:0", with_sims=True)
+        for x in (buf.fused, buf.sim_k, buf.sim_v):
+            x.fill_(float("nan"))
+        ctx.tf_score(p, kk, vv, buf.fused, buf.sim_k, buf.sim_v, buf.ws)
+        torch.cuda.synchronize()
+        return buf.fused, buf.sim_k, buf.sim_v
+
+    for fusion, inclusive in ((B.TF_FUSE_EQ2, False), (B.TF_FUSE_EQ2, True), (B.TF_FUSE_KEY_ONLY, False)):
+        long = scores(700, fusion, inclusive)
+        for n in (1, 128, 129, 256, 300, 384, 385, 512, 513):
+            short = scores(n, fusion, inclusive)
+            for x, y in list(zip(short, long))[:3 if fusion == B.TF_FUSE_EQ2 else 2]:
+                assert torch.equal(x, y[..., :n]), (fusion, inclusive, n)
+
+
 def test_score_degenerate_inputs(ctx):
     _say("score degenerate")
     n = 200
