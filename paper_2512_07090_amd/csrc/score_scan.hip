@@ -258,12 +258,22 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
                 for (int c = 0; c < 8; ++c) carry[c] += totals[s][8 * l + c];
         }
     }
-    for (int s = 0; !EMA && seg_tot && s < seg; ++s) {
-        const float* p = seg_tot + ((long long)chain * nseg + s) * kHeadDim + 8 * l;
-        const float4 a = *reinterpret_cast<const float4*>(p);
-        const float4 b = *reinterpret_cast<const float4*>(p + 4);
-        carry[0] += a.x; carry[1] += a.y; carry[2] += a.z; carry[3] += a.w;
-        carry[4] += b.x; carry[5] += b.y; carry[6] += b.z; carry[7] += b.w;
+    // (the totals of eight segments under way at once; past the last one, that one again)
+    constexpr int kTotals = 8;
+    for (int s0 = 0; !EMA && seg_tot && s0 < seg; s0 += kTotals) {
+        float4 a[kTotals], b[kTotals];
+#pragma unroll
+        for (int u = 0; u < kTotals; ++u) {
+            const float* p = seg_tot + ((long long)chain * nseg + min(s0 + u, seg - 1)) * kHeadDim + 8 * l;
+            a[u] = *reinterpret_cast<const float4*>(p);
+            b[u] = *reinterpret_cast<const float4*>(p + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < kTotals; ++u)
+            if (s0 + u < seg) {
+                carry[0] += a[u].x; carry[1] += a[u].y; carry[2] += a[u].z; carry[3] += a[u].w;
+                carry[4] += b[u].x; carry[5] += b[u].y; carry[6] += b[u].z; carry[7] += b[u].w;
+            }
     }
 
     Row8<T> buf0[kR], buf1[kR], buf2[kR];
@@ -408,9 +418,10 @@ struct ScorePlan {
 // Segments of a chain.  Never more than keep every workgroup of the launch resident at once (their registers
 // allow two bf16 workgroups a compute unit, one fp32): a second round of a few workgroups takes as long
 // as the first.  Times are whole calls of tf_score at `chains` x tokens.
-// Exact mean: a workgroup adds up the totals of all segments before its own, one load after the other, so the
-// time is about tiles / nseg + nseg / 10 tile times: at most sqrt(10 tiles) segments, or 16 where each has a
-// compute unit (8 x 16384 31.7 us with 64, 25.8 with 32; 2 x 32768 41.0 with 256, 27.9 with 52).  The totals pass reads all but the last
+// Exact mean: a workgroup adds up the totals of all segments before its own, eight loads at a time, so the
+// time is about tiles / nseg + nseg / 20 tile times: at most sqrt(20 tiles) segments, or 16 where each has a
+// compute unit (16 chains x 8192 23.3 us with 22 segments, 22.4 with 32; 2 x 32768 25.8 with 52, 23.9 with 64, 26.4
+// with 128; one load at a time these took 23.4 and 30.6 with the fewer ones).  The totals pass reads all but the last
 // segment a second time, which is not worth it from kOneSegment chains on where that would make two
 // segments (192 x 8192 117 with one, 123 with two; 240 x 16384 230 and 258), but is for three of a long
 // row (160 x 3000 49.9 with one, 46.5 with three; 160 x 32768 442 and 404; only 160 x 1777 33.9 and 34.7).
@@ -434,7 +445,7 @@ static ScorePlan plan_score(int chains, int most, int n, bool f32, bool ema, int
         const int few = std::max(2, tiles_of(std::min(one_a_cu, most))), many = std::max(4, tiles_of(std::min(resident, most)));
         tiles_per_seg = few + 2 <= 1.45 * (many + 2) ? few : many;
     } else {
-        int nseg = std::min({resident, most, std::max((int)sqrt(10.0 * tiles), std::min(one_a_cu, 16))});
+        int nseg = std::min({resident, most, std::max((int)sqrt(20.0 * tiles), std::min(one_a_cu, 16))});
         if (chains >= kOneSegment && (nseg < 3 || tiles < kManyTiles)) nseg = 1;
         tiles_per_seg = std::max(tiles < kManyTiles ? 1 : 2, tiles_of(nseg));
     }
