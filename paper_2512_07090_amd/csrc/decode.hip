@@ -136,7 +136,7 @@ __device__ __forceinline__ double wave_sum(double v)
 }
 
 template <typename T>
-__global__ __launch_bounds__(1024) void decode_score_kernel(
+__device__ __forceinline__ void score_row(
     const T* __restrict__ k, const T* __restrict__ v, double* __restrict__ anchor_k,
     double* __restrict__ anchor_v, int32_t* __restrict__ seen, int32_t* __restrict__ skipped,
     float* __restrict__ tau, int32_t* __restrict__ cache_len, int32_t* __restrict__ overflow,
@@ -249,6 +249,33 @@ __global__ __launch_bounds__(1024) void decode_score_kernel(
     }
 }
 #pragma clang fp contract(fast)
+
+// The kernels of a step take their arguments as one block: a launch handles each argument by itself, and 40 of them
+// were 0.6 of a call's 6.5 us on the host.  (The bodies are functions of their own for the pointers' sake,
+// which are known not to overlap as arguments only.)
+template <typename T> struct ScoreArgs {
+    const T *k, *v;
+    double *anchor_k, *anchor_v;
+    int32_t *seen, *skipped;
+    float* tau;
+    int32_t *cache_len, *overflow;
+    T *k_cache, *v_cache;
+    int capacity, Hkv, ema;
+    double gamma;
+    int inclusive, fusion, warmup;
+    float target, eta;
+    uint8_t* skip_out;
+    float* fused_out;
+    int32_t* tickets;
+    int n_tickets;
+};
+template <typename T>
+__global__ __launch_bounds__(1024) void decode_score_kernel(const ScoreArgs<T> a)
+{
+    score_row<T>(a.k, a.v, a.anchor_k, a.anchor_v, a.seen, a.skipped, a.tau, a.cache_len, a.overflow, a.k_cache, a.v_cache,
+                 a.capacity, a.Hkv, a.ema, a.gamma, a.inclusive, a.fusion, a.warmup, a.target, a.eta, a.skip_out,
+                 a.fused_out, a.tickets, a.n_tickets);
+}
 
 // sum over the four lanes that share lane % 16
 __device__ __forceinline__ float wave_group_sum(float v)
@@ -487,11 +514,11 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
 // 22.3, 31.0 us; 8 x 32 / 8 x 2048 27.3 -> 22.4; 1 x 32 / 32 x 2048 22.4 -> 18.3.  Distance from 64 bits as before (1.65e-3, the
 // rounding of the output).
 template <int G>
-__global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
+__device__ __forceinline__ void attend_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
     float* __restrict__ part, int32_t* __restrict__ tickets, uint16_t* __restrict__ o, int B, int Hq, int Hkv,
-    int capacity, int part_split, DecodeSplits splits, float scale_log2e)
+    int capacity, int part_split, const DecodeSplits& splits, float scale_log2e)
 {
     constexpr bool kTwice = 3 * G > 16;              // the third parts get a product of their own
     constexpr int kCols = kTwice ? 2 * G : 3 * G;    // columns of O^T in use
@@ -668,6 +695,24 @@ __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(
         merge_slices<uint16_t, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, part_split);
 }
 
+struct AttendArgs {
+    const uint16_t *q, *k_cache, *v_cache;
+    const int32_t* cache_len;
+    const uint8_t* skip;
+    float* part;
+    int32_t* tickets;
+    uint16_t* o;
+    int B, Hq, Hkv, capacity, part_split;
+    DecodeSplits splits;
+    float scale_log2e;
+};
+template <int G>
+__global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(const AttendArgs a)
+{
+    attend_bf16<G>(a.q, a.k_cache, a.v_cache, a.cache_len, a.skip, a.part, a.tickets, a.o, a.B, a.Hq, a.Hkv, a.capacity,
+                   a.part_split, a.splits, a.scale_log2e);
+}
+
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
 // One workgroup per (tensor, batch row, KV head) and 8 * LANES columns: a group of LANES lanes folds
 // every (1024 / LANES)-th row in Horner form, A <- g^stride A + x (g = 1 for the exact mean, whose
@@ -787,10 +832,10 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
     const int g = decode_heads_per_wg(a.B, a.Hq, a.Hkv);
     // tickets of the attention's workgroups behind the partial results
     int32_t* const tickets = (int32_t*)(a.part + (size_t)a.B * a.Hq * a.n_split * kDecodePartFloats);
-    decode_score_kernel<T><<<dim3(a.B), dim3(threads), 0, s>>>(
+    decode_score_kernel<T><<<dim3(a.B), dim3(threads), 0, s>>>(ScoreArgs<T>{
         k, v, a.anchor_k, a.anchor_v, a.seen, a.skipped, a.tau, a.cache_len, a.overflow,
         (T*)a.k_cache, (T*)a.v_cache, a.capacity, a.Hkv, a.ema, a.gamma, a.inclusive, a.fusion, a.warmup,
-        a.target, a.eta, a.skip, a.fused, tickets, a.n_split > 1 ? a.Hq / g : 0);
+        a.target, a.eta, a.skip, a.fused, tickets, a.n_split > 1 ? a.Hq / g : 0});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float sl2 = a.scale * 1.4426950408889634f;
@@ -799,8 +844,8 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
     do {                                                                                          \
         if constexpr (sizeof(T) == 2)                                                             \
             decode_attend_bf16_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                        \
-                q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv,   \
-                a.capacity, a.n_split, splits, sl2);                                              \
+                AttendArgs{q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv, a.capacity, \
+                           a.n_split, splits, sl2});                                              \
         else                                                                                      \
             decode_attend_f32_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                         \
                 q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, a.Hkv,        \
