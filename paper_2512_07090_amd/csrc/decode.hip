@@ -510,8 +510,9 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
 //                 to five heads are there anyway.  Their products with V are added up in fp32 at the end.
 // What bounds it is the way of the keys from memory, and for short rows the first loads (2 to 4 us) and the merge (6 us). In fp32
 // on the vector pipe, as above, 480 instructions a wave went into 16 keys of four heads, 2 us for 64 keys with two
-// workgroups on a compute unit.  A step with a kept token, 1 x 32 / 8 heads x 2000, 16384 and 32768 keys: 17.0, 30.6, 39.4 -> 13.6,
-// 22.3, 31.0 us; 8 x 32 / 8 x 2048 27.3 -> 22.4; 1 x 32 / 32 x 2048 22.4 -> 18.3.  Distance from 64 bits as before (1.65e-3, the
+// workgroups on a compute unit.  A step with a kept token (scoring included), 1 x 32 / 8 heads x 2000, 16384 and 32768 keys:
+// 17.0, 30.6, 39.2 -> 13.8, 22.4, 31.1 us; 8 x 32 / 8 x 2048 27.3 -> 21.6; 1 x 32 / 32 x 2048 22.4 -> 16.9; 8 x 32 / 32 x 2048
+// 55 -> 49.  Distance from 64 bits as before (1.65e-3, the
 // rounding of the output).
 template <int G>
 __device__ __forceinline__ void attend_bf16(
