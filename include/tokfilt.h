@@ -283,6 +283,8 @@ tf_status tf_decode_prefill(tf_ctx *ctx, const tf_params *p, float eta, float ta
  * queries attend over the row's whole cache, itself included.  Run over a sequence from
  * tf_decode_init this equals tf_filtered_attention_online on that sequence (scores to rounding;
  * decisions equal whenever the scores compare equally with the thresholds).
+ * Rows are independent: a row's results, rounding included, follow from its own state and token, `p`,
+ * state->capacity and ws_bytes, not from the other rows' decisions.
  *   q       in  [batch][n_q_heads][128], k, v  in [batch][n_kv_heads][128], contiguous, p->dtype
  *   o       out [batch][n_q_heads][128]: attention output, all zero for a skipped token
  *   skip    out [batch] u8: 1 = skipped

@@ -519,7 +519,7 @@ __device__ __forceinline__ void attend_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
     float* __restrict__ part, int32_t* __restrict__ tickets, uint16_t* __restrict__ o, int B, int Hq, int Hkv,
-    int capacity, int part_split, const DecodeSplits& splits, float scale_log2e)
+    int capacity, int n_split, float scale_log2e)
 {
     constexpr bool kTwice = 3 * G > 16;              // the third parts get a product of their own
     constexpr int kCols = kTwice ? 2 * G : 3 * G;    // columns of O^T in use
@@ -530,12 +530,13 @@ __device__ __forceinline__ void attend_bf16(
     __shared__ int drawn;
     const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // The workgroups are dealt out to the rows that attend, as many slices a row as suit their number: with a share for
-    // the skipped ones too, half of the chip idles where half of the tokens are skipped (16 steps of 8 x 32 / 32 heads x 2048 keys
-    // with about half of the rows skipped: 589 us, 557 dealt out).
+    // The workgroups are dealt out to the rows that attend: where skipped rows have a share of the grid, their places
+    // on the compute units stay empty (16 steps of 8 x 32 / 32 heads x 2048 keys with about half of the rows
+    // skipped: 533 us, 506 dealt out; of 8 x 32 / 8 280 and 275).  How a row is sliced does not depend on
+    // the other rows, so neither do its bits.
     const int groups = Hq / G;   // of query heads
     const bool dealt = B <= kDecodeDealt;
-    const int mine = min(dealt ? lane : (int)blockIdx.x / (groups * splits.n[0]), B - 1);
+    const int mine = min(dealt ? lane : (int)blockIdx.x / (groups * n_split), B - 1);
     const int mine_len = cache_len[mine];
     const bool attends = skip[mine] == 0 && (!dealt || lane < B);
     const unsigned long long rows = __ballot(attends);
@@ -546,7 +547,6 @@ __device__ __forceinline__ void attend_bf16(
             for (int i = threadIdx.x; i < G * kHeadDim; i += 256) o[(long long)blockIdx.x * G * kHeadDim + i] = 0;
     }
     if (rows == 0) return;
-    const int n_split = splits.n[dealt ? __popcll(rows) - 1 : 0];
     const int sp = blockIdx.x % n_split;
     const int hg = (blockIdx.x / n_split) % groups;
     int b = blockIdx.x / n_split / groups, len = mine_len;
@@ -660,7 +660,7 @@ __device__ __forceinline__ void attend_bf16(
         }
     if (lane < G) { stat[wave][lane][0] = mx; stat[wave][lane][1] = sum; }
     __syncthreads();
-    float* const part0 = part + ((long long)b * Hq + hq0) * part_split * kPartStride;   // [head][slice]
+    float* const part0 = part + ((long long)b * Hq + hq0) * n_split * kPartStride;   // [head][slice]
     constexpr int kPairs = kPartStride / 2;   // the last one: running max, sum
     auto combine = [&](auto n_waves) {
         for (int i = threadIdx.x; i < G * kPairs; i += 256) {
@@ -685,7 +685,7 @@ __device__ __forceinline__ void attend_bf16(
                 v.y = fmaf(n.y + o_part[w][g][c + 1], wt, v.y);
             }
             if (c == kHeadDim) v = {m_all, den};
-            if (len > chunk) put_shared(part0 + ((long long)g * part_split + sp) * kPartStride + c, v);
+            if (len > chunk) put_shared(part0 + ((long long)g * n_split + sp) * kPartStride + c, v);
             else if (c < kHeadDim) { store_out(out + g * kHeadDim + c, v.x / den); store_out(out + g * kHeadDim + c + 1, v.y / den); }
         }
     };
@@ -693,7 +693,7 @@ __device__ __forceinline__ void attend_bf16(
     if (hi - lo <= 32) combine(std::integral_constant<int, 1>());
     else combine(std::integral_constant<int, 4>());
     if (len > chunk)
-        merge_slices<uint16_t, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, part_split);
+        merge_slices<uint16_t, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, n_split);
 }
 
 struct AttendArgs {
@@ -703,15 +703,14 @@ struct AttendArgs {
     float* part;
     int32_t* tickets;
     uint16_t* o;
-    int B, Hq, Hkv, capacity, part_split;
-    DecodeSplits splits;
+    int B, Hq, Hkv, capacity, n_split;
     float scale_log2e;
 };
 template <int G>
 __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(const AttendArgs a)
 {
     attend_bf16<G>(a.q, a.k_cache, a.v_cache, a.cache_len, a.skip, a.part, a.tickets, a.o, a.B, a.Hq, a.Hkv, a.capacity,
-                   a.part_split, a.splits, a.scale_log2e);
+                   a.n_split, a.scale_log2e);
 }
 
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
@@ -846,24 +845,14 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
         if constexpr (sizeof(T) == 2)                                                             \
             decode_attend_bf16_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                        \
                 AttendArgs{q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv, a.capacity, \
-                           a.n_split, splits, sl2});                                              \
+                           a.n_split, sl2});                                                      \
         else                                                                                      \
             decode_attend_f32_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                         \
                 q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, a.Hkv,        \
                 a.capacity, a.n_split, sl2);                                                      \
     } while (0)
     const T *k_cache = (const T*)a.k_cache, *v_cache = (const T*)a.v_cache;
-    int grid = a.B * groups * a.n_split;
-    DecodeSplits splits;
-    if (sizeof(T) == 2) {
-        grid = 0;
-        const bool dealt = a.B <= kDecodeDealt;
-        for (int rows = dealt ? 1 : a.B; rows <= a.B; ++rows) {   // rows that attend
-            const int n = std::min(a.n_split, decode_slices(rows * groups, a.n_cu));
-            splits.n[dealt ? rows - 1 : 0] = (uint8_t)n;
-            grid = std::max(grid, rows * groups * n);
-        }
-    }
+    const int grid = a.B * groups * a.n_split;
     if (g == 8) TF_DECODE_ATTEND(8);
     else if (g == 4) TF_DECODE_ATTEND(4);
     else if (g == 2) TF_DECODE_ATTEND(2);
@@ -884,7 +873,8 @@ int decode_heads_per_wg(int B, int Hq, int Hkv)
     return group == 2 || group == 4 ? group : 1;  // other ratios: one query head per workgroup
 }
 
-int decode_slices(int rows, int n_cu)
+// Slices of each of `rows` caches that a step reads.
+static int decode_slices(int rows, int n_cu)
 {
     // One workgroup on a compute unit has enough keys under way, and a merge of more slices costs more than more
     // workgroups bring (a step of 1 x 32 / 8 heads x 16384: 25.7 us with 512, 22.3 with 256; 1 x 32 / 32 x 2048: 22.0,
@@ -901,20 +891,28 @@ int decode_slices(int rows, int n_cu)
     return split;
 }
 
-int decode_max_split(bool bf16, int B, int Hq, int Hkv, int n_cu)
+int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
 {
     const int g = decode_heads_per_wg(B, Hq, Hkv), rows = B * (Hq / g);
-    // bf16: the slices of a row that attends alone
-    if (bf16) return decode_slices(B <= kDecodeDealt ? Hq / g : rows, n_cu);
+    if (bf16) {
+        // By the batch rows that attend on average: by those that do attend in a step, a row's rounding would depend on its
+        // neighbours.  Where the number varies from step to step whole rounds are not worth more slices (16 steps of 8 x
+        // 40 / 40 x 2048, half of the rows skipped: 586 us with one slice, 618 with three; 8 x 32 / 32 x 2048, a quarter:
+        // 600 with one, 687 with four; 16 x 32 / 32 x 1024, a quarter: 628 with one, 681 with two), but they are
+        // where only one row now and then leaves a second round (8 x 40 / 40 x 2048, a tenth: 1052 and 961).
+        const int attending = std::max(1, (int)lround(B * (1.0 - target))), caches = attending * (Hq / g);
+        if (attending == B || (attending == B - 1 && caches > n_cu)) return decode_slices(caches, n_cu);
+        return std::min(kDecodeMaxSplit, std::max(1, n_cu / caches));
+    }
     // as many workgroups as are resident at once: four on a compute unit, two where they take four or eight heads (8 x 32 /
     // 8 heads x 4000 41 -> 34 us, 1 x 64 / 16 x 4000 35 -> 23, against 1024 workgroups for these too)
     return std::min(kDecodeMaxSplit, std::max(1, ((g >= 4 ? 2 : 4) * n_cu + rows - 1) / rows));
 }
 
-size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv)
+size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv, double target)
 {
     const size_t rows = (size_t)B * Hq;
-    return (rows * decode_max_split(bf16, B, Hq, Hkv) * kDecodePartFloats + rows) * sizeof(float);
+    return (rows * decode_max_split(bf16, B, Hq, Hkv, target) * kDecodePartFloats + rows) * sizeof(float);
 }
 
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s)

@@ -73,7 +73,6 @@ constexpr int kDecodeMaxSplit = 64;
 constexpr int kDecodeSlice = 64, kDecodeSliceBf16 = 128;   // keys of a slice at least: one pass of its workgroup
 constexpr int kDecodePartFloats = kHeadDim + 2;     // floats of one slice's partial result
 constexpr int kDecodeDealt = 64;                    // batch rows up to which workgroups are dealt out to the rows that attend (a lane each)
-struct DecodeSplits { uint8_t n[kDecodeDealt]; };   // slices of a row by the number of rows that attend, less one
 struct DecodeArgs {
     int B, Hq, Hkv, capacity;
     double *anchor_k, *anchor_v;                    // [B][Hkv][128]
@@ -87,12 +86,11 @@ struct DecodeArgs {
     float* fused;                                   // out [B]
     float* part;                                    // scratch [B][Hq][n_split][kDecodePartFloats], tickets
     int n_split;                                    // 1 .. decode_max_split()
-    int n_cu;                                       // compute units
 };
 int decode_heads_per_wg(int B, int Hq, int Hkv);           // query heads one workgroup handles (they share a KV head)
-int decode_slices(int rows, int n_cu);                     // of each of `rows` caches that a step in bf16 reads
-int decode_max_split(bool bf16, int B, int Hq, int Hkv, int n_cu = 256);   // n_cu: compute units; workspaces are sized for 256
-size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv);
+// target: share of the tokens to be skipped; n_cu: compute units (workspaces are sized for 256)
+int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu = 256);
+size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv, double target);
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s);
 // state after a prompt of n rows that the batched online path has processed: anchors from K and
 // V (element strides kvs for batch, head, position), caches from the kept rows (kept_idx

@@ -460,7 +460,7 @@ size_t tf_decode_workspace_bytes(const tf_params* p)
 {
     const char* why;
     if (check_shape(p, &why) != TF_OK) return 0;
-    return std::max(decode_least_bytes(p), align256(tf::decode_scratch_bytes(p->dtype != TF_F32, p->batch, p->n_q_heads, p->n_kv_heads)));
+    return std::max(decode_least_bytes(p), align256(tf::decode_scratch_bytes(p->dtype != TF_F32, p->batch, p->n_q_heads, p->n_kv_heads, p->prune_ratio)));
 }
 
 tf_status tf_decode_init(tf_ctx* ctx, const tf_params* p, const tf_decode_state* state, float tau0,
@@ -538,13 +538,12 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
     a.skip = skip;
     a.fused = fused;
     a.part = (float*)ws;
-    a.n_cu = ctx->n_cu;
     // each slice at least one pass of keys, and no more slices than the workspace holds with their tickets
     const bool bf16 = p->dtype != TF_F32;
     const size_t rows = (size_t)p->batch * p->n_q_heads;
     const int room = (int)std::min<size_t>(tf::kDecodeMaxSplit, (ws_bytes / sizeof(float) - rows) / (rows * tf::kDecodePartFloats));
     const int slice = bf16 ? tf::kDecodeSliceBf16 : tf::kDecodeSlice;
-    a.n_split = std::min({tf::decode_max_split(bf16, p->batch, p->n_q_heads, p->n_kv_heads, ctx->n_cu),
+    a.n_split = std::min({tf::decode_max_split(bf16, p->batch, p->n_q_heads, p->n_kv_heads, p->prune_ratio, ctx->n_cu),
                           (state->capacity + slice - 1) / slice, room});
     return dev(ctx, tf::launch_decode_step(a, p->dtype, q, k, v, o, (hipStream_t)stream), "decode step launch");
 }

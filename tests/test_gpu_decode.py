@@ -206,9 +206,9 @@ def test_decode_slices_follow_the_keys_held(ctx, case):
 
 @pytest.mark.parametrize("case", [(5, 4, 4), (5, 4, 2), (5, 16, 4), (9, 64, 8), (3, 6, 2), (64, 8, 2), (65, 8, 2), (8, 40, 40)])
 def test_decode_rows_that_attend_share_the_grid(ctx, case):
-    """bf16: how many slices a row is cut into depends on how many rows attend.  Rows of different length around the
-    blocks of 32 keys, all, some, one or none of them skipped: attention in 64 bits over the rows held, zero rows
-    for the others, and the caches as they were outside of the new rows."""
+    """bf16: the workgroups are dealt out to the rows that attend.  Rows of different length around the blocks of 32
+    keys, all, some, one or none of them skipped: attention in 64 bits over the rows held, zero rows for the
+    others, and the caches as they were outside of the new rows."""
     Bn, Hq, Hkv = case
     _say("decode dealt rows %s" % (case,))
     cap = 1100
@@ -245,6 +245,36 @@ def test_decode_rows_that_attend_share_the_grid(ctx, case):
                     assert torch.equal(c[b, :, n - 1], new[b])
                     c[b, :, n - 1] = old[b, :, n - 1]
             assert torch.equal(c, old)
+
+
+@pytest.mark.parametrize("case", [("bf16", 8, 32, 32), ("bf16", 5, 32, 8), ("bf16", 3, 40, 40), ("bf16", 2, 64, 8),
+                                  ("bf16", 65, 8, 2), ("f32", 4, 4, 2)])
+def test_decode_row_does_not_depend_on_the_other_rows_decisions(ctx, case):
+    """A row that attends has the same bits whether all rows of the batch attend with it, some, or none."""
+    dt, Bn, Hq, Hkv = case
+    _say("decode neighbours %s" % (case,))
+    cap, dtype = 2048, torch.float32 if dt == "f32" else torch.bfloat16
+    p = B.make_params((Bn, Hq, 1, 128), (Bn, Hkv, 1, 128), dtype, 0.5, 0)
+    buf = B.DecodeBuffers(p, cap)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    q = torch.randn((Bn, Hq, 128), device="cuda", generator=g).to(dtype)
+    k, v = (torch.randn((Bn, Hkv, 128), device="cuda", generator=g).to(dtype) for _ in range(2))
+    for c in (buf.k_cache, buf.v_cache):
+        c.copy_(torch.randn(c.shape, device="cuda", generator=g))
+    held = [max(1, cap - 333 * (b % 7)) for b in range(Bn)]
+    every = None
+    for skipped in ([], [Bn - 1], list(range(1, Bn, 2)), list(range(1, Bn)), list(range(Bn - 1))):
+        ctx.tf_decode_init(p, buf.state, 50.0)
+        buf.tau[skipped] = -50.0
+        buf.cache_len.copy_(torch.tensor([n - 1 for n in held], dtype=torch.int32))
+        buf.ws.fill_(0xFF)
+        ctx.tf_decode_step(p, 0.0, buf.state, q, k, v, buf.o, buf.skip, buf.fused, buf.ws)
+        torch.cuda.synchronize()
+        assert buf.skip.nonzero().flatten().tolist() == skipped
+        if every is None:
+            every = buf.o.clone()
+        attend = [b for b in range(Bn) if b not in skipped]
+        assert torch.equal(buf.o[attend], every[attend]), skipped
 
 
 def test_decode_step_with_eight_heads_per_kv_head(ctx):
