@@ -38,19 +38,8 @@ __device__ __forceinline__ void load8(const float* p, float* x)
     x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 // the same in two steps: the bytes, and the floats they hold
-template <typename T> struct Raw8;
-template <> struct Raw8<uint16_t> { typedef uint4 type; };
-template <> struct Raw8<float> { struct type { float4 lo, hi; }; };
-__device__ __forceinline__ void unpack8(uint4 r, float* x)
-{
-    const unsigned w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        x[2 * i] = __uint_as_float(w[i] << 16);
-        x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-}
-__device__ __forceinline__ void unpack8(const Raw8<float>::type& r, float* x)
+struct Raw8 { float4 lo, hi; };
+__device__ __forceinline__ void unpack8(const Raw8& r, float* x)
 {
     x[0] = r.lo.x; x[1] = r.lo.y; x[2] = r.lo.z; x[3] = r.lo.w;
     x[4] = r.hi.x; x[5] = r.hi.y; x[6] = r.hi.z; x[7] = r.hi.w;
@@ -412,13 +401,13 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
         for (int c = 0; c < 8; ++c) { qf[g][c] *= scale_log2e; acc[g][c] = 0.f; }
         mx[g] = kLowest; sum[g] = 0.f;
     }
-    Raw8<float>::type k_raw[4], v_raw[4];
+    Raw8 k_raw[4], v_raw[4];
     auto request = [&](int j) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int ju = min(j + 16 * u, hi - 1);  // a valid row; its score is discarded below
-            k_raw[u] = *reinterpret_cast<const Raw8<float>::type*>(kb + (long long)ju * kHeadDim);
-            v_raw[u] = *reinterpret_cast<const Raw8<float>::type*>(vb + (long long)ju * kHeadDim);
+            k_raw[u] = *reinterpret_cast<const Raw8*>(kb + (long long)ju * kHeadDim);
+            v_raw[u] = *reinterpret_cast<const Raw8*>(vb + (long long)ju * kHeadDim);
         }
     };
     // (eight heads leave no registers for keys ahead: with them one workgroup is left on a compute unit)

@@ -28,7 +28,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kR = 8;               // rows per thread per tile
 constexpr int kTile = 16 * kR;      // rows per tile
-constexpr int kOwnTotals = 4;       // segments of one tile up to which the scan adds up the totals by itself
+// segments of one tile up to which the scan adds up the totals by itself (fp32 rows have twice the bytes)
+template <typename T> constexpr int kOwnTotals = sizeof(T) == 2 ? 4 : 2;
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -221,7 +222,8 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
     for (int c = 0; c < 8; ++c) carry[c] = 0.f;
     if constexpr (!EMA) {
         if (!seg_tot && seg > 0) {
-            __shared__ float before[kOwnTotals - 1][16][kHeadDim], totals[kOwnTotals - 1][kHeadDim];
+            constexpr int kMost = kOwnTotals<T> - 1;
+            __shared__ float before[kMost][16][kHeadDim], totals[kMost][kHeadDim];
             auto add_up = [&](auto count) {
                 constexpr int N = decltype(count)::value;   // segments before this one, a tile each
                 Row8<T> rows[N][kR];
@@ -241,10 +243,14 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
                     for (int c = 0; c < 8; ++c) before[s][rg][8 * l + c] = acc[c];
                 }
             };
-            static_assert(kOwnTotals == 4, "one case each");
-            if (seg == 1) add_up(std::integral_constant<int, 1>());
-            else if (seg == 2) add_up(std::integral_constant<int, 2>());
-            else add_up(std::integral_constant<int, 3>());
+            static_assert(kMost == 1 || kMost == 3, "one case each");
+            if constexpr (kMost == 1) {
+                add_up(std::integral_constant<int, 1>());
+            } else {
+                if (seg == 1) add_up(std::integral_constant<int, 1>());
+                else if (seg == 2) add_up(std::integral_constant<int, 2>());
+                else add_up(std::integral_constant<int, 3>());
+            }
             __syncthreads();
             for (int i = tid; i < seg * kHeadDim; i += kThreads) {
                 float sum = 0.f;
@@ -520,7 +526,7 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
     // A short row's segments of one tile add up the tiles before theirs by themselves, with the same arithmetic: up to
     // three tiles more to load at once cost less than a launch for the totals (bf16, 64 chains x 333 rows: 3.0 and 5.6
     // us -> 6.4; fp32, twice the bytes, x 512 with three tiles: 4.0 and 7.9 -> 12.8).
-    const bool own_totals = p.nseg <= (sizeof(T) == 2 ? kOwnTotals : 2) && p.seg_len == kTile;
+    const bool own_totals = p.nseg <= kOwnTotals<T> && p.seg_len == kTile;
     if (own_totals) seg_tot = nullptr;
     else if (p.nseg > 1) {
         segment_totals_kernel<T><<<dim3(chains * (p.nseg - 1)), dim3(kThreads), 0, s>>>(
