@@ -893,8 +893,11 @@ int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
         if (attending == B || (attending == B - 1 && caches > n_cu)) return decode_slices(caches, n_cu);
         return std::min(kDecodeMaxSplit, std::max(1, n_cu / caches));
     }
-    // as many workgroups as are resident at once: four on a compute unit, two where they take four or eight heads (8 x 32 /
-    // 8 heads x 4000 41 -> 34 us, 1 x 64 / 16 x 4000 35 -> 23, against 1024 workgroups for these too)
+    // fp32: two workgroups a compute unit where they take four or eight heads, as many as are resident at once (224 and 249
+    // registers); four where they take one or two, which is more than the three and two that are (164 and 186): many rows
+    // gain from it what they lose in rounds, few do not (16 steps with half of the rows skipped, one / two / three / four a
+    // compute unit: 8 x 40 / 40 heads x 2000 keys 1270, 1215, 1134, 1120 us; 8 x 32 / 32 x 1000 451, 489, 502, 482; 1 x 32 /
+    // 32 x 4000 296, 299, 303, 319; 1 x 32 / 16 x 6000 249, 253, 294, 315; 4 x 32 / 8 x 2000 with one and two 274, 283).
     return std::min(kDecodeMaxSplit, std::max(1, ((g >= 4 ? 2 : 4) * n_cu + rows - 1) / rows));
 }
 

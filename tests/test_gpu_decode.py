@@ -279,7 +279,7 @@ def test_decode_row_does_not_depend_on_the_other_rows_decisions(ctx, case):
 
 def test_decode_step_with_eight_heads_per_kv_head(ctx):
     """Eight query heads read a cache once: 8 rows of 64 / 8 heads x 4000 keys take no longer than of 64 / 16 heads, twice
-    the caches (46 and 59 us a step; 80 with the registers of one workgroup on a compute unit)."""
+    the caches (34 and 49 us a step; 80 with one workgroup on a compute unit)."""
     _say("decode eight heads, time")
     us = {}
     for hkv in (8, 16):
@@ -303,8 +303,8 @@ def test_decode_step_with_eight_heads_per_kv_head(ctx):
 
 
 def test_decode_step_does_not_pay_for_empty_slices(ctx):
-    """The first tokens of a sequence take about as long in a cache of 32768 rows as in one of 1024 (10.3 and 8.9
-    us a step; 20.8 and 12.2 with every slice that the cache has room for)."""
+    """The first tokens of a sequence take about as long in a cache of 32768 rows as in one of 1024 (7.3 us a
+    step in both; 20.8 and 12.2 with every slice that the cache has room for)."""
     _say("decode empty slices")
     us = {}
     for cap in (1024, 32768):

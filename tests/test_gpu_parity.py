@@ -641,15 +641,17 @@ def test_attend_tiles_of_128(ctx, shape):
     (8, 32, 8, 249, False),     # one such tile a group
     (8, 32, 32, 600, False),    # tiles of 256, one by one, an odd number of them
     (2, 40, 8, 1025, False),    # the same with a last tile of one row
-    (8, 40, 40, 127, False),    # half a tile a group: tiles of 128
+    (8, 40, 40, 127, False),    # half a tile a group: tiles of 128 by four waves, one key tile or two
+    (2, 40, 40, 700, False),    # tiles of 128 by four waves, up to eleven key tiles
     (8, 32, 32, 300, True),     # pairs, rows of different length, one of them empty
-    (4, 12, 4, 385, True),      # tiles of 128, ditto
+    (4, 12, 4, 385, True),      # tiles of 128 by eight waves, ditto
+    (3, 24, 24, 700, True),     # tiles of 128 by four waves, ditto
 ])
 @pytest.mark.parametrize("course", ["level", "rising", "leap"])
 def test_attend_many_groups_as_a_few_of_them(ctx, shape, course):
     """Which tile size and order of tiles a call gets depends on how much there is to do: groups of
-    a large call against the same groups in a call of their own, which gets tiles of 128 (compared with
-    the oracle by the other tests) and with the oracle.  A query's arithmetic is the same in every plan, so
+    a large call against the same groups in a call of their own, which gets tiles of 128 by eight waves (compared
+    with the oracle by the other tests) and with the oracle.  A query's arithmetic is the same in every plan, so
     the rows are equal bit for bit, also where logits outgrow the softmax reference ("rising") and where
     they leap by more than fp32 holds (a factor of 2^190 from one key to the next) and a tile is done again."""
     b, hq, hkv, m, ragged = shape
@@ -696,6 +698,36 @@ def test_attend_many_groups_as_a_few_of_them(ctx, shape, course):
                     ref = oracle.attend(q[row:row + 1, h * r:(h + 1) * r].cpu(), k[row:row + 1, h:h + 1].cpu(), v[row:row + 1, h:h + 1].cpu(), kept)
                     for x in (part, got):
                         assert np.abs(x.cpu().numpy() - ref).max() <= ATTN_TOL[q.dtype]
+
+
+@pytest.mark.parametrize("b,m", [(8, 1), (8, 33), (8, 65), (8, 97), (8, 128), (4, 257), (3, 289), (3, 384), (2, 513), (2, 577)])
+@pytest.mark.parametrize("course", ["rise", "jump", "fall", "saw"])
+def test_attend_four_waves_at_block_borders(ctx, b, m, course):
+    """The inputs of test_attend_softmax_reference_at_block_borders in calls of 40 heads a row, which get tiles of 128 by
+    four waves: the same bits as two heads of a row in a call of their own, which that test compares with the oracle."""
+    _say("attend four waves b=%d m=%d %s" % (b, m, course))
+    n, hq = m + 7, 40
+    g = torch.Generator(device="cuda").manual_seed(600 + m)
+    q, k, v = (torch.randn(b, h, n, 128, device="cuda", generator=g) for h in (hq, 1, 1))
+    x = torch.arange(m, device="cuda") / max(m - 1, 1)
+    c = {"rise": 3 * x, "jump": 3 * (x > 0.5).float(), "fall": 3 * (1 - x), "saw": 3 * ((5 * x) % 1.0)}[course]
+    k *= 0.05
+    k[:, 0, 3:3 + m] += 2.0 * c[:, None]
+    q, k, v = (q * 0.05 + 2.0).bfloat16(), k.bfloat16(), v.bfloat16()
+    idx = torch.arange(3, 3 + m, device="cuda", dtype=torch.int32).repeat(b, 1)
+
+    def attend(rows, heads):
+        qq, kk, vv = q[rows, :heads].contiguous(), k[rows].contiguous(), v[rows].contiguous()
+        p = B.make_params(tuple(qq.shape), tuple(kk.shape), q.dtype, 0.0)
+        O = torch.full_like(qq, float("nan"))
+        ctx.tf_attend(p, qq, kk, vv, idx[rows].contiguous(), m, O, B.Buffers(p, "cuda:0").ws)
+        torch.cuda.synchronize()
+        return O
+
+    whole = attend(slice(0, b), hq)
+    assert torch.isfinite(whole).all()
+    for row in range(b):
+        assert torch.equal(whole[row:row + 1, :2], attend(slice(row, row + 1), 2))
 
 
 def test_attend_late_keys_leave_earlier_queries_alone(ctx):
