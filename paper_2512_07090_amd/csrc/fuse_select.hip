@@ -56,22 +56,19 @@ __global__ __launch_bounds__(kFuseThreads) void fuse_kernel(const float* __restr
     float* cv = stage + (size_t)H * kFuseTokens;
     const int b = blockIdx.y;
     const int tok = threadIdx.x & (kFuseTokens - 1);
-    const int hg = threadIdx.x / kFuseTokens;
+    const int hg = __builtin_amdgcn_readfirstlane(threadIdx.x / kFuseTokens);   // a wave each
     const int t = blockIdx.x * kFuseTokens + tok;
     if (t < n) {
         // key-only / value-only scores read one tensor's cosines (the other was not computed)
         const float* pk = (mode == 3 ? sim_v : sim_k) + (long long)b * H * n + t;
         const float* pv = (mode == 2 ? sim_k : sim_v) + (long long)b * H * n + t;
-        // eight heads of each tensor under way at a time (past the last head: that one again)
+        // eight heads of each tensor under way at a time
         constexpr int kStep = kFuseThreads / kFuseTokens, kBatch = 8;
         for (int h0 = hg; h0 < H; h0 += kStep * kBatch) {
             float k[kBatch], v[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const long long at = (long long)min(h0 + u * kStep, H - 1) * n;
-                k[u] = pk[at];
-                v[u] = pv[at];
-            }
+            for (int u = 0; u < kBatch; ++u)
+                if (const int h = h0 + u * kStep; h < H) { k[u] = pk[(long long)h * n]; v[u] = pv[(long long)h * n]; }
 #pragma unroll
             for (int u = 0; u < kBatch; ++u)
                 if (const int h = h0 + u * kStep; h < H) { ck[h * kFuseTokens + tok] = k[u]; cv[h * kFuseTokens + tok] = v[u]; }
@@ -314,11 +311,12 @@ __global__ __launch_bounds__(kSelThreads) void select_compact_kernel(
         constexpr int kEach = kFuseFloats / kSelThreads;   // all of a thread's loads under way at once
         float k[kEach], v[kEach];
 #pragma unroll
-        for (int u = 0; u < kEach; ++u) {
-            const int i = min(u * kSelThreads + tid, H * n - 1);
-            k[u] = pk[i];
-            v[u] = pv[i];
-        }
+        for (int u = 0; u < kEach; ++u)
+            if (u * kSelThreads < H * n) {   // (uniform)
+                const int i = min(u * kSelThreads + tid, H * n - 1);
+                k[u] = pk[i];
+                v[u] = pv[i];
+            }
 #pragma unroll
         for (int u = 0; u < kEach; ++u)
             if (const int i = u * kSelThreads + tid; i < H * n) { cos_k[i] = k[u]; cos_v[i] = v[u]; }
