@@ -264,16 +264,17 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
                 for (int c = 0; c < 8; ++c) carry[c] += totals[s][8 * l + c];
         }
     }
-    // (the totals of eight segments under way at once; past the last one, that one again)
+    // (the totals of eight segments under way at once)
     constexpr int kTotals = 8;
     for (int s0 = 0; !EMA && seg_tot && s0 < seg; s0 += kTotals) {
         float4 a[kTotals], b[kTotals];
 #pragma unroll
-        for (int u = 0; u < kTotals; ++u) {
-            const float* p = seg_tot + ((long long)chain * nseg + min(s0 + u, seg - 1)) * kHeadDim + 8 * l;
-            a[u] = *reinterpret_cast<const float4*>(p);
-            b[u] = *reinterpret_cast<const float4*>(p + 4);
-        }
+        for (int u = 0; u < kTotals; ++u)
+            if (s0 + u < seg) {   // (uniform)
+                const float* p = seg_tot + ((long long)chain * nseg + s0 + u) * kHeadDim + 8 * l;
+                a[u] = *reinterpret_cast<const float4*>(p);
+                b[u] = *reinterpret_cast<const float4*>(p + 4);
+            }
 #pragma unroll
         for (int u = 0; u < kTotals; ++u)
             if (s0 + u < seg) {
