@@ -189,7 +189,9 @@ __global__ __launch_bounds__(kThreads) void segment_totals_kernel(
 // first_tensor: 0 to walk K and V, or, with a single tensor (key-only / value-only scores),
 // the tensor to walk (0 = K, 1 = V).
 // STREAM: see load_tile (chosen by the host from the size of K and V).
-template <typename T, bool EMA, bool INCL, bool STREAM>
+// OWN: the totals before a segment are made here, from the tiles themselves (an instance of its own: within the
+// others its registers and LDS cost long fp32 rows 2 to 3 %).
+template <typename T, bool EMA, bool INCL, bool STREAM, bool OWN>
 __global__ __launch_bounds__(kThreads) void scan_score_kernel(
     const T* __restrict__ K, const T* __restrict__ V, long long s_b, long long s_h, long long s_t,
     int BH, int Hkv, int n, int nseg, int seg_len, const float* __restrict__ seg_tot,
@@ -220,8 +222,8 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
     float carry[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) carry[c] = 0.f;
-    if constexpr (!EMA) {
-        if (!seg_tot && seg > 0) {
+    if constexpr (OWN) {
+        if (seg > 0) {
             constexpr int kMost = kOwnTotals<T> - 1;
             __shared__ float before[kMost][16][kHeadDim], totals[kMost][kHeadDim];
             auto add_up = [&](auto count) {
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(kThreads) void scan_score_kernel(
     }
     // (the totals of eight segments under way at once)
     constexpr int kTotals = 8;
-    for (int s0 = 0; !EMA && seg_tot && s0 < seg; s0 += kTotals) {
+    for (int s0 = 0; !EMA && !OWN && s0 < seg; s0 += kTotals) {
         float4 a[kTotals], b[kTotals];
 #pragma unroll
         for (int u = 0; u < kTotals; ++u)
@@ -479,12 +481,14 @@ static int ema_warm_rows(float gamma)
 }
 
 template <typename T, bool EMA, bool INCL, typename... Args>
-static void launch_scan(bool stream_loads, int grid, hipStream_t s, Args... args)
+static void launch_scan(bool stream_loads, bool own_totals, int grid, hipStream_t s, Args... args)
 {
     if (stream_loads)
-        scan_score_kernel<T, EMA, INCL, true><<<dim3(grid), dim3(kThreads), 0, s>>>(args...);
+        scan_score_kernel<T, EMA, INCL, true, false><<<dim3(grid), dim3(kThreads), 0, s>>>(args...);
+    else if (EMA || !own_totals)
+        scan_score_kernel<T, EMA, INCL, false, false><<<dim3(grid), dim3(kThreads), 0, s>>>(args...);
     else
-        scan_score_kernel<T, EMA, INCL, false><<<dim3(grid), dim3(kThreads), 0, s>>>(args...);
+        scan_score_kernel<T, EMA, INCL, false, !EMA><<<dim3(grid), dim3(kThreads), 0, s>>>(args...);
 }
 
 template <typename T>
@@ -515,31 +519,33 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
             p = ScorePlan{(tiles + tiles_per_seg - 1) / tiles_per_seg, tiles_per_seg * kTile};
         }
         if (inclusive)
-            launch_scan<T, true, true>(stream_loads, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2],
+            launch_scan<T, true, true>(stream_loads, false, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2],
                                        BH, d.Hkv, d.n, p.nseg, p.seg_len, seg_tot, sim_k, sim_v,
                                        first_tensor, gamma, warm);
         else
-            launch_scan<T, true, false>(stream_loads, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2],
+            launch_scan<T, true, false>(stream_loads, false, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2],
                                         BH, d.Hkv, d.n, p.nseg, p.seg_len, seg_tot, sim_k, sim_v,
                                         first_tensor, gamma, warm);
         return hipGetLastError();
     }
     // A short row's segments of one tile add up the tiles before theirs by themselves, with the same arithmetic: up to
-    // three tiles more to load at once cost less than a launch for the totals (bf16, 64 chains x 333 rows: 3.0 and 5.6
-    // us -> 6.4; fp32, twice the bytes, x 512 with three tiles: 4.0 and 7.9 -> 12.8).
-    const bool own_totals = p.nseg <= kOwnTotals<T> && p.seg_len == kTile;
-    if (own_totals) seg_tot = nullptr;
-    else if (p.nseg > 1) {
+    // two tiles more to load at once cost less than a launch for the totals (whole calls: bf16, 120 chains x 333 rows
+    // 12.2 -> 10.4 us; fp32, twice the bytes, a kernel of 12.8 against two of 4.0 and 7.9 from three tiles on).  Three more
+    // do while no two workgroups share a compute unit (64 chains x 500 rows 10.4 -> 9.8; 80 chains 11.8 and 13.1,
+    // 128 12.5 and 14.6).
+    const bool own_totals = !stream_loads && p.nseg > 1 && p.nseg <= kOwnTotals<T> && p.seg_len == kTile &&
+                            (p.nseg <= 3 || chains * p.nseg <= n_cu);
+    if (p.nseg > 1 && !own_totals) {
         segment_totals_kernel<T><<<dim3(chains * (p.nseg - 1)), dim3(kThreads), 0, s>>>(
             K, V, d.kvs[0], d.kvs[1], d.kvs[2], BH, d.Hkv, d.n, p.nseg, p.seg_len, seg_tot,
             first_tensor);
     }
     if (inclusive)
-        launch_scan<T, false, true>(stream_loads, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2], BH,
+        launch_scan<T, false, true>(stream_loads, own_totals, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2], BH,
                                     d.Hkv, d.n, p.nseg, p.seg_len, seg_tot, sim_k, sim_v, first_tensor,
                                     0.f, 0);
     else
-        launch_scan<T, false, false>(stream_loads, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2], BH,
+        launch_scan<T, false, false>(stream_loads, own_totals, chains * p.nseg, s, K, V, d.kvs[0], d.kvs[1], d.kvs[2], BH,
                                      d.Hkv, d.n, p.nseg, p.seg_len, seg_tot, sim_k, sim_v, first_tensor,
                                      0.f, 0);
     return hipGetLastError();
