@@ -296,10 +296,10 @@ __device__ __forceinline__ Float2 get_shared(const float* p)
 }
 
 // Behind a slice's partial result, which the workgroup has just written: the workgroup that draws the last ticket merges
-// the `used` slices of its G heads into the output rows.
-template <typename T, int G>
+// the `used` slices of its heads into the output rows.
+template <typename T>
 __device__ __forceinline__ void merge_slices(float* part0, T* out, float (*weight)[kDecodeMaxSplit + 1], int* drawn,
-                                             int32_t* ticket, int used, int n_split)
+                                             int32_t* ticket, int heads, int used, int n_split)
 {
     // every partial result of this workgroup is in memory before its ticket is drawn
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -311,46 +311,49 @@ __device__ __forceinline__ void merge_slices(float* part0, T* out, float (*weigh
     // Numerators of the first kBatch slices of this thread's two columns, requested before their weights are known
     // (16 slices at a time, one column a thread: eight round trips to memory in a row with 64 slices of four heads).
     // The last ones of a batch repeat a slice with weight 0.
-    constexpr int kBatch = 32;
-    const int pairs = G * kHeadDim / 2;
-    Float2 x[kBatch];
-    auto fetch = [&](int i, int l) {
-        const float* pr = part0 + (long long)(i / (kHeadDim / 2)) * n_split * kPartStride + 2 * (i % (kHeadDim / 2));
+    const int pairs = heads * kHeadDim / 2;
+    auto merge = [&](auto batch) {
+        constexpr int kBatch = decltype(batch)::value;
+        Float2 x[kBatch];
+        auto fetch = [&](int i, int l) {
+            const float* pr = part0 + (long long)(i / (kHeadDim / 2)) * n_split * kPartStride + 2 * (i % (kHeadDim / 2));
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) x[u] = get_shared(pr + min(l + u, used - 1) * kPartStride);
-    };
-    if ((int)threadIdx.x < pairs) fetch(threadIdx.x, 0);
-    // weights of the slices, per head, and their weighted sum behind them
-    for (int g = threadIdx.x >> 6; g < G; g += 4) {
-        const int l = threadIdx.x & 63;
-        Float2 own = {kLowest, 0.f};
-        if (l < used) own = get_shared(part0 + ((long long)g * n_split + l) * kPartStride + kHeadDim);
-        float m_all = own.x;
+            for (int u = 0; u < kBatch; ++u) x[u] = get_shared(pr + min(l + u, used - 1) * kPartStride);
+        };
+        if ((int)threadIdx.x < pairs) fetch(threadIdx.x, 0);
+        // weights of the slices, per head, and their weighted sum behind them
+        for (int g = threadIdx.x >> 6; g < heads; g += 4) {
+            const int l = threadIdx.x & 63;
+            Float2 own = {kLowest, 0.f};
+            if (l < used) own = get_shared(part0 + ((long long)g * n_split + l) * kPartStride + kHeadDim);
+            float m_all = own.x;
 #pragma unroll
-        for (int step = 1; step < 64; step *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, step));
-        const float wt = __builtin_amdgcn_exp2f(own.x - m_all);
-        float den = own.y * wt;
+            for (int step = 1; step < 64; step *= 2) m_all = fmaxf(m_all, __shfl_xor(m_all, step));
+            const float wt = __builtin_amdgcn_exp2f(own.x - m_all);
+            float den = own.y * wt;
 #pragma unroll
-        for (int step = 1; step < 64; step *= 2) den += __shfl_xor(den, step);
-        weight[g][l] = wt;   // 0 from `used` on
-        if (l == 0) weight[g][kDecodeMaxSplit] = den;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < pairs; i += 256) {
-        const int g = i / (kHeadDim / 2), c = 2 * (i % (kHeadDim / 2));
-        Float2 num = {0.f, 0.f};
-        for (int l = 0; l < used; l += kBatch) {
-            if (l > 0 || i >= 256) fetch(i, l);
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                num.x = fmaf(x[u].x, weight[g][l + u], num.x);
-                num.y = fmaf(x[u].y, weight[g][l + u], num.y);
-            }
+            for (int step = 1; step < 64; step *= 2) den += __shfl_xor(den, step);
+            weight[g][l] = wt;   // 0 from `used` on
+            if (l == 0) weight[g][kDecodeMaxSplit] = den;
         }
-        const float den = weight[g][kDecodeMaxSplit];
-        store_out(out + g * kHeadDim + c, num.x / den);
-        store_out(out + g * kHeadDim + c + 1, num.y / den);
-    }
+        __syncthreads();
+        for (int i = threadIdx.x; i < pairs; i += 256) {
+            const int g = i / (kHeadDim / 2), c = 2 * (i % (kHeadDim / 2));
+            Float2 num = {0.f, 0.f};
+            for (int l = 0; l < used; l += kBatch) {
+                if (l > 0 || i >= 256) fetch(i, l);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u) {
+                    num.x = fmaf(x[u].x, weight[g][l + u], num.x);
+                    num.y = fmaf(x[u].y, weight[g][l + u], num.y);
+                }
+            }
+            const float den = weight[g][kDecodeMaxSplit];
+            store_out(out + g * kHeadDim + c, num.x / den);
+            store_out(out + g * kHeadDim + c + 1, num.y / den);
+        }
+    };
+    merge(std::integral_constant<int, 32>());
 }
 
 // Attention of the new token over one slice of its row's cache in fp32, for the G query heads that
@@ -485,30 +488,31 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
         else if (c < kHeadDim) { store_out(out + g * kHeadDim + c, v.x / den); store_out(out + g * kHeadDim + c + 1, v.y / den); }
     }
     if (len > chunk)
-        merge_slices<float, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, n_split);
+        merge_slices<float>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], G, (len + chunk - 1) / chunk, n_split);
 }
 
 // The same for bf16 rows, on the matrix pipe; a wave takes blocks of 32 keys.
 //   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = 16 rows of K as they lie in memory, B = the queries
-//                 (column c: head c % G), so a lane has the scores of one head for eight keys.
+//                 (column c: head c % G of the group, the last one again where it has fewer than G), so a
+//                 lane has the scores of one head for eight keys.
 //   O^T += V^T P^T  A: a lane loads 8 columns of the eight keys whose weights it holds (the contraction order over keys is
 //                 the one in which they come out of the first product) and transposes them within its own
 //                 registers; the 16 columns of product i are 8 c + i.
 //   weights       stay fp32: a weight is the exact sum of three bf16 parts (8 bits of the mantissa each), and the
 //                 parts of a head's weight are columns of their own of P^T (column c: part c / G), which with one
 //                 to five heads are there anyway.  Their products with V are added up in fp32 at the end.
-// What bounds it is the way of the keys from memory, and for short rows the first loads (2 to 4 us) and the merge (6 us). In fp32
-// on the vector pipe, as above, 480 instructions a wave went into 16 keys of four heads, 2 us for 64 keys with two
-// workgroups on a compute unit.  A step with a kept token (scoring included), 1 x 32 / 8 heads x 2000, 16384 and 32768 keys:
-// 17.0, 30.6, 39.2 -> 13.8, 22.4, 31.1 us; 8 x 32 / 8 x 2048 27.3 -> 21.6; 1 x 32 / 32 x 2048 22.4 -> 16.9; 8 x 32 / 32 x 2048
-// 55 -> 49.  Distance from 64 bits as before (1.65e-3, the
-// rounding of the output).
-template <int G>
+// What bounds it is the way of the keys from memory, and for short rows the first loads (2 to 4 us) and the
+// merge (6 us).  In fp32 on the vector pipe, as above, 480 instructions a wave went into 16 keys of four heads, 2 us
+// for 64 keys with two workgroups on a compute unit.  A step with a kept token, scoring included (half of the tokens to
+// be skipped): 1 x 32 / 8 heads x 2000, 16384 and 32768 keys 16.1, 29.9, 36.8 -> 12.7, 21.4, 29.9 us; 8 x 32 / 8 x
+// 2048 26.0 -> 22.9; 1 x 32 / 32 x 2048 23.2 -> 14.8; 8 x 32 / 32 x 2048 53.9 -> 50.9, 48.0 if all rows are known
+// to attend.  Distance from 64 bits as before (1.65e-3, the rounding of the output).
+template <int G, bool FULL>
 __device__ __forceinline__ void attend_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
     float* __restrict__ part, int32_t* __restrict__ tickets, uint16_t* __restrict__ o, int B, int Hq, int Hkv,
-    int capacity, int n_split, float scale_log2e)
+    int parts, int per, int capacity, int n_split, float scale_log2e)
 {
     constexpr bool kTwice = 3 * G > 16;              // the third parts get a product of their own
     constexpr int kCols = kTwice ? 2 * G : 3 * G;    // columns of O^T in use
@@ -523,7 +527,11 @@ __device__ __forceinline__ void attend_bf16(
     // on the compute units stay empty (16 steps of 8 x 32 / 32 heads x 2048 keys with about half of the rows
     // skipped: 533 us, 506 dealt out; of 8 x 32 / 8 280 and 275).  How a row is sliced does not depend on
     // the other rows, so neither do its bits.
-    const int groups = Hq / G;   // of query heads
+    // Groups of query heads: G of them (FULL), or at most G, the heads of a KV head in `parts` groups of `per` and the last
+    // one of what is left.
+    const int groups = FULL ? Hq / G : Hkv * parts, ratio = Hq / Hkv;
+    auto first_head = [&](int hg) { return FULL ? hg * G : hg / parts * ratio + hg % parts * per; };
+    auto heads_of = [&](int hg) { return FULL ? G : min(per, ratio - hg % parts * per); };
     const bool dealt = B <= kDecodeDealt;
     const int mine = min(dealt ? lane : (int)blockIdx.x / (groups * n_split), B - 1);
     const int mine_len = cache_len[mine];
@@ -531,9 +539,10 @@ __device__ __forceinline__ void attend_bf16(
     const unsigned long long rows = __ballot(attends);
     // zero rows, by the first workgroups of the grid
     if (blockIdx.x < B * groups) {
-        const int zb = blockIdx.x / groups;
+        const int zb = blockIdx.x / groups, zg = blockIdx.x % groups;
         if (dealt ? !(rows >> zb & 1) : skip[zb] != 0)
-            for (int i = threadIdx.x; i < G * kHeadDim; i += 256) o[(long long)blockIdx.x * G * kHeadDim + i] = 0;
+            for (int i = threadIdx.x; i < heads_of(zg) * kHeadDim; i += 256)
+                o[((long long)zb * Hq + first_head(zg)) * kHeadDim + i] = 0;
     }
     if (rows == 0) return;
     const int sp = blockIdx.x % n_split;
@@ -546,7 +555,7 @@ __device__ __forceinline__ void attend_bf16(
         len = __shfl(mine_len, b);
     }
     len = __builtin_amdgcn_readfirstlane(len);
-    const int hq0 = hg * G, hk = hq0 / (Hq / Hkv);
+    const int hq0 = first_head(hg), hk = hq0 / ratio, heads = heads_of(hg);
     uint16_t* const out = o + ((long long)b * Hq + hq0) * kHeadDim;
     const long long row0 = ((long long)b * Hkv + hk) * capacity;
     const uint16_t* kb = k_cache + row0 * kHeadDim + 8 * g4;
@@ -578,7 +587,7 @@ __device__ __forceinline__ void attend_bf16(
     bf16x8 qf[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-        qf[s] = *reinterpret_cast<const bf16x8*>(q + ((long long)b * Hq + hq0 + c16 % G) * kHeadDim + 32 * s + 8 * g4);
+        qf[s] = *reinterpret_cast<const bf16x8*>(q + ((long long)b * Hq + hq0 + (FULL ? c16 % G : min(c16 % G, heads - 1))) * kHeadDim + 32 * s + 8 * g4);
     f32x4 acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -652,7 +661,7 @@ __device__ __forceinline__ void attend_bf16(
     float* const part0 = part + ((long long)b * Hq + hq0) * n_split * kPartStride;   // [head][slice]
     constexpr int kPairs = kPartStride / 2;   // the last one: running max, sum
     auto combine = [&](auto n_waves) {
-        for (int i = threadIdx.x; i < G * kPairs; i += 256) {
+        for (int i = threadIdx.x; i < heads * kPairs; i += 256) {
             const int g = i / kPairs, c = 2 * (i - g * kPairs);
             float m_all = kLowest;
 #pragma unroll
@@ -682,7 +691,7 @@ __device__ __forceinline__ void attend_bf16(
     if (hi - lo <= 32) combine(std::integral_constant<int, 1>());
     else combine(std::integral_constant<int, 4>());
     if (len > chunk)
-        merge_slices<uint16_t, G>(part0, out, weight, &drawn, &tickets[b * (Hq / G) + hg], (len + chunk - 1) / chunk, n_split);
+        merge_slices<uint16_t>(part0, out, weight, &drawn, &tickets[b * groups + hg], heads, (len + chunk - 1) / chunk, n_split);
 }
 
 struct AttendArgs {
@@ -692,14 +701,14 @@ struct AttendArgs {
     float* part;
     int32_t* tickets;
     uint16_t* o;
-    int B, Hq, Hkv, capacity, n_split;
+    int B, Hq, Hkv, parts, per, capacity, n_split;
     float scale_log2e;
 };
-template <int G>
+template <int G, bool FULL>
 __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(const AttendArgs a)
 {
-    attend_bf16<G>(a.q, a.k_cache, a.v_cache, a.cache_len, a.skip, a.part, a.tickets, a.o, a.B, a.Hq, a.Hkv, a.capacity,
-                   a.n_split, a.scale_log2e);
+    attend_bf16<G, FULL>(a.q, a.k_cache, a.v_cache, a.cache_len, a.skip, a.part, a.tickets, a.o, a.B, a.Hq, a.Hkv, a.parts,
+                   a.per, a.capacity, a.n_split, a.scale_log2e);
 }
 
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
@@ -818,23 +827,23 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
                                 hipStream_t s)
 {
     const int threads = std::min(1024, (32 * a.Hkv + 63) / 64 * 64);  // 16 lanes per (tensor, head)
-    const int g = decode_heads_per_wg(a.B, a.Hq, a.Hkv);
+    const int g = decode_heads_per_wg(sizeof(T) == 2, a.B, a.Hq, a.Hkv);
+    const int ratio = a.Hq / a.Hkv, parts = (ratio + g - 1) / g, groups = a.Hkv * parts;
     // tickets of the attention's workgroups behind the partial results
     int32_t* const tickets = (int32_t*)(a.part + (size_t)a.B * a.Hq * a.n_split * kDecodePartFloats);
     decode_score_kernel<T><<<dim3(a.B), dim3(threads), 0, s>>>(ScoreArgs<T>{
         k, v, a.anchor_k, a.anchor_v, a.seen, a.skipped, a.tau, a.cache_len, a.overflow,
         (T*)a.k_cache, (T*)a.v_cache, a.capacity, a.Hkv, a.ema, a.gamma, a.inclusive, a.fusion, a.warmup,
-        a.target, a.eta, a.skip, a.fused, tickets, a.n_split > 1 ? a.Hq / g : 0});
+        a.target, a.eta, a.skip, a.fused, tickets, a.n_split > 1 ? groups : 0});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float sl2 = a.scale * 1.4426950408889634f;
-    const int groups = a.Hq / g;
-#define TF_DECODE_ATTEND(G)                                                                       \
+#define TF_DECODE_ATTEND(G, FULL)                                                                 \
     do {                                                                                          \
         if constexpr (sizeof(T) == 2)                                                             \
-            decode_attend_bf16_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                        \
-                AttendArgs{q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv, a.capacity, \
-                           a.n_split, sl2});                                                      \
+            decode_attend_bf16_kernel<G, FULL><<<dim3(grid), dim3(256), 0, s>>>(                  \
+                AttendArgs{q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv, parts,     \
+                           (ratio + parts - 1) / parts, a.capacity, a.n_split, sl2});             \
         else                                                                                      \
             decode_attend_f32_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                         \
                 q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, a.Hkv,        \
@@ -842,34 +851,41 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
     } while (0)
     const T *k_cache = (const T*)a.k_cache, *v_cache = (const T*)a.v_cache;
     const int grid = a.B * groups * a.n_split;
-    if (g == 8) TF_DECODE_ATTEND(8);
-    else if (g == 4) TF_DECODE_ATTEND(4);
-    else if (g == 2) TF_DECODE_ATTEND(2);
-    else TF_DECODE_ATTEND(1);
+    if (ratio % g != 0) {   // bf16: some workgroups have fewer heads
+        if (g == 8) TF_DECODE_ATTEND(8, false);
+        else TF_DECODE_ATTEND(4, false);
+    } else if (g == 8) TF_DECODE_ATTEND(8, true);
+    else if (g == 4) TF_DECODE_ATTEND(4, true);
+    else if (g == 2) TF_DECODE_ATTEND(2, true);
+    else TF_DECODE_ATTEND(1, true);
 #undef TF_DECODE_ATTEND
     return hipGetLastError();
 }
 
 }  // namespace
 
-int decode_heads_per_wg(int B, int Hq, int Hkv)
+int decode_heads_per_wg(bool bf16, int B, int Hq, int Hkv)
 {
-    const int group = Hq / Hkv;
-    // Where few caches are read, eight heads are better shared out to two workgroups that read them twice: the slices of
-    // four are merged in half the time (a step of 1 row of 16 / 2 heads x 16384 keys: 20.8 us with eight heads, 18.0
-    // with four; 1 x 64 / 8 x 4000: 18.5 and 16.6; fp32 16 x 64 / 8 x 4000 112 and 161).
-    if (group == 8) return B * Hkv < 48 ? 4 : 8;
-    return group == 2 || group == 4 ? group : 1;  // other ratios: one query head per workgroup
+    const int ratio = Hq / Hkv;
+    // Heads that share a KV head share workgroups, whatever their number: one by one each reads the cache for itself (a
+    // step of 1 x 128 / 8 heads x 5000 keys: 33.6 us, 16.8 by fours; 8 x 40 / 8 x 2000: 55 and 23; 4 x 71 / 1 x 2000: 37
+    // and 20; below some 500 keys one by one is up to 0.5 us faster).  More than four go by eights, but by
+    // fours where few caches are read: the slices of four are merged in half the time (1 x 16 / 2 x 16384: 20.2
+    // by eights, 17.7 by fours; 1 x 64 / 8 x 4000: 17.6 and 15.9; 8 x 28 / 4 x 2000: 20.0 and 18.4; but 8 x 64 / 8 x
+    // 4000: 33.8 and 48.5; 16 x 48 / 8 x 2000: 32.6 and 48; fp32 16 x 64 / 8 x 4000: 108 and 159).
+    if (bf16 && ratio > 2) return ratio <= 4 || B * Hkv < 48 ? 4 : 8;
+    if (ratio == 8) return B * Hkv < 48 ? 4 : 8;
+    return ratio == 2 || ratio == 4 ? ratio : 1;   // (fp32, other ratios: one by one)
 }
 
 // Slices of each of `rows` caches that a step reads.
 static int decode_slices(int rows, int n_cu)
 {
     // One workgroup on a compute unit has enough keys under way, and a merge of more slices costs more than more
-    // workgroups bring (a step of 1 x 32 / 8 heads x 16384: 25.7 us with 512, 22.3 with 256; 1 x 32 / 32 x 2048: 22.0,
-    // 19.6 and 18.3 with 1024, 512 and 256; 8 x 32 / 32 x 256: 21.7, 18.5 and 16).  Where rows do not fill whole
-    // rounds of the compute units, the fewest slices that come within a tenth of even shares, in up to four
-    // rounds (8 x 40 / 40 x 2048, 320 rows: 96 us with 320 workgroups, 80 with 640, 72.5 with 960).
+    // workgroups bring (a step of 1 x 32 / 8 heads x 16384 keys: 24.9 us with 512, 21.5 with 256; 1 x 32 / 32 x 2048:
+    // 18.9, 16.0 and 15.2 with 1024, 512 and 256; 8 x 32 / 32 x 256: 19.0, 15.1 and 13.0).  Where rows do not fill
+    // whole rounds of the compute units, the fewest slices that come within a tenth of even shares, in up to
+    // four rounds (8 x 40 / 40 x 2048, 320 rows: 73.7 us with 320 workgroups, 68.1 with 640, 65.1 with 960).
     const int most = std::min(kDecodeMaxSplit, 4 * n_cu / rows);
     int split = std::min(kDecodeMaxSplit, std::max(1, n_cu / rows));
     int busiest = (rows * split + n_cu - 1) / n_cu;   // workgroups of the busiest compute unit
@@ -882,14 +898,14 @@ static int decode_slices(int rows, int n_cu)
 
 int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
 {
-    const int g = decode_heads_per_wg(B, Hq, Hkv), rows = B * (Hq / g);
+    const int g = decode_heads_per_wg(bf16, B, Hq, Hkv), groups = Hkv * ((Hq / Hkv + g - 1) / g), rows = B * groups;
     if (bf16) {
         // By the batch rows that attend on average: by those that do attend in a step, a row's rounding would depend on its
         // neighbours.  Where the number varies from step to step whole rounds are not worth more slices (16 steps of 8 x
         // 40 / 40 x 2048, half of the rows skipped: 586 us with one slice, 618 with three; 8 x 32 / 32 x 2048, a quarter:
         // 600 with one, 687 with four; 16 x 32 / 32 x 1024, a quarter: 628 with one, 681 with two), but they are
         // where only one row now and then leaves a second round (8 x 40 / 40 x 2048, a tenth: 1052 and 961).
-        const int attending = std::max(1, (int)lround(B * (1.0 - target))), caches = attending * (Hq / g);
+        const int attending = std::max(1, (int)lround(B * (1.0 - target))), caches = attending * groups;
         if (attending == B || (attending == B - 1 && caches > n_cu)) return decode_slices(caches, n_cu);
         return std::min(kDecodeMaxSplit, std::max(1, n_cu / caches));
     }

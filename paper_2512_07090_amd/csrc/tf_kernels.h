@@ -87,7 +87,7 @@ struct DecodeArgs {
     float* part;                                    // scratch [B][Hq][n_split][kDecodePartFloats], tickets
     int n_split;                                    // 1 .. decode_max_split()
 };
-int decode_heads_per_wg(int B, int Hq, int Hkv);           // query heads one workgroup handles (they share a KV head)
+int decode_heads_per_wg(bool bf16, int B, int Hq, int Hkv);   // query heads one workgroup handles at most (they share a KV head)
 // target: share of the tokens to be skipped; n_cu: compute units (workspaces are sized for 256)
 int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu = 256);
 size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv, double target);

@@ -247,6 +247,41 @@ def test_decode_rows_that_attend_share_the_grid(ctx, case):
             assert torch.equal(c, old)
 
 
+@pytest.mark.parametrize("case", [   # batch, query heads, KV heads: by fours, by eights (from 48 caches on)
+    (2, 5, 1), (3, 14, 2), (1, 71, 1), (2, 18, 2), (4, 16, 1), (48, 5, 1), (25, 14, 2), (48, 13, 1), (24, 18, 2), (48, 3, 1)])
+def test_decode_any_number_of_heads_per_kv_head(ctx, case):
+    """bf16: heads that share a KV head share workgroups, of which the last may have fewer.  Every head's attention in 64
+    bits over the rows held, in one and in several slices, and zero rows of skipped tokens."""
+    Bn, Hq, Hkv = case
+    _say("decode heads %s" % (case,))
+    cap = 900
+    p = B.make_params((Bn, Hq, 1, 128), (Bn, Hkv, 1, 128), torch.bfloat16, 0.5, 0)
+    buf = B.DecodeBuffers(p, cap)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    q, k, v = (torch.randn((Bn, h, 128), device="cuda", generator=g).bfloat16() for h in (Hq, Hkv, Hkv))
+    for c in (buf.k_cache, buf.v_cache):
+        c.copy_(torch.randn(c.shape, device="cuda", generator=g))
+    held = [(900, 1, 128, 129, 33, 640)[b % 6] for b in range(Bn)]
+    skipped = list(range(4, Bn, 5))
+    ctx.tf_decode_init(p, buf.state, 50.0)
+    buf.tau[skipped] = -50.0
+    buf.cache_len.copy_(torch.tensor([n - 1 for n in held], dtype=torch.int32))
+    buf.ws.fill_(0xFF)
+    buf.o.fill_(float("nan"))
+    ctx.tf_decode_step(p, 0.0, buf.state, q, k, v, buf.o, buf.skip, buf.fused, buf.ws)
+    torch.cuda.synchronize()
+    assert buf.skip.nonzero().flatten().tolist() == skipped
+    for b, n in enumerate(held):
+        if b in skipped:
+            assert not buf.o[b].any()
+            continue
+        kk, vv = (c[b, :, :n].double().repeat_interleave(Hq // Hkv, 0) for c in (buf.k_cache, buf.v_cache))
+        w = torch.softmax((kk * q[b].double()[:, None]).sum(2) / 128 ** 0.5, 1)
+        out = (w[:, :, None] * vv).sum(1)
+        # fp32 weights: what is left is the output's rounding, half a unit of bf16
+        assert ((buf.o[b].double() - out).abs() <= 2.0 ** -8 * out.abs() + 1e-5).all(), (b, n)
+
+
 @pytest.mark.parametrize("case", [("bf16", 8, 32, 32), ("bf16", 5, 32, 8), ("bf16", 3, 40, 40), ("bf16", 2, 64, 8),
                                   ("bf16", 65, 8, 2), ("f32", 4, 4, 2)])
 def test_decode_row_does_not_depend_on_the_other_rows_decisions(ctx, case):
