@@ -3,9 +3,9 @@
 // queries and keys are the kept tokens, addressed through kept_idx, so "causal" means key rank
 // <= query rank in the compacted order).
 //
-// Flash-style kernel for gfx950.  One work item covers 256 (eight waves of two blocks of 16: NW = 8, QB = 2) or 128 (QB = 1,
-// or NW = 4) kept queries, two waves per SIMD with 256 registers each.  It walks the key tiles (64 kept keys) once, K and V rows
-// gathered through kept_idx into LDS (two stages each).
+// Flash-style kernel for gfx950.  One work item covers 256 (eight waves of two blocks of 16: NW = 8, QB = 2)
+// or 128 (QB = 1, or NW = 4) kept queries, two waves per SIMD with 256 registers each.  It walks the key
+// tiles (64 kept keys) once, K and V rows gathered through kept_idx into LDS (two stages each).
 //   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = K rows from LDS, B = Q fragments held in
 //                 registers for the whole item.  The transposed product puts one query per
 //                 lane column, so P^T goes from the accumulators to the next product's operand
@@ -38,10 +38,10 @@
 //                 0.299 instead of 0.282 ms at 8 x 32 heads x 2048 kept on all-zero inputs).
 //   zero rows     The rows of the filtered positions between a query and the next kept token
 //                 are written as zeros together with the query's row (kept_idx is ascending).
-//   small calls   Eight waves of 16 queries take a key tile in about the time of four waves of 32 (1.1 us; they read twice
-//                 the operands from LDS) and share an item's first loads and output rows, which is most of a short
-//                 item: 1 x 32 heads x 167 kept 11.4 -> 8.7 us, x 512 18.2 -> 15.8, x 1024 28.1 -> 24.9.  (In 128
-//                 registers, two such workgroups on a CU, they spill: 70 us.)
+//   small calls   Eight waves of 16 queries take a key tile in about the time of four waves of 32 (1.1 us;
+//                 they read twice the operands from LDS) and share an item's first loads and output rows,
+//                 which is most of a short item: 1 x 32 heads x 167 kept 11.4 -> 8.7 us, x 512 18.2 -> 15.8,
+//                 x 1024 28.1 -> 24.9.  (In 128 registers, two such workgroups on a CU, they spill: 70 us.)
 //   scheduling    One persistent workgroup of eight waves per CU (or two of four) walks a static list of pairs
 //                 of query tiles (tile p with tile n_qt - 1 - p: equal causal work) or, where there
 //                 are too few pairs to go round, of single tiles; see the kernel and plan_attend().
@@ -145,17 +145,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     constexpr int NP = 8 / NW;     // passes of the workgroup over a tile when loading it
     constexpr int WQ = 16 * QB;    // queries per wave
     constexpr int kBM = WQ * NW;   // kept queries per work item
-    // operand fragments in flight from LDS, per tensor (four waves, which hold two passes of rows: with three 24 registers
-    // are spilled, 9 with two, all of them outside the tile loop; eight waves spill none in pairs, 2 one by one; with
-    // QB = 1 four to eight are no faster than three)
+    // operand fragments in flight from LDS, per tensor (four waves, which hold two passes of rows: with three
+    // 24 registers are spilled, 9 with two, all of them outside the tile loop; eight waves spill none in
+    // pairs, 2 one by one; with QB = 1 four to eight are no faster than three)
     constexpr int kRing = NW == 8 ? 3 : 2;
     __shared__ __attribute__((aligned(16))) uint16_t smem[2 * kKTile + 2 * kVTile];
     uint16_t* const k_lds = smem;               // 2 stages of K
     uint16_t* const v_lds = smem + 2 * kKTile;  // 2 stages of V^T
-    // Eight waves: output staging of its own (141 KB of LDS in all): a wave stages and writes its rows without
-    // a workgroup barrier on either side, so the waves leave an item, and start on the next
-    // item's first loads, as each gets there.  Four waves: two workgroups share a CU's LDS (70 KB each)
-    // and overlap each other's item ends, the rows are staged over the K tiles.
+    // Tiles of 256: output staging of its own (141 KB of LDS in all): a wave stages and writes its rows
+    // without a workgroup barrier on either side, so the waves leave an item, and start on the next item's
+    // first loads, as each gets there.  Tiles of 128: the rows are staged over the K tiles, behind the tile
+    // loop's last barrier, and a barrier of its own keeps the next item's first K tile from them; four waves
+    // so that two workgroups share a CU's LDS (70 KB each) and overlap each other's item ends.
     constexpr bool kOwnStage = NW == 8 && QB == 2;
     __shared__ __attribute__((aligned(16))) uint16_t own_stage[kOwnStage ? kBM * kOStr : 8];
     uint16_t* const ostage = kOwnStage ? own_stage : k_lds;
@@ -176,10 +177,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     // K and V of the few groups it is working on.  Correctness does not depend on where a
     // workgroup really runs, only the L2 hit rate does.
     const int n_groups = d.B * d.Hq;
-    // Static schedule (SINGLES: an entry is one tile; uniform rows list the longest tiles of all groups first): workgroup j of XCD x (x = id % n_xcd, as the dispatcher deals them) walks
-    // entries j, j + W, ... of the XCD's list of (group, pair of query tiles); a pair joins
-    // query tile p with n_qt - 1 - p, so every entry is the same amount of causal work, and the
-    // workgroups that share a group start on it together and stream the same K / V tiles.
+    // Static schedule (SINGLES: an entry is one tile; uniform rows list the longest tiles of all groups
+    // first): workgroup j of XCD x (x = id % n_xcd, as the dispatcher deals them) walks entries j, j + W, ...
+    // of the XCD's list of (group, pair of query tiles); a pair joins query tile p with n_qt - 1 - p, so
+    // every entry is the same amount of causal work, and the workgroups that share a group start on it
+    // together and stream the same K / V tiles.
     const int x = blockIdx.x % n_xcd, j = blockIdx.x / n_xcd;
     const int nwx = (gridDim.x + n_xcd - 1 - x) / n_xcd;  // workgroups whose id % n_xcd is x
     const int g_lo = x * n_groups / n_xcd;
@@ -208,8 +210,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
     int rb = g_lo / d.Hq, row_e0 = 0;
     bool exact = false;  // the item is done again, see below
     for (int it = 0;; ++it) {
-    // Tiles one by one, longest first: odd rounds backwards, and of two workgroups on a compute unit the second half of
-    // them, so that a long tile goes with a short one (3 x 32 x 2048: 125 -> 115 us; four waves, 1 x 32 x 2048: 49.6 -> 46.7).
+    // Tiles one by one, longest first: odd rounds backwards, and of two workgroups on a compute unit the
+    // second half of them, so that a long tile goes with a short one (3 x 32 x 2048: 125 -> 115 us; four
+    // waves, 1 x 32 x 2048: 49.6 -> 46.7).
     const int first = NW == 8 ? (it & 1 ? 0 : nwx) : n_cu / n_xcd;
     const int e = !SINGLES ? j + (it >> 1) * nwx : it * nwx + (j < first ? j : nwx - 1 - (j - min(first, nwx)));
     int pr, bh, m, nq;
@@ -602,14 +605,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
         }                                                                                      \
     } while (0)
 
-    // Iteration kt: scores of the two blocks of K tile kt, weights of blocks 2 kt - 1 and 2 kt, products
-    // of blocks 2 kt - 2 and 2 kt - 1 with V tile kt - 1.  It writes K(kt + 1) and V(kt) to
-    // the stages that K(kt - 1) and V(kt - 2) have left; iteration n_kt only finishes.  A wave runs n_kt + 1 iterations with a barrier after each but the
-    // last, whatever it has to compute in them.
-    // Delivering K(kt + 1) requests K(kt + 2) into the same registers, V(kt) likewise V(kt + 1), with
-    // off_k and off_v; the positions of the tile after (pos_n) are requested before the rows, because
-    // loads return in order and positions behind a row that misses the L2 would hold up the
-    // next request.
+    // Iteration kt: scores of the two blocks of K tile kt, weights of blocks 2 kt - 1 and 2 kt, products of
+    // blocks 2 kt - 2 and 2 kt - 1 with V tile kt - 1.  It writes K(kt + 1) and V(kt) to the stages that K(kt
+    // - 1) and V(kt - 2) have left; iteration n_kt only finishes.  A wave runs n_kt + 1 iterations with a
+    // barrier after each but the last, whatever it has to compute in them.  Delivering K(kt + 1) requests
+    // K(kt + 2) into the same registers, V(kt) likewise V(kt + 1), with off_k and off_v; the positions of the
+    // tile after (pos_n) are requested before the rows, because loads return in order and positions behind a
+    // row that misses the L2 would hold up the next request.
 #define TF_DELIVER_K(MORE)                                                                     \
     do {                                                                                       \
         if (MORE) {                                                                            \
@@ -772,8 +774,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attend_bf16_kernel(
         const int ze = __shfl(qpos, 0);
         for (int g = ln >> 4; g < ze; g += 4) *reinterpret_cast<uint4*>(Oc + (long long)g * d.os[2]) = zero4;
     }
-    // (no barrier here: the last tile-loop iteration ended with one, after which nobody reads a
-    // tile stage, and the staging area is not shared)
+    // (no barrier here: after the one behind the tile loop nobody reads a tile stage; the staging area is not
+    // shared, or, over the K tiles, protected by the barrier before the next item's first K tile)
     }  // items
 }
 

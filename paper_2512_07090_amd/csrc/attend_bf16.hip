@@ -1,5 +1,5 @@
-// Causal softmax attention over the kept tokens, bf16 inputs: which form of the kernel (attend_bf16.h) a call gets, and its
-// launch.
+// Causal softmax attention over the kept tokens, bf16 inputs: which form of the kernel (attend_bf16.h) a call
+// gets, and its launch.
 #include "attend_bf16.h"
 #include "attend_plan.h"
 

@@ -1,5 +1,5 @@
-// Causal softmax attention over the kept tokens, bf16 inputs: tiles of 128 queries by eight waves of 16 (plan_attend() says
-// when).
+// Causal softmax attention over the kept tokens, bf16 inputs: tiles of 128 queries by eight waves of 16
+// (plan_attend() says when).
 #include "attend_bf16.h"
 
 namespace tf {

@@ -104,15 +104,14 @@ __global__ void decode_init_kernel(double* anchor_k, double* anchor_v, long long
     if (i < B) { seen[i] = 0; skipped[i] = 0; tau[i] = tau0; cache_len[i] = 0; overflow[i] = 0; }
 }
 
-// One workgroup per batch row; a 16-lane group per (tensor, KV head) pair, columns 32 i + 2 l and the next of lane l, so
-// that its accesses to an anchor are 256 bytes side by side (with eight columns in a row a lane, four accesses
-// a lane went to each 64 bytes: a skipped token of 8 x 32 KV heads 10.4 us, 7.6 like this; of 128 24.3 and 12.0).
-// The float operations of the threshold rule are the ones of the batched online decision, in
-// the same order, with contraction switched off, so both forms agree bit for bit.
-// Latency is what this kernel costs, so the row's scalars are fetched up front by the lane
-// that needs them, the head statistics are reduced by one wave rather than one lane, the anchors
-// are stored before the decision, which they do not depend on, and the first row of a group stays in
-// registers for the cache.
+// One workgroup per batch row; a 16-lane group per (tensor, KV head) pair, columns 32 i + 2 l and the next of
+// lane l, so that its accesses to an anchor are 256 bytes side by side (with eight columns in a row a lane,
+// four accesses a lane went to each 64 bytes: a skipped token of 8 x 32 KV heads 10.4 us, 7.6 like this; of
+// 128 24.3 and 12.0).  The float operations of the threshold rule are the ones of the batched online
+// decision, in the same order, with contraction switched off, so both forms agree bit for bit.  Latency is
+// what this kernel costs, so the row's scalars are fetched up front by the lane that needs them, the head
+// statistics are reduced by one wave rather than one lane, the anchors are stored before the decision, which
+// they do not depend on, and the first row of a group stays in registers for the cache.
 #pragma clang fp contract(off)
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -239,9 +238,9 @@ __device__ __forceinline__ void score_row(
 }
 #pragma clang fp contract(fast)
 
-// The kernels of a step take their arguments as one block: a launch handles each argument by itself, and 40 of them
-// were 0.6 of a call's 6.5 us on the host.  (The bodies are functions of their own for the pointers' sake,
-// which are known not to overlap as arguments only.)
+// The kernels of a step take their arguments as one block: a launch handles each argument by itself, and 40
+// of them were 0.6 of a call's 6.5 us on the host.  (The bodies are functions of their own for the pointers'
+// sake, which are known not to overlap as arguments only.)
 template <typename T> struct ScoreArgs {
     const T *k, *v;
     double *anchor_k, *anchor_v;
@@ -295,8 +294,8 @@ __device__ __forceinline__ Float2 get_shared(const float* p)
     return __builtin_bit_cast(Float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// Behind a slice's partial result, which the workgroup has just written: the workgroup that draws the last ticket merges
-// the `used` slices of its heads into the output rows.
+// Behind a slice's partial result, which the workgroup has just written: the workgroup that draws the last
+// ticket merges the `used` slices of its heads into the output rows.
 template <typename T>
 __device__ __forceinline__ void merge_slices(float* part0, T* out, float (*weight)[kDecodeMaxSplit + 1], int* drawn,
                                              int32_t* ticket, int heads, int used, int n_split)
@@ -308,10 +307,10 @@ __device__ __forceinline__ void merge_slices(float* part0, T* out, float (*weigh
     __syncthreads();
     if (*drawn != used - 1) return;
 
-    // Numerators of the first kBatch slices of this thread's two columns, requested before their weights are known
-    // (16 slices at a time, one column a thread: eight round trips to memory in a row with 64 slices of four heads).
-    // The last ones of a batch repeat a slice with weight 0, so few slices go in a small one (1 x 32 / 8 heads x 500
-    // keys, four slices: 12.2 us a step in a batch of 32, 11.5 in one of eight).
+    // Numerators of the first kBatch slices of this thread's two columns, requested before their weights are
+    // known (16 slices at a time, one column a thread: eight round trips to memory in a row with 64 slices of
+    // four heads).  The last ones of a batch repeat a slice with weight 0, so few slices go in a small one (1
+    // x 32 / 8 heads x 500 keys, four slices: 12.2 us a step in a batch of 32, 11.5 in one of eight).
     const int pairs = heads * kHeadDim / 2;
     auto merge = [&](auto batch) {
         constexpr int kBatch = decltype(batch)::value;
@@ -387,8 +386,8 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
     const float* kb = k_cache + row0 * kHeadDim + c8 * 8;
     const float* vb = v_cache + row0 * kHeadDim + c8 * 8;
     // Slices are of at least kDecodeSlice keys, whatever the cache has room for, and the workgroups of those
-    // without a key have nothing to do.  One row of 8 groups in a cache of 32768: 4 keys 20.8 -> 10.3 us a step, 300
-    // 21.1 -> 13.8, 2000 22.7 -> 16.9, against 64 slices of which the most were empty.
+    // without a key have nothing to do.  One row of 8 groups in a cache of 32768: 4 keys 20.8 -> 10.3 us a
+    // step, 300 21.1 -> 13.8, 2000 22.7 -> 16.9, against 64 slices of which the most were empty.
     const int chunk = max(kDecodeSlice, ((len + n_split - 1) / n_split + 15) & ~15);
     const int lo = sp * chunk, hi = min(len, lo + chunk);
     if (skipped | (lo >= len)) {
@@ -494,21 +493,24 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
 }
 
 // The same for bf16 rows, on the matrix pipe; a wave takes blocks of 32 keys.
-//   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = 16 rows of K as they lie in memory, B = the queries
-//                 (column c: head c % G of the group, the last one again where it has fewer than G), so a
-//                 lane has the scores of one head for eight keys.
-//   O^T += V^T P^T  A: a lane loads 8 columns of the eight keys whose weights it holds (the contraction order over keys is
-//                 the one in which they come out of the first product) and transposes them within its own
-//                 registers; the 16 columns of product i are 8 c + i.
-//   weights       stay fp32: a weight is the exact sum of three bf16 parts (8 bits of the mantissa each), and the
-//                 parts of a head's weight are columns of their own of P^T (column c: part c / G), which with one
-//                 to five heads are there anyway.  Their products with V are added up in fp32 at the end.
+//   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = 16 rows of K as they lie in memory, B = the queries (column c:
+//                 head c % G of the group, the last one again where it has fewer than G), so a lane has the
+//                 scores of one head for eight keys.
+//   O^T += V^T P^T  A: a lane loads 8 columns of the eight keys whose weights it holds (the contraction order
+//                 over keys is the one in which they come out of the first product) and transposes them
+//                 within its own registers; the 16 columns of product i are 8 c + i.
+//   weights       stay fp32: a weight is the exact sum of three bf16 parts (8 bits of the mantissa each), and
+//                 the parts of a head's weight are columns of their own of P^T (column c: part c / G), which
+//                 with one to five heads are there anyway.  Their products with V are added up in fp32 at the
+//                 end.  (An infinite value meets parts that are zero: where the products of whole weights
+//                 gave an infinity, these give no number.  Non-finite inputs are outside the contract.)
 // What bounds it is the way of the keys from memory, and for short rows the first loads (2 to 4 us) and the
-// merge (6 us).  In fp32 on the vector pipe, as above, 480 instructions a wave went into 16 keys of four heads, 2 us
-// for 64 keys with two workgroups on a compute unit.  A step with a kept token, scoring included (half of the tokens to
-// be skipped): 1 x 32 / 8 heads x 2000, 16384 and 32768 keys 16.1, 29.9, 36.8 -> 12.7, 21.4, 29.9 us; 8 x 32 / 8 x
-// 2048 26.0 -> 22.9; 1 x 32 / 32 x 2048 23.2 -> 14.8; 8 x 32 / 32 x 2048 53.9 -> 50.9, 48.0 if all rows are known
-// to attend.  Distance from 64 bits as before (1.65e-3, the rounding of the output).
+// merge (6 us).  In fp32 on the vector pipe, as above, 480 instructions a wave went into 16 keys of four
+// heads, 2 us for 64 keys with two workgroups on a compute unit.  A step with a kept token, scoring included
+// (half of the tokens to be skipped): 1 x 32 / 8 heads x 2000, 16384 and 32768 keys 16.1, 29.9, 36.8 -> 12.7,
+// 21.4, 29.9 us; 8 x 32 / 8 x 2048 26.0 -> 22.9; 1 x 32 / 32 x 2048 23.2 -> 14.8; 8 x 32 / 32 x 2048 53.9 ->
+// 50.9, 48.0 if all rows are known to attend.  Distance from 64 bits as before (1.65e-3, the rounding of the
+// output).
 template <int G, bool FULL>
 __device__ __forceinline__ void attend_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
@@ -525,12 +527,11 @@ __device__ __forceinline__ void attend_bf16(
     __shared__ int drawn;
     const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // The workgroups are dealt out to the rows that attend: where skipped rows have a share of the grid, their places
-    // on the compute units stay empty (16 steps of 8 x 32 / 32 heads x 2048 keys with about half of the rows
-    // skipped: 533 us, 506 dealt out; of 8 x 32 / 8 280 and 275).  How a row is sliced does not depend on
-    // the other rows, so neither do its bits.
-    // Groups of query heads: G of them (FULL), or at most G, the heads of a KV head in `parts` groups of `per` and the last
-    // one of what is left.
+    // The workgroups are dealt out to the rows that attend: where skipped rows have a share of the grid,
+    // their places on the compute units stay empty (16 steps of 8 x 32 / 32 heads x 2048 keys with about half
+    // of the rows skipped: 533 us, 506 dealt out; of 8 x 32 / 8 280 and 275).  How a row is sliced does not
+    // depend on the other rows, so neither do its bits.  Groups of query heads: G of them (FULL), or at most
+    // G, the heads of a KV head in `parts` groups of `per` and the last one of what is left.
     const int groups = FULL ? Hq / G : Hkv * parts, ratio = Hq / Hkv;
     auto first_head = [&](int hg) { return FULL ? hg * G : hg / parts * ratio + hg % parts * per; };
     auto heads_of = [&](int hg) { return FULL ? G : min(per, ratio - hg % parts * per); };
@@ -580,9 +581,9 @@ __device__ __forceinline__ void attend_bf16(
         for (int e = 0; e < 8; ++e)
             v_raw[e] = *reinterpret_cast<const u32x4*>(vb + (long long)min(j + 16 * (e >> 2) + 4 * g4 + (e & 3), hi - 1) * kHeadDim);
     };
-    // A wave's blocks in turn, each KV head from another one on: workgroups that walk caches side by side in step meet in
-    // the same memory channels at some distances of the caches (8 x 32 / 32 heads x 2048 keys from memory: 70 us a
-    // step in caches of 2064 rows, 58 to 62 in others; like this 62 in all of them).
+    // A wave's blocks in turn, each KV head from another one on: workgroups that walk caches side by side in
+    // step meet in the same memory channels at some distances of the caches (8 x 32 / 32 heads x 2048 keys
+    // from memory: 70 us a step in caches of 2064 rows, 58 to 62 in others; like this 62 in all of them).
     const int first = lo + 32 * wave, blocks = max(0, (hi - first + 127) / 128);
     int j = blocks ? first + 128 * (hk % blocks) : hi;
     if (blocks) { request_k(j); request_v(j); }
@@ -869,12 +870,13 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
 int decode_heads_per_wg(bool bf16, int B, int Hq, int Hkv)
 {
     const int ratio = Hq / Hkv;
-    // Heads that share a KV head share workgroups, whatever their number: one by one each reads the cache for itself (a
-    // step of 1 x 128 / 8 heads x 5000 keys: 33.6 us, 16.8 by fours; 8 x 40 / 8 x 2000: 55 and 23; 4 x 71 / 1 x 2000: 37
-    // and 20; below some 500 keys one by one is up to 0.5 us faster).  More than four go by eights, but by
-    // fours where few caches are read: the slices of four are merged in half the time (1 x 16 / 2 x 16384: 20.2
-    // by eights, 17.7 by fours; 1 x 64 / 8 x 4000: 17.6 and 15.9; 8 x 28 / 4 x 2000: 20.0 and 18.4; but 8 x 64 / 8 x
-    // 4000: 33.8 and 48.5; 16 x 48 / 8 x 2000: 32.6 and 48; fp32 16 x 64 / 8 x 4000: 108 and 159).
+    // Heads that share a KV head share workgroups, whatever their number: one by one each reads the cache for
+    // itself (a step of 1 x 128 / 8 heads x 5000 keys: 33.6 us, 16.8 by fours; 8 x 40 / 8 x 2000: 55 and 23;
+    // 4 x 71 / 1 x 2000: 37 and 20; below some 500 keys one by one is up to 0.5 us faster).  More than four
+    // go by eights, but by fours where few caches are read: the slices of four are merged in half the time (1
+    // x 16 / 2 x 16384: 20.2 by eights, 17.7 by fours; 1 x 64 / 8 x 4000: 17.6 and 15.9; 8 x 28 / 4 x 2000:
+    // 20.0 and 18.4; but 8 x 64 / 8 x 4000: 33.8 and 48.5; 16 x 48 / 8 x 2000: 32.6 and 48; fp32 16 x 64 / 8
+    // x 4000: 108 and 159).
     if (bf16 && ratio > 2) return ratio <= 4 || B * Hkv < 48 ? 4 : 8;
     if (ratio == 8) return B * Hkv < 48 ? 4 : 8;
     return ratio == 2 || ratio == 4 ? ratio : 1;   // (fp32, other ratios: one by one)
@@ -883,11 +885,12 @@ int decode_heads_per_wg(bool bf16, int B, int Hq, int Hkv)
 // Slices of each of `rows` caches that a step reads.
 static int decode_slices(int rows, int n_cu)
 {
-    // One workgroup on a compute unit has enough keys under way, and a merge of more slices costs more than more
-    // workgroups bring (a step of 1 x 32 / 8 heads x 16384 keys: 24.9 us with 512, 21.5 with 256; 1 x 32 / 32 x 2048:
-    // 18.9, 16.0 and 15.2 with 1024, 512 and 256; 8 x 32 / 32 x 256: 19.0, 15.1 and 13.0).  Where rows do not fill
-    // whole rounds of the compute units, the fewest slices that come within a tenth of even shares, in up to
-    // four rounds (8 x 40 / 40 x 2048, 320 rows: 73.7 us with 320 workgroups, 68.1 with 640, 65.1 with 960).
+    // One workgroup on a compute unit has enough keys under way, and a merge of more slices costs more than
+    // more workgroups bring (a step of 1 x 32 / 8 heads x 16384 keys: 24.9 us with 512, 21.5 with 256; 1 x 32
+    // / 32 x 2048: 18.9, 16.0 and 15.2 with 1024, 512 and 256; 8 x 32 / 32 x 256: 19.0, 15.1 and 13.0).
+    // Where rows do not fill whole rounds of the compute units, the fewest slices that come within a tenth of
+    // even shares, in up to four rounds (8 x 40 / 40 x 2048, 320 rows: 73.7 us with 320 workgroups, 68.1 with
+    // 640, 65.1 with 960).
     const int most = std::min(kDecodeMaxSplit, 4 * n_cu / rows);
     int split = std::min(kDecodeMaxSplit, std::max(1, n_cu / rows));
     int busiest = (rows * split + n_cu - 1) / n_cu;   // workgroups of the busiest compute unit
@@ -902,20 +905,22 @@ int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
 {
     const int g = decode_heads_per_wg(bf16, B, Hq, Hkv), groups = Hkv * ((Hq / Hkv + g - 1) / g), rows = B * groups;
     if (bf16) {
-        // By the batch rows that attend on average: by those that do attend in a step, a row's rounding would depend on its
-        // neighbours.  Where the number varies from step to step whole rounds are not worth more slices (16 steps of 8 x
-        // 40 / 40 x 2048, half of the rows skipped: 586 us with one slice, 618 with three; 8 x 32 / 32 x 2048, a quarter:
-        // 600 with one, 687 with four; 16 x 32 / 32 x 1024, a quarter: 628 with one, 681 with two), but they are
-        // where only one row now and then leaves a second round (8 x 40 / 40 x 2048, a tenth: 1052 and 961).
+        // By the batch rows that attend on average: by those that do attend in a step, a row's rounding would
+        // depend on its neighbours.  Where the number varies from step to step whole rounds are not worth
+        // more slices (16 steps of 8 x 40 / 40 x 2048, half of the rows skipped: 586 us with one slice, 618
+        // with three; 8 x 32 / 32 x 2048, a quarter: 600 with one, 687 with four; 16 x 32 / 32 x 1024, a
+        // quarter: 628 with one, 681 with two), but they are where only one row now and then leaves a second
+        // round (8 x 40 / 40 x 2048, a tenth: 1052 and 961).
         const int attending = std::max(1, (int)lround(B * (1.0 - target))), caches = attending * groups;
         if (attending == B || (attending == B - 1 && caches > n_cu)) return decode_slices(caches, n_cu);
         return std::min(kDecodeMaxSplit, std::max(1, n_cu / caches));
     }
-    // fp32: two workgroups a compute unit where they take four or eight heads, as many as are resident at once (224 and 249
-    // registers); four where they take one or two, which is more than the three and two that are (164 and 186): many rows
-    // gain from it what they lose in rounds, few do not (16 steps with half of the rows skipped, one / two / three / four a
-    // compute unit: 8 x 40 / 40 heads x 2000 keys 1270, 1215, 1134, 1120 us; 8 x 32 / 32 x 1000 451, 489, 502, 482; 1 x 32 /
-    // 32 x 4000 296, 299, 303, 319; 1 x 32 / 16 x 6000 249, 253, 294, 315; 4 x 32 / 8 x 2000 with one and two 274, 283).
+    // fp32: two workgroups a compute unit where they take four or eight heads, as many as are resident at
+    // once (224 and 249 registers); four where they take one or two, which is more than the three and two
+    // that are (164 and 186): many rows gain from it what they lose in rounds, few do not (16 steps with half
+    // of the rows skipped, one / two / three / four a compute unit: 8 x 40 / 40 heads x 2000 keys 1270, 1215,
+    // 1134, 1120 us; 8 x 32 / 32 x 1000 451, 489, 502, 482; 1 x 32 / 32 x 4000 296, 299, 303, 319; 1 x 32 /
+    // 16 x 6000 249, 253, 294, 315; 4 x 32 / 8 x 2000 with one and two 274, 283).
     return std::min(kDecodeMaxSplit, std::max(1, ((g >= 4 ? 2 : 4) * n_cu + rows - 1) / rows));
 }
 

@@ -9,9 +9,10 @@ namespace {
 
 // ------------------------------------------------------------------------------ fusion
 // 64 tokens per workgroup.  All 256 threads stage the tokens' per-head cosines in LDS
-// ([head][token]: global reads and LDS accesses are unit-stride across a wave), eight heads a thread under way at
-// once (one by one, as it was, 32 heads were eight round trips to memory in a row: 8 x 4096 tokens 6.3 -> 5.2 us); then one thread per token takes the
-// mean and the two-pass variance over the heads (the head count is a run-time value).
+// ([head][token]: global reads and LDS accesses are unit-stride across a wave), eight heads a
+// thread under way at once (one by one, 32 heads are eight round trips to memory in a row: 8 x
+// 4096 tokens 6.3 -> 5.2 us); then one thread per token takes the mean and the two-pass variance
+// over the heads (the head count is a run-time value).
 constexpr int kFuseTokens = 64;
 constexpr int kFuseThreads = 256;
 
@@ -233,8 +234,9 @@ __global__ __launch_bounds__(kSelThreads) void compact_kernel(const uint8_t* __r
 // Everything at or below the token found is kept.  What bounds it: short rows a chain of some 15
 // barriers and LDS round trips, long rows the passes over 32 scores a thread on the one compute unit
 // that works on a row.  One row of 32768 tokens: 55 -> 24 us against four radix passes in thread
-// order, 2 x 8192: 16 -> 9.3, 8 x 4096: 11.4 -> 7.4, 333: 8.1 -> 4.9.  Reductions and scans of a wave in the VALU
-// (through LDS, a chain of twelve accesses for the range alone: 8 x 4096 9.4 -> 8.2, 1 x 2048 6.6 -> 5.8).
+// order, 2 x 8192: 16 -> 9.3, 8 x 4096: 11.4 -> 7.4, 333: 8.1 -> 4.9.  Reductions and scans of a
+// wave are made in the VALU (through LDS, a chain of twelve accesses for the range alone, in another
+// timing: 8 x 4096 9.4 -> 8.2, 1 x 2048 6.6 -> 5.8).
 constexpr int kBins = 2048;
 constexpr int kMaxCand = 256;
 constexpr int kLevels = 4;
@@ -266,9 +268,10 @@ __device__ __forceinline__ int rank_below(unsigned long long ballot)
 //
 // FUSE: the scores are not there yet; the workgroup makes them from the row's cosines (at most
 // kFuseFloats a tensor, staged in LDS) with the arithmetic of fuse_kernel and writes them to `fused`.
-// That takes about 2 us here and 4 in a launch of its own; a longer row, or one with more heads, would keep
-// one compute unit loading what fuse_kernel spreads over many.  Whole calls: 32 heads x 333 tokens
-// 29.4 -> 27.3 us, fp32 32 x 512 36.9 -> 35.5 (the kernel 9.5 -> 7.6 with all loads under way at once); 8 heads x 2048 tokens (four a thread) 0.5 us slower a call.
+// That takes about 2 us here and 4 in a launch of its own; a longer row, or one with more heads,
+// would keep one compute unit loading what fuse_kernel spreads over many.  Whole calls: 32 heads x
+// 333 tokens 29.4 -> 27.3 us, fp32 32 x 512 36.9 -> 35.5 (the kernel 9.5 -> 7.6 with all loads under
+// way at once); 8 heads x 2048 tokens (four a thread) 0.5 us slower a call.
 constexpr int kFuseFloats = 16384;
 
 template <int IPT, bool FUSE>

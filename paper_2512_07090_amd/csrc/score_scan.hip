@@ -425,24 +425,24 @@ struct ScorePlan {
 };
 
 // Segments of a chain.  Never more than keep every workgroup of the launch resident at once (their registers
-// allow two bf16 workgroups a compute unit, one fp32): a second round of a few workgroups takes as long
-// as the first.  Times are whole calls of tf_score at `chains` x tokens.
-// Exact mean: a workgroup adds up the totals of all segments before its own, eight loads at a time, so the
-// time is about tiles / nseg + nseg / 20 tile times: at most sqrt(20 tiles) segments, or 16 where each has a
-// compute unit (16 chains x 8192 23.3 us with 22 segments, 22.4 with 32; 2 x 32768 25.8 with 52, 23.9 with 64, 26.4
-// with 128; one load at a time these took 23.4 and 30.6 with the fewer ones).  The totals pass reads all but the last
-// segment a second time, which is not worth it from kOneSegment chains on where that would make two
-// segments (192 x 8192 117 with one, 123 with two; 240 x 16384 230 and 258), but is for three of a long
-// row (160 x 3000 49.9 with one, 46.5 with three; 160 x 32768 442 and 404; only 160 x 1777 33.9 and 34.7).
-// A segment has at least two tiles where there are many (16 x 3001 16.4 -> 14.7).
-// Incremental anchor: a segment walks two more tiles to warm up (gamma 0.9).  As short as one workgroup a
-// compute unit allows (16 x 5000 14.4 us with 3 tiles, 15.9 with 4; 2 x 8192 11.5 with 2, 14.8 with 4; 48 x
-// 2688 20.9 with 5, 24.2 with 4 and two a compute unit), or, with four tiles or more, as two of them allow,
-// which slows each by about 1.45 (48 x 3968 24.3 with 4, 27 with 7; 160 x 1777 29.9 with 5, 37.4 with 4).
+// allow two bf16 workgroups a compute unit, one fp32): a second round of a few workgroups takes as long as
+// the first.  Times are whole calls of tf_score at `chains` x tokens.  Exact mean: a workgroup adds up the
+// totals of all segments before its own, eight loads at a time, so the time is about tiles / nseg + nseg / 20
+// tile times: at most sqrt(20 tiles) segments, or 16 where each has a compute unit (16 chains x 8192 23.3 us
+// with 22 segments, 22.4 with 32; 2 x 32768 25.8 with 52, 23.9 with 64, 26.4 with 128; one load at a time
+// these took 23.4 and 30.6 with the fewer ones).  The totals pass reads all but the last segment a second
+// time, which is not worth it from kOneSegment chains on where that would make two segments (192 x 8192 117
+// with one, 123 with two; 240 x 16384 230 and 258), but is for three of a long row (160 x 3000 49.9 with one,
+// 46.5 with three; 160 x 32768 442 and 404; only 160 x 1777 33.9 and 34.7).  A segment has at least two tiles
+// where there are many (16 x 3001 16.4 -> 14.7).  Incremental anchor: a segment walks two more tiles to warm
+// up (gamma 0.9).  As short as one workgroup a compute unit allows (16 x 5000 14.4 us with 3 tiles, 15.9 with
+// 4; 2 x 8192 11.5 with 2, 14.8 with 4; 48 x 2688 20.9 with 5, 24.2 with 4 and two a compute unit), or, with
+// four tiles or more, as two of them allow, which slows each by about 1.45 (48 x 3968 24.3 with 4, 27 with 7;
+// 160 x 1777 29.9 with 5, 37.4 with 4).
 constexpr int kOneSegment = 150, kManyTiles = 20;
 
-// chains: of this launch (one tensor's for the key-only and value-only scores); most: segments a chain's totals have
-// room for.
+// chains: of this launch (one tensor's for the key-only and value-only scores); most: segments a chain's
+// totals have room for.
 static ScorePlan plan_score(int chains, int most, int n, bool f32, bool ema, int n_cu)
 {
     const int tiles = (n + kTile - 1) / kTile;
@@ -528,11 +528,11 @@ static hipError_t launch_score_t(const Dims& d, const T* K, const T* V, float* s
                                         first_tensor, gamma, warm);
         return hipGetLastError();
     }
-    // A short row's segments of one tile add up the tiles before theirs by themselves, with the same arithmetic: up to
-    // two tiles more to load at once cost less than a launch for the totals (whole calls: bf16, 120 chains x 333 rows
-    // 12.2 -> 10.4 us; fp32, twice the bytes, a kernel of 12.8 against two of 4.0 and 7.9 from three tiles on).  Three more
-    // do while no two workgroups share a compute unit (64 chains x 500 rows 10.4 -> 9.8; 80 chains 11.8 and 13.1,
-    // 128 12.5 and 14.6).
+    // A short row's segments of one tile add up the tiles before theirs by themselves, with the same
+    // arithmetic: up to two tiles more to load at once cost less than a launch for the totals (whole calls:
+    // bf16, 120 chains x 333 rows 12.2 -> 10.4 us; fp32, twice the bytes, a kernel of 12.8 against two of 4.0
+    // and 7.9 from three tiles on).  Three more do while no two workgroups share a compute unit (64 chains x
+    // 500 rows 10.4 -> 9.8; 80 chains 11.8 and 13.1, 128 12.5 and 14.6).
     const bool own_totals = !stream_loads && p.nseg > 1 && p.nseg <= kOwnTotals<T> && p.seg_len == kTile &&
                             (p.nseg <= 3 || chains * p.nseg <= n_cu);
     if (p.nseg > 1 && !own_totals) {

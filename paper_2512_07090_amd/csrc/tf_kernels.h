@@ -59,9 +59,9 @@ hipError_t launch_zero_filtered(const Dims& d, int dtype, const uint8_t* keep, v
 hipError_t launch_attend_f32(const Dims& d, float scale, const float* Q, const float* K,
                              const float* V, const int32_t* kept_idx, float* O,
                              const int32_t* counts, long long idx_stride, hipStream_t s);
-// n_cu: compute
-// units of the device (one persistent workgroup each, or two half as large); n_xcd: its accelerator dies (each with an
-// L2 of its own); expected: with counts, about how many tokens a row keeps (only the speed depends on it).  hipErrorInvalidValue if a (batch, head) slice of K / V spans 4 GiB or more.
+// n_cu: compute units of the device (one persistent workgroup each, or two half as large); n_xcd: its
+// accelerator dies (each with an L2 of its own); expected: with counts, about how many tokens a row keeps
+// (only the speed depends on it).  hipErrorInvalidValue if a (batch, head) slice of K / V spans 4 GiB or more.
 hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const void* K,
                               const void* V, const int32_t* kept_idx, void* O, int n_cu, int n_xcd,
                               const int32_t* counts, int expected, long long idx_stride, hipStream_t s);
