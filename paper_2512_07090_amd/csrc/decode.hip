@@ -516,7 +516,7 @@ __device__ __forceinline__ void attend_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ cache_len, const uint8_t* __restrict__ skip,
     float* __restrict__ part, int32_t* __restrict__ tickets, uint16_t* __restrict__ o, int B, int Hq, int Hkv,
-    int parts, int per, int capacity, int n_split, float scale_log2e)
+    int parts, int per, int capacity, int n_few, int n_split, float scale_log2e)
 {
     constexpr bool kTwice = 3 * G > 16;              // the third parts get a product of their own
     constexpr int kCols = kTwice ? 2 * G : 3 * G;    // columns of O^T in use
@@ -527,18 +527,17 @@ __device__ __forceinline__ void attend_bf16(
     __shared__ int drawn;
     const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // The workgroups are dealt out to the rows that attend: where skipped rows have a share of the grid,
-    // their places on the compute units stay empty (16 steps of 8 x 32 / 32 heads x 2048 keys with about half
-    // of the rows skipped: 533 us, 506 dealt out; of 8 x 32 / 8 280 and 275).  How a row is sliced does not
-    // depend on the other rows, so neither do its bits.  Groups of query heads: G of them (FULL), or at most
-    // G, the heads of a KV head in `parts` groups of `per` and the last one of what is left.
+    // Groups of query heads: G of them (FULL), or at most G, the heads of a KV head in `parts` groups of `per`
+    // and the last one of what is left.
     const int groups = FULL ? Hq / G : Hkv * parts, ratio = Hq / Hkv;
     auto first_head = [&](int hg) { return FULL ? hg * G : hg / parts * ratio + hg % parts * per; };
     auto heads_of = [&](int hg) { return FULL ? G : min(per, ratio - hg % parts * per); };
+    // The workgroups are dealt out to the rows that attend: where skipped rows have a share of the grid,
+    // their places on the compute units stay empty (16 steps of 8 x 32 / 32 heads x 2048 keys with about half
+    // of the rows skipped: 533 us, 506 dealt out; of 8 x 32 / 8 280 and 275).
     const bool dealt = B <= kDecodeDealt;
-    const int mine = min(dealt ? lane : (int)blockIdx.x / (groups * n_split), B - 1);
-    const int mine_len = cache_len[mine];
-    const bool attends = skip[mine] == 0 && (!dealt || lane < B);
+    const int lane_row = min(lane, B - 1), lane_len = dealt ? cache_len[lane_row] : 0;
+    const bool attends = dealt && lane < B && skip[lane_row] == 0;
     const unsigned long long rows = __ballot(attends);
     // zero rows, by the first workgroups of the grid
     if (blockIdx.x < B * groups) {
@@ -547,15 +546,25 @@ __device__ __forceinline__ void attend_bf16(
             for (int i = threadIdx.x; i < heads_of(zg) * kHeadDim; i += 256)
                 o[((long long)zb * Hq + first_head(zg)) * kHeadDim + i] = 0;
     }
-    if (rows == 0) return;
-    const int sp = blockIdx.x % n_split;
-    const int hg = (blockIdx.x / n_split) % groups;
-    int b = blockIdx.x / n_split / groups, len = mine_len;
+    // first the n_few slices that every row has, then those that only long rows have
+    int at = blockIdx.x, slices = n_few, sp = 0;
+    if (const int of_all = (dealt ? __popcll(rows) : B) * groups * n_few; at >= of_all) {
+        if (n_split == n_few) return;
+        at -= of_all;
+        slices = n_split - n_few;
+        sp = n_few;
+    }
+    sp += at % slices;
+    const int hg = at / slices % groups;
+    int b = at / slices / groups, len;
     if (dealt) {   // the b-th row that attends
         const unsigned long long here = __ballot(attends && __popcll(rows & ((1ull << lane) - 1)) == b);
         if (here == 0) return;
         b = __builtin_ctzll(here);
-        len = __shfl(mine_len, b);
+        len = __shfl(lane_len, b);
+    } else {
+        if (b >= B || skip[b] != 0) return;
+        len = cache_len[b];
     }
     len = __builtin_amdgcn_readfirstlane(len);
     const int hq0 = first_head(hg), hk = hq0 / ratio, heads = heads_of(hg);
@@ -563,7 +572,9 @@ __device__ __forceinline__ void attend_bf16(
     const long long row0 = ((long long)b * Hkv + hk) * capacity;
     const uint16_t* kb = k_cache + row0 * kHeadDim + 8 * g4;
     const uint16_t* vb = v_cache + row0 * kHeadDim + 8 * c16;
-    const int chunk = max(kDecodeSliceBf16, ((len + n_split - 1) / n_split + 31) & ~31);
+    // How a row is sliced follows from its own length, not from the other rows, and so do its bits.
+    const int n_row = len >= n_split * kDecodeLongSlice ? n_split : n_few;
+    const int chunk = max(kDecodeSliceBf16, ((len + n_row - 1) / n_row + 31) & ~31);
     const int lo = sp * chunk, hi = min(len, lo + chunk);
     if (lo >= len) return;
 
@@ -704,14 +715,14 @@ struct AttendArgs {
     float* part;
     int32_t* tickets;
     uint16_t* o;
-    int B, Hq, Hkv, parts, per, capacity, n_split;
+    int B, Hq, Hkv, parts, per, capacity, n_few, n_split;
     float scale_log2e;
 };
 template <int G, bool FULL>
 __global__ __launch_bounds__(256, 2) void decode_attend_bf16_kernel(const AttendArgs a)
 {
     attend_bf16<G, FULL>(a.q, a.k_cache, a.v_cache, a.cache_len, a.skip, a.part, a.tickets, a.o, a.B, a.Hq, a.Hkv, a.parts,
-                   a.per, a.capacity, a.n_split, a.scale_log2e);
+                   a.per, a.capacity, a.n_few, a.n_split, a.scale_log2e);
 }
 
 // Hand-off from the batched path: the anchors as they stand after all n rows of a prompt.
@@ -846,7 +857,7 @@ hipError_t launch_decode_step_t(const DecodeArgs& a, const T* q, const T* k, con
         if constexpr (sizeof(T) == 2)                                                             \
             decode_attend_bf16_kernel<G, FULL><<<dim3(grid), dim3(256), 0, s>>>(                  \
                 AttendArgs{q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.B, a.Hq, a.Hkv, parts,     \
-                           (ratio + parts - 1) / parts, a.capacity, a.n_split, sl2});             \
+                           (ratio + parts - 1) / parts, a.capacity, a.n_few, a.n_split, sl2});    \
         else                                                                                      \
             decode_attend_f32_kernel<G><<<dim3(grid), dim3(256), 0, s>>>(                         \
                 q, k_cache, v_cache, a.cache_len, a.skip, a.part, tickets, o, a.Hq, a.Hkv,        \
@@ -901,7 +912,7 @@ static int decode_slices(int rows, int n_cu)
     return split;
 }
 
-int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
+DecodeSplit decode_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
 {
     const int g = decode_heads_per_wg(bf16, B, Hq, Hkv), groups = Hkv * ((Hq / Hkv + g - 1) / g), rows = B * groups;
     if (bf16) {
@@ -912,8 +923,15 @@ int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
         // quarter: 628 with one, 681 with two), but they are where only one row now and then leaves a second
         // round (8 x 40 / 40 x 2048, a tenth: 1052 and 961).
         const int attending = std::max(1, (int)lround(B * (1.0 - target))), caches = attending * groups;
-        if (attending == B || (attending == B - 1 && caches > n_cu)) return decode_slices(caches, n_cu);
-        return std::min(kDecodeMaxSplit, std::max(1, n_cu / caches));
+        const bool steady = attending == B || (attending == B - 1 && caches > n_cu);
+        const int few = steady ? decode_slices(caches, n_cu) : std::min(kDecodeMaxSplit, std::max(1, n_cu / caches));
+        // Long rows, where merging costs little beside the keys, get a round of the compute units for each batch
+        // row if they can, so that whole rounds are walked whatever attends (16 steps, 8 x 32 / 32 x 8000, half
+        // of the rows skipped: 1732 us with two slices, 1656 with eight; 2 x 40 / 40 x 20000, a quarter: 1967
+        // with three, 1881 with six; at 704 keys a slice they are even: 3 x 32 / 32 x 5000 565 with four and
+        // 572 with eight slices, x 6000 677 and 659; 8 x 32 / 8 x 8000 491 with 8 and 579 with 32).
+        const bool varies = B > 1 && target > 0.0;
+        return {few, varies ? std::max(few, std::min(4 * few, decode_slices(groups, n_cu))) : few};
     }
     // fp32: two workgroups a compute unit where they take four or eight heads, as many as are resident at
     // once (224 and 249 registers); four where they take one or two, which is more than the three and two
@@ -921,13 +939,14 @@ int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu)
     // of the rows skipped, one / two / three / four a compute unit: 8 x 40 / 40 heads x 2000 keys 1270, 1215,
     // 1134, 1120 us; 8 x 32 / 32 x 1000 451, 489, 502, 482; 1 x 32 / 32 x 4000 296, 299, 303, 319; 1 x 32 /
     // 16 x 6000 249, 253, 294, 315; 4 x 32 / 8 x 2000 with one and two 274, 283).
-    return std::min(kDecodeMaxSplit, std::max(1, ((g >= 4 ? 2 : 4) * n_cu + rows - 1) / rows));
+    const int n = std::min(kDecodeMaxSplit, std::max(1, ((g >= 4 ? 2 : 4) * n_cu + rows - 1) / rows));
+    return {n, n};
 }
 
 size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv, double target)
 {
     const size_t rows = (size_t)B * Hq;
-    return (rows * decode_max_split(bf16, B, Hq, Hkv, target) * kDecodePartFloats + rows) * sizeof(float);
+    return (rows * decode_split(bf16, B, Hq, Hkv, target).most * kDecodePartFloats + rows) * sizeof(float);
 }
 
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s)

@@ -67,10 +67,11 @@ hipError_t launch_attend_bf16(const Dims& d, float scale, const void* Q, const v
                               const int32_t* counts, int expected, long long idx_stride, hipStream_t s);
 
 // ---- per-token (decoding) form ----------------------------------------------------------------
-// Slices of a row's cache per group of query heads, merged by the workgroup that ends last: as many as make the
-// workgroups of decode_max_split(), at most one per lane of the wave that weighs them.
+// Slices of a row's cache per group of query heads, merged by the workgroup that ends last: as many as
+// decode_split() says, at most one per lane of the wave that weighs them.
 constexpr int kDecodeMaxSplit = 64;
 constexpr int kDecodeSlice = 64, kDecodeSliceBf16 = 128;   // keys of a slice at least: one pass of its workgroup
+constexpr int kDecodeLongSlice = 704;               // keys a slice has at least where a row is cut into `most` slices
 constexpr int kDecodePartFloats = kHeadDim + 2;     // floats of one slice's partial result
 constexpr int kDecodeDealt = 64;                    // batch rows up to which workgroups are dealt out to the rows that attend (a lane each)
 struct DecodeArgs {
@@ -85,11 +86,12 @@ struct DecodeArgs {
     uint8_t* skip;                                  // out [B]
     float* fused;                                   // out [B]
     float* part;                                    // scratch [B][Hq][n_split][kDecodePartFloats], tickets
-    int n_split;                                    // 1 .. decode_max_split()
+    int n_few, n_split;                             // 1 .. decode_split()
 };
+struct DecodeSplit { int few, most; };              // slices of a row; of one of kDecodeLongSlice * most keys or more (bf16)
 int decode_heads_per_wg(bool bf16, int B, int Hq, int Hkv);   // query heads one workgroup handles at most (they share a KV head)
 // target: share of the tokens to be skipped; n_cu: compute units (workspaces are sized for 256)
-int decode_max_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu = 256);
+DecodeSplit decode_split(bool bf16, int B, int Hq, int Hkv, double target, int n_cu = 256);
 size_t decode_scratch_bytes(bool bf16, int B, int Hq, int Hkv, double target);
 hipError_t launch_decode_init(const DecodeArgs& a, float tau0, hipStream_t s);
 // state after a prompt of n rows that the batched online path has processed: anchors from K and

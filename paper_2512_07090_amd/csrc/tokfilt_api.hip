@@ -210,7 +210,7 @@ tf_status decode_args(tf_ctx* ctx, const tf_params* p, const tf_decode_state* st
     a->gamma = (double)p->ema_gamma;
     a->target = (float)p->prune_ratio; a->eta = 0.f;
     a->scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->head_dim);
-    a->skip = nullptr; a->fused = nullptr; a->part = nullptr; a->n_split = 1;
+    a->skip = nullptr; a->fused = nullptr; a->part = nullptr; a->n_few = a->n_split = 1;
     return TF_OK;
 }
 
@@ -543,8 +543,11 @@ tf_status tf_decode_step(tf_ctx* ctx, const tf_params* p, float eta, const tf_de
     const size_t rows = (size_t)p->batch * p->n_q_heads;
     const int room = (int)std::min<size_t>(tf::kDecodeMaxSplit, (ws_bytes / sizeof(float) - rows) / (rows * tf::kDecodePartFloats));
     const int slice = bf16 ? tf::kDecodeSliceBf16 : tf::kDecodeSlice;
-    a.n_split = std::min({tf::decode_max_split(bf16, p->batch, p->n_q_heads, p->n_kv_heads, p->prune_ratio, ctx->n_cu),
-                          (state->capacity + slice - 1) / slice, room});
+    const int held = std::min((state->capacity + slice - 1) / slice, room);
+    const tf::DecodeSplit split = tf::decode_split(bf16, p->batch, p->n_q_heads, p->n_kv_heads, p->prune_ratio, ctx->n_cu);
+    a.n_few = std::min(split.few, held);
+    // (a cache without room for a long row has no use for a long row's slices)
+    a.n_split = state->capacity >= split.most * tf::kDecodeLongSlice ? std::min(split.most, held) : a.n_few;
     return dev(ctx, tf::launch_decode_step(a, p->dtype, q, k, v, o, (hipStream_t)stream), "decode step launch");
 }
 

@@ -312,6 +312,42 @@ def test_decode_row_does_not_depend_on_the_other_rows_decisions(ctx, case):
         assert torch.equal(buf.o[attend], every[attend]), skipped
 
 
+@pytest.mark.parametrize("case", [(3, 40, 40, 6 * 704), (66, 16, 16, 4 * 704)])   # ..., keys from which a row has more slices
+def test_decode_long_rows_have_slices_of_their_own(ctx, case):
+    """bf16, batches in which some tokens are skipped: rows of so many keys are cut finer.  Rows on both sides of the border,
+    all, some or one of them attending: the same bits, attention in 64 bits, and zero rows for the others."""
+    Bn, Hq, Hkv, long = case
+    _say("decode long rows %s" % (case,))
+    cap = long + 40
+    p = B.make_params((Bn, Hq, 1, 128), (Bn, Hkv, 1, 128), torch.bfloat16, 0.5, 0)
+    buf = B.DecodeBuffers(p, cap)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    q, k, v = (torch.randn((Bn, h, 128), device="cuda", generator=g).bfloat16() for h in (Hq, Hkv, Hkv))
+    for c in (buf.k_cache, buf.v_cache):
+        c.copy_(torch.randn(c.shape, device="cuda", generator=g, dtype=torch.bfloat16))
+    held = [(long + 33, long - 1, long, 100)[b % 4] for b in range(Bn)]
+    every = None
+    for skipped in ([], [1], list(range(1, Bn)), list(range(0, Bn, 2))):
+        ctx.tf_decode_init(p, buf.state, 50.0)
+        buf.tau[skipped] = -50.0
+        buf.cache_len.copy_(torch.tensor([n - 1 for n in held], dtype=torch.int32))
+        buf.ws.fill_(0xFF)
+        buf.o.fill_(float("nan"))
+        ctx.tf_decode_step(p, 0.0, buf.state, q, k, v, buf.o, buf.skip, buf.fused, buf.ws)
+        torch.cuda.synchronize()
+        assert buf.skip.nonzero().flatten().tolist() == skipped
+        if every is None:
+            every = buf.o.clone()
+        attend = [b for b in range(Bn) if b not in skipped]
+        assert torch.equal(buf.o[attend], every[attend]) and not buf.o[skipped].any(), skipped
+    for b in (0, 1, 2, Bn - 1):
+        kk, vv = (c[b, :, :held[b]].double().repeat_interleave(Hq // Hkv, 0) for c in (buf.k_cache, buf.v_cache))
+        w = torch.softmax((kk * q[b].double()[:, None]).sum(2) / 128 ** 0.5, 1)
+        out = (w[:, :, None] * vv).sum(1)
+        # fp32 weights: what is left is the output's rounding, half a unit of bf16
+        assert ((every[b].double() - out).abs() <= 2.0 ** -8 * out.abs() + 1e-5).all(), b
+
+
 def test_decode_step_with_eight_heads_per_kv_head(ctx):
     """Eight query heads read a cache once: 8 rows of 64 / 8 heads x 4000 keys take no longer than of 64 / 16 heads, twice
     the caches (34 and 49 us a step; 80 with one workgroup on a compute unit)."""
