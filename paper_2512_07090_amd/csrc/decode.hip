@@ -507,9 +507,9 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : 1) void decode_attend_f32_kernel(
 // What bounds it is the way of the keys from memory, and for short rows the first loads (2 to 4 us) and the
 // merge (6 us).  In fp32 on the vector pipe, as above, 480 instructions a wave went into 16 keys of four
 // heads, 2 us for 64 keys with two workgroups on a compute unit.  A step with a kept token, scoring included
-// (half of the tokens to be skipped): 1 x 32 / 8 heads x 2000, 16384 and 32768 keys 16.1, 29.9, 36.8 -> 12.7,
-// 21.4, 29.9 us; 8 x 32 / 8 x 2048 26.0 -> 22.9; 1 x 32 / 32 x 2048 23.2 -> 14.8; 8 x 32 / 32 x 2048 53.9 ->
-// 50.9, 48.0 if all rows are known to attend.  Distance from 64 bits as before (1.65e-3, the rounding of the
+// (half of the tokens to be skipped): 1 x 32 / 8 heads x 2000, 16384 and 32768 keys 16.0, 29.7, 36.7 -> 12.9,
+// 21.6, 29.9 us; 8 x 32 / 8 x 2048 26.1 -> 21.2; 1 x 32 / 32 x 2048 22.6 -> 14.7; 8 x 32 / 32 x 2048 52.7 ->
+// 49.6, 47.2 if all rows are known to attend.  Distance from 64 bits as before (1.65e-3, the rounding of the
 // output).
 template <int G, bool FULL>
 __device__ __forceinline__ void attend_bf16(

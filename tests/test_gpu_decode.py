@@ -350,7 +350,7 @@ def test_decode_long_rows_have_slices_of_their_own(ctx, case):
 
 def test_decode_step_with_eight_heads_per_kv_head(ctx):
     """Eight query heads read a cache once: 8 rows of 64 / 8 heads x 4000 keys take no longer than of 64 / 16 heads, twice
-    the caches (34 and 49 us a step; 80 with one workgroup on a compute unit)."""
+    the caches (32 and 48 us a step; 80 with one workgroup on a compute unit)."""
     _say("decode eight heads, time")
     us = {}
     for hkv in (8, 16):
